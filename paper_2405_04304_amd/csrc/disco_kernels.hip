@@ -2166,110 +2166,256 @@ hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
 // classifier training and evaluation (the step after the loop: features and labels in, parameters out)
 // ---------------------------------------------------------------------------------------------
 //
-// One workgroup; thread h owns hidden unit h (its row of W1, b1[h], w2[h]) and its gradients, so the
-// only cross-thread quantity is the pre-sigmoid output z of a sample (a workgroup sum per sample).
-// The standardised training set sits in LDS for the whole run.  Full-batch gradient descent on the
-// mean binary cross-entropy; all arithmetic fp32 except the feature statistics (double).
+// One workgroup of 16 wavefronts.  A unit of work is a tile of 16 examples: both products of a gradient step are
+// contractions over 16 (the 12 features, a constant 1 for b1, three zeros), so they run on the fp32 matrix instruction
+// 16x16x4.  Forward, D[example][unit] = F . W1^T: lane l holds unit l % 16 and the four examples 4 (l / 16) + v, so the
+// pre-sigmoid output is a weighted sum over the lanes of a row (DPP), the example's error comes back as four in-row
+// broadcasts, and the masked errors are already the A operand of the backward product G[unit][feature] = M^T . F whose
+// k index runs over l / 16.  Tiles are dealt round-robin to the wavefronts; their G (and the gradient of w2, one more sum
+// over the same lanes) are added up in wavefront order through LDS and every parameter is updated by the thread that
+// owns it: results do not depend on timing.  All arithmetic fp32 except the feature statistics (double).
+// What bounds it is the issue rate of one compute unit (a tile is 32 matrix and about 250 vector instructions, the update
+// of the parameters another 130 per wavefront, four wavefronts on a SIMD) and two workgroup barriers: 4.4 us a step at
+// 200 examples and 64 units.  The form before took one example after another (a workgroup-wide sum per example, about
+// 480 ns each): 38.4 ms for 400 such steps, 1.77 ms now.  More workgroups would put a hand-off between workgroups (about
+// 2.5 us) into every step.
 
-constexpr int TRAIN_MAX_N = 2560;               // samples that fit in LDS (12 floats each)
+constexpr int TRAIN_MAX_N = 2560;               // examples that fit in LDS (12 floats each)
+constexpr int TRAIN_NW = 16;
 
-__global__ __launch_bounds__(256) void k_clf_train(TrainArgs a) {
-  __shared__ float fs[TRAIN_MAX_N * 12];
-  __shared__ float mu_s[12], isd_s[12];
-  __shared__ float zpart[4];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, nw = blockDim.x >> 6;
-  const int N = a.n, H = a.hidden;
-  if (t < 12) {
+// Workgroup barrier that orders LDS accesses only: __syncthreads also waits for the wavefront's stores to memory (the
+// loss of the step), a round trip of half a microsecond.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// HT: 16-unit tiles of the hidden layer; NMAX: examples that the LDS array holds; PW: tiles per reduction pass (all of
+// them in one pass where the LDS has room for 16 wavefronts' gradients beside the examples).
+template <int HT, int NMAX, int PW>
+__global__ __launch_bounds__(TRAIN_NW * 64) void k_clf_train(TrainArgs a) {
+  constexpr int NW = TRAIN_NW, NP = HT / PW;
+  constexpr bool KEEP = HT <= 4;                  // activations stay in registers between the two products (else: computed again)
+  static_assert(HT % PW == 0 && PW * 256 <= NW * 64 && NMAX % 16 == 0, "one owner thread per parameter and pass");
+  __shared__ float fs[NMAX * 12];                 // standardised examples
+  __shared__ f32x4 wB[HT][64];                    // [W1 | b1] as B operands: lane 16 (i % 4) + h % 16, component i / 4
+  __shared__ float w2s[2][HT * 16];               // this step's and the next step's w2
+  __shared__ f32x4 red[NW][PW][64];
+  __shared__ float red2[NW][PW * 16];
+  __shared__ float red3[NW][2];
+  constexpr bool YS = NMAX <= TRAIN_MAX_N / 2;    // room for the labels too
+  __shared__ float ys[YS ? NMAX : 1];
+  __shared__ float mu_s[12], isd_s[12], b2_s;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 15, g = lane >> 4;
+  const int N = a.n, H = a.hidden, tiles = (N + 15) >> 4;
+  if (w < 12) {                                   // wavefront w: mean and deviation of feature w, in a fixed order
     double sum = 0.0;
-    for (int n = 0; n < N; ++n) sum += (double)a.feats[(size_t)n * 12 + t];
+    for (int n = lane; n < N; n += 64) sum += (double)a.feats[(size_t)n * 12 + w];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
     const double mu = sum / N;
     double var = 0.0;
-    for (int n = 0; n < N; ++n) { const double d = (double)a.feats[(size_t)n * 12 + t] - mu; var += d * d; }
+    for (int n = lane; n < N; n += 64) { const double x = (double)a.feats[(size_t)n * 12 + w] - mu; var += x * x; }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) var += __shfl_xor(var, d);
     double sd = sqrt(var / N);
     if (sd < 1e-6) sd = 1e-6;
-    mu_s[t] = (float)mu; isd_s[t] = (float)(1.0 / sd);
+    if (lane == 0) { mu_s[w] = (float)mu; isd_s[w] = (float)(1.0 / sd); }
   }
   __syncthreads();
-  for (int i = t; i < N * 12; i += blockDim.x) fs[i] = (a.feats[i] - mu_s[i % 12]) * isd_s[i % 12];
-  const bool live = t < H;
-  float w1[12], b1 = 0.f, w2 = 0.f, b2 = a.params[H * 14];
+  for (int i = t; i < tiles * 16 * 12; i += NW * 64) fs[i] = i < N * 12 ? (a.feats[i] - mu_s[i % 12]) * isd_s[i % 12] : 0.f;
+  if (YS) for (int i = t; i < tiles * 16; i += NW * 64) ys[i] = i < N ? (float)a.labels[i] : 0.f;
+  // the parameters this thread owns: of pass p, element t of the pass's G records (unit h, column i: 12 weights, then b1),
+  // and for t < 16 PW the w2 of unit (16 PW) p + t
+  float own[NP], own2[NP];
+  const int oi = (t >> 2) & 15;
+  auto own_h = [&](int p) { return (p * PW + (t >> 8)) * 16 + 4 * ((t >> 6) & 3) + (t & 3); };
 #pragma unroll
-  for (int i = 0; i < 12; ++i) w1[i] = live ? a.params[t * 12 + i] : 0.f;
-  if (live) { b1 = a.params[H * 12 + t]; w2 = a.params[H * 13 + t]; }
+  for (int p = 0; p < NP; ++p) {
+    own[p] = 0.f; own2[p] = 0.f;
+    if (t < PW * 256) {
+      const int h = own_h(p);
+      if (h < H && oi < 12) own[p] = a.params[h * 12 + oi];
+      if (h < H && oi == 12) own[p] = a.params[H * 12 + h];
+      reinterpret_cast<float*>(&wB[h >> 4][(oi & 3) * 16 + (h & 15)])[oi >> 2] = own[p];
+    }
+    if (t < PW * 16) {
+      const int h = p * PW * 16 + t;
+      if (h < H) own2[p] = a.params[H * 13 + h];
+      w2s[0][h] = own2[p];
+    }
+  }
+  float b2 = a.params[H * 14];
+  if (t == 0) b2_s = b2;
   __syncthreads();
   const float inv_n = 1.0f / (float)N;
-  for (int ep = 0; ep < a.epochs; ++ep) {
-    float gw1[12], gb1 = 0.f, gw2 = 0.f, gb2 = 0.f, loss = 0.f;
+  int cur = 0;
+  for (int ep = 0; ep < a.epochs; ++ep, cur ^= 1) {
+    f32x4 G[HT];
+    float gw2[HT], gb2 = 0.f, loss = 0.f;
 #pragma unroll
-    for (int i = 0; i < 12; ++i) gw1[i] = 0.f;
-    for (int n = 0; n < N; ++n) {
-      const float* f = fs + n * 12;
-      float pre = b1;
+    for (int r = 0; r < HT; ++r) { G[r] = f32x4{0.f, 0.f, 0.f, 0.f}; gw2[r] = 0.f; }
+    const float bias2 = b2_s;
+    for (int tile = w; tile < tiles; tile += NW) {
+      const int n0 = tile * 16, mine = n0 + 4 * g + (lane & 3);        // the example whose error this lane forms
+      const bool live = mine < N;
+      const float y = YS ? ys[mine] : (float)a.labels[live ? mine : N - 1];
+      float fa[4], fb[4];
 #pragma unroll
-      for (int i = 0; i < 12; ++i) pre += w1[i] * f[i];
-      const float act = live ? fmaxf(pre, 0.f) : 0.f;
-      float z = wave_sum(w2 * act);
-      if (nw > 1) {
-        if (lane == 0) zpart[wv] = z;
-        __syncthreads();
-        z = zpart[0];
-        for (int ww = 1; ww < nw; ++ww) z += zpart[ww];
-        __syncthreads();
+      for (int j = 0; j < 3; ++j) fa[j] = fs[(n0 + col) * 12 + 4 * j + g];
+      fa[3] = (g == 0 && n0 + col < N) ? 1.f : 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        fb[v] = fs[(n0 + 4 * g + v) * 12 + min(col, 11)];
+        asm volatile("" : "+v"(fb[v]));           // (a load for every lane: no branch around it)
+        fb[v] = col < 12 ? fb[v] : (col == 12 ? 1.f : 0.f);
       }
-      z += b2;
-      const float y = (float)a.labels[n];
-      loss += fmaxf(z, 0.f) - z * y + log1pf(expf(-fabsf(z)));
-      const float dz = (1.0f / (1.0f + expf(-z)) - y) * inv_n;
-      gw2 += dz * act;
-      gb2 += dz;
-      const float da = pre > 0.f ? dz * w2 : 0.f;
-      gb1 += da;
+      auto forward = [&](int r) {
+        f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f};
+        const f32x4 wv = wB[r][lane];
 #pragma unroll
-      for (int i = 0; i < 12; ++i) gw1[i] += da * f[i];
+        for (int j = 0; j < 4; ++j) p = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j], wv[j], p, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p[v] = fmaxf(p[v], 0.f);
+        return p;
+      };
+      f32x4 act[KEEP ? HT : 1], z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < HT; ++r) {
+        const f32x4 p = forward(r);
+        const float w2 = w2s[cur][r * 16 + col];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[v] += w2 * p[v];
+        if (KEEP) act[r] = p;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        z[v] += dpp_f<DPP_QUAD_XOR1, 0xF>(0.f, z[v]);
+        z[v] += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, z[v]);
+        z[v] += dpp_f<DPP_ROW_HALF_MIRROR, 0xF>(0.f, z[v]);
+        z[v] += dpp_f<DPP_ROW_MIRROR, 0xF>(0.f, z[v]);
+      }
+      const int vm = lane & 3;
+      const float zz = (vm == 0 ? z[0] : vm == 1 ? z[1] : vm == 2 ? z[2] : z[3]) + bias2;
+      // sigmoid(z) and log(1 + e^-|z|) from one exponential; the logarithm's argument rounds to u, which is put right by
+      // the factor E / (u - 1) (the library's log1pf was a third of the step's instructions)
+      const float E = expf(-fabsf(zz)), u = 1.0f + E, ru = 1.0f / u, du = u - 1.0f;
+      float dz = ((zz >= 0.f ? ru : E * ru) - y) * inv_n;
+      dz = live ? dz : 0.f;
+      const float term = fmaxf(zz, 0.f) - zz * y + (du == 0.f ? E : logf(u) * (E / du));
+      gb2 += col < 4 ? dz : 0.f;
+      loss += live && col < 4 ? term : 0.f;
+      const float e[4] = {dpp_f<0x00, 0xF>(dz, dz), dpp_f<0x55, 0xF>(dz, dz), dpp_f<0xAA, 0xF>(dz, dz), dpp_f<0xFF, 0xF>(dz, dz)};
+#pragma unroll
+      for (int r = 0; r < HT; ++r) {
+        const f32x4 p = KEEP ? act[KEEP ? r : 0] : forward(r);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          gw2[r] += e[v] * p[v];
+          G[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[v] > 0.f ? e[v] : 0.f, fb[v], G[r], 0, 0, 0);
+        }
+      }
     }
-    if (t == 0 && a.loss) a.loss[ep] = loss * inv_n;
+    gb2 = wave_sum(gb2); loss = wave_sum(loss);
 #pragma unroll
-    for (int i = 0; i < 12; ++i) w1[i] -= a.lr * gw1[i];
-    b1 -= a.lr * gb1; w2 -= a.lr * gw2; b2 -= a.lr * gb2;
+    for (int p = 0; p < NP; ++p) {
+      if (p > 0) lds_barrier();                   // the pass before has been read
+#pragma unroll
+      for (int q = 0; q < PW; ++q) {
+        red[w][q][lane] = G[p * PW + q];
+        red2[w][q * 16 + col] = row4_sum(gw2[p * PW + q]);   // four lanes, one value
+      }
+      if (p == 0 && lane == 0) { red3[w][0] = gb2; red3[w][1] = loss; }
+      lds_barrier();
+      if (t < PW * 256) {
+        const float* rp = reinterpret_cast<const float*>(&red[0][0][0]) + t;
+        float s = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) s += rp[ww * PW * 256];
+        const int h = own_h(p);
+        if (h < H && oi < 13) {
+          own[p] -= a.lr * (s * w2s[cur][h]);
+          reinterpret_cast<float*>(&wB[h >> 4][(oi & 3) * 16 + (h & 15)])[oi >> 2] = own[p];
+        }
+      }
+      if (t < PW * 16) {
+        float s = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) s += red2[ww][t];
+        own2[p] -= a.lr * s;
+        w2s[cur ^ 1][p * PW * 16 + t] = own2[p];
+      }
+      if (p == 0 && t == NW * 64 - 1) {           // the last wavefront: in most shapes it owns the fewest live parameters
+        float sb = 0.f, sl = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) { sb += red3[ww][0]; sl += red3[ww][1]; }
+        b2 -= a.lr * sb;
+        b2_s = b2;
+        if (a.loss) a.loss[ep] = sl * inv_n;
+      }
+    }
+    lds_barrier();
   }
   // fold the standardisation into W1 and b1: the classifier consumes raw features
-  if (live) {
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (t < PW * 256) {
+      const int h = own_h(p);
+      if (h < H && oi < 12) a.params[h * 12 + oi] = own[p] * isd_s[oi];
+    }
+    if (t < PW * 16 && p * PW * 16 + t < H) a.params[H * 13 + p * PW * 16 + t] = own2[p];
+  }
+  if (t < H) {
     float shift = 0.f;
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
-      const float wf = w1[i] * isd_s[i];
-      a.params[t * 12 + i] = wf;
-      shift += wf * mu_s[i];
-    }
-    a.params[H * 12 + t] = b1 - shift;
-    a.params[H * 13 + t] = w2;
+    for (int i = 0; i < 12; ++i) shift += reinterpret_cast<const float*>(&wB[t >> 4][(i & 3) * 16 + (t & 15)])[i >> 2] * isd_s[i] * mu_s[i];
+    a.params[H * 12 + t] = reinterpret_cast<const float*>(&wB[t >> 4][t & 15])[3] - shift;
   }
-  if (t == 0) a.params[H * 14] = b2;
+  if (t == NW * 64 - 1) a.params[H * 14] = b2;
+}
+
+template <int HT, int PW>
+static void launch_clf_train_ht(const TrainArgs& a, hipStream_t s) {
+  if (a.n <= TRAIN_MAX_N / 2) hipLaunchKernelGGL((k_clf_train<HT, TRAIN_MAX_N / 2, PW>), dim3(1), dim3(TRAIN_NW * 64), 0, s, a);
+  else hipLaunchKernelGGL((k_clf_train<HT, TRAIN_MAX_N, 1>), dim3(1), dim3(TRAIN_NW * 64), 0, s, a);
 }
 
 hipError_t launch_clf_train(const TrainArgs& a, hipStream_t s) {
   if (a.n < 1 || a.n > TRAIN_MAX_N || a.hidden < 1 || a.hidden > 256 || a.epochs < 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_clf_train, dim3(1), dim3(((a.hidden + 63) / 64) * 64), 0, s, a);
+  if (a.hidden <= 32) launch_clf_train_ht<2, 2>(a, s);
+  else if (a.hidden <= 64) launch_clf_train_ht<4, 4>(a, s);
+  else if (a.hidden <= 128) launch_clf_train_ht<8, 4>(a, s);
+  else launch_clf_train_ht<16, 4>(a, s);
   return hipGetLastError();
 }
 
 // Scores of given feature vectors and the confusion counts of "accepted iff C >= tau" against the
 // labels: counts[0..3] = true positives, false positives, false negatives, true negatives.
+// The parameters go to LDS once per workgroup and four threads share an example's hidden units (a quarter each, added in
+// quarter order): a thread that read all the parameters from memory waited for one unit's after another's
+// (200 examples, 64 units: 12.8 us, 5.5 us now).
 __global__ __launch_bounds__(256) void k_clf_eval(EvalArgs a) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= a.n) return;
-  const int H = a.hidden;
+  __shared__ float ps[256 * 14 + 1];
+  __shared__ float part[4][64];
+  const int e = threadIdx.x & 63, quarter = threadIdx.x >> 6, H = a.hidden;
+  const int n = blockIdx.x * 64 + e;
+  for (int i = threadIdx.x; i < H * 14 + 1; i += 256) ps[i] = a.params[i];
   float f[12];
 #pragma unroll
-  for (int i = 0; i < 12; ++i) f[i] = a.feats[(size_t)n * 12 + i];
+  for (int i = 0; i < 12; ++i) f[i] = n < a.n ? a.feats[(size_t)n * 12 + i] : 0.f;
+  __syncthreads();
+  const int h1 = H * (quarter + 1) / 4;
   float z = 0.f;
-  for (int h = 0; h < H; ++h) {                    // fixed order
-    float pre = a.params[H * 12 + h];
+  for (int h = H * quarter / 4; h < h1; ++h) {     // fixed order
+    float pre = ps[H * 12 + h];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) pre += a.params[h * 12 + i] * f[i];
-    z += fmaxf(pre, 0.f) * a.params[H * 13 + h];
+    for (int i = 0; i < 12; ++i) pre += ps[h * 12 + i] * f[i];
+    z += fmaxf(pre, 0.f) * ps[H * 13 + h];
   }
-  const float c = 1.0f / (1.0f + expf(-(z + a.params[H * 14])));
+  part[quarter][e] = z;
+  __syncthreads();
+  if (quarter != 0 || n >= a.n) return;
+  z = (part[0][e] + part[1][e]) + (part[2][e] + part[3][e]);
+  const float c = 1.0f / (1.0f + expf(-(z + ps[H * 14])));
   if (a.scores) a.scores[n] = c;
   if (a.counts && a.labels) {
     const int pred = c >= a.tau ? 1 : 0, y = a.labels[n] != 0 ? 1 : 0;
@@ -2279,7 +2425,7 @@ __global__ __launch_bounds__(256) void k_clf_eval(EvalArgs a) {
 
 hipError_t launch_clf_eval(const EvalArgs& a, hipStream_t s) {
   if (a.n < 1 || a.hidden < 1 || a.hidden > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_clf_eval, dim3((a.n + 255) / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_clf_eval, dim3((a.n + 63) / 64), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

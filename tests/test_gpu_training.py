@@ -76,6 +76,23 @@ def test_train_matches_oracle(n, hidden, epochs):
     assert torch.equal(clf2.dev, clf.dev) and torch.equal(loss2, loss)
 
 
+@pytest.mark.parametrize("n,hidden", [(1, 1), (15, 33), (16, 16), (17, 65), (63, 256), (65, 128), (1280, 31), (1281, 129), (2560, 256)])
+def test_train_tile_edges_match_oracle(n, hidden):
+    """Tiles of 16 examples dealt to 16 wavefronts, tiles of 16 hidden units in templates of 32 / 64 / 128 / 256 units, examples in
+    LDS up to 1280 beside one reduction pass and up to 2560 beside several: the edges of each, at the bars of the test above."""
+    feats, y, init = _data(n, 3 * n + hidden, hidden)
+    want, losses = O.clf_train(feats, y, init, 12, 0.1)
+    clf, loss = _gpu_train(feats, y, init, 12, 0.1)
+    assert torch.allclose(loss.double(), torch.tensor(losses, dtype=torch.float64), rtol=2e-4, atol=2e-6)
+    got = clf.params()
+    for k in ("W1", "b1", "w2", "b2"):
+        scale = float(want[k].abs().max())
+        assert float((got[k] - want[k]).abs().max()) <= 2e-3 * scale + 1e-5, k
+    scores, counts = _gpu_eval(clf, feats, y, 0.5)
+    ref = torch.tensor(O.clf_eval(feats, y, want, 0.5)["scores"])
+    assert float((scores.double() - ref).abs().max()) < 1e-3 and sum(counts) == n
+
+
 def test_eval_counts_by_hand_and_zero_epochs():
     zero = {"W1": torch.zeros(4, 12), "b1": torch.zeros(4), "w2": torch.zeros(4), "b2": torch.zeros(1)}
     lab = torch.tensor([1, 1, 0, 1, 0], dtype=torch.int32)
