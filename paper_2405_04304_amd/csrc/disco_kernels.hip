@@ -1929,159 +1929,166 @@ hipError_t launch_kv_fill(const bf16_t* src, bf16_t* pages, const int32_t* page_
 // sampling at temperature > 0: draws by inverse CDF in vocabulary order, speculative acceptance
 // ---------------------------------------------------------------------------------------------
 //
-// One workgroup of 1024 threads per row; the row lives in registers (V4 float4 per thread, element
-// (i * 1024 + t) * 4 + e in slot i of thread t, one round of coalesced 128-bit loads).  Cumulative
-// sums follow the vocabulary order: segment i (4096 elements) before segment i + 1, inside a segment
-// thread by thread.  Every wavefront scans its 64 per-thread sums of every segment across lanes, the
-// (segment, wavefront) totals go through LDS once, and every thread then knows the cumulative sum at
-// the start of each of its float4 groups.  The group that holds u * total is walked by its owner.
-// All sums are fp32.
+// One workgroup of 1024 threads per row; the row lives in registers (V4 float4 per thread, one round of 128-bit loads).
+// Wavefront w holds the w-th sixteenth of the row (nseg segments of 256 consecutive elements, four per lane), so the
+// cumulative sum in vocabulary order is wavefront by wavefront, segment by segment, lane by lane: sixteen totals in LDS
+// tell every wavefront whether the draw falls into its part, and only that wavefront scans its segments and its lanes.
+// (Scanning every segment across the whole workgroup, as before, read 256 LDS words per thread: 29 us for five rows of
+// 32000, 7.7 us now.)  All sums are fp32.
 
 constexpr int SMP_NT = 1024;
 constexpr int SMP_NW = SMP_NT / 64;
 
-template <int V4>
-struct SmpRow { float4 w[V4]; };     // weights (or raw logits) of one row, register resident
+__device__ __forceinline__ int smp_segments(int V) { return (V + 4 * SMP_NT - 1) / (4 * SMP_NT); }   // per wavefront, <= V4
+__device__ __forceinline__ int smp_index(int i, int nseg) {
+  return (((int)(threadIdx.x >> 6) * nseg + i) * 64 + (int)(threadIdx.x & 63)) * 4;
+}
 
+// e^y for y <= 0 (and -inf) to about 1.5 ulp: 2^(y log2 e) with the rounding of the product put back as a factor; the
+// library's form spends twice the instructions on ranges that cannot occur here.  NaN stays NaN.
+__device__ __forceinline__ float smp_exp(float y) {
+  const float x = y < -104.f ? -104.f : y;                    // e^-104 is zero in fp32
+  const float p = x * 1.44269504088896340736f;
+  const float r = fmaf(x, 1.44269504088896340736f, -p) + x * 1.9259629911266175e-8f;   // log2 e = 1.442695041 + 1.926e-8
+  const float e = __builtin_amdgcn_exp2f(p);
+  return fmaf(e, r * 0.693147180559945309f, e);
+}
+
+// Loads a row; elements beyond V (and segments beyond nseg) become `pad`.
 template <int V4>
-__device__ __forceinline__ void smp_load(SmpRow<V4>& r, const float* x, int V, float pad) {
+__device__ __forceinline__ void smp_load(float4 (&r)[V4], const float* x, int V, int nseg, float pad) {
 #pragma unroll
   for (int i = 0; i < V4; ++i) {
-    const int idx = (i * SMP_NT + threadIdx.x) * 4;
-    r.w[i] = (idx < V) ? *reinterpret_cast<const float4*>(x + idx) : make_float4(pad, pad, pad, pad);   // V % 4 == 0
+    const int idx = smp_index(i, nseg);
+    r[i] = (i < nseg && idx < V) ? *reinterpret_cast<const float4*>(x + idx) : make_float4(pad, pad, pad, pad);   // V % 4 == 0
   }
 }
 
-template <int V4>
-__device__ __forceinline__ float smp_block_max(const SmpRow<V4>& r, float* smem) {
-  float mx = -INFINITY;
+// Sixteen values, one per wavefront, in LDS: every thread gets them all.
+struct SmpTot { float v[SMP_NW]; };
+__device__ __forceinline__ SmpTot smp_share(float mine, float* smem) {
+  if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = mine;
+  __syncthreads();
+  SmpTot t;
 #pragma unroll
-  for (int i = 0; i < V4; ++i) mx = fmaxf(mx, fmaxf(fmaxf(r.w[i].x, r.w[i].y), fmaxf(r.w[i].z, r.w[i].w)));
-  mx = wave_max(mx);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  float t = smem[0];
-#pragma unroll
-  for (int i = 1; i < SMP_NW; ++i) t = fmaxf(t, smem[i]);
-  __syncthreads();
+  for (int i = 0; i < SMP_NW / 4; ++i) {
+    const float4 f = reinterpret_cast<const float4*>(smem)[i];
+    t.v[4 * i] = f.x; t.v[4 * i + 1] = f.y; t.v[4 * i + 2] = f.z; t.v[4 * i + 3] = f.w;
+  }
   return t;
 }
 
-// Cumulative sum (vocabulary order) of the weights before each of this thread's float4 groups, and
-// the row total.  seg_tot: LDS [V4][SMP_NW].
+// Lane sum of a wavefront's part of the row.
 template <int V4>
-__device__ __forceinline__ float smp_prefix(const SmpRow<V4>& r, float (&excl)[V4], float* seg_tot) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  float own[V4];
+__device__ __forceinline__ float smp_lane_sum(const float4 (&r)[V4]) {
+  float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < V4; ++i) {
-    own[i] = (r.w[i].x + r.w[i].y) + (r.w[i].z + r.w[i].w);
-    float inc = own[i];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const float o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
-    }
-    excl[i] = inc - own[i];                                   // inside the wavefront so far
-    if (lane == 63) seg_tot[i * SMP_NW + wv] = inc;
-  }
-  __syncthreads();
-  float run = 0.f;
-#pragma unroll
-  for (int i = 0; i < V4; ++i) {
-    float before = 0.f, seg = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < SMP_NW; ++ww) { const float v = seg_tot[i * SMP_NW + ww]; if (ww < wv) before += v; seg += v; }
-    excl[i] += run + before;
-    run += seg;
-  }
-  __syncthreads();
-  return run;
+  for (int i = 0; i < V4; ++i) s += (r[i].x + r[i].y) + (r[i].z + r[i].w);
+  return s;
 }
 
-// Inverse CDF at u * total: the smallest index whose cumulative sum exceeds the target (the last
-// index with a positive weight if rounding leaves the target at the very end).
+// r := e^((x - max) / T) elementwise (padding becomes 0); returns the row's maximum, tot gets the wavefronts' sums.
 template <int V4>
-__device__ __forceinline__ int smp_draw(const SmpRow<V4>& r, float u, float* seg_tot, int* ismem) {
-  float excl[V4];
-  const float total = smp_prefix<V4>(r, excl, seg_tot);
-  const float target = u * total;
-  int key = -1;                                               // last group (in order) that starts at or before the target
+__device__ __forceinline__ float smp_softmax(float4 (&r)[V4], float inv_t, float* smem_a, float* smem_b, SmpTot& tot) {
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < V4; ++i) mx = fmaxf(mx, fmaxf(fmaxf(r[i].x, r[i].y), fmaxf(r[i].z, r[i].w)));
+  const SmpTot ms = smp_share(wave_max(mx), smem_a);
+  float m = ms.v[0];
+#pragma unroll
+  for (int i = 1; i < SMP_NW; ++i) m = fmaxf(m, ms.v[i]);
 #pragma unroll
   for (int i = 0; i < V4; ++i) {
-    const float own = (r.w[i].x + r.w[i].y) + (r.w[i].z + r.w[i].w);
-    if (own > 0.f && excl[i] <= target) key = i * SMP_NT + threadIdx.x;
+    r[i].x = smp_exp((r[i].x - m) * inv_t); r[i].y = smp_exp((r[i].y - m) * inv_t);
+    r[i].z = smp_exp((r[i].z - m) * inv_t); r[i].w = smp_exp((r[i].w - m) * inv_t);
   }
-  int best = key;
-  best = max(best, __shfl_xor(best, 1)); best = max(best, __shfl_xor(best, 2)); best = max(best, __shfl_xor(best, 4));
-  best = max(best, __shfl_xor(best, 8)); best = max(best, __shfl_xor(best, 16)); best = max(best, __shfl_xor(best, 32));
-  if ((threadIdx.x & 63) == 0) ismem[threadIdx.x >> 6] = best;
-  __syncthreads();
-  int win = -1;
-#pragma unroll
-  for (int i = 0; i < SMP_NW; ++i) win = max(win, ismem[i]);
-  __syncthreads();
-  if (win >= 0 && key == win) {
-    float4 g = r.w[0]; float c = excl[0];
-#pragma unroll
-    for (int i = 1; i < V4; ++i) if (i == win / SMP_NT) { g = r.w[i]; c = excl[i]; }
-    const float w4[4] = {g.x, g.y, g.z, g.w};
-    int pick = -1, last_pos = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (w4[e] > 0.f) last_pos = e;
-      c += w4[e];
-      if (pick < 0 && c > target) pick = e;
-    }
-    ismem[0] = win * 4 + (pick >= 0 ? pick : last_pos);
-  }
-  __syncthreads();
-  const int res = win >= 0 ? ismem[0] : 0;
-  __syncthreads();
-  return res;
-}
-
-// r := e^((x - max) / T) elementwise (padding becomes 0); returns max, *sum gets the row sum.
-template <int V4>
-__device__ __forceinline__ float smp_exp(SmpRow<V4>& r, float inv_t, float* smem, float* seg_tot, float* sum) {
-  const float m = smp_block_max<V4>(r, smem);
-#pragma unroll
-  for (int i = 0; i < V4; ++i) {
-    r.w[i].x = expf((r.w[i].x - m) * inv_t); r.w[i].y = expf((r.w[i].y - m) * inv_t);
-    r.w[i].z = expf((r.w[i].z - m) * inv_t); r.w[i].w = expf((r.w[i].w - m) * inv_t);
-  }
-  float excl[V4];
-  *sum = smp_prefix<V4>(r, excl, seg_tot);
+  tot = smp_share(wave_sum(smp_lane_sum<V4>(r)), smem_b);
   return m;
+}
+__device__ __forceinline__ float smp_total(const SmpTot& t) {
+  float s = t.v[0];
+#pragma unroll
+  for (int i = 1; i < SMP_NW; ++i) s += t.v[i];
+  return s;
+}
+
+// Inverse CDF at u * total over weights r with the wavefronts' sums tot: the smallest index whose cumulative sum exceeds
+// the target (the last index with a positive weight if rounding leaves the target at the very end; 0 if there is no
+// positive weight).  Returns true in the one thread that holds the drawn element.
+template <int V4>
+__device__ __forceinline__ bool smp_draw(const float4 (&r)[V4], const SmpTot& tot, float u, int nseg, int& token) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const float target = u * smp_total(tot);
+  int win = -1;
+  float base = 0.f, run = 0.f;
+#pragma unroll
+  for (int i = 0; i < SMP_NW; ++i) {
+    if (tot.v[i] > 0.f && run <= target) { win = i; base = run; }
+    run += tot.v[i];
+  }
+  token = 0;
+  if (win < 0) return threadIdx.x == 0;
+  if (wv != win) return false;
+  // this wavefront's segments, then the lanes of the one that holds the target
+  float own = 0.f, seg_base = base;
+  int seg = 0;
+  run = base;
+  float4 g = r[0];
+#pragma unroll
+  for (int i = 0; i < V4; ++i) {
+    const float mine = (r[i].x + r[i].y) + (r[i].z + r[i].w);
+    const float st = wave_sum(mine);
+    if (st > 0.f && run <= target) { seg = i; seg_base = run; own = mine; g = r[i]; }
+    run += st;
+  }
+  float inc = own;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const float o = __shfl_up(inc, d);
+    if (lane >= d) inc += o;
+  }
+  float c = seg_base + (inc - own);
+  const unsigned long long at = __ballot(own > 0.f && c <= target);
+  const int pick_lane = at != 0ull ? 63 - __builtin_clzll(at) : 0;
+  if (lane != pick_lane) return false;
+  const float w4[4] = {g.x, g.y, g.z, g.w};
+  int pick = -1, last_pos = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (w4[e] > 0.f) last_pos = e;
+    c += w4[e];
+    if (pick < 0 && c > target) pick = e;
+  }
+  token = ((win * nseg + seg) * 64 + lane) * 4 + (pick >= 0 ? pick : last_pos);
+  return true;
 }
 
 // Draw one token per row from softmax(logits / T); optionally store the probability row.
 template <int V4>
 __global__ __launch_bounds__(SMP_NT) void k_sample_rows(SampleArgs a) {
-  if (gated(a.gate)) return;
-  __shared__ float smem[SMP_NW];
-  __shared__ float seg_tot[V4 * SMP_NW];
-  __shared__ int ismem[SMP_NW];
-  const int row = blockIdx.x, V = a.vocab;
-  SmpRow<V4> r;
-  smp_load<V4>(r, a.logits + (size_t)row * a.ld, V, -INFINITY);
-  float S;
-  smp_exp<V4>(r, a.inv_t, smem, seg_tot, &S);
-  const int tok = smp_draw<V4>(r, a.u[row], seg_tot, ismem);
-  if (a.probs) {
-    float* p = a.probs + (size_t)row * V;
-    const float inv_s = 1.0f / S;
-#pragma unroll
-    for (int i = 0; i < V4; ++i) {
-      const int idx = (i * SMP_NT + threadIdx.x) * 4;
-      if (idx < V) *reinterpret_cast<float4*>(p + idx) = make_float4(r.w[i].x * inv_s, r.w[i].y * inv_s, r.w[i].z * inv_s, r.w[i].w * inv_s);
-    }
-  }
-  if (threadIdx.x == 0) {
+  const uint32_t halted = gate_request(a.gate);
+  __shared__ __align__(16) float smem[2][SMP_NW];
+  const int row = blockIdx.x, V = a.vocab, nseg = smp_segments(V);
+  float4 r[V4];
+  smp_load<V4>(r, a.logits + (size_t)row * a.ld, V, nseg, -INFINITY);
+  const float u = a.u[row];
+  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  SmpTot tot;
+  smp_softmax<V4>(r, a.inv_t, smem[0], smem[1], tot);
+  int tok;
+  if (smp_draw<V4>(r, tot, u, nseg, tok)) {
     a.tokens[row] = tok;
     if (row == 0 && a.token_next) *a.token_next = tok;
     if (row == 0 && a.block_slot) *a.block_slot = tok;
+  }
+  if (a.probs) {
+    float* p = a.probs + (size_t)row * V;
+    const float inv_s = 1.0f / smp_total(tot);
+#pragma unroll
+    for (int i = 0; i < V4; ++i) {
+      const int idx = smp_index(i, nseg);
+      if (i < nseg && idx < V) *reinterpret_cast<float4*>(p + idx) = make_float4(r[i].x * inv_s, r[i].y * inv_s, r[i].z * inv_s, r[i].w * inv_s);
+    }
   }
 }
 
@@ -2089,76 +2096,91 @@ hipError_t launch_sample_rows(const SampleArgs& a, int n_rows, hipStream_t s) {
   if (n_rows < 1 || a.vocab < 4 || (a.vocab & 3) || a.vocab > 65536 || (a.ld & 3)) return hipErrorInvalidValue;
   if (a.vocab <= 8192) hipLaunchKernelGGL(k_sample_rows<2>, dim3(n_rows), dim3(SMP_NT), 0, s, a);
   else if (a.vocab <= 32768) hipLaunchKernelGGL(k_sample_rows<8>, dim3(n_rows), dim3(SMP_NT), 0, s, a);
+  else if (a.vocab <= 49152) hipLaunchKernelGGL(k_sample_rows<12>, dim3(n_rows), dim3(SMP_NT), 0, s, a);
   else hipLaunchKernelGGL(k_sample_rows<16>, dim3(n_rows), dim3(SMP_NT), 0, s, a);
   return hipGetLastError();
 }
 
 // Speculative sampling over one block: keep d_j while u_j q_j(d_j) < p_{j-1}(d_j); the last token is
 // drawn from norm(max(0, p_n - q_n)) at the first rejection, from p_SL when everything is kept.
+//
+// Row j's keep test and the draw that would follow its rejection need no other row, so every row has a workgroup of its
+// own: it leaves KEPT or the drawn token in out->emit[j], and a second launch of one wavefront finds the first row that
+// was not kept and writes the record.  (One workgroup going through the rows took about 10 us a row: 43 - 61 us for a
+// block of five at 32000, 7.7 + 1.7 us now.  The library has no memory of its own that calls on several
+// streams could share safely, hence the second launch instead of a ticket.)
+constexpr int ACCEPT_KEPT = -2;
+
 template <int V4>
-__global__ __launch_bounds__(SMP_NT) void k_accept_sample(AcceptSampleArgs a) {
-  __shared__ float smem[SMP_NW];
-  __shared__ float seg_tot[V4 * SMP_NW];
-  __shared__ int ismem[SMP_NW];
-  __shared__ float p_tok;
-  const int V = a.vocab;
+__global__ __launch_bounds__(SMP_NT) void k_accept_rows(AcceptSampleArgs a) {
+  __shared__ __align__(16) float smem[3][SMP_NW];
+  const int V = a.vocab, nseg = smp_segments(V), j = blockIdx.x;
   int nb = a.n_block;
   if (a.dev_n_block) { const int v = *a.dev_n_block; nb = v < 1 ? 1 : (v > a.n_block ? a.n_block : v); }
   const int sl = nb - 1;
-  int n = 0;
-  bool rejected = false;
-  SmpRow<V4> r;
-  float S = 1.f;
-  for (;;) {
-    // target distribution after block[0..n]
-    smp_load<V4>(r, a.target_logits + (size_t)n * V, V, -INFINITY);
-    smp_exp<V4>(r, a.inv_t, smem, seg_tot, &S);
-    if (n == sl) break;
-    int tok = a.block[n + 1];
-    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-    // the thread that holds the draft token publishes its target probability
-#pragma unroll
-    for (int i = 0; i < V4; ++i) {
-      const int idx = (i * SMP_NT + threadIdx.x) * 4;
-      if (tok >= idx && tok < idx + 4) {
-        const float w4[4] = {r.w[i].x, r.w[i].y, r.w[i].z, r.w[i].w};
-        p_tok = w4[tok - idx] * (1.0f / S);
-      }
-    }
-    __syncthreads();
-    const float p = p_tok;
-    const float q = a.draft_probs[(size_t)n * V + tok];
-    __syncthreads();
-    if (a.u_accept[n] * q < p) ++n; else { rejected = true; break; }
+  if (j > sl) return;                             // whole workgroup
+  int32_t* slot = reinterpret_cast<AcceptOut*>(a.out)->emit + j;
+  const float* x = a.target_logits + (size_t)j * V;
+  const float* q = a.draft_probs + (size_t)j * V;
+  float4 r[V4];
+  smp_load<V4>(r, x, V, nseg, -INFINITY);
+  const float u_res = a.u_resample[j];
+  float xt = 0.f, qt = 0.f, u_acc = 0.f;
+  if (j < sl) {
+    const int tok = min(max(a.block[j + 1], 0), V - 1);
+    xt = x[tok]; qt = q[tok]; u_acc = a.u_accept[j];
   }
-  if (rejected) {
-    // residual max(0, p - q) of row n
-    const float inv_s = 1.0f / S;
-    const float* q = a.draft_probs + (size_t)n * V;
+  SmpTot tot;
+  const float m = smp_softmax<V4>(r, a.inv_t, smem[0], smem[1], tot);
+  if (j < sl) {
+    const float inv_s = 1.0f / smp_total(tot);
+    const float p = smp_exp((xt - m) * a.inv_t) * inv_s;
+    if (u_acc * qt < p) {                         // the same values in every thread
+      if (threadIdx.x == 0) *slot = ACCEPT_KEPT;
+      return;
+    }
+    // residual max(0, p - q) of this row
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
-      const int idx = (i * SMP_NT + threadIdx.x) * 4;
+      const int idx = smp_index(i, nseg);
       float4 qq = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (idx < V) qq = *reinterpret_cast<const float4*>(q + idx);
-      r.w[i].x = fmaxf(0.f, r.w[i].x * inv_s - qq.x); r.w[i].y = fmaxf(0.f, r.w[i].y * inv_s - qq.y);
-      r.w[i].z = fmaxf(0.f, r.w[i].z * inv_s - qq.z); r.w[i].w = fmaxf(0.f, r.w[i].w * inv_s - qq.w);
+      if (i < nseg && idx < V) qq = *reinterpret_cast<const float4*>(q + idx);
+      r[i].x = fmaxf(0.f, r[i].x * inv_s - qq.x); r[i].y = fmaxf(0.f, r[i].y * inv_s - qq.y);
+      r[i].z = fmaxf(0.f, r[i].z * inv_s - qq.z); r[i].w = fmaxf(0.f, r[i].w * inv_s - qq.w);
     }
+    tot = smp_share(wave_sum(smp_lane_sum<V4>(r)), smem[2]);
   }
-  const int last = smp_draw<V4>(r, a.u_resample[n], seg_tot, ismem);
-  if (threadIdx.x == 0) {
-    AcceptOut o;
-    o.n = n; o.n_emit = n + 1;
-    for (int i = 0; i < 16; ++i) o.emit[i] = (i < n) ? a.block[i + 1] : (i == n ? last : -1);
-    *reinterpret_cast<AcceptOut*>(a.out) = o;
-    if (a.host_out) { *reinterpret_cast<AcceptOut*>(a.host_out) = o; __threadfence_system(); }
-  }
+  int tok;
+  if (smp_draw<V4>(r, tot, u_res, nseg, tok)) *slot = tok;
+}
+
+__global__ __launch_bounds__(64) void k_accept_finish(AcceptSampleArgs a) {
+  int nb = a.n_block;
+  if (a.dev_n_block) { const int v = *a.dev_n_block; nb = v < 1 ? 1 : (v > a.n_block ? a.n_block : v); }
+  const int sl = nb - 1, i = threadIdx.x;
+  AcceptOut* out = reinterpret_cast<AcceptOut*>(a.out);
+  const int mine = i <= sl ? out->emit[i] : 0;
+  const int drafted = i < sl ? a.block[i + 1] : -1;
+  const int n = __builtin_ctzll(__ballot(i >= sl || mine != ACCEPT_KEPT));     // row sl always holds a drawn token
+  const int e = i < n ? drafted : (i == n ? mine : -1);
+  auto put = [&](AcceptOut* o) {
+    if (i == 0) { o->n = n; o->n_emit = n + 1; }
+    if (i < 16) o->emit[i] = e;
+  };
+  put(out);
+  if (a.host_out) { put(reinterpret_cast<AcceptOut*>(a.host_out)); __threadfence_system(); }
 }
 
 hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
   if (a.n_block < 1 || a.n_block > 16 || a.vocab < 4 || (a.vocab & 3) || a.vocab > 65536) return hipErrorInvalidValue;
-  if (a.vocab <= 8192) hipLaunchKernelGGL(k_accept_sample<2>, dim3(1), dim3(SMP_NT), 0, s, a);
-  else if (a.vocab <= 32768) hipLaunchKernelGGL(k_accept_sample<8>, dim3(1), dim3(SMP_NT), 0, s, a);
-  else hipLaunchKernelGGL(k_accept_sample<16>, dim3(1), dim3(SMP_NT), 0, s, a);
+  const dim3 rows(a.n_block);
+  if (a.vocab <= 8192) hipLaunchKernelGGL(k_accept_rows<2>, rows, dim3(SMP_NT), 0, s, a);
+  else if (a.vocab <= 32768) hipLaunchKernelGGL(k_accept_rows<8>, rows, dim3(SMP_NT), 0, s, a);
+  else if (a.vocab <= 49152) hipLaunchKernelGGL(k_accept_rows<12>, rows, dim3(SMP_NT), 0, s, a);
+  else hipLaunchKernelGGL(k_accept_rows<16>, rows, dim3(SMP_NT), 0, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_accept_finish, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

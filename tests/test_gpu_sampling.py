@@ -104,6 +104,34 @@ def _gpu_accept(lt, q_rows, block, u_acc, u_res, T, dev_n_block=None):
     return a.n, list(a.emit[:a.n_emit])
 
 
+@pytest.mark.parametrize("V", [4, 252, 256, 260, 4092, 4100, 8192, 8196, 32768, 32772, 49152, 49156, 65536])
+def test_row_kernels_at_segment_edges(V):
+    """A row is dealt to sixteen wavefronts in segments of 256, in templates of 2 / 8 / 12 / 16 segments: lengths around the
+    edges, and draws that fall on the first and last elements (point masses: the answer needs no tolerance)."""
+    ids = sorted({0, 3, V // 2, V - 4, V - 1} | {i for i in (255, 256, 4095, 4096) if i < V})
+    logits = torch.full((len(ids), V), -200.0)
+    for r, i in enumerate(ids):
+        logits[r, i] = 0.0
+    for u in (0.0, 0.5, 1.0 - 2.0 ** -24):
+        toks, probs = _gpu_sample(logits, 1.0, torch.full((len(ids),), u))
+        assert toks == ids and torch.equal(probs, (logits == 0).to(torch.float32))
+    # one block per outcome: rows whose draft token is the target's are kept, the first other row draws the target's token
+    rows = min(len(ids), 6)
+    q = [torch.nn.functional.one_hot(torch.tensor(i), V).to(torch.float32) for i in ids[:rows - 1]]
+    lt = logits[:rows]
+    u_acc, u_res = torch.full((rows - 1,), 0.5), torch.full((rows,), 0.25)
+    n, emit = _gpu_accept(lt, q, [1] + ids[:rows - 1], u_acc, u_res, 1.0)
+    assert n == rows - 1 and emit == ids[:rows]
+    if rows > 2:
+        k = rows // 2
+        q[k - 1] = torch.nn.functional.one_hot(torch.tensor(ids[k]), V).to(torch.float32)
+        block = [1] + ids[:k - 1] + [ids[k]] + ids[k:rows - 1]
+        n, emit = _gpu_accept(lt, q, block, u_acc, u_res, 1.0)
+        assert n == k - 1 and emit == ids[:k]
+        n, emit = _gpu_accept(lt, q, block, u_acc, u_res, 1.0, dev_n_block=k)      # only the rows before the rejected one
+        assert n == k - 1 and emit == ids[:k]
+
+
 def test_accept_sample_matches_oracle():
     g = np.random.default_rng(5)
     n_cmp = n_flag = 0
