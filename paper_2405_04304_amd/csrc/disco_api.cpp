@@ -308,6 +308,7 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
 struct PfWs {
   Ws base;
   float* h; float* q; bf16_t* xn; bf16_t* xattn; bf16_t* xact; float* ssq; float* rstd;
+  float* planes;                             // sums of K ranges, where a matrix is cut along K
   size_t total;
 };
 
@@ -326,6 +327,7 @@ PfWs carve_prefill(const disco_model* m, int n_groups, int max_ctx, void* base) 
   w.xact = static_cast<bf16_t*>(take(sizeof(bf16_t) * 2 * rows * d.d_ff));
   w.ssq = static_cast<float*>(take(sizeof(float) * rows * (size_t)(d.d_model / 16)));
   w.rstd = static_cast<float*>(take(sizeof(float) * rows));
+  w.planes = static_cast<float*>(take(gemm_split_plane_bytes()));
   w.total = off;
   return w;
 }
@@ -387,7 +389,7 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
   auto dense = [&](const void* w, const bf16_t* x, size_t xs, int k, int n_rows) {
     DenseArgs a{};
     a.g.M = 16; a.g.W = static_cast<const bf16_t*>(w); a.g.X = x; a.g.KT = k / 32; a.g.n_rows = n_rows; a.g.grp = 1;
-    a.g.only_row = -1; a.n_groups = G; a.xs = xs; a.hi_only = hi_only;
+    a.g.only_row = -1; a.n_groups = G; a.xs = xs; a.hi_only = hi_only; a.g.planes = ws.planes;
     return a;
   };
   auto residual_update = [&](DenseArgs& a, const float* next_gain) {

@@ -15,6 +15,7 @@ enum Epi {
   EPI_QKV = 2,     // rotary (optional) + q store + paged K/V append
   EPI_SWIGLU = 3,  // silu(gate) * up  -> packed activation panel
   EPI_GELU = 4,    // gelu(y)          -> packed activation panel
+  EPI_SPLIT = 6,   // dense prompt pass: one K range's sums to `planes`; a launch of its own adds the ranges and runs an epilogue
   EPI_PARTIAL = 5, // h[m][n] += y             (O-projection, MLP down; K may be split over workgroups,
                    //                           partial planes in `out`, last workgroup adds them up)
 };
@@ -61,6 +62,7 @@ struct DenseArgs {
   size_t ssq_outs;      // floats between the groups' sum-of-squares slots
   const float* rstd;    // [group][16]: 1 / rms of the input rows (epilogues that read a normalised input)
   int hi_only;          // bf16 activations: the lo panels are not read
+  int k_split;          // set by the launcher: K ranges (partial sums at g.planes, gemm_split_plane_bytes())
   int tile_r, tile_t;   // set by the launcher: row blocks x token blocks walked by consecutive workgroups of an XCD
 };
 
@@ -181,6 +183,7 @@ hipError_t launch_qkv_attn(const GemmArgs& g, const AttnArgs& a, int* head_ready
                            hipStream_t s);
 // dense prompt pass (groups of 16 tokens; every group holds 16 rows, surplus rows are padding)
 hipError_t launch_gemm_dense(const DenseArgs& a, int epi, hipStream_t s);
+size_t gemm_split_plane_bytes();
 hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, float* rstd, int n_groups, hipStream_t s);
 hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, bool bf16_operands, hipStream_t s);
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s);

@@ -83,8 +83,8 @@ template <bool COH> __device__ __forceinline__ void st_h1(bf16_t* p, bf16_t v) {
   else *p = v;
 }
 
-// Store 4 consecutive-k activations of token m into the packed panels as bf16 hi/lo.
-template <bool COH = false>
+// Store 4 consecutive-k activations of token m into the packed panels as bf16 hi/lo (LO false: the lo panel has no reader).
+template <bool COH = false, bool LO = true>
 __device__ __forceinline__ void xpack_store4(bf16_t* X, int KT, int M, int m, int k, const float* v) {
   const int kt = k >> 5, grp = (k & 31) >> 3, e = k & 7;
   uint32_t hi[2], lo[2];
@@ -100,7 +100,7 @@ __device__ __forceinline__ void xpack_store4(bf16_t* X, int KT, int M, int m, in
   if (M <= 8) { off_hi = base + (size_t)m * 8; off_lo = base + (size_t)(m + 8) * 8; }
   else { off_hi = base + (size_t)m * 8; off_lo = (size_t)KT * 512 + base + (size_t)m * 8; }
   st_u2<COH>(X + off_hi, make_uint2(hi[0], hi[1]));
-  st_u2<COH>(X + off_lo, make_uint2(lo[0], lo[1]));
+  if (LO) st_u2<COH>(X + off_lo, make_uint2(lo[0], lo[1]));
 }
 
 // Wavefront reductions on the DPP cross-lane network (no LDS traffic): xor-1, xor-2 inside quads,
@@ -2583,6 +2583,13 @@ __device__ __forceinline__ void dense_epilogue(const DenseArgs& d, const int cb,
     if (ci < d.n_groups) {
     float rstd = 1.f;
     if (NORMED && d.rstd != nullptr) rstd = d.rstd[ci * 16 + m];
+    // the residual values of all row tiles are requested before the first of them is used (and stored over)
+    float4 hv[EPI == EPI_PARTIAL ? UNITS : 1];
+    if (EPI == EPI_PARTIAL) {
+#pragma unroll
+      for (int u = 0; u < UNITS; ++u)
+        hv[u] = *reinterpret_cast<const float4*>(a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out + rt[u] * 16 + 4 * g);
+    }
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       f32x4 y0 = acc[u * TPU][c] * rstd, y1 = acc[u * TPU + TPU - 1][c] * rstd;
@@ -2591,7 +2598,7 @@ __device__ __forceinline__ void dense_epilogue(const DenseArgs& d, const int cb,
         // residual-stream update h += X.W^T, panels of gain * h and this tile's sums of squares for the next GEMM
         const int col = t0 * 16 + 4 * g;
         float4* hp = reinterpret_cast<float4*>(a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out + col);
-        float4 h = *hp;
+        float4 h = hv[EPI == EPI_PARTIAL ? u : 0];
         h.x += y0[0]; h.y += y0[1]; h.z += y0[2]; h.w += y0[3];
         *hp = h;
         if (a.Xout != nullptr) {                  // deferred RMSNorm of the next GEMM (LayerNorm models: a norm launch instead)
@@ -2759,6 +2766,302 @@ __global__ __launch_bounds__(256) void k_gemm_dense(DenseArgs d) {
   if (live) dense_epilogue<EPI, RT, CG>(d, cb, rt, acc);
 }
 
+// The kernel of nearly every prompt: a workgroup of 8 wavefronts (WR x WC) owns WR x R2 blocks of 32 rows x WC x C2 blocks of
+// 32 panel columns.  With hi + lo panels 64 panel columns are 32 tokens (the lo products are added into the accumulators of
+// the hi products), with bf16 activations 64.  What bounds it: the matrix unit at the clock that the power limit leaves
+// (1.9 of 2.4 GHz; the main loop alone ran at 1.2 - 1.5 PFLOP/s depending on the card, in 94 % of its cycles), so
+// the loop is built to move little per product: both operands go from memory straight into LDS (no registers), 16 bytes per
+// lane in the packed tile order, which is also a conflict-free order of the 128-bit fragment reads, and 32x32x16
+// instructions read every fragment once per 128 x 64 wavefront tile.
+//
+// A stage holds one k-tile (32 columns of K) of the workgroup's row and panel tiles; NST stages form a ring.  Half steps of 16
+// columns are software-pipelined through two sets of fragment registers:
+//   first half:  matrix instructions of (kt, 0) while the fragments of (kt, 1) are read
+//   barrier:     every wavefront has waited for its own copies of stage kt + 1 and for its reads of stage kt
+//   second half: matrix instructions of (kt, 1) while the fragments of (kt + 1, 0) are read; the copies of k-tile
+//                kt + NST go into the stage that the barrier has just released
+//
+// Matrices with few tiles (d_model rows at some hundred tokens; every matrix at some tens) are cut along K as well: EPI_SPLIT
+// stores a range's sums, k_gemm_sum adds the ranges in order and runs the epilogue.  (Partial sums through write-through
+// stores and a ticket in one launch measured slower than no split at all: 110 us against 50 for 5120 x 5120 at 511 tokens.)
+__device__ __forceinline__ void lds_dma_16(const void* base, const uint32_t lane_off, const uint32_t lds) {
+  // m0 holds the LDS address of the wavefront's 1 KiB; the instruction has no register outputs
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// Epilogue of one wavefront: R2 pairs of row tiles (rt[2 q], rt[2 q + 1]; -1 past the matrix) x CA accumulators of 32 rows x
+// 32 tokens.  Lane: token column lane % 32 (two groups of 16), rows 8 i + 4 (lane / 32) .. + 3 of chunk i = 0 .. 3.
+template <int EPI, int R2, int CA, bool HI>
+__device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, const int (&rt)[2 * R2], const f32x16 (&acc)[R2][CA]) {
+  constexpr bool PAIR = EpiTraits<EPI>::pair;
+  const GemmArgs& a = d.g;
+  const int lane = threadIdx.x & 63, m = lane & 15, gh = lane >> 5;
+#pragma unroll
+  for (int c = 0; c < CA; ++c) {
+    const int ci = g0 + 2 * c + ((lane >> 4) & 1);
+    if (ci >= d.n_groups) continue;               // (half a wavefront at the ragged end)
+    const float rstd = (EPI != EPI_PARTIAL && d.rstd != nullptr) ? d.rstd[ci * 16 + m] : 1.f;
+    float4 hv[EPI == EPI_PARTIAL ? R2 : 1][4];
+    float* hrow = EPI == EPI_PARTIAL ? a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out : nullptr;
+    if (EPI == EPI_PARTIAL) {                     // all residual values of the column are requested before the first store
+#pragma unroll
+      for (int q = 0; q < R2; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          hv[q][i] = *reinterpret_cast<const float4*>(hrow + max(rt[2 * q + (i >> 1)], 0) * 16 + 8 * (i & 1) + 4 * gh);
+    }
+#pragma unroll
+    for (int q = 0; q < R2; ++q) {
+      float y[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[i][v] = acc[q][c][4 * i + v] * rstd;
+      if constexpr (PAIR) {
+        const int t0 = rt[2 * q];
+        if (t0 >= 0) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int g = 2 * i + gh;             // 4-row group of the 16-row tile
+            if constexpr (EPI == EPI_QKV) {
+              qkv_store(a, a.q + (size_t)ci * d.qs, t0 * 16 + 4 * g, m, a.pos0 + 16 * ci + m, y[i], y[i + 2]);
+            } else {
+              float act[4];
+#pragma unroll
+              for (int v = 0; v < 4; ++v) act[v] = y[i][v] / (1.0f + expf(-y[i][v])) * y[i + 2][v];
+              xpack_store4<false, !HI>(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, (t0 >> 1) * 16 + 4 * g, act);
+            }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+          const int t0 = rt[2 * q + tl];
+          if (t0 < 0) continue;
+          float sq = 0.f;
+#pragma unroll
+          for (int i2 = 0; i2 < 2; ++i2) {
+            const int i = 2 * tl + i2, col = t0 * 16 + 8 * i2 + 4 * gh;
+            if constexpr (EPI == EPI_PARTIAL) {
+              float4 h = hv[q][i];
+              h.x += y[i][0]; h.y += y[i][1]; h.z += y[i][2]; h.w += y[i][3];
+              *reinterpret_cast<float4*>(hrow + col) = h;
+              if (a.Xout != nullptr) {            // deferred RMSNorm of the next GEMM
+                const float4 gn = *reinterpret_cast<const float4*>(a.gain + col);
+                const float o[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
+                xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, col, o);
+                sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
+              }
+            } else {
+              float act[4];
+#pragma unroll
+              for (int v = 0; v < 4; ++v) act[v] = 0.5f * y[i][v] * (1.0f + erff(y[i][v] * 0.70710678118654752f));
+              xpack_store4<false, !HI>(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, col, act);
+            }
+          }
+          if constexpr (EPI == EPI_PARTIAL) {
+            if (a.Xout != nullptr) {
+              sq += __shfl_xor(sq, 32);           // (lanes l and l + 32 hold the same token: both are here)
+              if (gh == 0) a.ssq_out[(size_t)ci * d.ssq_outs + t0 * 16 + m] = sq;      // [slot][token]
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int EPI, int WR, int WC, int R2, int C2, int NST, int OCC, bool HI>
+__global__ __launch_bounds__(512, OCC) void k_gemm_tile(DenseArgs d) {
+  constexpr int NW = WR * WC, CA = HI ? C2 : C2 / 2;
+  constexpr int NA = 2 * R2 * WR, NBT = 2 * C2 * WC, NT = NA + NBT, PER = NT / NW;
+  constexpr int WG_G = HI ? NBT : NBT / 2;        // token groups per workgroup
+  static_assert(NW == 8 && NT % NW == 0, "eight wavefronts, equal shares of the copies");
+  __shared__ u32x4 st[NST][NT][64];
+  const GemmArgs& a = d.g;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / WC, wc = w % WC;
+  const int n_tiles = a.n_rows >> 4, KT = a.KT;
+  const int ncb = (d.n_groups + WG_G - 1) / WG_G, nrb = (n_tiles + NA - 1) / NA;
+  // ids go round-robin to the 8 XCDs: XCD x takes a contiguous run of the tiles, which are numbered 8 panel blocks wide, row by row
+  const int S = EPI == EPI_SPLIT ? d.k_split : 1, T = nrb * ncb * S, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int n_x = T / 8 + (xcd < T % 8 ? 1 : 0);
+  if (slot >= n_x) return;                        // whole workgroup
+  const int unit = xcd * (T / 8) + min(xcd, T % 8) + slot, ti = unit / S, seg = unit - ti * S;
+  const int k0 = EPI == EPI_SPLIT ? KT * seg / S : 0, k1 = EPI == EPI_SPLIT ? KT * (seg + 1) / S : KT;
+  const int per_pg = nrb * 8, pg = ti / per_pg, in_pg = ti - pg * per_pg;
+  const int width = min(8, ncb - pg * 8), rb = in_pg / width, cb = pg * 8 + in_pg - rb * width;
+  // row tile of slot s (0 .. NA - 1), -1 past the matrix: pairs (t, t + grp), grp a power of two (1: the tiles in order)
+  const int gs = __builtin_ctz(a.grp);
+  auto row_tile = [&](const int s) {
+    const int bp = (rb * NA + s) >> 1;
+    const int t = ((bp >> gs) << (gs + 1)) + (bp & (a.grp - 1)) + ((s & 1) ? a.grp : 0);
+    return bp < (n_tiles >> 1) ? t : -1;
+  };
+  const char* src[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int s = w + NW * i;
+    if (s < NA) {
+      src[i] = reinterpret_cast<const char*>(a.W) + (size_t)max(row_tile(s), 0) * KT * 1024;
+    } else {
+      // panel slots of a wavefront column: hi tiles of its groups, then their lo tiles, or (HI) one tile per group
+      const int b = s - NA, wb = b % (2 * C2), gl = HI ? b : b / (2 * C2) * C2 + wb % C2;
+      src[i] = reinterpret_cast<const char*>(a.X + (size_t)min(cb * WG_G + gl, d.n_groups - 1) * d.xs) + ((!HI && wb >= C2) ? (size_t)KT * 1024 : 0);
+    }
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&st[0][0][0];
+  auto dma = [&](const int i, const int kt, const int stg) {
+    const uint32_t off = (uint32_t)(kt < k1 ? kt : k1 - 1) * 1024u + (uint32_t)lane * 16u;
+    lds_dma_16(src[i], off, lds0 + (uint32_t)stg * (NT * 1024u) + (uint32_t)(w + NW * i) * 1024u);
+  };
+  const int tsel = (lane >> 4) & 1, pos = (lane >> 5) * 16 + (lane & 15);
+  auto rd = [&](const int sg, const int t0, const int s) { return st[sg][t0 + tsel][pos + 32 * s]; };
+  f32x16 acc[R2][CA];
+#pragma unroll
+  for (int r = 0; r < R2; ++r)
+#pragma unroll
+    for (int c = 0; c < CA; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+#pragma unroll
+  for (int k = 0; k < NST; ++k)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) dma(i, k0 + k, k);
+  struct Frag { u32x4 a[R2], b[C2]; };
+  Frag f0, f1;
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NST - 1) * PER) : "memory");
+#pragma unroll
+  for (int c = 0; c < C2; ++c) f0.b[c] = rd(0, NA + (wc * C2 + c) * 2, 0);
+#pragma unroll
+  for (int r = 0; r < R2; ++r) f0.a[r] = rd(0, (wr * R2 + r) * 2, 0);
+  auto half = [&](const Frag& cur, Frag& nxt, const int sg, const int s, const int kt, const int sd, const bool copy) {
+#pragma unroll
+    for (int q = 0; q < R2; ++q) {
+#pragma unroll
+      for (int c = q * C2 / R2; c < (q + 1) * C2 / R2; ++c) nxt.b[c] = rd(sg, NA + (wc * C2 + c) * 2, s);
+      nxt.a[q] = rd(sg, (wr * R2 + q) * 2, s);
+      if (copy)
+#pragma unroll
+        for (int i = q * PER / R2; i < (q + 1) * PER / R2; ++i) dma(i, kt, sd);
+#pragma unroll
+      for (int c = 0; c < C2; ++c)
+        acc[q][c % CA] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(cur.a[q]), as_bf16x8(cur.b[c]), acc[q][c % CA], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);          // keep the reads and copies spread between the matrix instructions
+    }
+  };
+  int sc = 0;                                     // stage of k-tile kt
+  for (int kt = k0; kt < k1; ++kt) {
+    const int sn = sc == NST - 1 ? 0 : sc + 1;
+    half(f0, f1, sc, 1, 0, 0, false);
+    // of the copies in flight (k-tiles kt + 1 .. kt + NST - 1) those of kt + 1 must have arrived
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NST - 2) * PER) : "memory");
+    half(f1, f0, sn, 0, kt + NST, sc, true);
+    sc = sn;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing is in flight into LDS when the workgroup gives it back
+  if constexpr (EPI == EPI_SPLIT) {
+    // this range's sums, in the lanes' own order: [unit][q][c][chunk][wavefront][lane][4]
+    float* plane = a.planes + (size_t)unit * (R2 * CA * 16 * NW * 64) + ((size_t)w * 64 + lane) * 4;
+#pragma unroll
+    for (int q = 0; q < R2; ++q)
+#pragma unroll
+      for (int c = 0; c < CA; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<float4*>(plane + (size_t)((q * CA + c) * 4 + i) * (NW * 256)) =
+              make_float4(acc[q][c][4 * i], acc[q][c][4 * i + 1], acc[q][c][4 * i + 2], acc[q][c][4 * i + 3]);
+  } else {
+    int rt[2 * R2];
+#pragma unroll
+    for (int r = 0; r < 2 * R2; ++r) rt[r] = row_tile(wr * 2 * R2 + r);
+    tile_epilogue<EPI, R2, CA, HI>(d, cb * WG_G + wc * 2 * CA, rt, acc);
+  }
+}
+
+// Sum of the K ranges that k_gemm_tile<EPI_SPLIT, 2, 4, 4, 2> left, in range order, and the epilogue: one wavefront per 32 rows
+// x 2 token groups.
+template <int EPI, bool HI>
+__global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
+  constexpr int CA = HI ? 2 : 1, R2 = 4, NW = 8;
+  const GemmArgs& a = d.g;
+  const int lane = threadIdx.x & 63, n_pairs = a.n_rows >> 5, n_gp = (d.n_groups + 1) >> 1;
+  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (id >= n_pairs * n_gp) return;
+  const int pr = id / n_gp, gp = id - pr * n_gp;  // 32-row pair of tiles, pair of token groups
+  const int rb = pr / (2 * R2), ps = pr - rb * 2 * R2, wr = ps / R2, q = ps - wr * R2;
+  const int cb = gp / (4 * CA), cs = gp - cb * 4 * CA, wc = cs / CA, c = cs - wc * CA;
+  const int WG_G = 8 * CA, ncb = (d.n_groups + WG_G - 1) / WG_G, nrb = ((a.n_rows >> 4) + 15) / 16;
+  const int per_pg = nrb * 8, pg = cb / 8, width = min(8, ncb - pg * 8), ti = pg * per_pg + rb * width + (cb - pg * 8);
+  const size_t PLANE = (size_t)R2 * CA * 16 * NW * 64;
+  const float* plane = a.planes + (size_t)ti * d.k_split * PLANE + (size_t)(q * CA + c) * 4 * (NW * 256) + ((size_t)(wr * 4 + wc) * 64 + lane) * 4;
+  f32x16 acc[1][1];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+  for (int s0 = 0; s0 < d.k_split; s0 += 4) {     // sixteen loads in flight
+    float4 t[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (s0 + s < d.k_split)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[s][i] = *reinterpret_cast<const float4*>(plane + (size_t)(s0 + s) * PLANE + (size_t)i * (NW * 256));
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (s0 + s < d.k_split)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[0][0][4 * i] += t[s][i].x; acc[0][0][4 * i + 1] += t[s][i].y; acc[0][0][4 * i + 2] += t[s][i].z; acc[0][0][4 * i + 3] += t[s][i].w;
+        }
+  }
+  const int gs = __builtin_ctz(a.grp), t0 = ((pr >> gs) << (gs + 1)) + (pr & (a.grp - 1));
+  const int rt[2] = {t0, t0 + a.grp};
+  tile_epilogue<EPI, 1, 1, HI>(d, 2 * gp, rt, acc);
+}
+
+// Bytes of partial sums that a split launch may use: 256 workgroups of 256 x 256.
+size_t gemm_split_plane_bytes() { return (size_t)256 * 256 * 256 * sizeof(float); }
+
+template <int EPI, bool HI>
+static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
+  DenseArgs d = d0;
+  const int n_tiles = d.g.n_rows / 16, KT = d.g.KT;
+  auto count = [&](const int na, const int nbt) { const int gg = nbt / (HI ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((d.n_groups + gg - 1) / gg); };
+  auto grid = [](const long t) { return dim3(8u * (unsigned)((t + 7) / 8)); };
+  // Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
+  // hi + lo only: 128-token accumulators).  Costs in units of half a compute unit's time for a 256 x 256 tile; the
+  // larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
+  // fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
+  // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
+  // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 115 with its sum.
+  const long t0 = count(8, 16), t1 = count(16, 16), t2 = count(32, 16);
+  const long rem = t0 % 512;
+  const double c0 = ((double)(t0 / 512) * 2.0 + (rem == 0 ? 0.0 : (rem <= 256 ? 1.4 : 2.0))) / 0.95;
+  const double c1 = (double)((t1 + 255) / 256) * 2.0, c2 = HI ? 1e30 : (double)((t2 + 255) / 256) * 4.0 / 1.06;
+  const double unit_us = 0.3 * KT;
+  double best = (c0 < c1 ? (c0 < c2 ? c0 : c2) : (c1 < c2 ? c1 : c2)) * unit_us;
+  int split = 1;
+  if (d.g.planes != nullptr)
+    for (int S = 2; S <= 16 && t1 * S <= 256 && KT / S >= 8; ++S) {
+      const double us = 2.0 / S * unit_us + 8.0 + (double)t1 * S * (HI ? 0.262 : 0.131) * 2.0 / 4.0;   // two passes over the partial sums at 4 TB/s, a launch
+      if (us < best) { best = us; split = S; }
+    }
+  if (split > 1) {
+    d.k_split = split;
+    hipLaunchKernelGGL((k_gemm_tile<EPI_SPLIT, 2, 4, 4, 2, 4, 2, HI>), grid(t1 * split), dim3(512), 0, s, d);
+    const long waves = (long)(n_tiles / 2) * ((d.n_groups + 1) / 2);
+    hipLaunchKernelGGL((k_gemm_sum<EPI, HI>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, d);
+    return hipGetLastError();
+  }
+  if constexpr (!HI) if (c2 < c0 && c2 < c1) {
+    hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 4, 4, 3, 2, HI>), grid(t2), dim3(512), 0, s, d);
+    return hipGetLastError();
+  }
+  if (c1 < c0) hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 4, 2, 4, 2, HI>), grid(t1), dim3(512), 0, s, d);
+  else hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 2, 2, 3, 4, HI>), grid(t0), dim3(512), 0, s, d);
+  return hipGetLastError();
+}
+
 template <int EPI, int NB, int RT, bool HI>
 static hipError_t launch_gemm_dense_rt(const DenseArgs& d, hipStream_t s) {
   constexpr int CG = HI ? 8 : 4;
@@ -2775,42 +3078,21 @@ static hipError_t launch_gemm_dense_rt(const DenseArgs& d, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Row tiles per wavefront (a workgroup covers 4 x RT tiles x CG token groups).  Larger tiles fetch every operand less
-// often, but the grid should fill the 256 compute units in its last round too: 5120 rows x 2048 tokens are 320
-// workgroups at RT = 4 (the last 64 run alone) and exactly 256 at RT = 5.  A tile count is taken only if it fills the
-// chip clearly better than the next larger one.  Two-tile epilogues need an even count; 128-row tiles need the bf16-activation
-// form (their accumulators fill the accumulation registers).
+// 64-row wavefront tiles unless they would leave compute units without a workgroup.
 template <int EPI, bool HI>
 static hipError_t launch_gemm_dense_e(const DenseArgs& d, hipStream_t s) {
-  constexpr bool PAIR = EpiTraits<EPI>::pair;
   constexpr int CG = HI ? 8 : 4;
   constexpr int NB = HI ? 4 : 5;                  // k-tiles of loads in flight per wavefront (measured best of 3..5 with two panels)
   const int n_tiles = d.g.n_rows / 16, ncb = (d.n_groups + CG - 1) / CG;
-  auto wgs_of = [&](int rt) { return (long)((n_tiles + 4 * rt - 1) / (4 * rt)) * ncb; };
-  // 64-row wavefront tiles unless they would leave compute units without a workgroup; 128-row tiles for the wide
-  // projections with bf16 activations
-  int best = wgs_of(4) >= 256 ? 4 : 2;
-  if (HI && (n_tiles % 8) == 0 && wgs_of(8) >= 256) best = 8;
-  if (wgs_of(best) <= 2 * 256 && cu_fill(wgs_of(best)) < 0.9) {        // at most two rounds: the idle share of the last one counts
-    const int cand[] = {6, 5, 4, 3, 2};            // largest first
-    for (int rt : cand) {
-      if ((PAIR && (rt & 1)) || n_tiles % rt) continue;
-      if (wgs_of(rt) >= 256 && cu_fill(wgs_of(rt)) >= 0.95) { best = rt; break; }
-    }
-  }
-  switch (best) {
-    case 8: if constexpr (HI) return launch_gemm_dense_rt<EPI, 3, 8, true>(d, s); else break;
-    case 6: return launch_gemm_dense_rt<EPI, HI ? 4 : 3, 6, HI>(d, s);   // fewer tiles in flight: 6 x NB weight tiles must fit the registers
-    case 5: if constexpr (!PAIR) return launch_gemm_dense_rt<EPI, 4, 5, HI>(d, s); else break;
-    case 4: return launch_gemm_dense_rt<EPI, NB, 4, HI>(d, s);
-    case 3: if constexpr (!PAIR) return launch_gemm_dense_rt<EPI, NB, 3, HI>(d, s); else break;
-    default: break;
-  }
+  if ((long)((n_tiles + 15) / 16) * ncb >= 256) return launch_gemm_dense_rt<EPI, NB, 4, HI>(d, s);
   return launch_gemm_dense_rt<EPI, NB, 2, HI>(d, s);
 }
 
 template <int EPI>
 static hipError_t launch_gemm_dense_h(const DenseArgs& d, hipStream_t s) {
+  // Narrow matrices and short prompts (K below 512 or fewer than 512 rows, up to 2047 tokens) leave a large-tile grid nearly empty:
+  // 4-layer model of width 256: 196 us against 184 at 33 tokens, 391 against 465 at 3000 (launches and all)
+  if ((d.g.KT >= 16 && d.g.n_rows >= 512) || d.n_groups >= 128) return d.hi_only ? launch_gemm_tile<EPI, true>(d, s) : launch_gemm_tile<EPI, false>(d, s);
   return d.hi_only ? launch_gemm_dense_e<EPI, true>(d, s) : launch_gemm_dense_e<EPI, false>(d, s);
 }
 

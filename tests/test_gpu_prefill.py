@@ -157,6 +157,22 @@ def test_prefill_bf16_activations_13b_shape_1024_tokens():
                   flags=BF16_ACT, tight=2e-2)
 
 
+# The large-tile GEMM: K cut into ranges (few tiles: 33 tokens), 128- and 256-row tiles (527), 512-row tiles (1700 tokens: the
+# 8192-row projection), ragged row blocks (d_ff 1440: 180 tiles in the last block of 16), ragged token groups, the K / V rows of
+# grouped heads, 16 k-tiles (the shortest K it takes) and 45 (odd).  The arithmetic per element is that of the other cases.
+TILE_B = W.ModelShape("B", 1, 512, 4, 128, 2, 1440, 512)
+TILE_B_WIDE = W.ModelShape("B", 1, 512, 4, 128, 4, 4096, 512)
+TILE_A = W.ModelShape("A", 1, 512, 8, 64, 1, 1536, 512, max_pos=2048)
+
+
+@pytest.mark.parametrize("shape, n, pre", [(TILE_B, 33, 3), (TILE_B, 257, 0), (TILE_B, 527, 7), (TILE_B_WIDE, 1700, 0), (TILE_A, 40, 0),
+                                           (TILE_A, 530, 5)])
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+def test_prefill_large_tiles(shape, n, pre, flags):
+    _prefill_case(shape, 31, n, pre=pre, what=f"large tiles {shape.family} d_ff {shape.d_ff}", sigma=0.03, flags=flags,
+                  tight=2e-2 if flags else None)
+
+
 def test_prefill_rejects_bad_arguments():
     shape = SMALL_B
     om, gm, okv, gkv, ws = setup_pair(shape, 11, capacity=64)
