@@ -21,6 +21,7 @@ namespace disco {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 #define NEG_BIG (-1.0e30f)
@@ -272,6 +273,19 @@ hipError_t launch_pack(const bf16_t* src, int64_t n, int64_t k, bf16_t* dst, int
 // atomics, no waiting, bitwise reproducible results.
 //
 // k_gemm launches a grid of (row groups, K ranges): every workgroup owns one unit.
+
+// Copies from memory into LDS, 16 bytes per lane to consecutive LDS addresses from `lds` on (uniform), without registers:
+// base (uniform) + lane_off, or an address per lane.  Completion is counted by vmcnt.
+__device__ __forceinline__ void lds_dma_16(const void* base, const uint32_t lane_off, const uint32_t lds) {
+  // m0 holds the LDS address of the wavefront's 1 KiB; the instruction has no register outputs
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void lds_dma_16(const void* lane_addr, const uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(lane_addr) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   union { u32x4 u; bf16x8 b; } c; c.u = v; return c.b;
@@ -1290,6 +1304,205 @@ __global__ __launch_bounds__(512) void k_attn_groups(AttnArgs a, int n_groups, s
   }
 }
 
+// Prompt pass, tiled: a wavefront owns 32 query columns (32 tokens of one head); the four wavefronts of a workgroup share one
+// K / V head: as many query heads of its group as divide four, times 32-token blocks.  K and V come through LDS in tiles of 64
+// positions (copied straight from the pages, two buffers: the next tile arrives during the arithmetic of this one), so a
+// cache entry is fetched once per 128 query columns instead of once per 32, and the matrix unit works on 32x32x16 instructions:
+//   S^T[key][query] = K . Q^T (q as hi + lo in registers), soft-max per query column (lane l and l + 32 share a column),
+//   O^T[chan][query] += V^T . P^T: the S accumulators are P's operand after one half-wavefront swap per register.
+// LDS chunks of 16 bytes are stored at (chunk xor row) so that both the copies (whole rows) and the fragment reads (one chunk
+// column of 16 rows) are free of bank conflicts.  Bound by the matrix unit and the soft-max's vector instructions, about
+// equal at hi + lo.  Measured per layer, 48 heads on one K / V head, 3001 tokens after 333: 333 us against 749 with 32 query
+// columns per pass over the cache; 40 heads, 2048 tokens, bf16 operands: 87 against 211.
+// Needs pages of a power of two of at least 8 tokens (a V^T chunk is 8 tokens of a channel).
+template <int DH, bool LO>
+__global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups, size_t x_stride, int hw_log2) {
+  constexpr int KB = 64, S16 = DH / 16, CB = DH / 32, CK = DH / 8, RPI = 64 / CK, PER = DH / 32;   // PER: copies of K (and of V) per wavefront and tile
+  __shared__ u32x4 ks[2][KB * CK], vs[2][DH * (KB / 8)];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, hf = lane >> 5;
+  const int HW = 1 << hw_log2, TW = 4 >> hw_log2, rep = a.nq / a.nkv, hgs = rep >> hw_log2;
+  const int kvh = blockIdx.x / hgs, head = kvh * rep + (blockIdx.x - kvh * hgs) * HW + (w & (HW - 1));
+  const int tbg = gridDim.y - 1 - blockIdx.y;                      // the longest ranges are scheduled first
+  const int rows = 16 * n_groups, r0 = 32 * (tbg * TW + (w >> hw_log2));
+  const int end = a.pos0 + min(32 * TW * (tbg + 1), rows);         // positions at or beyond it: not read (K) or not used (V)
+  const int w_end = r0 < rows ? a.pos0 + min(r0 + 32, rows) : 0;   // this wavefront's (0: no tokens of its own, it only copies)
+  const int r = min(r0 + col, rows - 1), qpos = a.pos0 + r, pt = a.page_tokens, pshift = __builtin_ctz(pt);
+  const uint32_t head_elems = (uint32_t)pt * DH, page_elems = 2u * (uint32_t)a.nkv * head_elems;   // (a page is far below 2^32 elements)
+
+  // positions this lane copies in a tile: K row of instruction i, V chunk (the same chunk of every channel it copies)
+  auto k_row = [&](const int i) { return RPI * (w + 4 * i) + lane / CK; };
+  const int v_swz = ((8 * w + (lane >> 3)) >> 1) & 7, v_chunk = (lane & 7) ^ v_swz;    // channel 8 (w + 4 i) + lane / 8: the swizzle does not depend on i
+  auto k_pos = [&](const int base, const int i) { return min(base + k_row(i), end - 1); };
+  auto v_pos = [&](const int base) { return min(base + 8 * v_chunk, (end - 1) & ~7); };
+  // physical pages of those positions; the next tile's are looked up one tile ahead
+  uint32_t kp[PER], vp;
+  auto pages = [&](const int base) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) kp[i] = (uint32_t)k_pos(base, i) >> pshift;
+    vp = (uint32_t)v_pos(base) >> pshift;
+    if (a.page_table) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) kp[i] = (uint32_t)a.page_table[kp[i]];
+      vp = (uint32_t)a.page_table[vp];
+    }
+  };
+  const uint32_t lds_k = lds_address(&ks[0][0]), lds_v = lds_address(&vs[0][0]);
+  auto copy = [&](const int base, const int buf) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int kr = k_row(i), off = k_pos(base, i) & (pt - 1);
+      const int c = (lane % CK) ^ (DH == 128 ? kr & 15 : (kr >> 1) & 7);
+      lds_dma_16(a.kv_layer + (uint64_t)kp[i] * page_elems + (uint32_t)(kvh * head_elems + off * DH + c * 8),
+                 lds_k + (uint32_t)(buf * KB * CK + (w + 4 * i) * 64) * 16u);
+    }
+    const int off = v_pos(base) & (pt - 1);
+    const bf16_t* vb = a.kv_layer + (uint64_t)vp * page_elems + (uint32_t)((a.nkv + kvh) * head_elems + (lane >> 3) * pt + off);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      lds_dma_16(vb + 8 * (w + 4 * i) * pt, lds_v + (uint32_t)(buf * DH * 8 + (w + 4 * i) * 64) * 16u);
+  };
+  const int n_kt = (end + KB - 1) / KB;
+  pages(0);
+  copy(0, 0);
+  if (n_kt > 1) pages(KB);
+
+  bf16x8 qh[S16], ql[LO ? S16 : 1];
+  {
+    const float* qp = a.q + (size_t)r * a.ldq + head * DH + 8 * hf;
+#pragma unroll
+    for (int s = 0; s < S16; ++s) {
+      const float4 x0 = *reinterpret_cast<const float4*>(qp + 16 * s), x1 = *reinterpret_cast<const float4*>(qp + 16 * s + 4);
+      const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+      union { bf16_t u[8]; bf16x8 v; } h, l;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { h.u[i] = f32_to_bf16(xv[i]); l.u[i] = LO ? f32_to_bf16(xv[i] - bf16_to_f32(h.u[i])) : (bf16_t)0; }
+      qh[s] = h.v;
+      if (LO) ql[LO ? s : 0] = l.v;
+    }
+  }
+  f32x16 O[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) O[c][v] = 0.f;
+  float m_run = NEG_BIG, l_run = 0.f;             // of column `col` (both halves hold the maximum; each its own keys' sum)
+  const float ce = a.scale * 1.44269504088896f;   // exp(scale (s - m)) = exp2(ce s - ce m)
+
+  // 32 positions (half kb of the tile in buffer buf, from position base on)
+  auto step = [&](const int base, const int buf, const int kb) {
+    const bool edge = base + 31 > a.pos0 + r0;    // some of them lie beyond the first query's (uniform)
+    const u32x4* kt = &ks[buf][(32 * kb + col) * CK];
+    const u32x4* vt = &vs[buf][col * 8];
+    const int kx = DH == 128 ? col & 15 : (col >> 1) & 7, vx = (col >> 1) & 7;
+    auto k_frag = [&](const int s) { return as_bf16x8(kt[(2 * s + hf) ^ kx]); };
+    auto v_frag = [&](const int s, const int c) { return vt[32 * c * 8 + ((4 * kb + 2 * s + hf) ^ vx)]; };
+    f32x16 S;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) S[v] = 0.f;
+    bf16x8 kk[3];                                 // fragments are read two steps ahead of their products
+    kk[0] = k_frag(0);
+    kk[1] = k_frag(1);
+#pragma unroll
+    for (int s = 0; s < S16; ++s) {
+      if (s + 2 < S16) kk[(s + 2) % 3] = k_frag(s + 2);
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[s % 3], qh[s], S, 0, 0, 0);
+      if (LO) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[s % 3], ql[LO ? s : 0], S, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    u32x4 vv[2][CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) vv[0][c] = v_frag(0, c);
+    if (edge) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (base + 8 * (v >> 2) + 4 * hf + (v & 3) > qpos) S[v] = NEG_BIG;
+    }
+    float mx = S[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, S[v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m_run, mx);
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0ull) {      // some column's maximum moved
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * ce);
+      l_run *= alpha;
+#pragma unroll
+      for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) O[c][v] *= alpha;
+      m_run = m_new;
+    }
+    const float mc = m_run * ce;
+    uint32_t ph[4][2], pl[4][2];
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(S[4 * i + 2 * t], ce, -mc)), e1 = __builtin_amdgcn_exp2f(fmaf(S[4 * i + 2 * t + 1], ce, -mc));
+        sum += e0 + e1;
+        const bf16_t h0 = f32_to_bf16(e0), h1 = f32_to_bf16(e1);
+        ph[i][t] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        pl[i][t] = LO ? (uint32_t)f32_to_bf16(e0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(e1 - bf16_to_f32(h1)) << 16) : 0u;
+      }
+    l_run += sum;
+    // lane half h holds keys 16 s + 4 h .. + 3 (chunk 2 s) and 16 s + 8 + 4 h .. + 3 (chunk 2 s + 1); the operand wants 16 s + 8 h .. + 7
+    auto operand = [&](const uint32_t (&x)[2], const uint32_t (&y)[2]) {
+      const auto a0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false), a1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+      return as_bf16x8(u32x4{(uint32_t)a0[0], (uint32_t)a1[0], (uint32_t)a0[1], (uint32_t)a1[1]});
+    };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (s == 0)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) vv[1][c] = v_frag(1, c);
+      const bf16x8 bh = operand(ph[2 * s], ph[2 * s + 1]);
+      bf16x8 bl = bh;
+      if constexpr (LO) bl = operand(pl[2 * s], pl[2 * s + 1]);
+      if (edge) {                                 // entries at or beyond w_end may be stale bytes: 0 * NaN would poison the sum
+        const int nv = w_end - (base + 16 * s + 8 * hf);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t keep = nv >= 2 * i + 2 ? 0xFFFFFFFFu : (nv == 2 * i + 1 ? 0xFFFFu : 0u);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) vv[s][c][i] &= keep;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < CB; ++c) O[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vv[s][c]), bh, O[c], 0, 0, 0);
+      if (LO)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) O[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vv[s][c]), bl, O[c], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  for (int t = 0; t < n_kt; ++t) {
+    const int base = t * KB, buf = t & 1;
+    // tile t has arrived and every wavefront has left the other buffer
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (t + 1 < n_kt) {
+      copy(base + KB, buf ^ 1);
+      if (t + 2 < n_kt) pages(base + 2 * KB);
+    }
+#pragma unroll 1
+    for (int kb = 0; kb < 2; ++kb) {
+      const int b = base + 32 * kb;
+      if (b >= w_end) break;
+      step(b, buf, kb);
+    }
+  }
+  if (w_end == 0 || r0 + col >= rows) return;
+  const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32));
+  bf16_t* X = a.Xout + (size_t)(r >> 4) * x_stride;
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float out4[4] = {O[c][4 * i] * inv, O[c][4 * i + 1] * inv, O[c][4 * i + 2] * inv, O[c][4 * i + 3] * inv};
+      xpack_store4<false, LO>(X, (a.nq * DH) >> 5, 16, r & 15, head * DH + 32 * c + 8 * i + 4 * hf, out4);
+    }
+}
+
 constexpr int ATTN_HEAD_MAX_CTX = 256;    // positions up to which the whole-head kernel is used (one step per wavefront);
                                           // beyond it the arithmetic of a head is worth spreading over several compute units
 
@@ -1320,6 +1533,22 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, bool bf16_operands, hipStream_t s) {
   if (a.M != 16 || n_groups < 1 || n_groups > 65535) return hipErrorInvalidValue;
+  // The tiled kernel walks the positions one tile after another, so it needs workgroups for half the compute units: hi + lo, us
+  // (tiles / groups), 48 heads on one K / V head 333 / 749 at 3001 tokens (1128 workgroups), 40 heads 32 / 39 at 511 (160),
+  // but 12 heads of 64 channels 20 / 12 at 511 (48); a whole pass of one 13B layer at 130 after 333 (80) 376 / 366
+  const int rep = a.nq / a.nkv, hw = rep % 4 == 0 ? 2 : (rep % 2 == 0 ? 1 : 0);       // log2 of the heads per workgroup
+  const int tbs = (n_groups + 1) / 2, tw = 4 >> hw;
+  const dim3 g(a.nq >> hw, (tbs + tw - 1) / tw);
+  if (a.page_tokens >= 8 && (a.page_tokens & (a.page_tokens - 1)) == 0 && (a.dh == 64 || a.dh == 128) && (long)g.x * g.y >= 128) {
+    if (a.dh == 128) {
+      if (bf16_operands) hipLaunchKernelGGL((k_attn_tiles<128, false>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
+      else hipLaunchKernelGGL((k_attn_tiles<128, true>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
+    } else {
+      if (bf16_operands) hipLaunchKernelGGL((k_attn_tiles<64, false>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
+      else hipLaunchKernelGGL((k_attn_tiles<64, true>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
+    }
+    return hipGetLastError();
+  }
   const dim3 g1(a.nq, (n_groups + ATTN_MG - 1) / ATTN_MG);
   if (a.dh == 128) {
     if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<128, false>), g1, dim3(512), 0, s, a, n_groups, x_stride);
@@ -2784,11 +3013,6 @@ __global__ __launch_bounds__(256) void k_gemm_dense(DenseArgs d) {
 // Matrices with few tiles (d_model rows at some hundred tokens; every matrix at some tens) are cut along K as well: EPI_SPLIT
 // stores a range's sums, k_gemm_sum adds the ranges in order and runs the epilogue.  (Partial sums through write-through
 // stores and a ticket in one launch measured slower than no split at all: 110 us against 50 for 5120 x 5120 at 511 tokens.)
-__device__ __forceinline__ void lds_dma_16(const void* base, const uint32_t lane_off, const uint32_t lds) {
-  // m0 holds the LDS address of the wavefront's 1 KiB; the instruction has no register outputs
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory");
-}
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // Epilogue of one wavefront: R2 pairs of row tiles (rt[2 q], rt[2 q + 1]; -1 past the matrix) x CA accumulators of 32 rows x
 // 32 tokens.  Lane: token column lane % 32 (two groups of 16), rows 8 i + 4 (lane / 32) .. + 3 of chunk i = 0 .. 3.
@@ -2911,7 +3135,7 @@ __global__ __launch_bounds__(512, OCC) void k_gemm_tile(DenseArgs d) {
       src[i] = reinterpret_cast<const char*>(a.X + (size_t)min(cb * WG_G + gl, d.n_groups - 1) * d.xs) + ((!HI && wb >= C2) ? (size_t)KT * 1024 : 0);
     }
   }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&st[0][0][0];
+  const uint32_t lds0 = lds_address(&st[0][0][0]);
   auto dma = [&](const int i, const int kt, const int stg) {
     const uint32_t off = (uint32_t)(kt < k1 ? kt : k1 - 1) * 1024u + (uint32_t)lane * 16u;
     lds_dma_16(src[i], off, lds0 + (uint32_t)stg * (NT * 1024u) + (uint32_t)(w + NW * i) * 1024u);

@@ -173,6 +173,23 @@ def test_prefill_large_tiles(shape, n, pre, flags):
                   tight=2e-2 if flags else None)
 
 
+# The tiled attention (128 workgroups or more): heads that share K / V by 1, 2, 3 and 4 (four, two or one head per workgroup), both
+# head widths, a last block of one token, an odd number of token groups, pages of 8 and 64, a start inside a tile of 64, and
+# one prompt just below the rule's line (32 heads x 12 token blocks / 4 = 96) beside one above.
+ATT_1 = W.ModelShape("B", 1, 512, 32, 64, 32, 512, 512)
+ATT_2 = W.ModelShape("B", 1, 256, 32, 64, 16, 512, 512)
+ATT_3 = W.ModelShape("B", 1, 256, 24, 64, 8, 512, 512)
+ATT_4 = W.ModelShape("A", 1, 256, 32, 128, 1, 512, 512, max_pos=1024)
+
+
+@pytest.mark.parametrize("shape, n, pre, page, permute", [(ATT_1, 385, 5, 16, True), (ATT_1, 384, 0, 16, False), (ATT_2, 513, 3, 8, True),
+                                                          (ATT_3, 700, 0, 64, False), (ATT_4, 559, 7, 32, True)])
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+def test_prefill_tiled_attention(shape, n, pre, page, permute, flags):
+    _prefill_case(shape, 41, n, pre=pre, page=page, permute=permute, what=f"tiled attention, {shape.n_heads} heads on {shape.n_kv_heads}",
+                  sigma=0.03, flags=flags, tight=2e-2 if flags else None)
+
+
 def test_prefill_rejects_bad_arguments():
     shape = SMALL_B
     om, gm, okv, gkv, ws = setup_pair(shape, 11, capacity=64)
