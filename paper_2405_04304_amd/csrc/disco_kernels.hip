@@ -886,10 +886,85 @@ hipError_t launch_vec_panel(const float* v, int d, bf16_t* Xout, hipStream_t s) 
   return hipGetLastError();
 }
 
+// The LayerNorm of a long prompt pass: one workgroup per group of 16 tokens, one wavefront per row, the row in registers (the same two-pass
+// variance as norm_row).  The panels are built in LDS, 512 columns at a time, and leave as whole 1 KiB tiles: one row per
+// workgroup wrote 16-byte pieces of lines that sixteen workgroups shared, and was bound by those partial lines (78 us against
+// 51 for 3008 rows of 6144).  16-byte chunks sit at (token xor eighth of the columns) in LDS, so that neither side has more
+// than two lanes on a bank.  Rows of up to 6144 values fit the registers.
+constexpr int NORM_GROUPS_MAX_D = 6144;
+__global__ __launch_bounds__(1024) void k_norm_groups(NormArgs a) {
+  constexpr int NC = NORM_GROUPS_MAX_D / 256;     // float4 per lane
+  __shared__ u32x4 s_hi[2][64][16], s_lo[2][64][16];             // [buffer][eight columns][token]
+  const int lane = threadIdx.x & 63, m = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = blockIdx.x, d = a.d, KT = d >> 5;
+  const float* h = a.h + (size_t)(grp * 16 + m) * d;
+  float4 x[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int k = c * 256 + lane * 4;
+    x[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (k < d) x[c] = *reinterpret_cast<const float4*>(h + k);
+  }
+  float mean = 0.f;
+  if (a.layernorm) {
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sum += (x[c].x + x[c].y) + (x[c].z + x[c].w);   // zero beyond d
+    mean = wave_sum(sum) / (float)d;
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (c * 256 + lane * 4 < d) {
+      const float x0 = x[c].x - mean, x1 = x[c].y - mean, x2 = x[c].z - mean, x3 = x[c].w - mean;
+      ss += (x0 * x0 + x1 * x1) + (x2 * x2 + x3 * x3);
+    }
+  ss = wave_sum(ss);
+  const float scale = 1.0f / sqrtf(ss / (float)d + a.eps);
+  u32x4* X = reinterpret_cast<u32x4*>(a.Xout + (size_t)grp * d * 32);
+#pragma unroll
+  for (int c0 = 0; c0 < NC; c0 += 2) {
+    if (c0 * 256 < d) {                           // uniform
+      const int buf = (c0 >> 1) & 1;
+#pragma unroll
+      for (int c = c0; c < c0 + 2; ++c) {
+        const int k = c * 256 + lane * 4;
+        if (k < d) {
+          const float4 g = *reinterpret_cast<const float4*>(a.g + k);
+          float o[4] = {(x[c].x - mean) * scale * g.x, (x[c].y - mean) * scale * g.y, (x[c].z - mean) * scale * g.z, (x[c].w - mean) * scale * g.w};
+          if (a.b) {
+            const float4 b = *reinterpret_cast<const float4*>(a.b + k);
+            o[0] += b.x; o[1] += b.y; o[2] += b.z; o[3] += b.w;
+          }
+          uint2 hi, lo;
+          const bf16_t h0 = f32_to_bf16(o[0]), h1 = f32_to_bf16(o[1]), h2 = f32_to_bf16(o[2]), h3 = f32_to_bf16(o[3]);
+          hi.x = (uint32_t)h0 | ((uint32_t)h1 << 16); hi.y = (uint32_t)h2 | ((uint32_t)h3 << 16);
+          lo.x = (uint32_t)f32_to_bf16(o[0] - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(o[1] - bf16_to_f32(h1)) << 16);
+          lo.y = (uint32_t)f32_to_bf16(o[2] - bf16_to_f32(h2)) | ((uint32_t)f32_to_bf16(o[3] - bf16_to_f32(h3)) << 16);
+          const int e8 = (c - c0) * 32 + (lane >> 1), at = m ^ (e8 & 15);
+          reinterpret_cast<uint2*>(&s_hi[buf][e8][at])[lane & 1] = hi;
+          reinterpret_cast<uint2*>(&s_lo[buf][e8][at])[lane & 1] = lo;
+        }
+      }
+      __syncthreads();                            // the chunk is complete; its buffer is written again two chunks on
+      const int e8 = threadIdx.x >> 4, t = threadIdx.x & 15, ke = c0 * 32 + e8;      // eight columns, token
+      if (ke * 8 < d) {
+        X[(size_t)ke * 16 + t] = s_hi[buf][e8][t ^ (e8 & 15)];
+        X[(size_t)KT * 64 + (size_t)ke * 16 + t] = s_lo[buf][e8][t ^ (e8 & 15)];
+      }
+    }
+  }
+}
+
 hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
   if (a.M < 1 || a.M > 16 || (a.d & 31) || a.d > 8192) return hipErrorInvalidValue;
   // prompt pass: n_groups groups of 16 slots each (then M == 16: two-panel layout)
   if (a.n_groups < 0 || (a.n_groups > 0 && a.M != 16)) return hipErrorInvalidValue;
+  // a workgroup per group needs groups for half the compute units: the embedding of 511 rows of 5120 (32 groups) took 39 us that
+  // way against 17, so fewer groups, and the embedding, which gathers, keep a workgroup per row
+  if (a.n_groups >= 128 && a.d <= NORM_GROUPS_MAX_D && a.tokens == nullptr && a.ssq_out == nullptr && a.gate == nullptr) {
+    hipLaunchKernelGGL(k_norm_groups, dim3((unsigned)a.n_groups), dim3(1024), 0, s, a);
+    return hipGetLastError();
+  }
   const unsigned rows = a.n_groups > 0 ? 16u * (unsigned)a.n_groups : (unsigned)a.M;
   if (a.d <= 2048) hipLaunchKernelGGL(k_norm<256>, dim3(rows), dim3(256), 0, s, a);
   else hipLaunchKernelGGL(k_norm<1024>, dim3(rows), dim3(1024), 0, s, a);
@@ -3334,27 +3409,33 @@ hipError_t launch_gemm_dense(const DenseArgs& d, int epi, hipStream_t s) {
   }
 }
 
-// 1 / rms of every row of the prompt pass from its per-tile sums of squares, added in slot order.
-__global__ __launch_bounds__(256) void k_rstd_groups(const float* __restrict__ ssq, int n_ssq, int d, float eps,
-                                                     float* __restrict__ rstd) {
-  __shared__ float part[16][16];
+// 1 / rms of every row of the prompt pass from its per-tile sums of squares: 64 partial sums per row, added in order (bound by
+// the latency of the few loads per thread: four in flight; 7.3 us with 16 partial sums and one load at a time, 4.8 now, d 5120).
+__global__ __launch_bounds__(1024) void k_rstd_groups(const float* __restrict__ ssq, int n_ssq, int d, float eps,
+                                                      float* __restrict__ rstd) {
+  __shared__ float part[64][16];
   const int r = blockIdx.x, m = threadIdx.x & 15, p = threadIdx.x >> 4;
   const float* sq = ssq + (size_t)r * n_ssq * 16;
   float s = 0.f;
-  for (int i = p; i < n_ssq; i += 16) s += sq[i * 16 + m];
+  for (int i0 = p; i0 < n_ssq; i0 += 256) {
+    float t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = i0 + 64 * i < n_ssq ? sq[(i0 + 64 * i) * 16 + m] : 0.f;
+    s += (t[0] + t[1]) + (t[2] + t[3]);
+  }
   part[p][m] = s;
   __syncthreads();
-  if (p == 0) {
+  if (threadIdx.x < 16) {
     float tot = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) tot += part[i][m];
+    for (int i = 0; i < 64; ++i) tot += part[i][m];
     rstd[r * 16 + m] = 1.0f / sqrtf(tot / (float)d + eps);
   }
 }
 
 hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, float* rstd, int n_groups, hipStream_t s) {
   if (n_groups < 1 || n_ssq < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_rstd_groups, dim3(n_groups), dim3(256), 0, s, ssq, n_ssq, d, eps, rstd);
+  hipLaunchKernelGGL(k_rstd_groups, dim3(n_groups), dim3(1024), 0, s, ssq, n_ssq, d, eps, rstd);
   return hipGetLastError();
 }
 

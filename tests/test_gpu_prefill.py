@@ -190,6 +190,13 @@ def test_prefill_tiled_attention(shape, n, pre, page, permute, flags):
                   sigma=0.03, flags=flags, tight=2e-2 if flags else None)
 
 
+@pytest.mark.parametrize("d, n", [(192, 2035), (512, 2048)])
+def test_prefill_layernorm_of_whole_groups(d, n):
+    """128 token groups or more: the LayerNorm launches that build whole panel tiles (a width that is no multiple of the 512
+    columns they take at a time, and one that is; a ragged last group)."""
+    _prefill_case(W.ModelShape("A", 1, d, 2, 64, 1, 256, 496, max_pos=2200), 51, n, page=32, what=f"LayerNorm of whole groups, d {d}")
+
+
 def test_prefill_rejects_bad_arguments():
     shape = SMALL_B
     om, gm, okv, gkv, ws = setup_pair(shape, 11, capacity=64)
