@@ -293,17 +293,34 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 
 // QKV epilogue of one lane: output features n0 .. n0+3 (lo4) and their rotary partners n0 + d_head/2 ..
 // (hi4) of token row m at position pos: rotation, then the query row or the paged K / V entry.
-template <bool COH = false>
-__device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos,
-                                          float (&lo4)[4], float (&hi4)[4]) {
+// What it reads besides the products: rotary factors and the physical page (qkv_operands; the skinny kernel asks for them
+// before its weight stream ends).
+struct QkvOps { float4 t0, t1; int pp; };
+__device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, const int pos) {
   const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
+  const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1, pt = a.page_tokens;
+  QkvOps o;
+  o.t0 = o.t1 = make_float4(0.f, 0.f, 0.f, 0.f); o.pp = 0;
+  if (a.rope_tab != nullptr && head < a.nq + a.nkv) {
+    // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
+    const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
+    o.t0 = tab[0]; o.t1 = tab[1];
+  }
+  if (head >= a.nq) {
+    const bool pow2 = (pt & (pt - 1)) == 0;
+    const int lp = pow2 ? pos >> __builtin_ctz(pt) : pos / pt;
+    o.pp = a.page_table ? a.page_table[lp] : lp;
+  }
+  return o;
+}
+template <bool COH = false>
+__device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos, const QkvOps& ops,
+                                          float (&lo4)[4], float (&hi4)[4]) {
+  const int dsh = a.dh == 128 ? 7 : 6;
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1;
   const bool is_v = head >= a.nq + a.nkv;
   if (a.rope_tab != nullptr && !is_v) {
-    // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
-    const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
-    const float4 t0 = tab[0], t1 = tab[1];
-    const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+    const float cs[4] = {ops.t0.x, ops.t0.z, ops.t1.x, ops.t1.z}, sn[4] = {ops.t0.y, ops.t0.w, ops.t1.y, ops.t1.w};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float x0 = lo4[v], x1 = hi4[v];
@@ -320,8 +337,7 @@ __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int
     const int kvh = head - a.nq - sel * a.nkv;
     const int pt = a.page_tokens;
     const bool pow2 = (pt & (pt - 1)) == 0;
-    const int lp = pow2 ? pos >> __builtin_ctz(pt) : pos / pt, off = pos - lp * pt;
-    const int pp = a.page_table ? a.page_table[lp] : lp;
+    const int off = pow2 ? pos & (pt - 1) : pos % pt, pp = ops.pp;
     bf16_t* blk = a.kv_layer + (((size_t)pp * 2 + sel) * a.nkv + kvh) * a.page_tokens * a.dh;
     if (!is_v) {                 // K: [token][d_head]
       bf16_t* dst = blk + (size_t)off * a.dh + c;
@@ -459,6 +475,34 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     }
     asm volatile("" ::: "memory");     // keep these loads ahead of the rest of the stream
   }
+  // vectors and table entries of the epilogue are requested here, by the wavefronts that will use them, so that their round trip
+  // runs beside the weight stream instead of behind it (multi-query draft model, 12 layers: 381 -> 376 us per draft step; the
+  // residual rows of the PARTIAL epilogue, asked for here too, made the O-projection 0.7 us slower: they stay behind)
+  constexpr int TPU = PAIR ? 2 : 1;               // tiles per unit
+  const bool ep = w < UNITS;                      // this wavefront finishes one output unit
+  const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16x16 result
+  int urt[TPU];
+#pragma unroll
+  for (int i = 0; i < TPU; ++i) {
+    const int r = (ep ? w : 0) * TPU + i;
+    // (runtime index into rt[] would spill it: select with a compile-time loop)
+    urt[i] = 0;
+#pragma unroll
+    for (int rr = 0; rr < RT; ++rr) if (rr == r) urt[i] = rt[rr];
+  }
+  float4 cg[LN ? TPU : 1], cb[LN ? TPU : 1];
+  QkvOps qops;
+  if ((LN || EPI == EPI_QKV) && ep && m < a.M) {
+    if (LN) {
+#pragma unroll
+      for (int i = 0; i < TPU; ++i) {
+        const int row = urt[i] * 16 + 4 * g;
+        cg[LN ? i : 0] = *reinterpret_cast<const float4*>(a.wg + row); cb[LN ? i : 0] = *reinterpret_cast<const float4*>(a.wb + row);
+      }
+    }
+    if (EPI == EPI_QKV) qops = qkv_operands(a, urt[0] * 16 + 4 * g, a.pos0 + m);
+    asm volatile("" ::: "memory");
+  }
 #pragma unroll
   for (int i = 0; i < U; ++i)
     if (kt0 + i * NW < kt_end) load_x(B[i], kt0 + i * NW);
@@ -509,18 +553,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     }
   }
   __syncthreads();
-  constexpr int TPU = PAIR ? 2 : 1;               // tiles per unit
-  const bool ep = w < UNITS;                      // this wavefront finishes one output unit
-  const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16x16 result
   f32x4 y[TPU];
-  int urt[TPU];
 #pragma unroll
   for (int i = 0; i < TPU; ++i) {
     const int r = (ep ? w : 0) * TPU + i;
-    // (runtime index into rt[] would spill it: select with a compile-time loop)
-    urt[i] = 0;
-#pragma unroll
-    for (int rr = 0; rr < RT; ++rr) if (rr == r) urt[i] = rt[rr];
     y[i] = sm.red[0][r][lane];
 #pragma unroll
     for (int ww = 1; ww < NW; ++ww) y[i] += sm.red[ww][r][lane];   // fixed order: deterministic
@@ -586,10 +622,9 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
       const float rstd = 1.0f / sqrtf(var + a.eps);
 #pragma unroll
       for (int i = 0; i < TPU; ++i) {
-        const int row = urt[i] * 16 + 4 * g;
-        const float4 cg = *reinterpret_cast<const float4*>(a.wg + row), cb = *reinterpret_cast<const float4*>(a.wb + row);
-        y[i][0] = rstd * (y[i][0] - mean * cg.x) + cb.x; y[i][1] = rstd * (y[i][1] - mean * cg.y) + cb.y;
-        y[i][2] = rstd * (y[i][2] - mean * cg.z) + cb.z; y[i][3] = rstd * (y[i][3] - mean * cg.w) + cb.w;
+        const float4 vg = cg[LN ? i : 0], vb = cb[LN ? i : 0];
+        y[i][0] = rstd * (y[i][0] - mean * vg.x) + vb.x; y[i][1] = rstd * (y[i][1] - mean * vg.y) + vb.y;
+        y[i][2] = rstd * (y[i][2] - mean * vg.z) + vb.z; y[i][3] = rstd * (y[i][3] - mean * vg.w) + vb.w;
       }
     } else {
       const float rstd = 1.0f / sqrtf(ss / (float)a.d_in + a.eps);
@@ -628,7 +663,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     float lo4[4], hi4[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) { lo4[v] = y[0][v]; hi4[v] = y[TPU - 1][v]; }
-    qkv_store<COH>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, lo4, hi4);
+    qkv_store<COH>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, qops, lo4, hi4);
   } else if (EPI == EPI_SWIGLU) {
     // tile 0 = gate rows, tile 1 = the matching up rows
     const int f = (urt[0] >> 1) * 16 + 4 * g;
@@ -2919,7 +2954,8 @@ __device__ __forceinline__ void dense_epilogue(const DenseArgs& d, const int cb,
         xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, t0 * 16 + 4 * g, act);
       } else if (EPI == EPI_QKV) {
         float lo4[4] = {y0[0], y0[1], y0[2], y0[3]}, hi4[4] = {y1[0], y1[1], y1[2], y1[3]};
-        qkv_store(a, a.q + (size_t)ci * d.qs, t0 * 16 + 4 * g, m, a.pos0 + 16 * ci + m, lo4, hi4);
+        const int n0 = t0 * 16 + 4 * g, pos = a.pos0 + 16 * ci + m;
+        qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, qkv_operands(a, n0, pos), lo4, hi4);
       } else if (EPI == EPI_SWIGLU) {
         const int f = (t0 >> 1) * 16 + 4 * g;
         float act[4];
@@ -3124,7 +3160,8 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
           for (int i = 0; i < 2; ++i) {
             const int g = 2 * i + gh;             // 4-row group of the 16-row tile
             if constexpr (EPI == EPI_QKV) {
-              qkv_store(a, a.q + (size_t)ci * d.qs, t0 * 16 + 4 * g, m, a.pos0 + 16 * ci + m, y[i], y[i + 2]);
+              const int n0 = t0 * 16 + 4 * g, pos = a.pos0 + 16 * ci + m;
+              qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, qkv_operands(a, n0, pos), y[i], y[i + 2]);
             } else {
               float act[4];
 #pragma unroll
