@@ -195,16 +195,6 @@ def micro(B, W, dev, reps):
     return out
 
 
-def dense_kernel_args(epi, n_tiles, n_groups, bf16_act):
-    """Template arguments the library's launch rule picks for a dense GEMM of n_tiles 16-row tiles over n_groups
-    token groups: <epilogue, k-tiles in flight, row tiles per wavefront, bf16 activations>."""
-    ncb = -(-n_groups // (8 if bf16_act else 4))
-    if bf16_act and n_tiles % 8 == 0 and -(-n_tiles // 32) * ncb >= 256:
-        return "%d, 3, 8, true" % epi
-    rt = 4 if -(-n_tiles // 16) * ncb >= 256 else 2
-    return "%d, %d, %d, %s" % (epi, 4 if bf16_act else 5, rt, "true" if bf16_act else "false")
-
-
 def prefill_bench(B, W, dev, reps, models=("68m_draft", "13b_target"), lengths=(512, 1024, 2048), bf16_act=False):
     """Prompt pass of both models at 512 / 1024 / 2048 tokens: the dense pass against the same prompt fed
     in blocks of 16 through the verification forward.  Rates are ALGORITHMIC flops (2 per weight and
@@ -273,8 +263,7 @@ def prefill_bench(B, W, dev, reps, models=("68m_draft", "13b_target"), lengths=(
                    "tokens_per_s": n / res["dense"],
                    "roofline": {"bound": "mfma", "achieved": gemm_flops / probe_ms / 1e9, "peak": MFMA_PEAK_TFLOPS,
                                 "unit": "TFLOP/s", "frac": gemm_flops / probe_ms / 1e9 / MFMA_PEAK_TFLOPS, "traffic": None,
-                                "kernel": "k_gemm_dense<%s> (MLP-input GEMM of the prompt pass)" % dense_kernel_args(
-                                    4 if shape.family == "A" else 3, rows_in // 16, (n + 15) // 16, bf16_act),
+                                "kernel": "k_gemm_tile<%d> (MLP-input GEMM of the prompt pass)" % (4 if shape.family == "A" else 3),
                                 "flops_per_launch": gemm_flops, "avg_launch_ms": probe_ms, "launches_timed": len(probe),
                                 "note": ("algorithmic flops = matrix-unit flops (bf16 activations)" if bf16_act else
                                          "algorithmic flops; the bf16 hi + lo activation panels make the matrix unit do twice as many")}}

@@ -63,7 +63,6 @@ struct DenseArgs {
   const float* rstd;    // [group][16]: 1 / rms of the input rows (epilogues that read a normalised input)
   int hi_only;          // bf16 activations: the lo panels are not read
   int k_split;          // set by the launcher: K ranges (partial sums at g.planes, gemm_split_plane_bytes())
-  int tile_r, tile_t;   // set by the launcher: row blocks x token blocks walked by consecutive workgroups of an XCD
 };
 
 struct NormArgs {

@@ -2897,216 +2897,11 @@ hipError_t launch_loop_finish(const int32_t* sl_count, const uint32_t* gate, voi
 // ---------------------------------------------------------------------------------------------
 //
 // The prompt is processed before the first iteration (Sec. 2: the target model is given a prompt).
-// With hundreds of tokens per pass the GEMMs are bound by the matrix unit, not by the weight stream,
-// so the tiling differs from the skinny kernel: a wavefront owns RT weight row tiles x 4 token groups
-// (16 x 16 accumulators each), walks the whole K range itself (no K split, no cross-wavefront
-// reduction), and every weight tile it fetches feeds 8 matrix instructions (hi and lo panel of 4
-// groups).  The four wavefronts of a workgroup take neighbouring row tiles and the SAME token groups.
-// Workgroup ids are dealt round-robin to the 8 XCDs; every row block belongs to one XCD, whose
-// workgroups walk tiles of several row blocks x several token blocks (see the kernel), so that its L2
-// serves each weight and activation slab to all workgroups of the tile.  Operand layouts, precision (bf16 hi + lo activations, fp32
-// accumulation) and epilogue arithmetic are those of the skinny kernel.
-
-// Epilogues of the dense kernels for one wavefront: RT row tiles x CG token groups of accumulators.
-template <int EPI, int RT, int CG>
-__device__ __forceinline__ void dense_epilogue(const DenseArgs& d, const int cb, const int (&rt)[RT], f32x4 (&acc)[RT][CG]) {
-  constexpr bool PAIR = EpiTraits<EPI>::pair;
-  constexpr int UNITS = PAIR ? RT / 2 : RT, TPU = PAIR ? 2 : 1;
-  constexpr bool NORMED = (EPI != EPI_PARTIAL);
-  const GemmArgs& a = d.g;
-  const int lane = threadIdx.x & 63;
-  const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16 x 16 result
-#pragma unroll
-  for (int c = 0; c < CG; ++c) {
-    const int ci = cb * CG + c;
-    if (ci < d.n_groups) {
-    float rstd = 1.f;
-    if (NORMED && d.rstd != nullptr) rstd = d.rstd[ci * 16 + m];
-    // the residual values of all row tiles are requested before the first of them is used (and stored over)
-    float4 hv[EPI == EPI_PARTIAL ? UNITS : 1];
-    if (EPI == EPI_PARTIAL) {
-#pragma unroll
-      for (int u = 0; u < UNITS; ++u)
-        hv[u] = *reinterpret_cast<const float4*>(a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out + rt[u] * 16 + 4 * g);
-    }
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      f32x4 y0 = acc[u * TPU][c] * rstd, y1 = acc[u * TPU + TPU - 1][c] * rstd;
-      const int t0 = rt[u * TPU];
-      if (EPI == EPI_PARTIAL) {
-        // residual-stream update h += X.W^T, panels of gain * h and this tile's sums of squares for the next GEMM
-        const int col = t0 * 16 + 4 * g;
-        float4* hp = reinterpret_cast<float4*>(a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out + col);
-        float4 h = hv[EPI == EPI_PARTIAL ? u : 0];
-        h.x += y0[0]; h.y += y0[1]; h.z += y0[2]; h.w += y0[3];
-        *hp = h;
-        if (a.Xout != nullptr) {                  // deferred RMSNorm of the next GEMM (LayerNorm models: a norm launch instead)
-          const float4 gn = *reinterpret_cast<const float4*>(a.gain + col);
-          const float o[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
-          xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, col, o);
-          const float sq = row4_sum((h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w));
-          if (g == 0) a.ssq_out[(size_t)ci * d.ssq_outs + t0 * 16 + m] = sq;    // [slot][token]
-        }
-      } else if (EPI == EPI_GELU) {
-        float act[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) act[v] = 0.5f * y0[v] * (1.0f + erff(y0[v] * 0.70710678118654752f));
-        xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, t0 * 16 + 4 * g, act);
-      } else if (EPI == EPI_QKV) {
-        float lo4[4] = {y0[0], y0[1], y0[2], y0[3]}, hi4[4] = {y1[0], y1[1], y1[2], y1[3]};
-        const int n0 = t0 * 16 + 4 * g, pos = a.pos0 + 16 * ci + m;
-        qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, qkv_operands(a, n0, pos), lo4, hi4);
-      } else if (EPI == EPI_SWIGLU) {
-        const int f = (t0 >> 1) * 16 + 4 * g;
-        float act[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) act[v] = y0[v] / (1.0f + expf(-y0[v])) * y1[v];
-        xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, f, act);
-      }
-    }
-    }
-  }
-}
-
-// The activation tiles are shared through LDS: wavefront w fetches the hi and lo tile
-// of token group w only (a quarter of the workgroup's activation tiles), a two-stage LDS ring hands
-// them to the other three, and the registers freed that way hold NB k-tiles of loads in flight.  One
-// workgroup barrier per k-tile; every wavefront runs the same trip count (idle ones compute on clamped
-// rows and store nothing).
-// HI: bf16 activations.  Only the hi panels are read, and the LDS slots and matrix instructions that the lo
-// panels took serve four more token groups instead: a workgroup then covers 8 token groups, the work per weight
-// tile is unchanged and the weights are fetched half as often.
-template <int EPI, int NB, int RT, bool HI>
-__global__ __launch_bounds__(256) void k_gemm_dense(DenseArgs d) {
-  constexpr int CG = HI ? 8 : 4, NWV = 4, NS = NB + 1;
-  constexpr bool PAIR = EpiTraits<EPI>::pair;
-  constexpr int UNITS = PAIR ? RT / 2 : RT;
-  __shared__ u32x4 bs[HI ? 3 : 2][8][64];
-  const GemmArgs& a = d.g;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int n_tiles = a.n_rows >> 4;
-  const int ncb = (d.n_groups + CG - 1) / CG;
-  const int nrb = (n_tiles + RT * NWV - 1) / (RT * NWV);
-  // Workgroup ids go round-robin to the 8 XCDs.  Within an XCD consecutive ids walk a tile of tile_r row
-  // blocks x tile_t token blocks (about as many workgroups as the XCD runs at once), so that what its L2
-  // must fetch for the workgroups in flight is tile_r weight slabs + tile_t activation slabs.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int per_tile = d.tile_r * d.tile_t, n_tg = (ncb + d.tile_t - 1) / d.tile_t;
-  const int tile = slot / per_tile, in_tile = slot % per_tile;
-  const int rbl = (tile / n_tg) * d.tile_r + in_tile / d.tile_t;          // row block index within the XCD
-  const int rb = rbl * 8 + xcd, cb = (tile % n_tg) * d.tile_t + in_tile % d.tile_t;
-  if (rb >= nrb || cb >= ncb) return;             // whole workgroup
-  const bool live = (rb * NWV + w) * RT < n_tiles;
-  const int b = live ? rb * NWV + w : n_tiles / RT - 1;
-  int rt[RT];
-  if (PAIR) {
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const int bp = b * UNITS + u, gs = __builtin_ctz(a.grp);   // the pairing distance is a power of two
-      rt[2 * u] = ((bp >> gs) << (gs + 1)) + (bp & (a.grp - 1));
-      rt[2 * u + 1] = rt[2 * u] + a.grp;
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < RT; ++r) rt[r] = b * RT + r;
-  }
-  const int KT = a.KT;
-  const u32x4* Wp[RT];
-#pragma unroll
-  for (int r = 0; r < RT; ++r) Wp[r] = reinterpret_cast<const u32x4*>(a.W) + (size_t)rt[r] * KT * 64 + lane;
-  // the two activation tiles this wavefront hands to the workgroup per k-tile: hi and lo panel of token group w, or
-  // (HI) the hi panels of token groups 2w and 2w + 1
-  const u32x4* Xw = reinterpret_cast<const u32x4*>(a.X + (size_t)min(cb * CG + (HI ? 2 * w : w), d.n_groups - 1) * d.xs) + lane;
-  const u32x4* Xw1 = HI ? reinterpret_cast<const u32x4*>(a.X + (size_t)min(cb * CG + 2 * w + 1, d.n_groups - 1) * d.xs) + lane
-                        : Xw + (size_t)a.KT * 64;
-  f32x4 acc[RT][CG];
-#pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int c = 0; c < CG; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  u32x4 A[NS][RT], Bw[NS][2];
-  auto gload = [&](u32x4 (&Ad)[RT], u32x4 (&Bd)[2], const int kt) {
-    const size_t t = (size_t)(kt < KT ? kt : KT - 1) * 64;
-    if (HI) { Bd[0] = Xw[t]; Bd[1] = Xw1[t]; }    // first: the pipelined form needs them one k-tile earlier than the weights
-#pragma unroll
-    for (int r = 0; r < RT; ++r) Ad[r] = Wp[r][t];
-    if (!HI) { Bd[0] = Xw[t]; Bd[1] = Xw1[t]; }
-  };
-#pragma unroll
-  for (int i = 0; i < NB; ++i) gload(A[i], Bw[i], i);
-  if constexpr (HI) {
-    // Three LDS stages, fragments read one k-tile ahead (with half the matrix work per k-tile the LDS round trip at the
-    // head of an iteration shows; with hi + lo panels it hides behind twice the matrix instructions, and this form,
-    // which asks for the activation tiles a k-tile earlier, measured slower there).  Iteration kt: request k-tile
-    // kt + NB from memory, read the fragments of k-tile kt + 1 from stage (kt + 1) % 3 (written an iteration ago,
-    // barrier passed) while the matrix instructions of k-tile kt run on the fragments read an iteration ago, put this
-    // wavefront's share of k-tile kt + 2 into stage (kt + 2) % 3 (its last readers passed two barriers ago), barrier.
-    static_assert(!HI || NB >= 3, "the activation tiles of k-tile kt + 2 go to LDS in iteration kt: they must have been requested before it");
-    bs[0][2 * w][lane] = Bw[0][0]; bs[0][2 * w + 1][lane] = Bw[0][1];
-    bs[1][2 * w][lane] = Bw[1][0]; bs[1][2 * w + 1][lane] = Bw[1][1];
-    __syncthreads();
-    u32x4 Bf[8], Bn[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) Bf[t] = bs[0][t][lane];
-    int st1 = 1, st2 = 2;                         // (kt + 1) % 3, (kt + 2) % 3
-    for (int kt0 = 0; kt0 < KT; kt0 += NS) {
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        const int kt = kt0 + i;
-        if (kt < KT) {                            // uniform over the workgroup
-          gload(A[(i + NB) % NS], Bw[(i + NB) % NS], kt + NB);
-#pragma unroll
-          for (int t = 0; t < 8; ++t) Bn[t] = bs[st1][t][lane];
-          bs[st2][2 * w][lane] = Bw[(i + 2) % NS][0];
-          bs[st2][2 * w + 1][lane] = Bw[(i + 2) % NS][1];
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-              acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(A[i][r]), as_bf16x8(Bf[c]), acc[r][c], 0, 0, 0);
-#pragma unroll
-          for (int t = 0; t < 8; ++t) Bf[t] = Bn[t];
-          st1 = st2; st2 = st2 == 2 ? 0 : st2 + 1;
-          __syncthreads();
-        }
-      }
-    }
-  } else {
-    static_assert(NB >= 2, "the slot refilled in an iteration must not be the one it hands to LDS");
-    bs[0][2 * w][lane] = Bw[0][0]; bs[0][2 * w + 1][lane] = Bw[0][1];
-    __syncthreads();
-    // Iteration kt: request k-tile kt + NB from memory, read the fragments of k-tile kt from LDS stage
-    // kt % 2, put this wavefront's share of k-tile kt + 1 into the other stage (its readers passed the
-    // barrier of the iteration before), run the matrix instructions of k-tile kt, barrier.
-    for (int kt0 = 0; kt0 < KT; kt0 += NS) {
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        const int kt = kt0 + i;
-        if (kt < KT) {                            // uniform over the workgroup
-          gload(A[(i + NB) % NS], Bw[(i + NB) % NS], kt + NB);
-          u32x4 Bf[8];
-#pragma unroll
-          for (int t = 0; t < 8; ++t) Bf[t] = bs[kt & 1][t][lane];
-          bs[(kt + 1) & 1][2 * w][lane] = Bw[(i + 1) % NS][0];
-          bs[(kt + 1) & 1][2 * w + 1][lane] = Bw[(i + 1) % NS][1];
-          // hi panels of all accumulators, then lo panels: no instruction reads the result of the one before it
-#pragma unroll
-          for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-              for (int c = 0; c < CG; ++c)
-                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(A[i][r]), as_bf16x8(Bf[2 * c + p]), acc[r][c], 0, 0, 0);
-          __syncthreads();
-        }
-      }
-    }
-  }
-  if (live) dense_epilogue<EPI, RT, CG>(d, cb, rt, acc);
-}
-
-// The kernel of nearly every prompt: a workgroup of 8 wavefronts (WR x WC) owns WR x R2 blocks of 32 rows x WC x C2 blocks of
+// With hundreds of tokens per pass the GEMMs are bound by the matrix unit, not by the weight stream, so the tiling differs from
+// the skinny kernel: both operands are shared by the wavefronts of a workgroup through LDS.  Operand layouts, precision (bf16
+// hi + lo activations, fp32 accumulation) and epilogue arithmetic are those of the skinny kernel.
+//
+// A workgroup of 8 wavefronts (WR x WC) owns WR x R2 blocks of 32 rows x WC x C2 blocks of
 // 32 panel columns.  With hi + lo panels 64 panel columns are 32 tokens (the lo products are added into the accumulators of
 // the hi products), with bf16 activations 64.  What bounds it: the matrix unit at the clock that the power limit leaves
 // (1.9 of 2.4 GHz; the main loop alone ran at 1.2 - 1.5 PFLOP/s depending on the card, in 94 % of its cycles), so
@@ -3365,17 +3160,22 @@ static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   auto count = [&](const int na, const int nbt) { const int gg = nbt / (HI ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((d.n_groups + gg - 1) / gg); };
   auto grid = [](const long t) { return dim3(8u * (unsigned)((t + 7) / 8)); };
   // Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
-  // hi + lo only: 128-token accumulators).  Costs in units of half a compute unit's time for a 256 x 256 tile; the
+  // hi + lo only: 128-token accumulators); 128 x 128 (c3) where a short K and a small grid leave nothing but the latency of the
+  // k-tiles.  Costs in units of half a compute unit's time for a 256 x 256 tile; the
   // larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
   // fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
   // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
   // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 115 with its sum.
-  const long t0 = count(8, 16), t1 = count(16, 16), t2 = count(32, 16);
+  // c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
+  const long t0 = count(8, 16), t1 = count(16, 16), t2 = count(32, 16), t3 = count(8, 8);
   const long rem = t0 % 512;
   const double c0 = ((double)(t0 / 512) * 2.0 + (rem == 0 ? 0.0 : (rem <= 256 ? 1.4 : 2.0))) / 0.95;
   const double c1 = (double)((t1 + 255) / 256) * 2.0, c2 = HI ? 1e30 : (double)((t2 + 255) / 256) * 4.0 / 1.06;
+  const double c3 = t3 <= 256 ? 1.35 : 1e30;
   const double unit_us = 0.3 * KT;
-  double best = (c0 < c1 ? (c0 < c2 ? c0 : c2) : (c1 < c2 ? c1 : c2)) * unit_us;
+  double best = (c0 < c1 ? (c0 < c2 ? c0 : c2) : (c1 < c2 ? c1 : c2));
+  if (c3 < best) best = c3;
+  best *= unit_us;
   int split = 1;
   if (d.g.planes != nullptr)
     for (int S = 2; S <= 16 && t1 * S <= 256 && KT / S >= 8; ++S) {
@@ -3389,6 +3189,10 @@ static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
     hipLaunchKernelGGL((k_gemm_sum<EPI, HI>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, d);
     return hipGetLastError();
   }
+  if (c3 < c0) {
+    hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 1, 2, 3, 4, HI>), grid(t3), dim3(512), 0, s, d);
+    return hipGetLastError();
+  }
   if constexpr (!HI) if (c2 < c0 && c2 < c1) {
     hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 4, 4, 3, 2, HI>), grid(t2), dim3(512), 0, s, d);
     return hipGetLastError();
@@ -3398,38 +3202,9 @@ static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int EPI, int NB, int RT, bool HI>
-static hipError_t launch_gemm_dense_rt(const DenseArgs& d, hipStream_t s) {
-  constexpr int CG = HI ? 8 : 4;
-  const int n_tiles = d.g.n_rows / 16, ncb = (d.n_groups + CG - 1) / CG;
-  const int nrb = (n_tiles + 4 * RT - 1) / (4 * RT);
-  DenseArgs a = d;
-  // about 64 workgroups run on an XCD at once: 8 x 8 for long prompts, 16 x 4 measured better at 8 token blocks
-  a.tile_t = ncb >= 16 ? 8 : (ncb < 4 ? ncb : 4);
-  const int nrbl = (nrb + 7) / 8;                 // row blocks per XCD
-  a.tile_r = 64 / a.tile_t < nrbl ? 64 / a.tile_t : nrbl;
-  const long long blocks = 8LL * ((nrbl + a.tile_r - 1) / a.tile_r) * ((ncb + a.tile_t - 1) / a.tile_t) * a.tile_r * a.tile_t;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_gemm_dense<EPI, NB, RT, HI>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-// 64-row wavefront tiles unless they would leave compute units without a workgroup.
-template <int EPI, bool HI>
-static hipError_t launch_gemm_dense_e(const DenseArgs& d, hipStream_t s) {
-  constexpr int CG = HI ? 8 : 4;
-  constexpr int NB = HI ? 4 : 5;                  // k-tiles of loads in flight per wavefront (measured best of 3..5 with two panels)
-  const int n_tiles = d.g.n_rows / 16, ncb = (d.n_groups + CG - 1) / CG;
-  if ((long)((n_tiles + 15) / 16) * ncb >= 256) return launch_gemm_dense_rt<EPI, NB, 4, HI>(d, s);
-  return launch_gemm_dense_rt<EPI, NB, 2, HI>(d, s);
-}
-
 template <int EPI>
 static hipError_t launch_gemm_dense_h(const DenseArgs& d, hipStream_t s) {
-  // Narrow matrices and short prompts (K below 512 or fewer than 512 rows, up to 2047 tokens) leave a large-tile grid nearly empty:
-  // 4-layer model of width 256: 196 us against 184 at 33 tokens, 391 against 465 at 3000 (launches and all)
-  if ((d.g.KT >= 16 && d.g.n_rows >= 512) || d.n_groups >= 128) return d.hi_only ? launch_gemm_tile<EPI, true>(d, s) : launch_gemm_tile<EPI, false>(d, s);
-  return d.hi_only ? launch_gemm_dense_e<EPI, true>(d, s) : launch_gemm_dense_e<EPI, false>(d, s);
+  return d.hi_only ? launch_gemm_tile<EPI, true>(d, s) : launch_gemm_tile<EPI, false>(d, s);
 }
 
 hipError_t launch_gemm_dense(const DenseArgs& d, int epi, hipStream_t s) {
