@@ -2918,7 +2918,7 @@ hipError_t launch_loop_finish(const int32_t* sl_count, const uint32_t* gate, voi
 //
 // Matrices with few tiles (d_model rows at some hundred tokens; every matrix at some tens) are cut along K as well: EPI_SPLIT
 // stores a range's sums, k_gemm_sum adds the ranges in order and runs the epilogue.  (Partial sums through write-through
-// stores and a ticket in one launch measured slower than no split at all: 110 us against 50 for 5120 x 5120 at 511 tokens.)
+// stores and a ticket in one launch measured slower than no split at all: 110 us against 50 + 16 for 5120 x 5120 at 511 tokens.)
 
 // Epilogue of one wavefront: R2 pairs of row tiles (rt[2 q], rt[2 q + 1]; -1 past the matrix) x CA accumulators of 32 rows x
 // 32 tokens.  Lane: token column lane % 32 (two groups of 16), rows 8 i + 4 (lane / 32) .. + 3 of chunk i = 0 .. 3.
@@ -3165,7 +3165,7 @@ static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   // larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
   // fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
   // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
-  // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 115 with its sum.
+  // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 137 + 17 for its sum.
   // c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
   const long t0 = count(8, 16), t1 = count(16, 16), t2 = count(32, 16), t3 = count(8, 8);
   const long rem = t0 % 512;
