@@ -324,8 +324,10 @@ __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float x0 = lo4[v], x1 = hi4[v];
-      lo4[v] = x0 * cs[v] - x1 * sn[v];
-      hi4[v] = x1 * cs[v] + x0 * sn[v];
+      // which product is rounded is stated here: left to the compiler it differed between the kernels that share this code,
+      // so that a query or key depended on the launch structure and on the block's length
+      lo4[v] = fmaf(x0, cs[v], -(x1 * sn[v]));
+      hi4[v] = fmaf(x1, cs[v], x0 * sn[v]);
     }
   }
   if (head < a.nq) {

@@ -91,6 +91,28 @@ def test_fused_launch_writes_the_same_cache_entries():
             assert torch.equal(bufs[0], bufs[1]), (shape.d_model, ctx, page_tokens)
 
 
+def test_fused_launch_rotates_queries_bitwise_like_the_projection_launch():
+    """The rotation rounds the same product in every kernel that runs it.  The query rows (fp32, in the workspace behind the
+    16 residual rows) show a difference in nearly every element, where a bf16 cache entry flips once in some 10^5."""
+    d = dev()
+    for shape in (W.scaled_shape(W.CFG1_DRAFT, n_layers=1, vocab=4096), W.scaled_shape(W.CFG2_TARGET, n_layers=1, vocab=4096)):
+        gm = B.DiscoModel(shape, W.make_weights(shape, 9, "bf16"), d)
+        ctx, dq = 130, shape.n_heads * shape.d_head
+        fill = W.make_kv_fill(shape, ctx, 3).to(d)
+        first = (64 * shape.d_model + 255) // 256 * 256
+        for M in (1, 5, 8, 9, 16):
+            got = []
+            for mode in (0, 2):
+                gkv, ws = B.DiscoKV(gm, ctx + 32, 16), gm.workspace(16, ctx + 32)
+                gkv.buf.zero_()
+                gkv.fill(fill)
+                _verify(gm, gkv, ws, W.make_tokens(3, M, shape.vocab).tolist(), mode)
+                got.append((ws.buf[first:first + 64 * dq].view(torch.float32).view(16, dq)[:M].clone(), gkv.buf.clone()))
+            assert float(got[0][0].abs().max()) > 0.0
+            assert torch.equal(got[0][0], got[1][0]), (shape.d_model, M)
+            assert torch.equal(got[0][1], got[1][1]), (shape.d_model, M)
+
+
 def _loop(gm, clf, fill, ctx, cap, tau, static_sl, ws, logits, tok0, force, mode):
     d = dev()
     kv = B.DiscoKV(gm, ctx + 32, 16)
