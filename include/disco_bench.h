@@ -26,6 +26,14 @@ float disco_probe_read_ms(void);
  * (disco_workspace_init).  Returns the previous value.  Process-wide.                                     */
 int disco_set_wait_limit(int polls);
 
+/* Testing and measurement aid: the kernels that disco_prefill_ex chooses for a prompt of n_tokens in a cache of
+ * page_tokens tokens per page, without a launch.  out[0 .. 3]: QKV projection, O-projection, MLP input, MLP output:
+ * the workgroup tile (0: 128 rows x 256 panel columns, 1: 256 x 256, 2: 512 x 256, 3: 128 x 128), or 100 + S where
+ * the matrix is cut along K into S ranges; out[4]: 1 if the attention runs in LDS tiles; out[5]: 1 if the LayerNorm
+ * launches take whole groups of 16 tokens.  0, or DISCO_EINVAL.                                            */
+struct disco_model;
+int disco_prefill_plan(const struct disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[6]);
+
 #ifdef __cplusplus
 }
 #endif

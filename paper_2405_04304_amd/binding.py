@@ -137,6 +137,7 @@ _SIGNATURES = {
     "disco_probe_enable": (C.c_int, [C.c_int]),
     "disco_probe_read_ms": (C.c_float, []),
     "disco_set_wait_limit": (C.c_int, [C.c_int]),
+    "disco_prefill_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_uint, C.c_int, C.POINTER(C.c_int)]),
 }
 EXPORTS = sorted(_SIGNATURES)
 
@@ -341,6 +342,13 @@ def disco_set_launch_mode(mode: int) -> int:
 
 def disco_set_wait_limit(polls: int) -> int:
     return int(lib().disco_set_wait_limit(polls))
+
+
+def disco_prefill_plan(model_handle, n_tokens: int, flags: int = 0, page_tokens: int = 16) -> dict:
+    """The kernels a prompt pass would launch (disco_bench.h): tile codes of its four matrices, attention, LayerNorm."""
+    out = (C.c_int * 6)()
+    _check(lib().disco_prefill_plan(model_handle, n_tokens, flags, page_tokens, out))
+    return {"qkv": out[0], "o": out[1], "mlp_in": out[2], "mlp_out": out[3], "attn_tiles": bool(out[4]), "norm_groups": bool(out[5])}
 
 
 def disco_probe_enable(layer: int) -> None:

@@ -1035,6 +1035,21 @@ int disco_set_wait_limit(int polls) {
   return prev;
 }
 
+int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[6]) {
+  if (!m || !out || n_tokens < 1 || n_tokens > DISCO_PREFILL_MAX || page_tokens < 4 || page_tokens % 4) return fail(DISCO_EINVAL, "bad argument");
+  const disco_model_desc& d = m->d;
+  const bool fam_a = d.family == DISCO_FAMILY_A, hi = (flags & DISCO_PREFILL_BF16_ACTIVATIONS) != 0;
+  const int G = (n_tokens + 15) / 16;
+  const int rows[4] = {m->d_qkv, d.d_model, fam_a ? d.d_ff : 2 * d.d_ff, d.d_model}, k[4] = {d.d_model, m->d_q, d.d_model, d.d_ff};
+  for (int i = 0; i < 4; ++i) {
+    const DensePlan p = gemm_dense_plan(rows[i], k[i] / 32, G, hi, true);
+    out[i] = p.split > 1 ? 100 + p.split : p.tile;
+  }
+  out[4] = attn_tiles_fit(d.n_heads, d.n_kv_heads, d.d_head, page_tokens, G) ? 1 : 0;
+  out[5] = fam_a && norm_groups_fit(d.d_model, G) ? 1 : 0;
+  return DISCO_OK;
+}
+
 int disco_probe_enable(int layer) {
   std::lock_guard<std::mutex> lock(g_probe_mu);
   g_probe_taken = false;

@@ -992,13 +992,15 @@ __global__ __launch_bounds__(1024) void k_norm_groups(NormArgs a) {
   }
 }
 
+// a workgroup per group needs groups for half the compute units: the embedding of 511 rows of 5120 (32 groups) took 39 us that
+// way against 17, so fewer groups, and the embedding, which gathers, keep a workgroup per row
+bool norm_groups_fit(int d, int n_groups) { return n_groups >= 128 && d <= NORM_GROUPS_MAX_D; }
+
 hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
   if (a.M < 1 || a.M > 16 || (a.d & 31) || a.d > 8192) return hipErrorInvalidValue;
   // prompt pass: n_groups groups of 16 slots each (then M == 16: two-panel layout)
   if (a.n_groups < 0 || (a.n_groups > 0 && a.M != 16)) return hipErrorInvalidValue;
-  // a workgroup per group needs groups for half the compute units: the embedding of 511 rows of 5120 (32 groups) took 39 us that
-  // way against 17, so fewer groups, and the embedding, which gathers, keep a workgroup per row
-  if (a.n_groups >= 128 && a.d <= NORM_GROUPS_MAX_D && a.tokens == nullptr && a.ssq_out == nullptr && a.gate == nullptr) {
+  if (a.tokens == nullptr && a.ssq_out == nullptr && a.gate == nullptr && norm_groups_fit(a.d, a.n_groups)) {
     hipLaunchKernelGGL(k_norm_groups, dim3((unsigned)a.n_groups), dim3(1024), 0, s, a);
     return hipGetLastError();
   }
@@ -1643,15 +1645,24 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The tiled kernel walks the positions one tile after another, so it needs workgroups for half the compute units: hi + lo, us
+// (tiles / groups), 48 heads on one K / V head 333 / 749 at 3001 tokens (1128 workgroups), 40 heads 32 / 39 at 511 (160),
+// but 12 heads of 64 channels 20 / 12 at 511 (48); a whole pass of one 13B layer at 130 after 333 (80) 376 / 366
+static int attn_tiles_hw_log2(int nq, int nkv) { const int rep = nq / nkv; return rep % 4 == 0 ? 2 : (rep % 2 == 0 ? 1 : 0); }   // log2 of the heads per workgroup
+static dim3 attn_tiles_grid(int nq, int nkv, int n_groups) {
+  const int hw = attn_tiles_hw_log2(nq, nkv), tbs = (n_groups + 1) / 2, tw = 4 >> hw;
+  return dim3(nq >> hw, (tbs + tw - 1) / tw);
+}
+bool attn_tiles_fit(int nq, int nkv, int dh, int page_tokens, int n_groups) {
+  const dim3 g = attn_tiles_grid(nq, nkv, n_groups);
+  return page_tokens >= 8 && (page_tokens & (page_tokens - 1)) == 0 && (dh == 64 || dh == 128) && (long)g.x * g.y >= 128;
+}
+
 hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, bool bf16_operands, hipStream_t s) {
   if (a.M != 16 || n_groups < 1 || n_groups > 65535) return hipErrorInvalidValue;
-  // The tiled kernel walks the positions one tile after another, so it needs workgroups for half the compute units: hi + lo, us
-  // (tiles / groups), 48 heads on one K / V head 333 / 749 at 3001 tokens (1128 workgroups), 40 heads 32 / 39 at 511 (160),
-  // but 12 heads of 64 channels 20 / 12 at 511 (48); a whole pass of one 13B layer at 130 after 333 (80) 376 / 366
-  const int rep = a.nq / a.nkv, hw = rep % 4 == 0 ? 2 : (rep % 2 == 0 ? 1 : 0);       // log2 of the heads per workgroup
-  const int tbs = (n_groups + 1) / 2, tw = 4 >> hw;
-  const dim3 g(a.nq >> hw, (tbs + tw - 1) / tw);
-  if (a.page_tokens >= 8 && (a.page_tokens & (a.page_tokens - 1)) == 0 && (a.dh == 64 || a.dh == 128) && (long)g.x * g.y >= 128) {
+  if (attn_tiles_fit(a.nq, a.nkv, a.dh, a.page_tokens, n_groups)) {
+    const dim3 g = attn_tiles_grid(a.nq, a.nkv, n_groups);
+    const int hw = attn_tiles_hw_log2(a.nq, a.nkv);
     if (a.dh == 128) {
       if (bf16_operands) hipLaunchKernelGGL((k_attn_tiles<128, false>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
       else hipLaunchKernelGGL((k_attn_tiles<128, true>), g, dim3(256), 0, s, a, n_groups, x_stride, hw);
@@ -3155,52 +3166,54 @@ __global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
 // Bytes of partial sums that a split launch may use: 256 workgroups of 256 x 256.
 size_t gemm_split_plane_bytes() { return (size_t)256 * 256 * 256 * sizeof(float); }
 
-template <int EPI, bool HI>
-static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
-  DenseArgs d = d0;
-  const int n_tiles = d.g.n_rows / 16, KT = d.g.KT;
-  auto count = [&](const int na, const int nbt) { const int gg = nbt / (HI ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((d.n_groups + gg - 1) / gg); };
-  auto grid = [](const long t) { return dim3(8u * (unsigned)((t + 7) / 8)); };
-  // Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
-  // hi + lo only: 128-token accumulators); 128 x 128 (c3) where a short K and a small grid leave nothing but the latency of the
-  // k-tiles.  Costs in units of half a compute unit's time for a 256 x 256 tile; the
-  // larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
-  // fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
-  // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
-  // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 137 + 17 for its sum.
-  // c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
-  const long t0 = count(8, 16), t1 = count(16, 16), t2 = count(32, 16), t3 = count(8, 8);
-  const long rem = t0 % 512;
-  const double c0 = ((double)(t0 / 512) * 2.0 + (rem == 0 ? 0.0 : (rem <= 256 ? 1.4 : 2.0))) / 0.95;
-  const double c1 = (double)((t1 + 255) / 256) * 2.0, c2 = HI ? 1e30 : (double)((t2 + 255) / 256) * 4.0 / 1.06;
-  const double c3 = t3 <= 256 ? 1.35 : 1e30;
+// Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
+// hi + lo only: 128-token accumulators); 128 x 128 (c3) where a short K and a small grid leave nothing but the latency of the
+// k-tiles.  Costs in units of half a compute unit's time for a 256 x 256 tile; the
+// larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
+// fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
+// 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
+// 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 137 + 17 for its sum.
+// c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
+DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, bool may_split) {
+  const int n_tiles = n_rows / 16;
+  auto count = [&](const int na, const int nbt) { const int gg = nbt / (hi_only ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((n_groups + gg - 1) / gg); };
+  const long wgs[4] = {count(8, 16), count(16, 16), count(32, 16), count(8, 8)};
+  const long rem = wgs[0] % 512;
+  const double c0 = ((double)(wgs[0] / 512) * 2.0 + (rem == 0 ? 0.0 : (rem <= 256 ? 1.4 : 2.0))) / 0.95;
+  const double c1 = (double)((wgs[1] + 255) / 256) * 2.0, c2 = hi_only ? 1e30 : (double)((wgs[2] + 255) / 256) * 4.0 / 1.06;
+  const double c3 = wgs[3] <= 256 ? 1.35 : 1e30;
   const double unit_us = 0.3 * KT;
   double best = (c0 < c1 ? (c0 < c2 ? c0 : c2) : (c1 < c2 ? c1 : c2));
   if (c3 < best) best = c3;
   best *= unit_us;
   int split = 1;
-  if (d.g.planes != nullptr)
-    for (int S = 2; S <= 16 && t1 * S <= 256 && KT / S >= 8; ++S) {
-      const double us = 2.0 / S * unit_us + 8.0 + (double)t1 * S * (HI ? 0.262 : 0.131) * 2.0 / 4.0;   // two passes over the partial sums at 4 TB/s, a launch
+  if (may_split)
+    for (int S = 2; S <= 16 && wgs[1] * S <= 256 && KT / S >= 8; ++S) {
+      const double us = 2.0 / S * unit_us + 8.0 + (double)wgs[1] * S * (hi_only ? 0.262 : 0.131) * 2.0 / 4.0;   // two passes over the partial sums at 4 TB/s, a launch
       if (us < best) { best = us; split = S; }
     }
-  if (split > 1) {
-    d.k_split = split;
-    hipLaunchKernelGGL((k_gemm_tile<EPI_SPLIT, 2, 4, 4, 2, 4, 2, HI>), grid(t1 * split), dim3(512), 0, s, d);
-    const long waves = (long)(n_tiles / 2) * ((d.n_groups + 1) / 2);
+  const int tile = split > 1 ? 1 : (c3 < c0 ? 3 : (c2 < c0 && c2 < c1 ? 2 : (c1 < c0 ? 1 : 0)));
+  return DensePlan{tile, split, wgs[tile]};
+}
+
+template <int EPI, bool HI>
+static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
+  DenseArgs d = d0;
+  const DensePlan p = gemm_dense_plan(d.g.n_rows, d.g.KT, d.n_groups, HI, d.g.planes != nullptr);
+  const dim3 grid(8u * (unsigned)((p.wgs * p.split + 7) / 8));
+  if (p.split > 1) {
+    d.k_split = p.split;
+    hipLaunchKernelGGL((k_gemm_tile<EPI_SPLIT, 2, 4, 4, 2, 4, 2, HI>), grid, dim3(512), 0, s, d);
+    const long waves = (long)(d.g.n_rows / 32) * ((d.n_groups + 1) / 2);
     hipLaunchKernelGGL((k_gemm_sum<EPI, HI>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, d);
     return hipGetLastError();
   }
-  if (c3 < c0) {
-    hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 1, 2, 3, 4, HI>), grid(t3), dim3(512), 0, s, d);
-    return hipGetLastError();
+  switch (p.tile) {
+    case 0: hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 2, 2, 3, 4, HI>), grid, dim3(512), 0, s, d); break;
+    case 1: hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 4, 2, 4, 2, HI>), grid, dim3(512), 0, s, d); break;
+    case 2: if constexpr (!HI) hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 4, 4, 3, 2, HI>), grid, dim3(512), 0, s, d); break;
+    default: hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 1, 2, 3, 4, HI>), grid, dim3(512), 0, s, d); break;
   }
-  if constexpr (!HI) if (c2 < c0 && c2 < c1) {
-    hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 4, 4, 3, 2, HI>), grid(t2), dim3(512), 0, s, d);
-    return hipGetLastError();
-  }
-  if (c1 < c0) hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 4, 2, 4, 2, HI>), grid(t1), dim3(512), 0, s, d);
-  else hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 2, 2, 3, 4, HI>), grid(t0), dim3(512), 0, s, d);
   return hipGetLastError();
 }
 
