@@ -1428,7 +1428,8 @@ __global__ __launch_bounds__(512) void k_attn_groups(AttnArgs a, int n_groups, s
 // column of 16 rows) are free of bank conflicts.  Bound by the matrix unit and the soft-max's vector instructions, about
 // equal at hi + lo.  Measured per layer, 48 heads on one K / V head, 3001 tokens after 333: 333 us against 749 with 32 query
 // columns per pass over the cache; 40 heads, 2048 tokens, bf16 operands: 87 against 211.
-// Needs pages of a power of two of at least 8 tokens (a V^T chunk is 8 tokens of a channel).
+// Needs pages of a power of two of at least 8 tokens (a V^T chunk is 8 tokens of a channel) and of fewer than 2^32 elements
+// (offsets inside a page are 32-bit; the page's own offset is 64-bit).
 template <int DH, bool LO>
 __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups, size_t x_stride, int hw_log2) {
   constexpr int KB = 64, S16 = DH / 16, CB = DH / 32, CK = DH / 8, RPI = 64 / CK, PER = DH / 32;   // PER: copies of K (and of V) per wavefront and tile
@@ -1442,7 +1443,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups,
   const int end = a.pos0 + min(32 * TW * (tbg + 1), rows);         // positions at or beyond it: not read (K) or not used (V)
   const int w_end = r0 < rows ? a.pos0 + min(r0 + 32, rows) : 0;   // this wavefront's (0: no tokens of its own, it only copies)
   const int r = min(r0 + col, rows - 1), qpos = a.pos0 + r, pt = a.page_tokens, pshift = __builtin_ctz(pt);
-  const uint32_t head_elems = (uint32_t)pt * DH, page_elems = 2u * (uint32_t)a.nkv * head_elems;   // (a page is far below 2^32 elements)
+  const uint32_t head_elems = (uint32_t)pt * DH, page_elems = 2u * (uint32_t)a.nkv * head_elems;   // below 2^32 (attn_tiles_fit)
 
   // positions this lane copies in a tile: K row of instruction i, V chunk (the same chunk of every channel it copies)
   auto k_row = [&](const int i) { return RPI * (w + 4 * i) + lane / CK; };
@@ -1655,7 +1656,8 @@ static dim3 attn_tiles_grid(int nq, int nkv, int n_groups) {
 }
 bool attn_tiles_fit(int nq, int nkv, int dh, int page_tokens, int n_groups) {
   const dim3 g = attn_tiles_grid(nq, nkv, n_groups);
-  return page_tokens >= 8 && (page_tokens & (page_tokens - 1)) == 0 && (dh == 64 || dh == 128) && (long)g.x * g.y >= 128;
+  const bool small_page = 2ull * (unsigned long long)nkv * page_tokens * dh < 1ull << 32;   // the kernel's offsets inside a page are 32 bits wide
+  return small_page && page_tokens >= 8 && (page_tokens & (page_tokens - 1)) == 0 && (dh == 64 || dh == 128) && (long)g.x * g.y >= 128;
 }
 
 hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, bool bf16_operands, hipStream_t s) {

@@ -262,6 +262,23 @@ def test_prefill_rejects_bad_arguments_before_any_launch():
         lib.disco_model_destroy(h)
 
 
+@pytest.mark.parametrize("nh, nkv, dh", [(40, 40, 128), (48, 1, 128), (32, 8, 64), (32, 1, 64)])
+def test_tiled_prompt_attention_only_where_a_page_offset_fits_32_bits(nh, nkv, dh):
+    """The tiled kernel's offsets inside a page are 32-bit numbers of elements: a page of 2^32 elements or more (a cache kept as
+    one page is accepted, whatever its size) has to go to the general kernel, whose offsets are 64 bits wide."""
+    rc, m = _model(n_heads=nh, n_kv_heads=nkv, d_head=dh)
+    assert rc == 0
+    tiled = []
+    for log2 in range(3, 28):
+        pt = 1 << log2
+        if B.disco_prefill_plan(m, 2048, page_tokens=pt)["attn_tiles"]:
+            tiled.append(pt)
+            # the last element a lane may address: the last token of the last channel of the last head's V block
+            assert (2 * nkv - 1) * pt * dh + (dh - 1) * pt + pt - 1 < 1 << 32, pt
+    assert tiled[0] == 8 and len(tiled) >= 10
+    B.lib().disco_model_destroy(m)
+
+
 def test_heuristic_lookahead_rule_by_hand():
     """The acceptance-following lookahead rule (the reading of the paper's unnamed heuristic: +up after a fully
     accepted block, -down otherwise, inside [1, cap]; nothing drafted: unchanged), on hand cases and on the
