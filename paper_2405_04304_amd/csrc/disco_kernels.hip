@@ -1501,8 +1501,13 @@ __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups,
   for (int c = 0; c < CB; ++c)
 #pragma unroll
     for (int v = 0; v < 16; ++v) O[c][v] = 0.f;
-  float m_run = NEG_BIG, l_run = 0.f;             // of column `col` (both halves hold the maximum; each its own keys' sum)
+  // of column `col` (both halves hold the maximum; each its own keys' sum).  The maximum starts far above DROPPED, so that keys
+  // without a score weigh nothing even where a column has met no other
+  constexpr float DROPPED = -1.0e33f;
+  float m_run = 0.5f * NEG_BIG / a.scale, l_run = 0.f;
   const float ce = a.scale * 1.44269504088896f;   // exp(scale (s - m)) = exp2(ce s - ce m)
+  float top = INFINITY;
+  asm("" : "+v"(top));                            // (with the constant in sight the compiler makes two instructions of each median)
 
   // 32 positions (half kb of the tile in buffer buf, from position base on)
   auto step = [&](const int base, const int buf, const int kb) {
@@ -1531,8 +1536,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups,
     if (edge) {
 #pragma unroll
       for (int v = 0; v < 16; ++v)
-        if (base + 8 * (v >> 2) + 4 * hf + (v & 3) > qpos) S[v] = NEG_BIG;
+        if (base + 8 * (v >> 2) + 4 * hf + (v & 3) > qpos) S[v] = DROPPED;
     }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) S[v] = __builtin_amdgcn_fmed3f(S[v], DROPPED, top);        // NaN becomes DROPPED, the rest stays
     float mx = S[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) mx = fmaxf(mx, S[v]);

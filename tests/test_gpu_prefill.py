@@ -190,6 +190,31 @@ def test_prefill_tiled_attention(shape, n, pre, page, permute, flags):
                   sigma=0.03, flags=flags, tight=2e-2 if flags else None)
 
 
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+def test_prefill_attention_drops_keys_without_a_score_at_every_length(flags):
+    """A cached key that holds NaN gives no score and weighs nothing: in the kernel of short prompts, of pages below 8 tokens
+    (here the other side of the comparison) and of the decode path, and so in the tiled kernel too."""
+    shape, ctx, n = ATT_1, 40, 400
+    d = dev()
+    gm = B.DiscoModel(shape, W.make_weights(shape, 41, "bf16", sigma=0.03), d)
+    fill = W.make_kv_fill(shape, ctx, 3)
+    fill[0, 0, 5, 7] = float("nan")                       # one key of one head, then all keys of another but the last two
+    fill[0, 0, :ctx - 2, 9] = float("nan")
+    toks = W.make_tokens(6, n, shape.vocab).to(d, torch.int32)
+    rows = []
+    for page in (4, 16):
+        gkv = B.DiscoKV(gm, ctx + n + 16, page)
+        gkv.fill(fill.to(d))
+        assert B.disco_prefill_plan(gm.handle, n, flags, page)["attn_tiles"] == (page == 16)
+        last = torch.empty(shape.vocab, dtype=torch.float32, device=d)
+        B.disco_prefill(gm, gkv, toks, n, last, gm.prefill_workspace(n, ctx + n + 16), flags=flags)
+        torch.cuda.synchronize()
+        rows.append(last)
+    assert bool(torch.isfinite(rows[0]).all()) and bool(torch.isfinite(rows[1]).all())
+    # both kernels sum the same terms in fp32 grade (2e-4: as the two launch structures are compared) or round q and P to bf16 alike
+    assert float((rows[0] - rows[1]).abs().max()) <= (5e-3 if flags else 2e-4) * float(rows[0].abs().max())
+
+
 @pytest.mark.parametrize("d, n", [(192, 2035), (512, 2048)])
 def test_prefill_layernorm_of_whole_groups(d, n):
     """128 token groups or more: the LayerNorm launches that build whole panel tiles (a width that is no multiple of the 512
