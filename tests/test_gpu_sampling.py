@@ -72,6 +72,38 @@ def test_sample_rows_match_oracle(V):
     assert float(probs[2][5]) == pytest.approx(0.5) and float(probs[2][7]) == 0.0
 
 
+@pytest.mark.parametrize("V", [4096, 32000, 49152, 65536])
+def test_probability_rows_keep_the_precision_of_expf(V):
+    """Logits on a grid of 2^-10 below a maximum of 0: x - max and the division by T = 1 are exact and the largest probability is
+    1 / S itself, so p_i / p_max differs from e^x_i by the exponential's rounding and one product's.  A correct rounding of a
+    value with a log-uniform mantissa has a relative rms error of 2^-23 / sqrt(12) * sqrt(0.541) = 2.53e-8, two of them 3.58e-8;
+    the bar is 12 % above (expf measures 3.6e-8, a shorter form of 1.5 ulp 4.4e-8)."""
+    g = torch.Generator().manual_seed(V)
+    logits = -torch.randint(0, 16 * 1024, (3, V), generator=g).to(torch.float32) / 1024
+    logits[:, 7] = 0.0
+    _, probs = _gpu_sample(logits, 1.0, torch.full((3,), 0.5))
+    got, want = probs.double() / probs[:, 7:8].double(), logits.double().exp()
+    rms = float((((got - want) / want) ** 2).mean().sqrt())
+    print(f"[sampling] V {V}: rms error of p / p_max {rms:.2e}", flush=True)
+    assert rms <= 4e-8
+
+
+def test_subnormal_weights_are_weights():
+    """e^-95 and e^-100 are subnormal in fp32 and not zero: the row stores them, a draw at 0 takes the first of them, and a
+    drafted token of such a probability is kept at u = 0."""
+    V = 4096
+    logits = torch.full((1, V), -300.0)
+    logits[0, 3], logits[0, 1234], logits[0, 4000] = -100.0, -95.0, 0.0
+    toks, probs = _gpu_sample(logits, 1.0, torch.zeros(1))
+    assert toks == [3]
+    want = logits.double().exp()
+    for i in (3, 1234):                                   # half a step of the subnormals (2^-149) for each of two roundings
+        assert abs(float(probs[0, i].double() - want[0, i])) <= 2.0 ** -149
+    q = [torch.nn.functional.one_hot(torch.tensor(1234), V).to(torch.float32)]
+    n, emit = _gpu_accept(torch.cat([logits, logits]), q, [0, 1234], torch.zeros(1), torch.tensor([0.5, 0.5]), 1.0)
+    assert (n, emit) == (1, [1234, 4000])
+
+
 def _accept_case(g, V, sl, T, mode):
     """Random block: target logits, draft rows near the target (so that keeps and rejections both occur)."""
     lt = torch.from_numpy(g.normal(size=(sl + 1, V)) * 2.0).to(torch.float32)
