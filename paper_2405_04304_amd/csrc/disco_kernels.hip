@@ -295,13 +295,15 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 // (hi4) of token row m at position pos: rotation, then the query row or the paged K / V entry.
 // What it reads besides the products: rotary factors and the physical page (qkv_operands; the skinny kernel asks for them
 // before its weight stream ends).
+// ROPE false: the model has no rotation (the LayerNorm family has learned positions).
 struct QkvOps { float4 t0, t1; int pp; };
+template <bool ROPE = true>
 __device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, const int pos) {
   const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1, pt = a.page_tokens;
   QkvOps o;
   o.t0 = o.t1 = make_float4(0.f, 0.f, 0.f, 0.f); o.pp = 0;
-  if (a.rope_tab != nullptr && head < a.nq + a.nkv) {
+  if (ROPE && a.rope_tab != nullptr && head < a.nq + a.nkv) {
     // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
     const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
     o.t0 = tab[0]; o.t1 = tab[1];
@@ -313,13 +315,13 @@ __device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, 
   }
   return o;
 }
-template <bool COH = false>
+template <bool COH = false, bool ROPE = true>
 __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos, const QkvOps& ops,
                                           float (&lo4)[4], float (&hi4)[4]) {
   const int dsh = a.dh == 128 ? 7 : 6;
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1;
   const bool is_v = head >= a.nq + a.nkv;
-  if (a.rope_tab != nullptr && !is_v) {
+  if (ROPE && a.rope_tab != nullptr && !is_v) {
     const float cs[4] = {ops.t0.x, ops.t0.z, ops.t1.x, ops.t1.z}, sn[4] = {ops.t0.y, ops.t0.w, ops.t1.y, ops.t1.w};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -373,6 +375,7 @@ struct GemmSmem {
   f32x4 red[NW][RT][64];
   float red_ssq[NW][64];
   float red_sum[LN ? NW : 1][64];                 // per-tile sums of a deferred LayerNorm
+  alignas(16) float ln[LN ? NW : 1][LN ? 64 : 4];        // its vectors: W . g of a wavefront's two tiles (or one), then W . b
   int s_last;
 };
 
@@ -478,8 +481,9 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     asm volatile("" ::: "memory");     // keep these loads ahead of the rest of the stream
   }
   // vectors and table entries of the epilogue are requested here, by the wavefronts that will use them, so that their round trip
-  // runs beside the weight stream instead of behind it (multi-query draft model, 12 layers: 381 -> 376 us per draft step; the
-  // residual rows of the PARTIAL epilogue, asked for here too, made the O-projection 0.7 us slower: they stay behind)
+  // runs beside the weight stream instead of behind it (a pass of the multi-query draft model, 12 layers, 5 tokens: 360 us behind
+  // it, 356 now; the residual rows of the PARTIAL epilogue, asked for here too, made the O-projection 0.7 us slower: they stay
+  // behind)
   constexpr int TPU = PAIR ? 2 : 1;               // tiles per unit
   const bool ep = w < UNITS;                      // this wavefront finishes one output unit
   const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16x16 result
@@ -492,19 +496,17 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
 #pragma unroll
     for (int rr = 0; rr < RT; ++rr) if (rr == r) urt[i] = rt[rr];
   }
-  float4 cg[LN ? TPU : 1], cb[LN ? TPU : 1];
+  // A lane holds one element of the two LayerNorm vectors until the reduction puts them into LDS: the 8 or 16 values that it needs
+  // itself would take some instances past 128 registers and so leave one resident workgroup per compute unit instead of two (a
+  // pass over two LayerNorm layers of 4096, 384 QKV workgroups: 252.7 us, 257.1 with the values in registers, 254.7 behind the
+  // stream).  The instances of two panels and four tiles have no register to spare and ask behind the stream (two layers of 5120,
+  // 12 tokens: 378.4 us, 380.5 before it)
+  float lnv = 0.f;
   QkvOps qops;
-  if ((LN || EPI == EPI_QKV) && ep && m < a.M) {
-    if (LN) {
-#pragma unroll
-      for (int i = 0; i < TPU; ++i) {
-        const int row = urt[i] * 16 + 4 * g;
-        cg[LN ? i : 0] = *reinterpret_cast<const float4*>(a.wg + row); cb[LN ? i : 0] = *reinterpret_cast<const float4*>(a.wb + row);
-      }
-    }
-    if (EPI == EPI_QKV) qops = qkv_operands(a, urt[0] * 16 + 4 * g, a.pos0 + m);
-    asm volatile("" ::: "memory");
-  }
+  constexpr bool EARLY = !(LN && P == 2 && RT == 4);
+  if (LN && EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
+  if (EPI == EPI_QKV && EARLY && ep && m < a.M) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
+  if (LN || EPI == EPI_QKV) asm volatile("" ::: "memory");
 #pragma unroll
   for (int i = 0; i < U; ++i)
     if (kt0 + i * NW < kt_end) load_x(B[i], kt0 + i * NW);
@@ -525,6 +527,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     }
   }
 
+  if (LN && !EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
   // hi + lo: same panel, columns n and n + 8 (P == 1), or two panels (P == 2)
   __syncthreads();                                // a previous unit of this workgroup has left the buffers
 #pragma unroll
@@ -552,6 +555,8 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
         ps += su[k];
       }
       sm.red_sum[w][lane] = ps;
+      asm volatile("" : "+v"(lnv));
+      sm.ln[w][lane] = lnv;
     }
   }
   __syncthreads();
@@ -624,7 +629,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
       const float rstd = 1.0f / sqrtf(var + a.eps);
 #pragma unroll
       for (int i = 0; i < TPU; ++i) {
-        const float4 vg = cg[LN ? i : 0], vb = cb[LN ? i : 0];
+        const float4 vg = *reinterpret_cast<const float4*>(&sm.ln[LN ? w : 0][i * 16 + 4 * g]), vb = *reinterpret_cast<const float4*>(&sm.ln[LN ? w : 0][32 + i * 16 + 4 * g]);
         y[i][0] = rstd * (y[i][0] - mean * vg.x) + vb.x; y[i][1] = rstd * (y[i][1] - mean * vg.y) + vb.y;
         y[i][2] = rstd * (y[i][2] - mean * vg.z) + vb.z; y[i][3] = rstd * (y[i][3] - mean * vg.w) + vb.w;
       }
@@ -663,9 +668,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   } else if (EPI == EPI_QKV) {
     // two tiles: features c .. c+3 and their rotary partners c + dh/2 .. of one head
     float lo4[4], hi4[4];
+    if (!EARLY) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
 #pragma unroll
     for (int v = 0; v < 4; ++v) { lo4[v] = y[0][v]; hi4[v] = y[TPU - 1][v]; }
-    qkv_store<COH>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, qops, lo4, hi4);
+    qkv_store<COH, !LN>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, qops, lo4, hi4);
   } else if (EPI == EPI_SWIGLU) {
     // tile 0 = gate rows, tile 1 = the matching up rows
     const int f = (urt[0] >> 1) * 16 + 4 * g;
