@@ -425,7 +425,10 @@ int disco_heuristic_next(int lookahead, int drafted, int accepted, int up, int d
  * instead).  dev_ws: device buffer of at least
  * disco_prefill_workspace_bytes(m, n_tokens, max_ctx >= kv->len + 16 * ceil(n_tokens / 16)) bytes,
  * 256-byte aligned, initialised once with disco_workspace_init (which zeroes the ticket counters at
- * its start; they sit at the offsets of an ordinary workspace).  Errors: EINVAL, ECAP, ESTATE, EHIP. */
+ * its start; they sit at the offsets of an ordinary workspace).  A workspace for a longer prompt serves
+ * shorter ones.  The last part of that size (at most 64 MiB, nothing for narrow models) holds sums of
+ * K ranges with which the matrices of short prompts fill the chip; a buffer without it, or with less of
+ * it, is accepted, and the pass then cuts K less often.  Errors: EINVAL, ECAP, ESTATE, EHIP.          */
 #define DISCO_PREFILL_MAX 8192
 size_t disco_prefill_workspace_bytes(const disco_model* m, int n_tokens, int max_ctx);
 int disco_prefill(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n_tokens,

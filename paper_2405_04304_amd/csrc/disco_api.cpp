@@ -308,7 +308,7 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
 struct PfWs {
   Ws base;
   float* h; float* q; bf16_t* xn; bf16_t* xattn; bf16_t* xact; float* ssq; float* rstd;
-  float* planes;                             // sums of K ranges, where a matrix is cut along K
+  float* planes;                             // sums of K ranges, where a matrix is cut along K: what a buffer has beyond `total`
   size_t total;
 };
 
@@ -327,9 +327,32 @@ PfWs carve_prefill(const disco_model* m, int n_groups, int max_ctx, void* base) 
   w.xact = static_cast<bf16_t*>(take(sizeof(bf16_t) * 2 * rows * d.d_ff));
   w.ssq = static_cast<float*>(take(sizeof(float) * rows * (size_t)(d.d_model / 16)));
   w.rstd = static_cast<float*>(take(sizeof(float) * rows));
-  w.planes = static_cast<float*>(take(gemm_split_plane_bytes()));
   w.total = off;
+  w.planes = reinterpret_cast<float*>(p ? p + off : nullptr);
   return w;
+}
+
+// The four matrices of a layer in the order of a pass: rows and columns.
+struct DenseShape { int rows, k; };
+void dense_shapes(const disco_model* m, DenseShape (&s)[4]) {
+  const disco_model_desc& d = m->d;
+  s[0] = {m->d_qkv, d.d_model}; s[1] = {d.d_model, m->d_q};
+  s[2] = {d.family == DISCO_FAMILY_A ? d.d_ff : 2 * d.d_ff, d.d_model}; s[3] = {d.d_model, d.d_ff};
+}
+
+// Partial sums of the K ranges of a pass over up to n_groups groups, whichever its length and precision (the shorter prompts
+// are the ones that are cut, and a workspace for a longer prompt serves them too).
+size_t split_plane_bytes(const disco_model* m, int n_groups) {
+  DenseShape s[4];
+  dense_shapes(m, s);
+  size_t most = 0;
+  for (int g = 1; g <= n_groups; ++g)
+    for (const DenseShape& x : s)
+      for (int hi = 0; hi < 2; ++hi) {
+        const size_t b = gemm_dense_plan(x.rows, x.k / 32, g, hi != 0, SIZE_MAX).plane_bytes;
+        if (b > most) most = b;
+      }
+  return round_up(most, 256);
 }
 
 }  // namespace
@@ -338,7 +361,8 @@ extern "C" {
 
 size_t disco_prefill_workspace_bytes(const disco_model* m, int n_tokens, int max_ctx) {
   if (!m || n_tokens < 1 || n_tokens > DISCO_PREFILL_MAX || max_ctx < 0) return 0;
-  return carve_prefill(m, (n_tokens + 15) / 16, max_ctx, nullptr).total;
+  const int n_groups = (n_tokens + 15) / 16;
+  return carve_prefill(m, n_groups, max_ctx, nullptr).total + split_plane_bytes(m, n_groups);
 }
 
 int disco_prefill(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n_tokens, float* dev_logits_last,
@@ -389,7 +413,7 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
   auto dense = [&](const void* w, const bf16_t* x, size_t xs, int k, int n_rows) {
     DenseArgs a{};
     a.g.M = 16; a.g.W = static_cast<const bf16_t*>(w); a.g.X = x; a.g.KT = k / 32; a.g.n_rows = n_rows; a.g.grp = 1;
-    a.g.only_row = -1; a.n_groups = G; a.xs = xs; a.hi_only = hi_only; a.g.planes = ws.planes;
+    a.g.only_row = -1; a.n_groups = G; a.xs = xs; a.hi_only = hi_only; a.g.planes = ws.planes; a.plane_bytes = ws_bytes - need;
     return a;
   };
   auto residual_update = [&](DenseArgs& a, const float* next_gain) {
@@ -1040,9 +1064,10 @@ int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int p
   const disco_model_desc& d = m->d;
   const bool fam_a = d.family == DISCO_FAMILY_A, hi = (flags & DISCO_PREFILL_BF16_ACTIVATIONS) != 0;
   const int G = (n_tokens + 15) / 16;
-  const int rows[4] = {m->d_qkv, d.d_model, fam_a ? d.d_ff : 2 * d.d_ff, d.d_model}, k[4] = {d.d_model, m->d_q, d.d_model, d.d_ff};
+  DenseShape s[4];
+  dense_shapes(m, s);
   for (int i = 0; i < 4; ++i) {
-    const DensePlan p = gemm_dense_plan(rows[i], k[i] / 32, G, hi, true);
+    const DensePlan p = gemm_dense_plan(s[i].rows, s[i].k / 32, G, hi, SIZE_MAX);
     out[i] = p.split > 1 ? 100 + p.split : p.tile;
   }
   out[4] = attn_tiles_fit(d.n_heads, d.n_kv_heads, d.d_head, page_tokens, G) ? 1 : 0;

@@ -62,7 +62,8 @@ struct DenseArgs {
   size_t ssq_outs;      // floats between the groups' sum-of-squares slots
   const float* rstd;    // [group][16]: 1 / rms of the input rows (epilogues that read a normalised input)
   int hi_only;          // bf16 activations: the lo panels are not read
-  int k_split;          // set by the launcher: K ranges (partial sums at g.planes, gemm_split_plane_bytes())
+  size_t plane_bytes;   // room for partial sums at g.planes: a matrix is cut along K only as far as they fit
+  int k_split;          // set by the launcher: K ranges
 };
 
 struct NormArgs {
@@ -183,12 +184,12 @@ hipError_t launch_qkv_attn(const GemmArgs& g, const AttnArgs& a, int* head_ready
 // dense prompt pass (groups of 16 tokens; every group holds 16 rows, surplus rows are padding)
 hipError_t launch_gemm_dense(const DenseArgs& a, int epi, hipStream_t s);
 // What the prompt pass launches for a matrix of n_rows x 32 KT and n_groups groups: workgroup tile (0 .. 3, see the function),
-// K ranges (1: not cut) and workgroups per range; whether its attention and its LayerNorms take the tiled kernels.
-struct DensePlan { int tile, split; long wgs; };
-DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, bool may_split);
+// K ranges (1: not cut), workgroups per range and bytes of partial sums (at most plane_bytes); whether its attention and its
+// LayerNorms take the tiled kernels.
+struct DensePlan { int tile, split; long wgs; size_t plane_bytes; };
+DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t plane_bytes);
 bool attn_tiles_fit(int nq, int nkv, int dh, int page_tokens, int n_groups);
 bool norm_groups_fit(int d, int n_groups);
-size_t gemm_split_plane_bytes();
 hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, float* rstd, int n_groups, hipStream_t s);
 hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, bool bf16_operands, hipStream_t s);
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s);

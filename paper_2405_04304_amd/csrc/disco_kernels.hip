@@ -3170,8 +3170,8 @@ __global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
   tile_epilogue<EPI, 1, 1, HI>(d, 2 * gp, rt, acc);
 }
 
-// Bytes of partial sums that a split launch may use: 256 workgroups of 256 x 256.
-size_t gemm_split_plane_bytes() { return (size_t)256 * 256 * 256 * sizeof(float); }
+// Bytes of one workgroup's partial sums of a K range.
+static size_t split_unit_bytes(bool hi_only) { return (size_t)256 * 128 * (hi_only ? 2 : 1) * sizeof(float); }
 
 // Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
 // hi + lo only: 128-token accumulators); 128 x 128 (c3) where a short K and a small grid leave nothing but the latency of the
@@ -3181,7 +3181,7 @@ size_t gemm_split_plane_bytes() { return (size_t)256 * 256 * 256 * sizeof(float)
 // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
 // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 137 + 17 for its sum.
 // c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
-DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, bool may_split) {
+DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t plane_bytes) {
   const int n_tiles = n_rows / 16;
   auto count = [&](const int na, const int nbt) { const int gg = nbt / (hi_only ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((n_groups + gg - 1) / gg); };
   const long wgs[4] = {count(8, 16), count(16, 16), count(32, 16), count(8, 8)};
@@ -3194,19 +3194,18 @@ DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, bool m
   if (c3 < best) best = c3;
   best *= unit_us;
   int split = 1;
-  if (may_split)
-    for (int S = 2; S <= 16 && wgs[1] * S <= 256 && KT / S >= 8; ++S) {
-      const double us = 2.0 / S * unit_us + 8.0 + (double)wgs[1] * S * (hi_only ? 0.262 : 0.131) * 2.0 / 4.0;   // two passes over the partial sums at 4 TB/s, a launch
-      if (us < best) { best = us; split = S; }
-    }
+  for (int S = 2; S <= 16 && wgs[1] * S <= 256 && KT / S >= 8 && (size_t)wgs[1] * S * split_unit_bytes(hi_only) <= plane_bytes; ++S) {
+    const double us = 2.0 / S * unit_us + 8.0 + (double)wgs[1] * S * (hi_only ? 0.262 : 0.131) * 2.0 / 4.0;   // two passes over the partial sums at 4 TB/s, a launch
+    if (us < best) { best = us; split = S; }
+  }
   const int tile = split > 1 ? 1 : (c3 < c0 ? 3 : (c2 < c0 && c2 < c1 ? 2 : (c1 < c0 ? 1 : 0)));
-  return DensePlan{tile, split, wgs[tile]};
+  return DensePlan{tile, split, wgs[tile], split > 1 ? (size_t)wgs[1] * split * split_unit_bytes(hi_only) : 0};
 }
 
 template <int EPI, bool HI>
 static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   DenseArgs d = d0;
-  const DensePlan p = gemm_dense_plan(d.g.n_rows, d.g.KT, d.n_groups, HI, d.g.planes != nullptr);
+  const DensePlan p = gemm_dense_plan(d.g.n_rows, d.g.KT, d.n_groups, HI, d.g.planes != nullptr ? d.plane_bytes : 0);
   const dim3 grid(8u * (unsigned)((p.wgs * p.split + 7) / 8));
   if (p.split > 1) {
     d.k_split = p.split;

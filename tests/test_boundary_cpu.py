@@ -262,6 +262,30 @@ def test_prefill_rejects_bad_arguments_before_any_launch():
         lib.disco_model_destroy(h)
 
 
+def test_prefill_workspace_grows_only_where_a_matrix_is_cut_along_k():
+    """Sums of K ranges take workspace where some prompt up to the length has a matrix that is cut, and none in a model whose K
+    never allows a cut; a longer prompt's workspace serves every shorter one; and what the call demands is the size without it."""
+    lib = B.lib()
+    rc, narrow = _model(d_model=448, n_heads=7, n_kv_heads=7, d_ff=448, vocab=256)          # 14 k-tiles
+    sizes = [lib.disco_prefill_workspace_bytes(narrow, n, 64) for n in (16, 32, 48)]
+    assert sizes[2] - sizes[1] == sizes[1] - sizes[0] and sizes[0] < 8 << 20
+    rc, wide = _model(d_model=5120, n_heads=40, n_kv_heads=40, d_head=128, d_ff=13824, vocab=32000)
+    sizes = [lib.disco_prefill_workspace_bytes(wide, n, 4096) for n in range(1, 3000, 16)]
+    assert all(b >= a for a, b in zip(sizes, sizes[1:]))
+    rc, kv, _ = _kv(wide, capacity=64)
+    assert lib.disco_prefill(wide, kv, FAKE, 33, None, FAKE, 4096, None) == B.EINVAL
+    need = int(re.search(r"(\d+) needed", B.last_error()).group(1))
+    full = lib.disco_prefill_workspace_bytes(wide, 33, 48)
+    assert 0 < full - need <= 64 << 20
+    for h in (narrow, wide):
+        for flags in (0, B.PREFILL_BF16_ACTIVATIONS):
+            cut = any(c > 100 for n in range(1, 3000, 16) for c in list(B.disco_prefill_plan(h, n, flags).values())[:4])
+            assert cut == (h is wide)
+    lib.disco_kv_destroy(kv)
+    for h in (narrow, wide):
+        lib.disco_model_destroy(h)
+
+
 @pytest.mark.parametrize("nh, nkv, dh", [(40, 40, 128), (48, 1, 128), (32, 8, 64), (32, 1, 64)])
 def test_tiled_prompt_attention_only_where_a_page_offset_fits_32_bits(nh, nkv, dh):
     """The tiled kernel's offsets inside a page are 32-bit numbers of elements: a page of 2^32 elements or more (a cache kept as

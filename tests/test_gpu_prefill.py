@@ -10,6 +10,8 @@ Tolerances as in test_gpu_parity.py (2e-2 stated, 2e-3 held).  The small models 
 (sigma 0.02), as the other full-width parity tests do: with wide weights at d_model 6144 both the dense
 pass and the block-wise prompt sit at 2e-3 (bf16 rounding of freshly computed keys and values under
 peaked attention), which is the regression bar itself."""
+import re
+
 import pytest
 import torch
 
@@ -220,6 +222,33 @@ def test_prefill_layernorm_of_whole_groups(d, n):
     """128 token groups or more: the LayerNorm launches that build whole panel tiles (a width that is no multiple of the 512
     columns they take at a time, and one that is; a ragged last group)."""
     _prefill_case(W.ModelShape("A", 1, d, 2, 64, 1, 256, 496, max_pos=2200), 51, n, page=32, what=f"LayerNorm of whole groups, d {d}")
+
+
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+def test_prefill_runs_in_a_workspace_without_room_for_k_ranges(flags):
+    """A buffer of the size that the call demands is enough: the K ranges that find no room are not made (the second buffer has
+    room for some), nothing is written behind the buffer, and the result is the same to summation order."""
+    shape, n = W.ModelShape("B", 1, 1024, 8, 128, 8, 2048, 512), 40
+    d = dev()
+    om, gm, okv, gkv, ws = setup_pair(shape, 61, capacity=n + 16, sigma=0.03)
+    plan = list(B.disco_prefill_plan(gm.handle, n, flags).values())[:4]
+    assert any(c > 100 for c in plan)
+    toks = torch.tensor(W.make_tokens(7, n, shape.vocab).tolist(), dtype=torch.int32, device=d)
+    full = gm.prefill_workspace(n, n + 16)
+    with pytest.raises(B.DiscoError) as e:
+        B.disco_prefill(gm, gkv, toks, n, None, B.Workspace(4096, d), flags=flags)
+    need = int(re.search(r"(\d+) needed", str(e.value)).group(1))
+    assert need < full.nbytes
+    ref = om.forward(toks.tolist(), okv)
+    for nbytes in (full.nbytes, (need + full.nbytes) // 2 // 256 * 256, need):
+        full.nbytes = nbytes
+        full.buf[nbytes:] = 0x5A
+        last = torch.empty(shape.vocab, dtype=torch.float32, device=d)
+        B.disco_prefill(gm, gkv, toks, n, last, full, flags=flags)
+        torch.cuda.synchronize()
+        check_logits(last[None], ref[-1:], f"workspace of {nbytes} bytes", **({"tight": 2e-2} if flags else {}))
+        assert bool((full.buf[nbytes:] == 0x5A).all())
+        B.disco_kv_rollback(gkv, 0)
 
 
 def test_prefill_rejects_bad_arguments():
