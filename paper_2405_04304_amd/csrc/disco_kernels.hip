@@ -278,10 +278,10 @@ hipError_t launch_pack(const bf16_t* src, int64_t n, int64_t k, bf16_t* dst, int
 // base (uniform) + lane_off, or an address per lane.  Completion is counted by vmcnt.
 __device__ __forceinline__ void lds_dma_16(const void* base, const uint32_t lane_off, const uint32_t lds) {
   // m0 holds the LDS address of the wavefront's 1 KiB; the instruction has no register outputs
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_dma_16(const void* lane_addr, const uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(lane_addr) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(lane_addr) : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
