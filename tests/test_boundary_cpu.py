@@ -8,6 +8,7 @@ import pytest
 
 import paper_2405_04304_amd as D
 from paper_2405_04304_amd import binding as B
+from workloads import synth as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FAKE = 0x7F0000000000  # 256-byte aligned address that is never touched
@@ -284,6 +285,42 @@ def test_prefill_workspace_grows_only_where_a_matrix_is_cut_along_k():
     lib.disco_kv_destroy(kv)
     for h in (narrow, wide):
         lib.disco_model_destroy(h)
+
+
+def test_tile_cases_cover_the_launch_rule_of_the_prompt_pass():
+    """Every (epilogue, tile or K ranges, precision) that the rule chooses for the model shapes of the workloads at 1 .. 3001
+    tokens has a case in test_gpu_prefill.py that runs it, and the rule still chooses there what the case says."""
+    from test_gpu_prefill import TILE_CASES
+    code = lambda c: "s" if c > 100 else c  # noqa: E731
+
+    def choices(shape, n, flags, handle):
+        plan, gelu = B.disco_prefill_plan(handle, n, flags), "gelu" if shape.family == "A" else "swiglu"
+        epi = {"qkv": "qkv", "o": "residual", "mlp_in": gelu, "mlp_out": "residual"}
+        return plan, {(epi[k], code(plan[k]), bool(flags)) for k in epi}
+
+    def handle_of(s):
+        rc, h = _model(family=0 if s.family == "A" else 1, n_layers=1, d_model=s.d_model, n_heads=s.n_heads, d_head=s.d_head,
+                       n_kv_heads=s.n_kv_heads, d_ff=s.d_ff, vocab=512, max_pos=8192)
+        assert rc == 0
+        return h
+
+    covered, chosen = set(), set()
+    for shape, pre, n, *want in TILE_CASES:
+        h = handle_of(shape)
+        for flags in (0, B.PREFILL_BF16_ACTIVATIONS):
+            plan, triples = choices(shape, n, flags, h)
+            for what, c in want[1 if flags else 0].items():
+                assert code(plan[what]) == c, (shape, n, flags, plan)
+            covered |= triples
+        B.lib().disco_model_destroy(h)
+    gqa = W.ModelShape("B", 4, 2048, 16, 128, 4, 5632, 32000)
+    for shape in (W.CFG0_TARGET, W.CFG1_DRAFT, W.CFG2_TARGET, W.CFG3_TARGET, W.CFG3_DRAFT, gqa):
+        h = handle_of(shape)
+        for n in range(1, 3002, 16):
+            for flags in (0, B.PREFILL_BF16_ACTIVATIONS):
+                chosen |= choices(shape, n, flags, h)[1]
+        B.lib().disco_model_destroy(h)
+    assert len(chosen) >= 30 and not chosen - covered, chosen - covered
 
 
 @pytest.mark.parametrize("nh, nkv, dh", [(40, 40, 128), (48, 1, 128), (32, 8, 64), (32, 1, 64)])

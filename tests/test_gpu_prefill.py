@@ -152,16 +152,16 @@ def test_prefill_bf16_activations_layouts_and_families():
 
 
 def test_prefill_bf16_activations_13b_shape_1024_tokens():
-    """Long enough for the 128-row wavefront tiles of the wide projections (the launch shape bench.py --prefill
+    """The wide projections on 256-row workgroup tiles and the K ranges of MLP-down (the launch shape bench.py --prefill
     --prefill-bf16-act times from 1024 tokens on), with a ragged last group."""
     shape = W.scaled_shape(W.CFG2_TARGET, n_layers=2)
     _prefill_case(shape, 0, 1000, pre=3, what="13B-shape x2 layers, 1000 tokens, bf16 activations", sigma=0.02, gain_jitter=0.0,
                   flags=BF16_ACT, tight=2e-2)
 
 
-# The large-tile GEMM: K cut into ranges (few tiles: 33 tokens), 128- and 256-row tiles (527), 512-row tiles (1700 tokens: the
-# 8192-row projection), ragged row blocks (d_ff 1440: 180 tiles in the last block of 16), ragged token groups, the K / V rows of
-# grouped heads, 16 k-tiles (the shortest K it takes) and 45 (odd).  The arithmetic per element is that of the other cases.
+# The large-tile GEMM against the oracle: 128 x 128 tiles and K ranges (33 .. 530 tokens), 128-, 256- and 512-row tiles of the
+# 8192-row projection (257 tokens in both precisions up to 1700), ragged row blocks (d_ff 1440: 180 tiles), ragged token groups,
+# the K / V rows of grouped heads, and k-tile counts of 16 and 45.
 TILE_B = W.ModelShape("B", 1, 512, 4, 128, 2, 1440, 512)
 TILE_B_WIDE = W.ModelShape("B", 1, 512, 4, 128, 4, 4096, 512)
 TILE_A = W.ModelShape("A", 1, 512, 8, 64, 1, 1536, 512, max_pos=2048)
@@ -173,6 +173,90 @@ TILE_A = W.ModelShape("A", 1, 512, 8, 64, 1, 1536, 512, max_pos=2048)
 def test_prefill_large_tiles(shape, n, pre, flags):
     _prefill_case(shape, 31, n, pre=pre, what=f"large tiles {shape.family} d_ff {shape.d_ff}", sigma=0.03, flags=flags,
                   tight=2e-2 if flags else None)
+
+
+# One prompt for every (epilogue, workgroup tile or K ranges, precision) that the launch rule can choose, with a ragged last row
+# block and token group: shape, tokens before, tokens, then the choices that the case is there for, fp32 grade and bf16
+# (codes of disco_prefill_plan, "s" for K ranges).  test_boundary_cpu.py checks that the list still covers the rule.
+def _one(family, d, nh, dh, nkv, ff):
+    return W.ModelShape(family, 2, d, nh, dh, nkv, ff, 512, max_pos=2048)
+
+
+TILE_CASES = [
+    (_one("A", 2112, 2, 64, 1, 192), 0, 37, {"qkv": "s", "o": 3, "mlp_in": "s"}, {"qkv": "s", "o": 3, "mlp_in": "s"}),
+    (_one("B", 2112, 2, 64, 1, 160), 3, 37, {"qkv": "s", "o": 3, "mlp_in": "s"}, {"qkv": "s", "o": 3, "mlp_in": "s"}),
+    (_one("B", 64, 43, 128, 43, 64), 5, 795, {"qkv": 2, "o": "s"}, {"qkv": 0, "o": "s"}),
+    (_one("B", 64, 43, 128, 43, 64), 0, 395, {"qkv": 0, "o": "s"}, {"qkv": 1, "o": "s"}),
+    (_one("B", 64, 43, 128, 43, 64), 9, 299, {"qkv": 1}, {"qkv": 1}),
+    (_one("B", 8000, 1, 64, 1, 64), 0, 1645, {"o": 2, "mlp_out": 2}, {"o": 1, "mlp_out": 1}),
+    (_one("B", 8000, 1, 64, 1, 64), 7, 785, {"o": 1, "mlp_out": 1}, {"o": 0, "mlp_out": 0}),
+    (_one("B", 8000, 1, 64, 1, 64), 0, 325, {"o": 0, "mlp_out": 0}, {"o": 3, "mlp_out": 3}),
+    (_one("A", 8000, 1, 64, 1, 64), 0, 785, {"o": 1, "mlp_out": 1}, {"o": 0, "mlp_out": 0}),
+    (_one("A", 192, 3, 128, 3, 16448), 0, 695, {"mlp_in": 2, "mlp_out": "s"}, {"mlp_in": 1, "mlp_out": "s"}),
+    (_one("A", 192, 3, 128, 3, 6464), 2, 795, {"mlp_in": 1}, {"mlp_in": 0}),
+    (_one("A", 192, 3, 128, 3, 6464), 0, 199, {"mlp_in": 3}, {"mlp_in": 3}),
+    (_one("A", 192, 3, 128, 3, 6464), 0, 515, {"mlp_in": 0, "qkv": 3}, {"mlp_in": 3, "qkv": 3}),
+    (_one("B", 192, 3, 128, 3, 8256), 0, 695, {"mlp_in": 2, "mlp_out": "s"}, {"mlp_in": 1, "mlp_out": "s"}),
+    (_one("B", 192, 3, 128, 3, 3232), 4, 795, {"mlp_in": 1}, {"mlp_in": 0}),
+    (_one("B", 192, 3, 128, 3, 3232), 0, 515, {"mlp_in": 0}, {"mlp_in": 3}),
+]
+
+
+def _entries(kv, capacity, page):
+    """Cached keys and values [layer, 2, position, head, channel] of a cache in identity order (the layout of disco.h)."""
+    s, pages = kv.model.shape, -(-capacity // page)
+    n = 2 * s.n_layers * pages * 2 * s.n_kv_heads * page * s.d_head
+    raw = kv.buf[kv.buf.numel() - n:].view(torch.bfloat16).view(s.n_layers, pages, 2, s.n_kv_heads, page * s.d_head).float()
+    k = raw[:, :, 0].unflatten(-1, (page, s.d_head)).permute(0, 1, 3, 2, 4)
+    v = raw[:, :, 1].unflatten(-1, (s.d_head, page)).permute(0, 1, 4, 2, 3)
+    return torch.stack([x.reshape(s.n_layers, pages * page, s.n_kv_heads, s.d_head) for x in (k, v)], 1)
+
+
+def _smooth_model(shape, seed):
+    """Weights of sigma <= 0.6 / sqrt(d_model): queries and keys of spread <= 0.6, scores of spread <= 0.36.
+    A key that lands on the next bf16 value (2^-7 of a channel) then moves its score, and so its share of the attention, by
+    less than 2^-8 of itself; with sigma 0.03 at d_model 8000 scores spread over 7 and one such key moves its share by 5 %,
+    which would be the comparison's largest difference (6.9e-3 of a row of second-layer entries was seen)."""
+    return B.DiscoModel(shape, W.make_weights(shape, seed, "bf16", sigma=min(0.03, 0.6 / shape.d_model ** 0.5), gain_jitter=0.2), dev())
+
+
+def _against_blocks(gm, pre, n, flags=0, page=16):
+    shape, d, cap = gm.shape, dev(), pre + n + 16
+    toks = W.make_tokens(72, pre + n, shape.vocab).to(d, torch.int32)
+    ws, am = gm.workspace(16, cap), torch.zeros(16, dtype=torch.int32, device=d)
+    kv_a, kv_b = B.DiscoKV(gm, cap, page), B.DiscoKV(gm, cap, page)
+    rows = torch.empty(16, shape.vocab, dtype=torch.float32, device=d)
+    for kv, end in ((kv_a, pre), (kv_b, pre + n)):
+        for i in range(0, end, 16):
+            m = min(16, end - i)
+            B.disco_verify(gm, kv, toks.data_ptr() + 4 * i, m, am, rows, ws)
+    last = torch.empty(shape.vocab, dtype=torch.float32, device=d)
+    B.disco_prefill(gm, kv_a, toks.data_ptr() + 4 * pre, n, last, gm.prefill_workspace(n, cap), flags=flags)
+    torch.cuda.synchronize()
+    ref = rows[(pre + n - 1) % 16]
+    assert bool(torch.isfinite(last).all())
+    assert float((last - ref).abs().max()) <= (2e-2 if flags else 2e-3) * float(ref.abs().max())
+    a, b = (_entries(kv, cap, page)[:, :, pre:pre + n] for kv in (kv_a, kv_b))
+    err = ((a - b).flatten(3).norm(dim=-1) / b.flatten(3).norm(dim=-1)).amax(dim=(1, 2))
+    print(f"[prefill] worst row of entries by layer: {[f'{float(x):.1e}' for x in err]}", flush=True)
+    assert float(err.max()) <= (2e-2 if flags else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+@pytest.mark.parametrize("case", range(len(TILE_CASES)))
+def test_prefill_every_tile_and_epilogue(case, flags):
+    """Against the prompt fed in blocks of 16 through the verification forward (other kernels, themselves held to the oracle):
+    the logits, and the entries of every position, whose second layer has read the first layer's result for every token.  Two
+    fp32-grade passes agree to some 1e-5, so an entry is the same bf16 value or the next one, which is at most 2^-7 of it away:
+    with the next one in up to a quarter of its entries a row is within 2^-8 of its norm (a rounding difference of 1e-5 moves
+    some 1 % of them).  With bf16 activations the bar is the one stated above."""
+    shape, pre, n, *want = TILE_CASES[case]
+    gm = _smooth_model(shape, 71)
+    plan = B.disco_prefill_plan(gm.handle, n, flags)
+    for what, code in want[1 if flags else 0].items():
+        assert (plan[what] > 100 if code == "s" else plan[what] == code), (what, plan)
+    print(f"[prefill] tiles: {shape.family} d {shape.d_model} ff {shape.d_ff} n {n} pre {pre} flags {flags}: {plan}", flush=True)
+    _against_blocks(gm, pre, n, flags)
 
 
 # The tiled attention (128 workgroups or more): heads that share K / V by 1, 2, 3 and 4 (four, two or one head per workgroup), both
