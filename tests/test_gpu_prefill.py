@@ -308,6 +308,16 @@ def test_prefill_layernorm_of_whole_groups(d, n):
     _prefill_case(W.ModelShape("A", 1, d, 2, 64, 1, 256, 496, max_pos=2200), 51, n, page=32, what=f"LayerNorm of whole groups, d {d}")
 
 
+@pytest.mark.parametrize("d, n, groups", [(1344, 2035, True), (6144, 2048, True), (6208, 2035, False), (1344, 2032, False)])
+def test_prefill_layernorm_of_whole_groups_over_several_chunks(d, n, groups):
+    """Three chunks of 512 columns, the last a part of one (the first LDS buffer is used again), the widest rows that the kernel
+    takes (twelve chunks), and just beyond its lines: one width above, one group less than 128."""
+    shape = W.ModelShape("A", 2, d, 1, 64, 1, 64, 512, max_pos=2200)
+    gm = _smooth_model(shape, 73)
+    assert B.disco_prefill_plan(gm.handle, n)["norm_groups"] == groups
+    _against_blocks(gm, 0, n)
+
+
 @pytest.mark.parametrize("flags", [0, BF16_ACT])
 def test_prefill_runs_in_a_workspace_without_room_for_k_ranges(flags):
     """A buffer of the size that the call demands is enough: the K ranges that find no room are not made (the second buffer has
