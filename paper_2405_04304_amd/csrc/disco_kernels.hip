@@ -2337,13 +2337,23 @@ __device__ __forceinline__ SmpTot smp_share(float mine, float* smem) {
   return t;
 }
 
+// Sum of N values pairwise: a value goes through log2 N roundings, where one after another it goes through up to N.
+template <int N>
+__device__ __forceinline__ float smp_pairwise(float (&s)[N]) {
+#pragma unroll
+  for (int w = 1; w < N; w *= 2)
+#pragma unroll
+    for (int i = 0; i + w < N; i += 2 * w) s[i] += s[i + w];
+  return s[0];
+}
+
 // Lane sum of a wavefront's part of the row.
 template <int V4>
 __device__ __forceinline__ float smp_lane_sum(const float4 (&r)[V4]) {
-  float s = 0.f;
+  float s[V4];
 #pragma unroll
-  for (int i = 0; i < V4; ++i) s += (r[i].x + r[i].y) + (r[i].z + r[i].w);
-  return s;
+  for (int i = 0; i < V4; ++i) s[i] = (r[i].x + r[i].y) + (r[i].z + r[i].w);
+  return smp_pairwise<V4>(s);
 }
 
 // r := e^((x - max) / T) elementwise (padding becomes 0); returns the row's maximum, tot gets the wavefronts' sums.
@@ -2365,10 +2375,10 @@ __device__ __forceinline__ float smp_softmax(float4 (&r)[V4], float inv_t, float
   return m;
 }
 __device__ __forceinline__ float smp_total(const SmpTot& t) {
-  float s = t.v[0];
+  float s[SMP_NW];
 #pragma unroll
-  for (int i = 1; i < SMP_NW; ++i) s += t.v[i];
-  return s;
+  for (int i = 0; i < SMP_NW; ++i) s[i] = t.v[i];
+  return smp_pairwise<SMP_NW>(s);
 }
 
 // Inverse CDF at u * total over weights r with the wavefronts' sums tot: the smallest index whose cumulative sum exceeds

@@ -88,6 +88,20 @@ def test_probability_rows_keep_the_precision_of_expf(V):
     assert rms <= 4e-8
 
 
+@pytest.mark.parametrize("V", [4096, 32000, 49152, 65536])
+def test_row_sums_are_pairwise(V):
+    """The largest probability of such rows is 1 / S: the rounding of S and of its reciprocal.  A sum whose parts are of like size at
+    every level of a tree gathers sqrt(1 + 1/2 + 1/4 + ..) = sqrt(2) roundings of 2.53e-8 rms, with the reciprocal's sqrt(3): 4.4e-8;
+    the bar is 25 % above.  (Lane and wavefront sums one after another: 6.0e-8 .. 6.9e-8.)"""
+    g = torch.Generator().manual_seed(V + 1)
+    logits = -torch.randint(0, 16 * 1024, (300, V), generator=g).to(torch.float32) / 1024
+    logits[:, 7] = 0.0
+    _, probs = _gpu_sample(logits, 1.0, torch.full((300,), 0.5))
+    err = probs[:, 7].double() * logits.double().exp().sum(1) - 1.0
+    print(f"[sampling] V {V}: rms error of 1 / S {float(err.square().mean().sqrt()):.2e}", flush=True)
+    assert float(err.square().mean().sqrt()) <= 5.5e-8
+
+
 def test_subnormal_weights_are_weights():
     """e^-95 and e^-100 are subnormal in fp32 and not zero: the row stores them, a draw at 0 takes the first of them, and a
     drafted token of such a probability is kept at u = 0."""
