@@ -293,16 +293,16 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 
 // QKV epilogue of one lane: output features n0 .. n0+3 (lo4) and their rotary partners n0 + d_head/2 ..
 // (hi4) of token row m at position pos: rotation, then the query row or the paged K / V entry.
-// What it reads besides the products: rotary factors and the physical page (qkv_operands; the skinny kernel asks for them
-// before its weight stream ends).
+// What it reads besides the products: rotary factors and the physical page (qkv_operands; the skinny kernel of the LayerNorm
+// family asks for them before its weight stream ends).
 // ROPE false: the model has no rotation (the LayerNorm family has learned positions).
-struct QkvOps { float4 t0, t1; int pp; };
+struct QkvOps { float4 t0, t1; int pp, off; };
 template <bool ROPE = true>
 __device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, const int pos) {
   const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1, pt = a.page_tokens;
   QkvOps o;
-  o.t0 = o.t1 = make_float4(0.f, 0.f, 0.f, 0.f); o.pp = 0;
+  o.t0 = o.t1 = make_float4(0.f, 0.f, 0.f, 0.f); o.pp = o.off = 0;
   if (ROPE && a.rope_tab != nullptr && head < a.nq + a.nkv) {
     // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
     const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
@@ -311,6 +311,7 @@ __device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, 
   if (head >= a.nq) {
     const bool pow2 = (pt & (pt - 1)) == 0;
     const int lp = pow2 ? pos >> __builtin_ctz(pt) : pos / pt;
+    o.off = pos - lp * pt;
     o.pp = a.page_table ? a.page_table[lp] : lp;
   }
   return o;
@@ -339,9 +340,7 @@ __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int
   } else {
     const int sel = is_v ? 1 : 0;
     const int kvh = head - a.nq - sel * a.nkv;
-    const int pt = a.page_tokens;
-    const bool pow2 = (pt & (pt - 1)) == 0;
-    const int off = pow2 ? pos & (pt - 1) : pos % pt, pp = ops.pp;
+    const int off = ops.off, pp = ops.pp;
     bf16_t* blk = a.kv_layer + (((size_t)pp * 2 + sel) * a.nkv + kvh) * a.page_tokens * a.dh;
     if (!is_v) {                 // K: [token][d_head]
       bf16_t* dst = blk + (size_t)off * a.dh + c;
@@ -480,21 +479,20 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     }
     asm volatile("" ::: "memory");     // keep these loads ahead of the rest of the stream
   }
-  // vectors and table entries of the epilogue are requested here, by the wavefronts that will use them, so that their round trip
-  // runs beside the weight stream instead of behind it (a pass of the multi-query draft model, 12 layers, 5 tokens: 360 us behind
-  // it, 356 now; the residual rows of the PARTIAL epilogue, asked for here too, made the O-projection 0.7 us slower: they stay
-  // behind)
+  // The vectors of a deferred LayerNorm (and the page of the keys and values) are requested here, by the wavefronts that will use
+  // them, so that their round trip runs beside the weight stream instead of behind it (a pass of the multi-query draft model, 12
+  // layers, 5 tokens: 360 us behind it, 357 now).  The other operands of the epilogues stay behind: the residual rows of the
+  // PARTIAL epilogue made the O-projection 0.7 us slower here, the rotary factors of the RMSNorm family a pass over two 13B layers
+  // 0.7 us (300.2 -> 300.9)
   constexpr int TPU = PAIR ? 2 : 1;               // tiles per unit
   const bool ep = w < UNITS;                      // this wavefront finishes one output unit
   const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16x16 result
-  int urt[TPU];
+  int urt[TPU];                                   // its tiles; known here only where they are needed here
 #pragma unroll
   for (int i = 0; i < TPU; ++i) {
-    const int r = (ep ? w : 0) * TPU + i;
-    // (runtime index into rt[] would spill it: select with a compile-time loop)
     urt[i] = 0;
 #pragma unroll
-    for (int rr = 0; rr < RT; ++rr) if (rr == r) urt[i] = rt[rr];
+    for (int rr = 0; rr < RT; ++rr) if (LN && rr == (ep ? w : 0) * TPU + i) urt[i] = rt[rr];
   }
   // A lane holds one element of the two LayerNorm vectors until the reduction puts them into LDS: the 8 or 16 values that it needs
   // itself would take some instances past 128 registers and so leave one resident workgroup per compute unit instead of two (a
@@ -503,8 +501,8 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   // 12 tokens: 378.4 us, 380.5 before it)
   float lnv = 0.f;
   QkvOps qops;
-  constexpr bool EARLY = !(LN && P == 2 && RT == 4);
-  if (LN && EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
+  constexpr bool EARLY = LN && !(P == 2 && RT == 4);
+  if (EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
   if (EPI == EPI_QKV && EARLY && ep && m < a.M) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
   if (LN || EPI == EPI_QKV) asm volatile("" ::: "memory");
 #pragma unroll
@@ -564,6 +562,9 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
 #pragma unroll
   for (int i = 0; i < TPU; ++i) {
     const int r = (ep ? w : 0) * TPU + i;
+    // (runtime index into rt[] would spill it: select with a compile-time loop)
+#pragma unroll
+    for (int rr = 0; rr < RT; ++rr) if (!LN && rr == r) urt[i] = rt[rr];
     y[i] = sm.red[0][r][lane];
 #pragma unroll
     for (int ww = 1; ww < NW; ++ww) y[i] += sm.red[ww][r][lane];   // fixed order: deterministic
