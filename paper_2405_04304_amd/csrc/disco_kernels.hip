@@ -504,7 +504,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   constexpr bool EARLY = LN && !(P == 2 && RT == 4);
   if (EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
   if (EPI == EPI_QKV && EARLY && ep && m < a.M) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
-  if (LN || EPI == EPI_QKV) asm volatile("" ::: "memory");
+  if (EARLY) asm volatile("" ::: "memory");
 #pragma unroll
   for (int i = 0; i < U; ++i)
     if (kt0 + i * NW < kt_end) load_x(B[i], kt0 + i * NW);
@@ -934,7 +934,8 @@ hipError_t launch_vec_panel(const float* v, int d, bf16_t* Xout, hipStream_t s) 
 // variance as norm_row).  The panels are built in LDS, 512 columns at a time, and leave as whole 1 KiB tiles: one row per
 // workgroup wrote 16-byte pieces of lines that sixteen workgroups shared, and was bound by those partial lines (78 us against
 // 51 for 3008 rows of 6144).  16-byte chunks sit at (token xor eighth of the columns) in LDS, so that neither side has more
-// than two lanes on a bank.  Rows of up to 6144 values fit the registers.
+// than two lanes on a bank.  Rows of up to 6144 values are held in registers (96 of the 128 that sixteen wavefronts leave a lane; nine
+// more go to scratch memory, 40 bytes a lane).
 constexpr int NORM_GROUPS_MAX_D = 6144;
 __global__ __launch_bounds__(1024) void k_norm_groups(NormArgs a) {
   constexpr int NC = NORM_GROUPS_MAX_D / 256;     // float4 per lane
@@ -2302,7 +2303,7 @@ hipError_t launch_kv_fill(const bf16_t* src, bf16_t* pages, const int32_t* page_
 // cumulative sum in vocabulary order is wavefront by wavefront, segment by segment, lane by lane: sixteen totals in LDS
 // tell every wavefront whether the draw falls into its part, and only that wavefront scans its segments and its lanes.
 // (Scanning every segment across the whole workgroup, as before, read 256 LDS words per thread: 29 us for five rows of
-// 32000, 7.7 us now.)  All sums are fp32.  The exponential is expf: a shorter form on the hardware's exp2 took 0.4 us less for
+// 32000, 8.8 us now.)  All sums are fp32.  The exponential is expf: a shorter form on the hardware's exp2 took 0.4 us less for
 // a block of five at 32000 (17.4 of 17.8 us) and 3.6 us at 65536 (of 32.6), but flushed weights below 2^-126 to zero, and its
 // rows were further from 64 bits (4.4e-8 rms of a weight against 3.6e-8).
 
@@ -2477,7 +2478,7 @@ hipError_t launch_sample_rows(const SampleArgs& a, int n_rows, hipStream_t s) {
 // Row j's keep test and the draw that would follow its rejection need no other row, so every row has a workgroup of its
 // own: it leaves KEPT or the drawn token in out->emit[j], and a second launch of one wavefront finds the first row that
 // was not kept and writes the record.  (One workgroup going through the rows took about 10 us a row: 43 - 61 us for a
-// block of five at 32000, 7.7 + 1.7 us now.  The library has no memory of its own that calls on several
+// block of five at 32000, 8.1 + 1.4 us now; above 49152 logits 22 registers go to scratch memory.  The library has no memory of its own that calls on several
 // streams could share safely, hence the second launch instead of a ticket.)
 constexpr int ACCEPT_KEPT = -2;
 
@@ -2570,7 +2571,8 @@ hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
 // of the parameters another 130 per wavefront, four wavefronts on a SIMD) and two workgroup barriers: 4.4 us a step at
 // 200 examples and 64 units.  The form before took one example after another (a workgroup-wide sum per example, about
 // 480 ns each): 38.4 ms for 400 such steps, 1.77 ms now.  More workgroups would put a hand-off between workgroups (about
-// 2.5 us) into every step.
+// 2.5 us) into every step.  More than 128 units do not fit the registers of sixteen wavefronts (33 go to scratch memory up to 1280
+// examples, 143 above): 50 steps over 200 examples with 256 units take 1.04 ms (7.28 before), 10 over 2560 1.70 ms (18.9).
 
 constexpr int TRAIN_MAX_N = 2560;               // examples that fit in LDS (12 floats each)
 constexpr int TRAIN_NW = 16;
@@ -2934,8 +2936,9 @@ hipError_t launch_loop_finish(const int32_t* sl_count, const uint32_t* gate, voi
 //
 // A workgroup of 8 wavefronts (WR x WC) owns WR x R2 blocks of 32 rows x WC x C2 blocks of
 // 32 panel columns.  With hi + lo panels 64 panel columns are 32 tokens (the lo products are added into the accumulators of
-// the hi products), with bf16 activations 64.  What bounds it: the matrix unit at the clock that the power limit leaves
-// (1.9 of 2.4 GHz; the main loop alone ran at 1.2 - 1.5 PFLOP/s depending on the card, in 94 % of its cycles), so
+// the hi products), with bf16 activations 64.  What bounds it: the matrix unit, busy in
+// 63 - 78 % of the cycles of a launch that fills the chip, at the 1.4 - 1.9 GHz that these launches run at in long passes (counters: W1
+// of the multi-query target at 3001 tokens 77 %, 13B gate/up at 2048 in bf16 75 %, QKV 63 %), so
 // the loop is built to move little per product: both operands go from memory straight into LDS (no registers), 16 bytes per
 // lane in the packed tile order, which is also a conflict-free order of the 128-bit fragment reads, and 32x32x16
 // instructions read every fragment once per 128 x 64 wavefront tile.
@@ -3185,13 +3188,15 @@ __global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
 static size_t split_unit_bytes(bool hi_only) { return (size_t)256 * 128 * (hi_only ? 2 : 1) * sizeof(float); }
 
 // Workgroup tiles: 128 rows x 256 panel columns, two workgroups per compute unit (c0); 256 x 256, one (c1); 512 x 256, one (c2,
-// hi + lo only: 128-token accumulators); 128 x 128 (c3) where a short K and a small grid leave nothing but the latency of the
-// k-tiles.  Costs in units of half a compute unit's time for a 256 x 256 tile; the
+// hi + lo only: 128-token accumulators); 128 x 128 (c3) for grids of up to 256 such tiles, where the
+// latency of the k-tiles is most of the time.  Costs in units of half a compute unit's time for a 256 x 256 tile; the
 // larger tiles move less per product (c2 6 % faster than c1, c1 5 % than c0 where all fill the chip), the smaller ones
 // fill it better: a lone c0 workgroup runs at 1 / 1.4 of its compute unit.  Measured, us (c0 / c1 / c2), hi + lo at
 // 511 tokens: 27648 x 5120 274 / 246 / 217, 15360 x 5120 150 / 133 / 185, 5120 x 5120 74 / 101 / -; at 3001:
 // 6400 x 6144 396 / 418 / 477.  Cut along K in S ranges: 5120 x 13824 at 511 tokens 214 (c0) against 137 + 17 for its sum.
-// c3 against c0: a pass of the 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196.
+// c3 against the best of the others, a whole pass: 68M shape at 60 tokens 131 / 142, at 600 in bf16 170 / 196; at a long K, two layers
+// of 3072 at 120 tokens 281 / 297, of 4096 at 16 tokens 315 / 326, one 13B layer at 16 tokens in bf16 266 / 271, but in hi + lo
+// 255 / 243 (and two layers of 2560 221 / 210): which of them gains there does not follow K, and the rule leaves that open.
 DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t plane_bytes) {
   const int n_tiles = n_rows / 16;
   auto count = [&](const int na, const int nbt) { const int gg = nbt / (hi_only ? 1 : 2); return (long)((n_tiles + na - 1) / na) * ((n_groups + gg - 1) / gg); };
