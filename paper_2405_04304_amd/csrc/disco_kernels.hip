@@ -291,39 +291,29 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   union { u32x4 u; bf16x8 b; } c; c.u = v; return c.b;
 }
 
+// Where the keys and values of a position go: physical page and offset in it.
+struct KvSlot { int page, off; };
+__device__ __forceinline__ KvSlot kv_slot(const GemmArgs& a, const int pos) {
+  const int pt = a.page_tokens;
+  const bool pow2 = (pt & (pt - 1)) == 0;
+  const int lp = pow2 ? pos >> __builtin_ctz(pt) : pos / pt;
+  return KvSlot{a.page_table ? a.page_table[lp] : lp, pos - lp * pt};
+}
+
 // QKV epilogue of one lane: output features n0 .. n0+3 (lo4) and their rotary partners n0 + d_head/2 ..
 // (hi4) of token row m at position pos: rotation, then the query row or the paged K / V entry.
-// What it reads besides the products: rotary factors and the physical page (qkv_operands; the skinny kernel of the LayerNorm
-// family asks for them before its weight stream ends).
-// ROPE false: the model has no rotation (the LayerNorm family has learned positions).
-struct QkvOps { float4 t0, t1; int pp, off; };
-template <bool ROPE = true>
-__device__ __forceinline__ QkvOps qkv_operands(const GemmArgs& a, const int n0, const int pos) {
-  const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
-  const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1, pt = a.page_tokens;
-  QkvOps o;
-  o.t0 = o.t1 = make_float4(0.f, 0.f, 0.f, 0.f); o.pp = o.off = 0;
-  if (ROPE && a.rope_tab != nullptr && head < a.nq + a.nkv) {
-    // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
-    const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
-    o.t0 = tab[0]; o.t1 = tab[1];
-  }
-  if (head >= a.nq) {
-    const bool pow2 = (pt & (pt - 1)) == 0;
-    const int lp = pow2 ? pos >> __builtin_ctz(pt) : pos / pt;
-    o.off = pos - lp * pt;
-    o.pp = a.page_table ? a.page_table[lp] : lp;
-  }
-  return o;
-}
-template <bool COH = false, bool ROPE = true>
-__device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos, const QkvOps& ops,
+// ROPE false: the model has no rotation (the LayerNorm family has learned positions).  SLOT: the caller has looked up kv_slot.
+template <bool COH = false, bool ROPE = true, bool SLOT = false>
+__device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos, KvSlot slot,
                                           float (&lo4)[4], float (&hi4)[4]) {
-  const int dsh = a.dh == 128 ? 7 : 6;
+  const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1;
   const bool is_v = head >= a.nq + a.nkv;
   if (ROPE && a.rope_tab != nullptr && !is_v) {
-    const float cs[4] = {ops.t0.x, ops.t0.z, ops.t1.x, ops.t1.z}, sn[4] = {ops.t0.y, ops.t0.w, ops.t1.y, ops.t1.w};
+    // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
+    const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
+    const float4 t0 = tab[0], t1 = tab[1];
+    const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float x0 = lo4[v], x1 = hi4[v];
@@ -340,7 +330,8 @@ __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int
   } else {
     const int sel = is_v ? 1 : 0;
     const int kvh = head - a.nq - sel * a.nkv;
-    const int off = ops.off, pp = ops.pp;
+    if (!SLOT) slot = kv_slot(a, pos);
+    const int off = slot.off, pp = slot.page;
     bf16_t* blk = a.kv_layer + (((size_t)pp * 2 + sel) * a.nkv + kvh) * a.page_tokens * a.dh;
     if (!is_v) {                 // K: [token][d_head]
       bf16_t* dst = blk + (size_t)off * a.dh + c;
@@ -500,10 +491,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   // stream).  The instances of two panels and four tiles have no register to spare and ask behind the stream (two layers of 5120,
   // 12 tokens: 378.4 us, 380.5 before it)
   float lnv = 0.f;
-  QkvOps qops;
+  KvSlot slot = {0, 0};
   constexpr bool EARLY = LN && !(P == 2 && RT == 4);
   if (EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
-  if (EPI == EPI_QKV && EARLY && ep && m < a.M) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
+  if (EPI == EPI_QKV && EARLY && ep && m < a.M && urt[0] * 16 >= a.nq * a.dh) slot = kv_slot(a, a.pos0 + m);
   if (EARLY) asm volatile("" ::: "memory");
 #pragma unroll
   for (int i = 0; i < U; ++i)
@@ -669,10 +660,9 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   } else if (EPI == EPI_QKV) {
     // two tiles: features c .. c+3 and their rotary partners c + dh/2 .. of one head
     float lo4[4], hi4[4];
-    if (!EARLY) qops = qkv_operands<!LN>(a, urt[0] * 16 + 4 * g, a.pos0 + m);
 #pragma unroll
     for (int v = 0; v < 4; ++v) { lo4[v] = y[0][v]; hi4[v] = y[TPU - 1][v]; }
-    qkv_store<COH, !LN>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, qops, lo4, hi4);
+    qkv_store<COH, !LN, EARLY>(a, a.q, urt[0] * 16 + 4 * g, m, a.pos0 + m, slot, lo4, hi4);
   } else if (EPI == EPI_SWIGLU) {
     // tile 0 = gate rows, tile 1 = the matching up rows
     const int f = (urt[0] >> 1) * 16 + 4 * g;
@@ -2990,7 +2980,7 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
             const int g = 2 * i + gh;             // 4-row group of the 16-row tile
             if constexpr (EPI == EPI_QKV) {
               const int n0 = t0 * 16 + 4 * g, pos = a.pos0 + 16 * ci + m;
-              qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, qkv_operands(a, n0, pos), y[i], y[i + 2]);
+              qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, KvSlot{}, y[i], y[i + 2]);
             } else {
               float act[4];
 #pragma unroll
