@@ -359,7 +359,7 @@ int disco_sample(const float* dev_logits, int n_rows, int vocab, int64_t ld_logi
  * last token is drawn from norm(max(0, p_n - q_n)), and from p_SL when all are kept, with
  * dev_u_resample[n] (n_block entries).  Writes n and the emitted tokens as disco_accept does.
  * dev_n_block (may be NULL) overrides n_block with a device-resident value in [1, n_block].
- * dev_out holds the rows' outcomes until the call's last launch: it must not overlap dev_block.       */
+ * dev_out may overlap dev_block (one workgroup then goes through the rows).                          */
 int disco_accept_sample(const int32_t* dev_block, int n_block, const int32_t* dev_n_block,
                         const float* dev_draft_probs, const float* dev_target_logits, int vocab,
                         float temperature, const float* dev_u_accept, const float* dev_u_resample,

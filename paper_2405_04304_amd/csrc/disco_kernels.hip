@@ -2472,15 +2472,16 @@ hipError_t launch_sample_rows(const SampleArgs& a, int n_rows, hipStream_t s) {
 // streams could share safely, hence the second launch instead of a ticket.)
 constexpr int ACCEPT_KEPT = -2;
 
-template <int V4>
-__global__ __launch_bounds__(SMP_NT) void k_accept_rows(AcceptSampleArgs a) {
-  __shared__ __align__(16) float smem[3][SMP_NW];
-  const int V = a.vocab, nseg = smp_segments(V), j = blockIdx.x;
+__device__ __forceinline__ int accept_last_row(const AcceptSampleArgs& a) {
   int nb = a.n_block;
   if (a.dev_n_block) { const int v = *a.dev_n_block; nb = v < 1 ? 1 : (v > a.n_block ? a.n_block : v); }
-  const int sl = nb - 1;
-  if (j > sl) return;                             // whole workgroup
-  int32_t* slot = reinterpret_cast<AcceptOut*>(a.out)->emit + j;
+  return nb - 1;
+}
+
+// Keep test and draw of row j: kept (uniform), or the token drawn; true in the one thread that holds the outcome.
+template <int V4>
+__device__ __forceinline__ bool accept_row(const AcceptSampleArgs& a, const int j, const int sl, float (&smem)[3][SMP_NW], bool& kept, int& token) {
+  const int V = a.vocab, nseg = smp_segments(V);
   const float* x = a.target_logits + (size_t)j * V;
   const float* q = a.draft_probs + (size_t)j * V;
   float4 r[V4];
@@ -2493,12 +2494,14 @@ __global__ __launch_bounds__(SMP_NT) void k_accept_rows(AcceptSampleArgs a) {
   }
   SmpTot tot;
   const float m = smp_softmax<V4>(r, a.inv_t, smem[0], smem[1], tot);
+  kept = false;
   if (j < sl) {
     const float inv_s = 1.0f / smp_total(tot);
     const float p = expf((xt - m) * a.inv_t) * inv_s;
     if (u_acc * qt < p) {                         // the same values in every thread
-      if (threadIdx.x == 0) *slot = ACCEPT_KEPT;
-      return;
+      kept = true;
+      token = ACCEPT_KEPT;
+      return threadIdx.x == 0;
     }
     // residual max(0, p - q) of this row
 #pragma unroll
@@ -2511,14 +2514,40 @@ __global__ __launch_bounds__(SMP_NT) void k_accept_rows(AcceptSampleArgs a) {
     }
     tot = smp_share(wave_sum(smp_lane_sum<V4>(r)), smem[2]);
   }
+  return smp_draw<V4>(r, tot, u_res, nseg, token);
+}
+
+template <int V4>
+__global__ __launch_bounds__(SMP_NT) void k_accept_rows(AcceptSampleArgs a) {
+  __shared__ __align__(16) float smem[3][SMP_NW];
+  const int j = blockIdx.x, sl = accept_last_row(a);
+  if (j > sl) return;                             // whole workgroup
+  bool kept;
   int tok;
-  if (smp_draw<V4>(r, tot, u_res, nseg, tok)) *slot = tok;
+  if (accept_row<V4>(a, j, sl, smem, kept, tok)) reinterpret_cast<AcceptOut*>(a.out)->emit[j] = tok;
+}
+
+// The same for a record that overlaps an input (a block that lies in it, say): one workgroup goes through the rows and writes only
+// when everything has been read.
+__global__ __launch_bounds__(SMP_NT) void k_accept_in_place(AcceptSampleArgs a) {
+  __shared__ __align__(16) float smem[3][SMP_NW];
+  const int sl = accept_last_row(a);
+  int n = -1, tok;
+  bool kept, mine;
+  do {                                            // uniform; row sl is never kept
+    if (++n > 0) __syncthreads();                 // smem is free again
+    mine = accept_row<16>(a, n, sl, smem, kept, tok);
+  } while (kept);
+  if (!mine) return;
+  AcceptOut o;
+  o.n = n; o.n_emit = n + 1;
+  for (int i = 0; i < 16; ++i) o.emit[i] = (i < n) ? a.block[i + 1] : (i == n ? tok : -1);
+  *reinterpret_cast<AcceptOut*>(a.out) = o;
+  if (a.host_out) { *reinterpret_cast<AcceptOut*>(a.host_out) = o; __threadfence_system(); }
 }
 
 __global__ __launch_bounds__(64) void k_accept_finish(AcceptSampleArgs a) {
-  int nb = a.n_block;
-  if (a.dev_n_block) { const int v = *a.dev_n_block; nb = v < 1 ? 1 : (v > a.n_block ? a.n_block : v); }
-  const int sl = nb - 1, i = threadIdx.x;
+  const int sl = accept_last_row(a), i = threadIdx.x;
   AcceptOut* out = reinterpret_cast<AcceptOut*>(a.out);
   const int mine = i <= sl ? out->emit[i] : 0;
   const int drafted = i < sl ? a.block[i + 1] : -1;
@@ -2534,6 +2563,17 @@ __global__ __launch_bounds__(64) void k_accept_finish(AcceptSampleArgs a) {
 
 hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
   if (a.n_block < 1 || a.n_block > 16 || a.vocab < 4 || (a.vocab & 3) || a.vocab > 65536) return hipErrorInvalidValue;
+  // the rows' workgroups leave their outcomes in the record while others still read the inputs: nothing may overlap it
+  auto overlaps = [&](const void* p, size_t words) {
+    const uintptr_t o = reinterpret_cast<uintptr_t>(a.out), q = reinterpret_cast<uintptr_t>(p);
+    return p != nullptr && q < o + sizeof(AcceptOut) && o < q + words * 4;
+  };
+  const size_t n = a.n_block, V = a.vocab;
+  if (overlaps(a.block, n) || overlaps(a.dev_n_block, 1) || overlaps(a.u_accept, n - 1) || overlaps(a.u_resample, n) ||
+      overlaps(a.draft_probs, (n - 1) * V) || overlaps(a.target_logits, n * V)) {
+    hipLaunchKernelGGL(k_accept_in_place, dim3(1), dim3(SMP_NT), 0, s, a);
+    return hipGetLastError();
+  }
   const dim3 rows(a.n_block);
   if (a.vocab <= 8192) hipLaunchKernelGGL(k_accept_rows<2>, rows, dim3(SMP_NT), 0, s, a);
   else if (a.vocab <= 32768) hipLaunchKernelGGL(k_accept_rows<8>, rows, dim3(SMP_NT), 0, s, a);

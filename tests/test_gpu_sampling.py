@@ -150,6 +150,23 @@ def _gpu_accept(lt, q_rows, block, u_acc, u_res, T, dev_n_block=None):
     return a.n, list(a.emit[:a.n_emit])
 
 
+@pytest.mark.parametrize("V", [252, 32000, 65536])
+def test_accept_sample_with_the_block_inside_the_record(V):
+    """The record may be written over the block it was made from: the same outcome as with buffers apart, for blocks that are kept
+    whole, rejected at once and in between, at every offset of the block in the record that lies on a word."""
+    d = dev()
+    for sl, mode, shift in ((0, "near", 0), (3, "same", 2), (6, "near", 1), (9, "far", 2), (12, "near", 3), (15, "same", 2)):
+        lt, q_rows, block, u_acc, u_res = _accept_case(np.random.default_rng(V + sl), V, sl, 1.0, mode)
+        want = _gpu_accept(lt, q_rows, block, u_acc, u_res, 1.0)
+        buf = torch.zeros(18 + 16, dtype=torch.int32, device=d)         # the record's 18 words and room for a block that sticks out
+        buf[shift:shift + sl + 1] = torch.tensor(block, dtype=torch.int32, device=d)
+        q = torch.stack(q_rows).to(d) if q_rows else torch.zeros(1, V, dtype=torch.float32, device=d)
+        B.disco_accept_sample(buf[shift:], sl + 1, q, lt.to(d).contiguous(), V, 1.0, u_acc.to(d), u_res.to(d), buf)
+        torch.cuda.synchronize()
+        got = buf[:18].cpu().tolist()
+        assert (got[0], got[2:2 + got[1]]) == want and got[1] == got[0] + 1 and got[2 + got[1]:] == [-1] * (16 - got[1]), (sl, mode, shift)
+
+
 @pytest.mark.parametrize("V", [4, 252, 256, 260, 4092, 4100, 8192, 8196, 32768, 32772, 49152, 49156, 65536])
 def test_row_kernels_at_segment_edges(V):
     """A row is dealt to sixteen wavefronts in segments of 256, in templates of 2 / 8 / 12 / 16 segments: lengths around the
