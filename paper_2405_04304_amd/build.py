@@ -13,6 +13,7 @@ def build(verbose: bool = True) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-x", "hip",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-mllvm", "-amdgpu-kernarg-preload-count=16",     # leading kernel arguments arrive in scalar registers
            "-Wall", "-Wno-unused-function",
            "-I", os.path.join(HERE, "..", "include")]
     cmd += [os.path.join(CSRC, s) for s in SOURCES]

@@ -45,6 +45,12 @@ __device__ __forceinline__ bool gated(const uint32_t* gate) {
 __device__ __forceinline__ uint32_t gate_request(const uint32_t* gate) {
   return gate != nullptr ? __builtin_nontemporal_load(gate) : 0u;
 }
+// Tests a requested flag (the same in every lane).  The value is opaque up to here: left to itself the compiler compares it, and
+// so waits for it, where it is requested, in front of the operand loads.
+__device__ __forceinline__ bool flag_set(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return __builtin_amdgcn_readfirstlane((int)v) != 0;
+}
 
 // Stores and loads of data that another workgroup of the SAME launch reads or has written (COH): agent-scope
 // relaxed atomics, which on gfx950 are write-through stores and L2-bypassing loads, coherent across the
@@ -111,6 +117,7 @@ __device__ __forceinline__ void xpack_store4(bf16_t* X, int KT, int M, int m, in
 #define DPP_QUAD_XOR2 0x4E
 #define DPP_ROW_HALF_MIRROR 0x141
 #define DPP_ROW_MIRROR 0x140
+#define DPP_ROW_ROR8 0x128
 #define DPP_ROW_BCAST15 0x142
 #define DPP_ROW_BCAST31 0x143
 
@@ -175,15 +182,22 @@ __device__ __forceinline__ bool last_arrival(int* counter, int n, int* s_flag) {
   return *s_flag != 0;
 }
 
+// A value and its partner 16 or 32 lanes away, one half of the wavefront each way round (vector instructions; a shuffle goes through
+// the LDS unit).  Lanes that are 16 and 32 apart must be active together.
+struct Pair32 { float a, b; };
+__device__ __forceinline__ Pair32 swap16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return Pair32{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Pair32 swap32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return Pair32{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float half_max(float v) { const Pair32 p = swap32(v); return fmaxf(p.a, p.b); }   // lanes l, l^32
+__device__ __forceinline__ float half_sum(float v) { const Pair32 p = swap32(v); return p.a + p.b; }
 // Across the four 16-lane rows of a wavefront (lanes l, l^16, l^32, l^48), every lane gets the result.
-__device__ __forceinline__ float row4_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16));
-  return fmaxf(v, __shfl_xor(v, 32));
-}
-__device__ __forceinline__ float row4_sum(float v) {
-  v += __shfl_xor(v, 16);
-  return v + __shfl_xor(v, 32);
-}
+__device__ __forceinline__ float row4_max(float v) { const Pair32 p = swap16(v); return half_max(fmaxf(p.a, p.b)); }
+__device__ __forceinline__ float row4_sum(float v) { const Pair32 p = swap16(v); return half_sum(p.a + p.b); }
 
 // Block-wide sum in a fixed order (deterministic); every thread gets the result.
 template <int NT>
@@ -441,6 +455,10 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     if (kt0 + i * NW < kt_end) load_w(A[i], kt0 + i * NW);
   asm volatile("" ::: "memory");
   hook();
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (kt0 + i * NW < kt_end) load_x(B[i], kt0 + i * NW);
+  asm volatile("" ::: "memory");
 
   // deferred RMSNorm: the panels hold g * h (not normalised).  The producer left one sum of squares
   // per token and 16-column tile; every lane fetches a few of them now (lane = token lane % 16,
@@ -472,9 +490,9 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   }
   // The vectors of a deferred LayerNorm (and the page of the keys and values) are requested here, by the wavefronts that will use
   // them, so that their round trip runs beside the weight stream instead of behind it (a pass of the multi-query draft model, 12
-  // layers, 5 tokens: 360 us behind it, 357 now).  The other operands of the epilogues stay behind: the residual rows of the
-  // PARTIAL epilogue made the O-projection 0.7 us slower here, the rotary factors of the RMSNorm family a pass over two 13B layers
-  // 0.7 us (300.2 -> 300.9)
+  // layers, 5 tokens: 360 us behind it, 357 now).  The rotary factors of the RMSNorm family stay behind (a pass over two 13B layers
+  // 300.2 us, 300.9 with them here), and so do the residual rows of 64-row PARTIAL units, whose stream is long (6144 rows, K 6144 and
+  // 24576, a launch: 34.0 us, 35.9 with them here); 16-row units ask here
   constexpr int TPU = PAIR ? 2 : 1;               // tiles per unit
   const bool ep = w < UNITS;                      // this wavefront finishes one output unit
   const int m = lane & 15, g = lane >> 4;         // token column, 4-row group of the 16x16 result
@@ -496,10 +514,21 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   if (EARLY && ep) lnv = ((lane & 32) ? a.wb : a.wg)[(TPU == 2 && (lane & 16) ? urt[TPU - 1] : urt[0]) * 16 + m];
   if (EPI == EPI_QKV && EARLY && ep && m < a.M && urt[0] * 16 >= a.nq * a.dh) slot = kv_slot(a, a.pos0 + m);
   if (EARLY) asm volatile("" ::: "memory");
-#pragma unroll
-  for (int i = 0; i < U; ++i)
-    if (kt0 + i * NW < kt_end) load_x(B[i], kt0 + i * NW);
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  float4 h = make_float4(0.f, 0.f, 0.f, 0.f), gn = h;
+  float* hp = nullptr;
+  auto load_residual = [&] {                      // (depends on no other workgroup of the launch)
+    const int col = (b * RT + (ep ? w : 0)) * 16 + 4 * g;
+    hp = a.h + (size_t)m * a.ld_out + col;
+    if (ep && m < a.M) {
+      h = ld_f4<COH>(hp);
+      if (a.Xout != nullptr) gn = *reinterpret_cast<const float4*>(a.gain + col);
+    }
+  };
+  if (EPI == EPI_PARTIAL && RT == 1) {
+    load_residual();
+    asm volatile("" ::: "memory");
+  }
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
   for (int kt = kt0; kt < kt_end; kt += U * NW) {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
@@ -524,7 +553,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     f32x4 y = acc[r];
     if (P == 1) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) y[v] = acc[r][v] + __shfl_xor(acc[r][v], 8);
+      for (int v = 0; v < 4; ++v) y[v] = acc[r][v] + dpp_f<DPP_ROW_ROR8, 0xF>(0.f, acc[r][v]);
     }
     sm.red[w][r][lane] = y;
   }
@@ -561,17 +590,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
     for (int ww = 1; ww < NW; ++ww) y[i] += sm.red[ww][r][lane];   // fixed order: deterministic
   }
 
-  // operands of the residual update that do not depend on other workgroups are fetched before the ticket
-  float4 h = make_float4(0.f, 0.f, 0.f, 0.f), gn = h;
-  float* hp = nullptr;
-  if (EPI == EPI_PARTIAL) {
-    const int col = urt[0] * 16 + 4 * g;
-    hp = a.h + (size_t)m * a.ld_out + col;
-    if (ep && m < a.M) {
-      h = ld_f4<COH>(hp);
-      if (a.Xout != nullptr) gn = *reinterpret_cast<const float4*>(a.gain + col);
-    }
-  }
+  if (EPI == EPI_PARTIAL && RT > 1) load_residual();   // ahead of the ticket
 
   if (n_seg > 1) {
     // this unit covers part of K: store the partial tiles, take a ticket; the last unit of the row
@@ -655,7 +674,7 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   if (EPI == EPI_STORE) {
     if (a.only_row >= 0 && m != a.only_row) return;
     const size_t row_off = a.only_row >= 0 ? 0 : (size_t)m * a.ld_out;
-    if (aborted != 0u) y[0] = f32x4{NAN, NAN, NAN, NAN};   // the forward's data is unusable: say so in its result
+    if (flag_set(aborted)) y[0] = f32x4{NAN, NAN, NAN, NAN};   // the forward's data is unusable: say so in its result
     st_f4<COH>(a.out + row_off + urt[0] * 16 + 4 * g, y[0][0], y[0][1], y[0][2], y[0][3]);
   } else if (EPI == EPI_QKV) {
     // two tiles: features c .. c+3 and their rotary partners c + dh/2 .. of one head
@@ -681,11 +700,21 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
   }
 }
 
+// Kernels of the decode path take what their first loads need as separate leading arguments (14 dwords at most; the library is built so that
+// these arrive in scalar registers with the launch) and the rest as a structure: read from the argument buffer, all of them stood
+// in front of the first load (0.36 us a launch: four tokens of the multi-query draft model 1505 us, 1436 with k_gemm changed).
+// `early`: the residual rows (PARTIAL) or the sums of squares of the input.
 template <int P, int RT, int EPI, int NW, int U, bool LN = false>
-__global__ __launch_bounds__(NW * 64) void k_gemm(GemmArgs a) {
+__global__ __launch_bounds__(NW * 64) void k_gemm(const bf16_t* W, const bf16_t* X, const uint32_t* gate, const float* early, int KT,
+                                                  int split_or_grp, int n_ssq, int M, const float* sum, GemmArgs a) {
   __shared__ GemmSmem<RT, NW, LN> sm;
+  a.W = W; a.X = X; a.gate = gate; a.KT = KT; a.M = M;
+  if constexpr (EPI == EPI_PARTIAL) { a.h = const_cast<float*>(early); a.n_split = split_or_grp; }
+  else { a.ssq = early; a.n_ssq = n_ssq; a.n_split = 1; a.grp = split_or_grp; if (LN) a.sum = sum; }
+  const int n_split = a.n_split;
   const int split = blockIdx.y;
-  const int kt_begin = (int)((int64_t)a.KT * split / a.n_split), kt_end = (int)((int64_t)a.KT * (split + 1) / a.n_split);
+  const int kt_begin = n_split == 1 ? 0 : (int)((unsigned)(KT * split) / (unsigned)n_split);
+  const int kt_end = n_split == 1 ? KT : (int)((unsigned)(KT * (split + 1)) / (unsigned)n_split);
   gemm_unit<P, RT, EPI, NW, U, false, NoHook, LN>(a, blockIdx.x, kt_begin, kt_end, split, a.n_split, sm);
 }
 
@@ -695,11 +724,13 @@ static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t s) {
   if (a.n_rows % rows) return hipErrorInvalidValue;
   if constexpr (EPI == EPI_QKV || EPI == EPI_GELU || EPI == EPI_STORE) {
     if (a.sum != nullptr) {                       // deferred LayerNorm
-      hipLaunchKernelGGL((k_gemm<P, RT, EPI, NW, U, true>), dim3(a.n_rows / rows, a.n_split), dim3(NW * 64), 0, s, a);
+      hipLaunchKernelGGL((k_gemm<P, RT, EPI, NW, U, true>), dim3(a.n_rows / rows, a.n_split), dim3(NW * 64), 0, s, a.W, a.X, a.gate,
+                         EPI == EPI_PARTIAL ? a.h : a.ssq, a.KT, EPI == EPI_PARTIAL ? a.n_split : a.grp, a.n_ssq, a.M, a.sum, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_gemm<P, RT, EPI, NW, U>), dim3(a.n_rows / rows, a.n_split), dim3(NW * 64), 0, s, a);
+  hipLaunchKernelGGL((k_gemm<P, RT, EPI, NW, U>), dim3(a.n_rows / rows, a.n_split), dim3(NW * 64), 0, s, a.W, a.X, a.gate,
+                         EPI == EPI_PARTIAL ? a.h : a.ssq, a.KT, EPI == EPI_PARTIAL ? a.n_split : a.grp, a.n_ssq, a.M, a.sum, a);
   return hipGetLastError();
 }
 
@@ -829,7 +860,7 @@ __device__ __forceinline__ void norm_row(const NormArgs& a, const int row, const
       }
     }
   }
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
   if (e) {
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
@@ -899,7 +930,9 @@ __device__ __forceinline__ void norm_row(const NormArgs& a, const int row, const
 }
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_norm(NormArgs a) {
+__global__ __launch_bounds__(NT) void k_norm(const int32_t* tokens, const bf16_t* tok_emb, const bf16_t* pos_emb, float* h, const uint32_t* gate, int d, int pos0,
+                                             int n_tok, int vocab, NormArgs a) {
+  a.tokens = tokens; a.tok_emb = tok_emb; a.pos_emb = pos_emb; a.h = h; a.gate = gate; a.d = d; a.pos0 = pos0; a.n_tok = n_tok; a.vocab = vocab;
   __shared__ float red[NT / 64 + 1];
   norm_row<NT>(a, blockIdx.x, -1, red, gate_request(a.gate));
 }
@@ -1003,8 +1036,9 @@ hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   const unsigned rows = a.n_groups > 0 ? 16u * (unsigned)a.n_groups : (unsigned)a.M;
-  if (a.d <= 2048) hipLaunchKernelGGL(k_norm<256>, dim3(rows), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_norm<1024>, dim3(rows), dim3(1024), 0, s, a);
+  const int nt = a.d <= 2048 ? 256 : 1024;
+  hipLaunchKernelGGL(nt == 256 ? k_norm<256> : k_norm<1024>, dim3(rows), dim3(nt), 0, s, a.tokens, a.tok_emb, a.pos_emb, a.h, a.gate, a.d, a.pos0,
+                     a.n_tok, a.vocab, a);
   return hipGetLastError();
 }
 
@@ -1049,7 +1083,7 @@ struct AttnWave {
   __device__ __forceinline__ AttnWave(const AttnArgs& a_, int head, int s1_, int pos0_ = -1, const float* q_ = nullptr) : a(a_) {
     const int lane = threadIdx.x & 63;
     j = lane & 15; g = lane >> 4;
-    kvh = head / (a.nq / a.nkv);
+    kvh = a.nkv == 1 ? 0 : (a.nq == a.nkv ? head : head / (a.nq / a.nkv));
     const int pos0 = pos0_ < 0 ? a.pos0 : pos0_;
     qb = q_ != nullptr ? q_ : a.q;
     total = pos0 + a.M; s1 = s1_ < 0 ? total : s1_; pt = a.page_tokens;
@@ -1210,7 +1244,7 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
   hook();
   if (base < s1 && !early) aw.issue(r0, base);
   aw.load_q(head);
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
   while (base < s1) {
     if (base + STEP < s1) aw.issue(r1, base + STEP);
     aw.step(r0, base);
@@ -1295,8 +1329,15 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
   }
 }
 
+// Leading arguments of the attention kernels (see k_gemm); heads: query heads + 65536 * K / V heads.
+#define ATTN_EARLY const bf16_t* kv_layer, const int32_t* page_table, const float* q, const uint32_t* gate, int page_tokens, int heads, int ldq, \
+                   int pos0, int M, int split_len
+#define ATTN_EARLY_SET(a) do { a.kv_layer = kv_layer; a.page_table = page_table; a.q = q; a.gate = gate; a.page_tokens = page_tokens; \
+  a.nq = heads & 0xffff; a.nkv = heads >> 16; a.ldq = ldq; a.pos0 = pos0; a.M = M; a.split_len = split_len; } while (0)
+#define ATTN_EARLY_ARGS(a) a.kv_layer, a.page_table, a.q, a.gate, a.page_tokens, a.nq | (a.nkv << 16), a.ldq, a.pos0, a.M, a.split_len
 template <int DH>
-__global__ __launch_bounds__(512) void k_attn_partial(AttnArgs a) {
+__global__ __launch_bounds__(512) void k_attn_partial(ATTN_EARLY, AttnArgs a) {
+  ATTN_EARLY_SET(a);
   __shared__ AttnSmem<DH, 8> sm;                  // eight wavefronts: a range of 256 positions is one step each (measured
   attn_range<DH, 8>(a, blockIdx.x, blockIdx.y, sm, gate_request(a.gate));   // 1.3 % of a 13B verification block against four)
 }
@@ -1317,7 +1358,7 @@ __device__ __forceinline__ void attn_whole_head(const AttnArgs& a, const int hea
   int base = w * WKEYS;
   if (base < total) aw.issue(r0, base);
   aw.load_q(head);
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
   while (base < total) {
     if (base + STEP < total) aw.issue(r1, base + STEP);
     aw.step(r0, base);
@@ -1349,7 +1390,8 @@ __device__ __forceinline__ void attn_whole_head(const AttnArgs& a, const int hea
 }
 
 template <int DH>
-__global__ __launch_bounds__(512) void k_attn_head(AttnArgs a) {
+__global__ __launch_bounds__(512) void k_attn_head(ATTN_EARLY, AttnArgs a) {
+  ATTN_EARLY_SET(a);
   attn_whole_head<DH>(a, blockIdx.x, gate_request(a.gate));
 }
 
@@ -1541,7 +1583,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups,
     float mx = S[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) mx = fmaxf(mx, S[v]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = half_max(mx);
     const float m_new = fmaxf(m_run, mx);
     if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0ull) {      // some column's maximum moved
       const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * ce);
@@ -1612,7 +1654,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_tiles(AttnArgs a, int n_groups,
     }
   }
   if (w_end == 0 || r0 + col >= rows) return;
-  const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32));
+  const float inv = 1.0f / half_sum(l_run);
   bf16_t* X = a.Xout + (size_t)(r >> 4) * x_stride;
 #pragma unroll
   for (int c = 0; c < CB; ++c)
@@ -1639,14 +1681,14 @@ int attn_split_len(int total) {
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s) {
   if (a.M < 1 || a.M > 16 || a.n_splits < 1 || a.counters == nullptr) return hipErrorInvalidValue;
   if (a.pos0 + a.M <= ATTN_HEAD_MAX_CTX) {
-    if (a.dh == 128) hipLaunchKernelGGL(k_attn_head<128>, dim3(a.nq), dim3(512), 0, s, a);
-    else if (a.dh == 64) hipLaunchKernelGGL(k_attn_head<64>, dim3(a.nq), dim3(512), 0, s, a);
+    if (a.dh == 128) hipLaunchKernelGGL(k_attn_head<128>, dim3(a.nq), dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
+    else if (a.dh == 64) hipLaunchKernelGGL(k_attn_head<64>, dim3(a.nq), dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
   const dim3 g1(a.nq, a.n_splits);
-  if (a.dh == 128) hipLaunchKernelGGL(k_attn_partial<128>, g1, dim3(512), 0, s, a);
-  else if (a.dh == 64) hipLaunchKernelGGL(k_attn_partial<64>, g1, dim3(512), 0, s, a);
+  if (a.dh == 128) hipLaunchKernelGGL(k_attn_partial<128>, g1, dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
+  else if (a.dh == 64) hipLaunchKernelGGL(k_attn_partial<64>, g1, dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -2103,7 +2145,7 @@ __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b,
       cw2 = a.clf_params[a.hidden * 13 + t];
     }
   }
-  if (halted != 0u) {                             // uniform over the launch; the loads above are dropped
+  if (flag_set(halted)) {                         // uniform over the launch; the loads above are dropped
     if (threadIdx.x == 0 && b == 0) out->executed = 0u;
     return -1;
   }
@@ -2137,14 +2179,17 @@ __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b,
   return classify_merge_finish<NT, CPT>(a, a.scratch + 64, nb, force, xf, k, sv, si, wtop, top_s, feat_s);
 }
 
-__global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(ClassifyArgs a) {
+__global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, const float* clf_params, const int32_t* force_token, uint32_t* gate, float* scratch,
+                                                                int vocab, int hidden, ClassifyArgs a) {
+  a.logits = logits; a.clf_params = clf_params; a.force_token = force_token; a.gate = gate; a.scratch = scratch; a.vocab = vocab; a.hidden = hidden;
   classify_unit<CM_MULTI_NT>(a, blockIdx.x, gridDim.x, gate_request(const_cast<const uint32_t*>(a.gate)));
 }
 
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s) {
   if (a.vocab < 1 || a.vocab > 65536) return hipErrorInvalidValue;
   if (a.scratch != nullptr && a.vocab >= 4096) {
-    hipLaunchKernelGGL(k_classify_multi, dim3((a.vocab + 4 * CM_MULTI_NT - 1) / (4 * CM_MULTI_NT)), dim3(CM_MULTI_NT), 0, s, a);
+    hipLaunchKernelGGL(k_classify_multi, dim3((a.vocab + 4 * CM_MULTI_NT - 1) / (4 * CM_MULTI_NT)), dim3(CM_MULTI_NT), 0, s, a.logits, a.clf_params,
+                       a.force_token, a.gate, a.scratch, a.vocab, a.hidden, a);
     return hipGetLastError();
   }
   if (a.vocab <= 8192) hipLaunchKernelGGL(k_classify<2>, dim3(1), dim3(FEAT_NT), 0, s, a);
@@ -2433,7 +2478,7 @@ __global__ __launch_bounds__(SMP_NT) void k_sample_rows(SampleArgs a) {
   float4 r[V4];
   smp_load<V4>(r, a.logits + (size_t)row * a.ld, V, nseg, -INFINITY);
   const float u = a.u[row];
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written yet
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
   SmpTot tot;
   smp_softmax<V4>(r, a.inv_t, smem[0], smem[1], tot);
   int tok;
@@ -3057,7 +3102,7 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
           }
           if constexpr (EPI == EPI_PARTIAL) {
             if (a.Xout != nullptr) {
-              sq += __shfl_xor(sq, 32);           // (lanes l and l + 32 hold the same token: both are here)
+              sq = half_sum(sq);                  // (lanes l and l + 32 hold the same token: both are here)
               if (gh == 0) a.ssq_out[(size_t)ci * d.ssq_outs + t0 * 16 + m] = sq;      // [slot][token]
             }
           }
@@ -3356,7 +3401,10 @@ struct HeadWaitHook {
 };
 
 template <int P, int RT, int U, int DH>
-__global__ __launch_bounds__(512) void k_qkv_attn(GemmArgs g, AttnArgs a, int* ready, unsigned* abort_word, int safe_end, int limit) {
+__global__ __launch_bounds__(512) void k_qkv_attn(const bf16_t* W, const bf16_t* X, const uint32_t* gate, const float* ssq, int KT, int grp, int n_ssq,
+                                                  int M, int heads, int pos0, GemmArgs g, AttnArgs a, int* ready, unsigned* abort_word, int safe_end, int limit) {
+  g.W = W; g.X = X; g.gate = gate; g.ssq = ssq; g.KT = KT; g.grp = grp; g.n_ssq = n_ssq; g.M = M; a.M = M; g.nq = heads; g.nkv = heads;
+  a.nq = heads; a.nkv = heads; g.pos0 = pos0; a.pos0 = pos0;
   constexpr int UH = DH / (16 * RT), G = 3 * UH;   // workgroups per q / K / V part of a head, per head
   static_assert(UH >= 1 && UH * 16 * RT == DH, "a head part is a whole number of workgroups");
   union Smem { GemmSmem<RT, 8> gemm; AttnSmem<DH, 8> attn; };
@@ -3366,7 +3414,7 @@ __global__ __launch_bounds__(512) void k_qkv_attn(GemmArgs g, AttnArgs a, int* r
   const int hu = part == 0 ? head : (part == 1 ? g.nq + head : g.nq + g.nkv + head);
   const uint32_t halted = gate_request(g.gate);
   gemm_unit<P, RT, EPI_QKV, 8, U, true>(g, hu * UH + sub, 0, g.KT, 0, 1, sm.gemm);
-  if (halted != 0u) return;                       // uniform over the launch; nothing has been written
+  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_waitcnt(0);                  // this wavefront's write-through stores have completed
   __syncthreads();                                // ... and those of the whole workgroup
@@ -3392,7 +3440,8 @@ static hipError_t launch_qkv_attn_cfg(const GemmArgs& g, const AttnArgs& a, int*
   static const long capacity = resident_capacity(reinterpret_cast<const void*>(k_qkv_attn<P, RT, U, DH>));
   const int wgs = g.n_rows / (16 * RT);
   if (wgs > capacity) return hipSuccess;          // not all resident at once: the caller launches the two kernels
-  hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH>), dim3(wgs), dim3(512), 0, s, g, a, ready, abort_word, safe_end, limit);
+  hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH>), dim3(wgs), dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M, g.nq,
+                     g.pos0, g, a, ready, abort_word, safe_end, limit);
   *launched = true;
   return hipGetLastError();
 }
