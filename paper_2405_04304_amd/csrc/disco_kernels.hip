@@ -1805,30 +1805,6 @@ __device__ __forceinline__ void wave_top10(float (&c)[N], float* out10) {
   }
 }
 
-// Ten largest of a workgroup's values: every wavefront's ten, then one thread per candidate ranks it:
-// a candidate's rank is the number of candidates that beat it (larger, or equal with a lower slot), a
-// permutation of 0 .. n-1, and ranks below ten are the answer in order.  No dependent cross-lane chain.
-template <int NT, int N>
-__device__ __forceinline__ void block_top10(float (&c)[N], float (*wtop)[10], float* top_s) {
-  const int wv = threadIdx.x >> 6;
-  wave_top10<N>(c, wtop[wv]);
-  __syncthreads();
-  constexpr int NC = (NT / 64) * 10;
-  if ((int)threadIdx.x < NC) {
-    const int me = threadIdx.x;
-    const float* cand = &wtop[0][0];
-    const float mine = cand[me];
-    float o[NC];
-#pragma unroll
-    for (int j = 0; j < NC; ++j) o[j] = cand[j];          // all reads in flight at once (broadcasts)
-    int rank = 0;
-#pragma unroll
-    for (int j = 0; j < NC; ++j) rank += (o[j] > mine || (o[j] == mine && j < me)) ? 1 : 0;
-    if (rank < 10) top_s[rank] = mine;
-  }
-  __syncthreads();
-}
-
 template <int V4>
 __global__ __launch_bounds__(FEAT_NT) void k_classify(ClassifyArgs a) {
   ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
@@ -1988,49 +1964,89 @@ __global__ __launch_bounds__(FEAT_NT) void k_classify(ClassifyArgs a) {
 // Classifier coefficients of one thread (hidden unit threadIdx.x), fetched early by the caller.
 struct ClfCoef { float w1[12]; float b1, w2, b2; };
 
-// Last stage of the feature / classifier computation, run by ONE workgroup of NT threads over nb
-// records {max, arg-max, S, T relative to the record's max, its ten largest values} (16 floats each,
-// written with agent-scope stores by the workgroups that reduced the logits): merged statistics in
-// record order, the ten largest of the nb * 10 candidates (CPT per thread), the forced logit in closed
-// form, features, classifier, halt decision and the loop's bookkeeping words.
-template <int NT, int CPT>
-__device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, const float* recs, const int nb, const int force,
-                                                      const float xf, const ClfCoef& k, float* sv, int* si, float (*wtop)[10],
-                                                      float* top_s, float* feat_s) {
-  ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
-  const int t = threadIdx.x;
-  VI bm; bm.v = -INFINITY; bm.i = 0x7fffffff;
-  float Sb = 0.f, Tb = 0.f, mb = 0.f;
-  if (t < nb) {
-    const float2 p0 = ld_agent2(recs + (size_t)t * CM_REC), p1 = ld_agent2(recs + (size_t)t * CM_REC + 2);
-    bm.v = p0.x; bm.i = __float_as_int(p0.y); mb = p0.x; Sb = p1.x; Tb = p1.y;
-  }
-  VI gbest = block_argmax<NT>(bm, sv, si);
-  float Sg = 0.f, Tg = 0.f;
-  if (t < nb) {
-    const float d = mb - gbest.v, f = expf(d);
-    Sg = Sb * f; Tg = f > 0.f ? f * (Tb + d * Sb) : 0.f;
-  }
-  Sg = block_sum<NT>(Sg, sv);
-  Tg = block_sum<NT>(Tg, sv);
-  // ten largest of the nb * 10 candidates (up to 3 per thread)
-  float cc[CPT];
+// {max, arg-max, sum e^(x - max), sum e^(x - max) (x - max)} of some logits, and the same of two sets together.
+struct SoftStat { float m; int i; float S, T; };
+__device__ __forceinline__ SoftStat stat_rescaled(SoftStat a, const float m) {      // relative to another maximum, m >= a.m
+  const float d = a.m - m, f = expf(d);
+  a.T = f > 0.f ? f * (a.T + d * a.S) : 0.f;                                        // (nothing was there: 0, not 0 * -inf)
+  a.S = f > 0.f ? f * a.S : 0.f;
+  return a;
+}
+
+// LDS of the computation in one workgroup of NT threads.
+template <int NT>
+struct ClassifySmem {
+  SoftStat st[NT / 64];
+  alignas(16) float wtop[NT / 64 * 10];
+  alignas(16) float feat[12];
+  float top[10], sum[NT / 64 + 1];
+  int last;
+};
+
+// Position of candidate `me` in descending order among NC candidates: how many beat it (larger, or equal with a lower slot): a
+// permutation of 0 .. NC - 1 without a dependent cross-lane chain.
+template <int NC>
+__device__ __forceinline__ int rank_of(const float* cand, const int me, const float mine) {
+  float o[NC];
 #pragma unroll
-  for (int q = 0; q < CPT; ++q) {
-    const int ci = t + q * NT;                               // candidate ci = record ci / 10, slot ci % 10
-    cc[q] = -INFINITY;
-    if (ci < nb * 10) {
-      const int rb = ci / 10, sl = ci % 10;
-      const float2 p = ld_agent2(recs + (size_t)rb * CM_REC + 4 + (sl & ~1));
-      cc[q] = (sl & 1) ? p.y : p.x;
+  for (int j = 0; j < NC; ++j) o[j] = cand[j];            // all reads in flight at once (broadcasts)
+  int rank = 0;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) rank += (o[j] > mine || (o[j] == mine && j < me)) ? 1 : 0;
+  return rank;
+}
+
+// Last stage of the feature / classifier computation, run by ONE workgroup of NT threads over nb <= 64
+// records {max, arg-max, S, T relative to the record's max, its ten largest values} (16 floats each,
+// written with agent-scope stores by the workgroups that reduced the logits).  The first wavefront merges the statistics (a record
+// per lane) while the others pick the ten largest of the nb * 10 candidates; then the forced logit in closed
+// form, features, classifier, halt decision and the loop's bookkeeping words.  What bounds it is the chain: two selections and the
+// hand-off.  Workgroup-wide reductions one after another (a maximum, two sums, the selection; two barriers each, twice) took 10.3 us a
+// call at 32000 logits; with reductions inside wavefronts that meet behind one barrier 8.5.
+template <int NT>
+__device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, const float* recs, const int nb, const int force,
+                                                      const float xf, const ClfCoef& k, ClassifySmem<NT>& sm) {
+  constexpr int NW = NT / 64, NC = (NW - 1) * 10;
+  constexpr int CPT = (640 * 256 / NT + (NT - 64) - 1) / (NT - 64);          // at most 64 slices (65536 logits at NT = 256): 640 candidates
+  ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
+  const int t = threadIdx.x, wv = t >> 6;
+  float* top_s = sm.top;
+  float* feat_s = sm.feat;
+  if (wv == 0) {
+    SoftStat r{-INFINITY, 0x7fffffff, 0.f, 0.f};
+    if (t < nb) {
+      const float2 p0 = ld_agent2(recs + (size_t)t * CM_REC), p1 = ld_agent2(recs + (size_t)t * CM_REC + 2);
+      r = SoftStat{p0.x, __float_as_int(p0.y), p1.x, p1.y};
+    }
+    const VI best = wave_argmax(VI{r.m, r.i});
+    r = stat_rescaled(r, best.v);
+    const float S = wave_sum(r.S), T = wave_sum(r.T);
+    if (t == 0) sm.st[0] = SoftStat{best.v, best.i, S, T};
+  } else {
+    float cc[CPT];
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+      const int ci = t - 64 + q * (NT - 64);                 // candidate ci = record ci / 10, slot ci % 10
+      cc[q] = ci < nb * 10 ? ld_f1<true>(recs + (size_t)(ci / 10) * CM_REC + 4 + ci % 10) : -INFINITY;
+    }
+    wave_top10<CPT>(cc, sm.wtop + (wv - 1) * 10);
+  }
+  __syncthreads();
+  float mx = sm.st[0].m, Sg = sm.st[0].S, Tg = sm.st[0].T;
+  int best_i = sm.st[0].i;
+  if (t < NC) {
+    const float mine = sm.wtop[t];
+    const int rank = rank_of<NC>(sm.wtop, t, mine);
+    if (rank < 10) {
+      if (force < 0) feat_s[rank] = (mine == -INFINITY) ? 0.f : expf(mine - mx) / Sg;
+      else top_s[rank] = mine;
     }
   }
-  block_top10<NT, CPT>(cc, wtop, top_s);
-  float mx = gbest.v;
   if (force >= 0) {
+    __syncthreads();
     // raise logit[force] from x_f to M + 4: shift every term to the new maximum, take the old
     // contribution of x_f out and put the new one (e^0 = 1, with (x - max) = 0) in
-    const float mnew = gbest.v + 4.0f;
+    const float mnew = mx + 4.0f;
     const float sh = expf(-4.0f), ef = expf(xf - mnew);
     Tg = sh * (Tg - 4.0f * Sg) - (ef > 0.f ? ef * (xf - mnew) : 0.f);
     Sg = sh * Sg - ef + 1.0f;
@@ -2044,12 +2060,12 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
       for (int i = 0, o = 1; i < 10 && o < 10; ++i) if (i != drop) top_s[o++] = old[i];
       st_f1<true>(a.logits + force, mnew);
     }
-    mx = mnew; gbest.v = mnew; gbest.i = force;
+    mx = mnew; best_i = force;
     __syncthreads();
+    if (t < 10) feat_s[t] = (top_s[t] == -INFINITY) ? 0.f : expf(top_s[t] - mx) / Sg;
   }
-  if (t < 10) feat_s[t] = (top_s[t] == -INFINITY) ? 0.f : expf(top_s[t] - mx) / Sg;
-  if (t == 10) feat_s[10] = logf(Sg) - Tg / Sg;
-  if (t == 11) feat_s[11] = a.pos_feature;
+  if (t == NT - 1) feat_s[10] = logf(Sg) - Tg / Sg;
+  if (t == NT - 2) feat_s[11] = a.pos_feature;
   __syncthreads();
   float contrib = 0.f;
   if (a.clf_params && t < a.hidden) {
@@ -2058,7 +2074,8 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
     for (int i = 0; i < 12; ++i) acc += k.w1[i] * feat_s[i];
     contrib = fmaxf(acc, 0.f) * k.w2;
   }
-  const float z = block_sum<NT>(contrib, sv);
+  float z = wave_sum(contrib);
+  if (a.hidden > 64) z = block_sum<NT>(contrib, sm.sum);     // (up to 64 units: all in the first wavefront, which finishes)
   if (t == 0) {
     float score = __builtin_nanf("");
     uint32_t halt = a.force_halt ? 1u : 0u;
@@ -2069,7 +2086,7 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
     // reference lookahead: a token that differs from the known continuation ends the block and is
     // not part of it (bit 1 of halt)
     bool mismatch = false;
-    if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && gbest.i != ref; }
+    if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && best_i != ref; }
     if (mismatch) halt = 3u;
     // perplexity rule (App. F's rule-based baseline): the block's draft tokens so far have perplexity
     // exp(-(1/j) sum ln p_i), p_i the draft's probability of its own token (the largest one); above the
@@ -2083,18 +2100,18 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
       score = expf(sum / (float)(sl_before + 1));
       if (score > a.ppl_threshold) halt |= 1u;
     }
-    out->token = gbest.i;
+    out->token = best_i;
 #pragma unroll
     for (int i = 0; i < 12; ++i) out->feats[i] = feat_s[i];
     out->score = score; out->halt = halt; out->executed = 1u;
     if (!mismatch) {
-      if (a.token_next) *a.token_next = gbest.i;
-      if (a.block_slot) *a.block_slot = gbest.i;
+      if (a.token_next) *a.token_next = best_i;
+      if (a.block_slot) *a.block_slot = best_i;
       if (a.sl_count) __hip_atomic_store(a.sl_count, sl_before + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (a.gate && halt) __hip_atomic_store(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  return gbest.i;
+  return best_i;
 }
 
 // The same computation spread over ceil(V / (4 NT)) workgroups (used when the caller gives scratch
@@ -2108,13 +2125,9 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
 // COH: the logits were written by other workgroups of the same launch.
 template <int NT, bool COH = false>
 __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b, const int nb, const uint32_t halted) {
+  constexpr int NW = NT / 64;
   ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
-  __shared__ float sv[NT / 64 + 1];
-  __shared__ int si[NT / 64 + 1];
-  __shared__ float top_s[10];
-  __shared__ float wtop[NT / 64][10];
-  __shared__ float feat_s[12];
-  __shared__ int s_last;
+  __shared__ ClassifySmem<NT> sm;
   const int t = threadIdx.x, V = a.vocab;
   const float* x = a.logits;
   float* rec = a.scratch + 64 + (size_t)b * CM_REC;          // scratch[0] is the ticket counter
@@ -2149,34 +2162,43 @@ __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b,
     if (threadIdx.x == 0 && b == 0) out->executed = 0u;
     return -1;
   }
+  // every wavefront reduces its own 256 logits; the workgroup's record is merged from those behind one barrier
+  const int wv = t >> 6;
   VI mine; mine.v = -INFINITY; mine.i = 0x7fffffff;
 #pragma unroll
   for (int e = 0; e < 4; ++e) { VI y; y.v = r4[e]; y.i = idx + e; mine = vi_best(mine, y); }
-  const VI best = block_argmax<NT>(mine, sv, si);
+  const VI wb = wave_argmax(mine);
   float S = 0.f, T = 0.f;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float d = r4[e] - best.v, ex = expf(d);
+    const float d = r4[e] - wb.v, ex = r4[e] == -INFINITY ? 0.f : expf(d);
     S += ex; T += ex > 0.f ? ex * d : 0.f;
   }
-  S = block_sum<NT>(S, sv);
-  T = block_sum<NT>(T, sv);
-  // this workgroup's ten largest values
-  {
-    float c4[4] = {r4[0], r4[1], r4[2], r4[3]};
-    block_top10<NT, 4>(c4, wtop, top_s);
+  S = wave_sum(S); T = wave_sum(T);
+  if ((t & 63) == 0) sm.st[wv] = SoftStat{wb.v, wb.i, S, T};
+  wave_top10<4>(r4, sm.wtop + wv * 10);
+  __syncthreads();
+  if (t < NW * 10) {
+    const float v = sm.wtop[t];
+    const int rank = rank_of<NW * 10>(sm.wtop, t, v);
+    if (rank < 10) st_f1<true>(rec + 4 + rank, v);
   }
-  if (t == 0) { st_agent2(rec, best.v, __int_as_float(best.i)); st_agent2(rec + 2, S, T); }
-  if (t >= 2 && t < 7) st_agent2(rec + 2 * t, top_s[2 * t - 4], top_s[2 * t - 3]);
-  if (!last_arrival(reinterpret_cast<int*>(a.scratch), nb, &s_last)) return -1;
+  if (t == NT - 1) {
+    VI best{sm.st[0].m, sm.st[0].i};
+#pragma unroll
+    for (int w = 1; w < NW; ++w) best = vi_best(best, VI{sm.st[w].m, sm.st[w].i});
+    float Sg = 0.f, Tg = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { const SoftStat r = stat_rescaled(sm.st[w], best.v); Sg += r.S; Tg += r.T; }
+    st_agent2(rec, best.v, __int_as_float(best.i)); st_agent2(rec + 2, Sg, Tg);
+  }
+  if (!last_arrival(reinterpret_cast<int*>(a.scratch), nb, &sm.last)) return -1;
 
   ClfCoef k;
 #pragma unroll
   for (int i = 0; i < 12; ++i) k.w1[i] = w1[i];
   k.b1 = cb1; k.w2 = cw2; k.b2 = cb2;
-  // at most 64 slices (65536 logits at NT = 256): 640 candidates
-  constexpr int CPT = (640 * 256 / NT + NT - 1) / NT;
-  return classify_merge_finish<NT, CPT>(a, a.scratch + 64, nb, force, xf, k, sv, si, wtop, top_s, feat_s);
+  return classify_merge_finish<NT>(a, a.scratch + 64, nb, force, xf, k, sm);
 }
 
 __global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, const float* clf_params, const int32_t* force_token, uint32_t* gate, float* scratch,
