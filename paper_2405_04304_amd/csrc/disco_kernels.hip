@@ -2662,23 +2662,26 @@ hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
 // classifier training and evaluation (the step after the loop: features and labels in, parameters out)
 // ---------------------------------------------------------------------------------------------
 //
-// One workgroup of 16 wavefronts.  A unit of work is a tile of 16 examples: both products of a gradient step are
-// contractions over 16 (the 12 features, a constant 1 for b1, three zeros), so they run on the fp32 matrix instruction
-// 16x16x4.  Forward, D[example][unit] = F . W1^T: lane l holds unit l % 16 and the four examples 4 (l / 16) + v, so the
-// pre-sigmoid output is a weighted sum over the lanes of a row (DPP), the example's error comes back as four in-row
-// broadcasts, and the masked errors are already the A operand of the backward product G[unit][feature] = M^T . F whose
-// k index runs over l / 16.  Tiles are dealt round-robin to the wavefronts; their G (and the gradient of w2, one more sum
-// over the same lanes) are added up in wavefront order through LDS and every parameter is updated by the thread that
-// owns it: results do not depend on timing.  All arithmetic fp32 except the feature statistics (double).
-// What bounds it is the issue rate of one compute unit (a tile is 32 matrix and about 250 vector instructions, the update
-// of the parameters another 130 per wavefront, four wavefronts on a SIMD) and two workgroup barriers: 4.4 us a step at
-// 200 examples and 64 units.  The form before took one example after another (a workgroup-wide sum per example, about
-// 480 ns each): 38.4 ms for 400 such steps, 1.77 ms now.  More workgroups would put a hand-off between workgroups (about
-// 2.5 us) into every step.  More than 128 units do not fit the registers of sixteen wavefronts (33 go to scratch memory up to 1280
-// examples, 143 above): 50 steps over 200 examples with 256 units take 1.04 ms (7.28 before), 10 over 2560 1.70 ms (18.9).
+// One workgroup.  A unit of work is a tile of 16 examples, and both products of a gradient step are contractions over at most 16
+// (the 12 features, a constant 1 for b1, three zeros; 16 examples), so they run on the matrix instruction.  The fp32 form of it
+// would be most of a step (two products of 200 examples and 64 units: 1.7 us), so operands go in as sums of three bf16 (24 bits:
+// x = x0 + x1 + x2), and the products that matter at fp32 are taken: forward f0 w0 + f0 w1 + f1 w0 + f1 w1 + f0 w2 + f2 w0 (what is left
+// out is below 2^-25 of a term) as three instructions of K = 32, and backward mask . (e F) in three parts, where the mask is exact: two
+// instructions of K = 32, the second half empty.
+// Forward, D[example][unit]: lane l holds unit l % 16 and the examples 4 (l / 16) + v, so the pre-sigmoid output is a weighted sum over
+// the lanes of a row.  A wavefront takes TP tiles at a time, and the sums of its 4 TP values are merged on the way (every exchange step halves the
+// number of registers), which leaves every lane of a row with the finished output of an example of its own (TP = 4; with TP = 1 four lanes share one): the
+// sigmoid and the loss are computed once per example.  The errors come back as in-row broadcasts, and the masked activations are already the B
+// operand of the backward product G[feature][unit] = (e F)^T . mask, whose k index runs over l / 16.  The gradient of w2 needs no sum over
+// the examples: sum_n e_n relu(w . f_n) = w . G.  Tiles are dealt round-robin; the wavefronts' G are added up in wavefront order through LDS
+// and every parameter is updated by the thread that owns it: results do not depend on timing.  Everything else is fp32 but the feature
+// statistics (double).
+// What bounds it: the instructions of one compute unit and, between them, two barriers with their LDS round trips.  200 examples with 64
+// units take 2.0 us a step (5000 cycles: products and masks 1800 for the two wavefronts of a SIMD, sums and sigmoid 800, backward 900,
+// update 1100), 4.4 on the fp32 matrix instruction; 1000 examples 7.6 (14.7), 200 examples with 128 units 3.5 (10.3).  More workgroups
+// would put a hand-off between workgroups (about 2.5 us) into every step.  Features that are not numbers make all parameters and the loss NaN.
 
 constexpr int TRAIN_MAX_N = 2560;               // examples that fit in LDS (12 floats each)
-constexpr int TRAIN_NW = 16;
 
 // Workgroup barrier that orders LDS accesses only: __syncthreads also waits for the wavefront's stores to memory (the
 // loss of the step), a round trip of half a microsecond.
@@ -2686,168 +2689,251 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// HT: 16-unit tiles of the hidden layer; NMAX: examples that the LDS array holds; PW: tiles per reduction pass (all of
-// them in one pass where the LDS has room for 16 wavefronts' gradients beside the examples).
-template <int HT, int NMAX, int PW>
-__global__ __launch_bounds__(TRAIN_NW * 64) void k_clf_train(TrainArgs a) {
-  constexpr int NW = TRAIN_NW, NP = HT / PW;
-  constexpr bool KEEP = HT <= 4;                  // activations stay in registers between the two products (else: computed again)
-  static_assert(HT % PW == 0 && PW * 256 <= NW * 64 && NMAX % 16 == 0, "one owner thread per parameter and pass");
-  __shared__ float fs[NMAX * 12];                 // standardised examples
-  __shared__ f32x4 wB[HT][64];                    // [W1 | b1] as B operands: lane 16 (i % 4) + h % 16, component i / 4
-  __shared__ float w2s[2][HT * 16];               // this step's and the next step's w2
+// Two floats as sums of three bf16 each; a part holds the first float's in its low half.
+struct Bf16x3 { uint32_t p[3]; };
+__device__ __forceinline__ Bf16x3 split3(float a, float b) {
+  Bf16x3 s;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s.p[i] = pack_bf16(a, b);
+    a -= __uint_as_float(s.p[i] << 16); b -= __uint_as_float(s.p[i] & 0xffff0000u);
+  }
+  return s;
+}
+// max(x, 0), one instruction (fmaxf is two).  Not in assembly: what reads a matrix instruction's result must be visible to the compiler,
+// which puts the wait states in between.
+__device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
+// 1.0 (bf16) where an activation is positive, 0 where it is not: its bits as bf16 (none set only at 0 or below 2^-134) cut to one, times
+// 1.0's.  (The minimum in assembly: the compiler makes a comparison and a select of every half of the pair; the product is
+// left to it, since it has to know what a matrix instruction reads.)
+__device__ __forceinline__ uint32_t relu_mask(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+  uint32_t m = pack_bf16(a, b);
+  asm("v_pk_min_u16 %0, %0, %1" : "+v"(m) : "v"(0x00010001u));
+  return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, m) * (u16x2){0x3F80, 0x3F80}));
+}
+// own ? b : a of this lane plus the other of the two from the lane that CTRL names
+template <int CTRL>
+__device__ __forceinline__ float merge_halves(float a, float b, bool own) {
+  const float mine = own ? b : a, other = own ? a : b;
+  return mine + dpp_f<CTRL, 0xF>(0.f, other);
+}
+
+// HT: 16-unit tiles of the hidden layer; NW wavefronts; TP: example tiles per wavefront and round; PW: unit tiles per reduction
+// pass; NMAX: examples that the LDS array holds.  One round (NMAX = 16 NW TP): the examples' operands stay in registers.
+template <int HT, int NW, int TP, int PW, int NMAX>
+__global__ __launch_bounds__(NW * 64) void k_clf_train(TrainArgs a) {
+  constexpr int NP = HT / PW, ROUND = NW * TP;
+  constexpr bool ONE = NMAX == ROUND * 16, YS = NMAX <= TRAIN_MAX_N / 2;      // YS: room for the labels too
+  static_assert(HT % PW == 0 && PW <= NW && (TP == 1 || TP == 2 || TP == 4), "one owner thread per parameter and pass");
+  __shared__ __align__(16) float fs[NMAX * 12];   // standardised examples
+  __shared__ u32x4 wS[3][HT][2][16];              // [W1 | b1] in three parts: [unit tile][eight columns][unit]: reads without conflicts
+  __shared__ float w2s[HT * 16];
   __shared__ f32x4 red[NW][PW][64];
-  __shared__ float red2[NW][PW * 16];
-  __shared__ float red3[NW][2];
-  constexpr bool YS = NMAX <= TRAIN_MAX_N / 2;    // room for the labels too
+  __shared__ float2 red3[NW][64];
   __shared__ float ys[YS ? NMAX : 1];
-  __shared__ float mu_s[12], isd_s[12], b2_s;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 15, g = lane >> 4;
+  __shared__ float mu_s[16], isd_s[16], b2_s;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), col = lane & 15, g = lane >> 4;
   const int N = a.n, H = a.hidden, tiles = (N + 15) >> 4;
-  if (w < 12) {                                   // wavefront w: mean and deviation of feature w, in a fixed order
+  for (int f = w; f < 12; f += NW) {              // mean and deviation of a feature, in a fixed order
     double sum = 0.0;
-    for (int n = lane; n < N; n += 64) sum += (double)a.feats[(size_t)n * 12 + w];
+    for (int n = lane; n < N; n += 64) sum += (double)a.feats[(size_t)n * 12 + f];
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
     const double mu = sum / N;
     double var = 0.0;
-    for (int n = lane; n < N; n += 64) { const double x = (double)a.feats[(size_t)n * 12 + w] - mu; var += x * x; }
+    for (int n = lane; n < N; n += 64) { const double x = (double)a.feats[(size_t)n * 12 + f] - mu; var += x * x; }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) var += __shfl_xor(var, d);
     double sd = sqrt(var / N);
     if (sd < 1e-6) sd = 1e-6;
-    if (lane == 0) { mu_s[w] = (float)mu; isd_s[w] = (float)(1.0 / sd); }
+    if (lane == 0) { mu_s[f] = (float)mu; isd_s[f] = (float)(1.0 / sd); }
   }
   __syncthreads();
   for (int i = t; i < tiles * 16 * 12; i += NW * 64) fs[i] = i < N * 12 ? (a.feats[i] - mu_s[i % 12]) * isd_s[i % 12] : 0.f;
   if (YS) for (int i = t; i < tiles * 16; i += NW * 64) ys[i] = i < N ? (float)a.labels[i] : 0.f;
-  // the parameters this thread owns: of pass p, element t of the pass's G records (unit h, column i: 12 weights, then b1),
-  // and for t < 16 PW the w2 of unit (16 PW) p + t
-  float own[NP], own2[NP];
-  const int oi = (t >> 2) & 15;
-  auto own_h = [&](int p) { return (p * PW + (t >> 8)) * 16 + 4 * ((t >> 6) & 3) + (t & 3); };
+  // thread (w, lane) owns, of unit tile p PW + w, unit `col` and columns 4 g .. 4 g + 3 (12 weights, then b1), and a copy of its w2
+  float own[NP][4], own2[NP];
+  auto unit = [&](int p) { return (p * PW + w) * 16 + col; };
+  auto put_w = [&](int p) {
+    const Bf16x3 s0 = split3(own[p][0], own[p][1]), s1 = split3(own[p][2], own[p][3]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) reinterpret_cast<uint2*>(&wS[i][p * PW + w][g >> 1][col])[g & 1] = make_uint2(s0.p[i], s1.p[i]);
+    if (g == 0) w2s[unit(p)] = own2[p];
+  };
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    own[p] = 0.f; own2[p] = 0.f;
-    if (t < PW * 256) {
-      const int h = own_h(p);
-      if (h < H && oi < 12) own[p] = a.params[h * 12 + oi];
-      if (h < H && oi == 12) own[p] = a.params[H * 12 + h];
-      reinterpret_cast<float*>(&wB[h >> 4][(oi & 3) * 16 + (h & 15)])[oi >> 2] = own[p];
-    }
-    if (t < PW * 16) {
-      const int h = p * PW * 16 + t;
-      if (h < H) own2[p] = a.params[H * 13 + h];
-      w2s[0][h] = own2[p];
+    if (w < PW) {
+      const int h = unit(p);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 4 * g + v;
+        own[p][v] = h < H && i < 12 ? a.params[h * 12 + i] : (h < H && i == 12 ? a.params[H * 12 + h] : 0.f);
+      }
+      own2[p] = h < H ? a.params[H * 13 + h] : 0.f;
+      put_w(p);
     }
   }
   float b2 = a.params[H * 14];
   if (t == 0) b2_s = b2;
   __syncthreads();
   const float inv_n = 1.0f / (float)N;
-  int cur = 0;
-  for (int ep = 0; ep < a.epochs; ++ep, cur ^= 1) {
+  // operands of the examples of tile q of a round that begins at tile `base`
+  struct Fwd { u32x4 p0, p1, p02; };              // A operands: f0 | f0, f1 | f1, f0 | f2 (16 columns each)
+  struct Bwd { float x[4]; };                     // column `col` of examples 4 g + v
+  auto tile_of = [&](int base, int q) { return base + w + NW * q; };
+  auto fwd_operand = [&](int tile, Fwd& f) {
+    const float* row = fs + (min(tile, tiles - 1) * 16 + col) * 12 + ((g & 1) ? 8 : 0);
+    const float4 x = *reinterpret_cast<const float4*>(row), y4 = *reinterpret_cast<const float4*>(row + ((g & 1) ? 0 : 4));
+    const float4 y = (g & 1) ? make_float4(1.f, 0.f, 0.f, 0.f) : y4;
+    const Bf16x3 s[4] = {split3(x.x, x.y), split3(x.z, x.w), split3(y.x, y.y), split3(y.z, y.w)};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { f.p0[i] = s[i].p[0]; f.p1[i] = s[i].p[1]; f.p02[i] = g < 2 ? s[i].p[0] : s[i].p[2]; }
+  };
+  auto bwd_operand = [&](int tile, Bwd& f) {
+    const int n0 = min(tile, tiles - 1) * 16 + 4 * g;
+    float x[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = fs[(n0 + v) * 12 + min(col, 11)];
+    asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));            // (loads for every lane: no branch around them)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f.x[v] = col < 12 ? x[v] : (col == 12 ? 1.f : 0.f);
+  };
+  const int q_mine = col & (TP - 1), v_mine = col >> 2;           // this lane's example of a round: tile q_mine, row 4 g + v_mine
+  const bool counts = TP == 4 || (TP == 2 ? (col & 2) == 0 : (col & 3) == 0);   // one lane per example
+  Fwd fk[ONE ? TP : 1];
+  Bwd bk[ONE ? TP : 1];
+  if constexpr (ONE) {
+#pragma unroll
+    for (int q = 0; q < TP; ++q) { fwd_operand(tile_of(0, q), fk[q]); bwd_operand(tile_of(0, q), bk[q]); }
+  }
+  for (int ep = 0; ep < a.epochs; ++ep) {
     f32x4 G[HT];
-    float gw2[HT], gb2 = 0.f, loss = 0.f;
+    float gb2 = 0.f, loss = 0.f;
 #pragma unroll
-    for (int r = 0; r < HT; ++r) { G[r] = f32x4{0.f, 0.f, 0.f, 0.f}; gw2[r] = 0.f; }
+    for (int r = 0; r < HT; ++r) G[r] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float bias2 = b2_s;
-    for (int tile = w; tile < tiles; tile += NW) {
-      const int n0 = tile * 16, mine = n0 + 4 * g + (lane & 3);        // the example whose error this lane forms
+    for (int base = 0; base + w < tiles; base += ROUND) {
+      const int mine = (base + w + NW * q_mine) * 16 + 4 * g + v_mine;
       const bool live = mine < N;
-      const float y = YS ? ys[mine] : (float)a.labels[live ? mine : N - 1];
-      float fa[4], fb[4];
+      const float y = YS ? ys[live ? mine : 0] : (float)a.labels[live ? mine : 0];
+      u32x4 m01[HT], m23[HT];                     // masks of rows 0, 1 and 2, 3 (component q)
+      float z[TP][4];
 #pragma unroll
-      for (int j = 0; j < 3; ++j) fa[j] = fs[(n0 + col) * 12 + 4 * j + g];
-      fa[3] = (g == 0 && n0 + col < N) ? 1.f : 0.f;
+      for (int q = 0; q < TP; ++q)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        fb[v] = fs[(n0 + 4 * g + v) * 12 + min(col, 11)];
-        asm volatile("" : "+v"(fb[v]));           // (a load for every lane: no branch around it)
-        fb[v] = col < 12 ? fb[v] : (col == 12 ? 1.f : 0.f);
+        for (int v = 0; v < 4; ++v) z[q][v] = 0.f;
+      Fwd ft[TP];
+#pragma unroll
+      for (int q = 0; q < TP; ++q) {
+        if constexpr (ONE) ft[q] = fk[q];
+        else fwd_operand(tile_of(base, q), ft[q]);
       }
-      auto forward = [&](int r) {
-        f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f};
-        const f32x4 wv = wB[r][lane];
+      // the products of several unit tiles go out before the first result is read: an instruction's result takes longer than its issue
+      constexpr int RB = HT < 8 / TP ? HT : 8 / TP;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) p = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j], wv[j], p, 0, 0, 0);
+      for (int r0 = 0; r0 < HT; r0 += RB) {
+        f32x4 p[RB][TP];
+        float w2[RB];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) p[v] = fmaxf(p[v], 0.f);
-        return p;
-      };
-      f32x4 act[KEEP ? HT : 1], z = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int rr = 0; rr < RB; ++rr) {
+          const int r = r0 + rr;
+          const u32x4 w01 = wS[g >> 1][r][g & 1][col], w20 = wS[g < 2 ? 2 : 0][r][g & 1][col];
+          w2[rr] = w2s[r * 16 + col];
 #pragma unroll
-      for (int r = 0; r < HT; ++r) {
-        const f32x4 p = forward(r);
-        const float w2 = w2s[cur][r * 16 + col];
+          for (int q = 0; q < TP; ++q) {
+            p[rr][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ft[q].p02), as_bf16x8(w20), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            p[rr][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ft[q].p1), as_bf16x8(w01), p[rr][q], 0, 0, 0);
+            p[rr][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ft[q].p0), as_bf16x8(w01), p[rr][q], 0, 0, 0);
+          }
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 3 * RB * TP, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 15 * RB * TP, 0);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) z[v] += w2 * p[v];
-        if (KEEP) act[r] = p;
+        for (int rr = 0; rr < RB; ++rr)
+#pragma unroll
+          for (int q = 0; q < TP; ++q) {
+            f32x4& x = p[rr][q];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) { x[v] = relu(x[v]); z[q][v] += w2[rr] * x[v]; }
+            m01[r0 + rr][q] = relu_mask(x[0], x[1]); m23[r0 + rr][q] = relu_mask(x[2], x[3]);
+          }
       }
+      float s[TP];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        z[v] += dpp_f<DPP_QUAD_XOR1, 0xF>(0.f, z[v]);
-        z[v] += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, z[v]);
-        z[v] += dpp_f<DPP_ROW_HALF_MIRROR, 0xF>(0.f, z[v]);
-        z[v] += dpp_f<DPP_ROW_MIRROR, 0xF>(0.f, z[v]);
+      for (int q = 0; q < TP; ++q) {
+        const float r02 = merge_halves<DPP_ROW_ROR8>(z[q][0], z[q][2], (col & 8) != 0), r13 = merge_halves<DPP_ROW_ROR8>(z[q][1], z[q][3], (col & 8) != 0);
+        s[q] = merge_halves<DPP_ROW_HALF_MIRROR>(r02, r13, (col & 4) != 0);       // lanes of bank v: row 4 g + v
       }
-      const int vm = lane & 3;
-      const float zz = (vm == 0 ? z[0] : vm == 1 ? z[1] : vm == 2 ? z[2] : z[3]) + bias2;
+      float zz;
+      if constexpr (TP == 4) {
+        const float s02 = merge_halves<DPP_QUAD_XOR2>(s[0], s[2], (col & 2) != 0), s13 = merge_halves<DPP_QUAD_XOR2>(s[1], s[3], (col & 2) != 0);
+        zz = merge_halves<DPP_QUAD_XOR1>(s02, s13, (col & 1) != 0);
+      } else {
+        if constexpr (TP == 2) zz = merge_halves<DPP_QUAD_XOR1>(s[0], s[1], (col & 1) != 0);
+        else zz = s[0] + dpp_f<DPP_QUAD_XOR1, 0xF>(0.f, s[0]);
+        zz += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, zz);
+      }
+      zz += bias2;
       // sigmoid(z) and log(1 + e^-|z|) from one exponential; the logarithm's argument rounds to u, which is put right by
       // the factor E / (u - 1) (the library's log1pf was a third of the step's instructions)
       const float E = expf(-fabsf(zz)), u = 1.0f + E, ru = 1.0f / u, du = u - 1.0f;
       float dz = ((zz >= 0.f ? ru : E * ru) - y) * inv_n;
       dz = live ? dz : 0.f;
-      const float term = fmaxf(zz, 0.f) - zz * y + (du == 0.f ? E : logf(u) * (E / du));
-      gb2 += col < 4 ? dz : 0.f;
-      loss += live && col < 4 ? term : 0.f;
-      const float e[4] = {dpp_f<0x00, 0xF>(dz, dz), dpp_f<0x55, 0xF>(dz, dz), dpp_f<0xAA, 0xF>(dz, dz), dpp_f<0xFF, 0xF>(dz, dz)};
+      const float e4[4][4] = {{dpp_f<0x150, 0xF>(0.f, dz), dpp_f<0x154, 0xF>(0.f, dz), dpp_f<0x158, 0xF>(0.f, dz), dpp_f<0x15C, 0xF>(0.f, dz)},
+                              {dpp_f<0x151, 0xF>(0.f, dz), dpp_f<0x155, 0xF>(0.f, dz), dpp_f<0x159, 0xF>(0.f, dz), dpp_f<0x15D, 0xF>(0.f, dz)},
+                              {dpp_f<0x152, 0xF>(0.f, dz), dpp_f<0x156, 0xF>(0.f, dz), dpp_f<0x15A, 0xF>(0.f, dz), dpp_f<0x15E, 0xF>(0.f, dz)},
+                              {dpp_f<0x153, 0xF>(0.f, dz), dpp_f<0x157, 0xF>(0.f, dz), dpp_f<0x15B, 0xF>(0.f, dz), dpp_f<0x15F, 0xF>(0.f, dz)}};
 #pragma unroll
-      for (int r = 0; r < HT; ++r) {
-        const f32x4 p = KEEP ? act[KEEP ? r : 0] : forward(r);
+      for (int q = 0; q < TP; ++q) {
+        Bwd bt;
+        if constexpr (ONE) bt = bk[q];
+        else bwd_operand(tile_of(base, q), bt);
+        const Bf16x3 s0 = split3(e4[q][0] * bt.x[0], e4[q][1] * bt.x[1]), s1 = split3(e4[q][2] * bt.x[2], e4[q][3] * bt.x[3]);
+        const u32x4 x01 = {s0.p[0], s1.p[0], s0.p[1], s1.p[1]};
+        const u32x4 x2 = {s0.p[2], s1.p[2], 0u, 0u};
+        // one opcode for all of them: the accumulator is passed on only between like instructions (16x16x16 products among them
+        // gave wrong sums where two on one accumulator stood close together)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          gw2[r] += e[v] * p[v];
-          G[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[v] > 0.f ? e[v] : 0.f, fb[v], G[r], 0, 0, 0);
+        for (int r = 0; r < HT; ++r) {
+          const u32x4 mk = {m01[r][q], m23[r][q], m01[r][q], m23[r][q]};
+          G[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x2), as_bf16x8(mk), G[r], 0, 0, 0);
+          G[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x01), as_bf16x8(mk), G[r], 0, 0, 0);
         }
       }
+      // (behind the products, whose results are not read yet)
+      const float term = fmaxf(zz, 0.f) - zz * y + (du == 0.f ? E : logf(u) * (E / du));
+      gb2 += counts ? dz : 0.f;
+      loss += live && counts ? term : 0.f;
     }
-    gb2 = wave_sum(gb2); loss = wave_sum(loss);
+    red3[w][lane] = make_float2(gb2, loss);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       if (p > 0) lds_barrier();                   // the pass before has been read
 #pragma unroll
-      for (int q = 0; q < PW; ++q) {
-        red[w][q][lane] = G[p * PW + q];
-        red2[w][q * 16 + col] = row4_sum(gw2[p * PW + q]);   // four lanes, one value
-      }
-      if (p == 0 && lane == 0) { red3[w][0] = gb2; red3[w][1] = loss; }
+      for (int q = 0; q < PW; ++q) red[w][q][lane] = G[p * PW + q];
       lds_barrier();
-      if (t < PW * 256) {
-        const float* rp = reinterpret_cast<const float*>(&red[0][0][0]) + t;
-        float s = 0.f;
+      if (w < PW) {
+        f32x4 s = red[0][w][lane];
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) s += rp[ww * PW * 256];
-        const int h = own_h(p);
-        if (h < H && oi < 13) {
-          own[p] -= a.lr * (s * w2s[cur][h]);
-          reinterpret_cast<float*>(&wB[h >> 4][(oi & 3) * 16 + (h & 15)])[oi >> 2] = own[p];
-        }
-      }
-      if (t < PW * 16) {
-        float s = 0.f;
+        for (int ww = 1; ww < NW; ++ww) s += red[ww][w][lane];
+        const float lw2 = a.lr * own2[p];
+        const float gw2 = row4_sum((own[p][0] * s[0] + own[p][1] * s[1]) + (own[p][2] * s[2] + own[p][3] * s[3]));
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) s += red2[ww][t];
-        own2[p] -= a.lr * s;
-        w2s[cur ^ 1][p * PW * 16 + t] = own2[p];
+        for (int v = 0; v < 4; ++v) own[p][v] -= lw2 * s[v];
+        own2[p] -= a.lr * gw2;
+        put_w(p);
       }
-      if (p == 0 && t == NW * 64 - 1) {           // the last wavefront: in most shapes it owns the fewest live parameters
+      if (p == NP - 1 && w == NW - 1) {           // the last wavefront: with fewer unit tiles than wavefronts it owns no weights
         float sb = 0.f, sl = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) { sb += red3[ww][0]; sl += red3[ww][1]; }
+        for (int ww = 0; ww < NW; ++ww) { const float2 x = red3[ww][lane]; sb += x.x; sl += x.y; }
+        sb = wave_sum(sb); sl = wave_sum(sl);
         b2 -= a.lr * sb;
-        b2_s = b2;
-        if (a.loss) a.loss[ep] = sl * inv_n;
+        if (lane == 0) {
+          b2_s = b2;
+          if (a.loss) a.loss[ep] = sl * inv_n;
+        }
       }
     }
     lds_barrier();
@@ -2855,36 +2941,53 @@ __global__ __launch_bounds__(TRAIN_NW * 64) void k_clf_train(TrainArgs a) {
   // fold the standardisation into W1 and b1: the classifier consumes raw features
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    if (t < PW * 256) {
-      const int h = own_h(p);
-      if (h < H && oi < 12) a.params[h * 12 + oi] = own[p] * isd_s[oi];
-    }
-    if (t < PW * 16 && p * PW * 16 + t < H) a.params[H * 13 + p * PW * 16 + t] = own2[p];
-  }
-  if (t < H) {
-    float shift = 0.f;
+    if (w < PW) {
+      const int h = unit(p);
+      float shift = 0.f;
+      if (g < 3) {
 #pragma unroll
-    for (int i = 0; i < 12; ++i) shift += reinterpret_cast<const float*>(&wB[t >> 4][(i & 3) * 16 + (t & 15)])[i >> 2] * isd_s[i] * mu_s[i];
-    a.params[H * 12 + t] = reinterpret_cast<const float*>(&wB[t >> 4][t & 15])[3] - shift;
+        for (int v = 0; v < 4; ++v) shift += own[p][v] * isd_s[4 * g + v] * mu_s[4 * g + v];
+      }
+      shift = row4_sum(shift);
+      if (h < H) {
+        if (g < 3) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) a.params[h * 12 + 4 * g + v] = own[p][v] * isd_s[4 * g + v];
+        } else {
+          a.params[H * 12 + h] = own[p][0] - shift;
+          a.params[H * 13 + h] = own2[p];
+        }
+      }
+    }
   }
   if (t == NW * 64 - 1) a.params[H * 14] = b2;
 }
 
-template <int HT, int PW>
+// Shapes by the number of examples.  Up to 64: four wavefronts, a tile each; 128: eight; 256: eight with two tiles each (of 16 wavefronts with one
+// tile the update waits longer than the shared sigmoids save: 2.07 us a step against 2.32 at 200 examples and 64 units; four
+// wavefronts with four tiles 2.33).  Beyond that rounds of 32 tiles (16 with more than 64 units, whose masks take the registers), over
+// examples that are split anew in every step.  More than 128 units: four wavefronts, 512 registers each.
+template <int HT>
 static void launch_clf_train_ht(const TrainArgs& a, hipStream_t s) {
-  if (a.n <= TRAIN_MAX_N / 2) hipLaunchKernelGGL((k_clf_train<HT, TRAIN_MAX_N / 2, PW>), dim3(1), dim3(TRAIN_NW * 64), 0, s, a);
-  else hipLaunchKernelGGL((k_clf_train<HT, TRAIN_MAX_N, 1>), dim3(1), dim3(TRAIN_NW * 64), 0, s, a);
+  constexpr int NW = HT > 8 ? 4 : 8, TP = HT > 4 ? 2 : 4, PW = HT > NW ? NW : HT, P4 = HT > 4 ? 4 : HT, PWL = HT > 8 ? 1 : (HT > 2 ? 2 : HT);
+  if (a.n <= 64) { hipLaunchKernelGGL((k_clf_train<HT, 4, 1, P4, 64>), dim3(1), dim3(256), 0, s, a); return; }
+  if constexpr (HT <= 8) {
+    if (a.n <= 128) { hipLaunchKernelGGL((k_clf_train<HT, 8, 1, HT, 128>), dim3(1), dim3(512), 0, s, a); return; }
+    if (a.n <= 256) { hipLaunchKernelGGL((k_clf_train<HT, 8, 2, HT, 256>), dim3(1), dim3(512), 0, s, a); return; }
+  }
+  if (a.n <= TRAIN_MAX_N / 2) hipLaunchKernelGGL((k_clf_train<HT, NW, TP, PW, TRAIN_MAX_N / 2>), dim3(1), dim3(NW * 64), 0, s, a);
+  else hipLaunchKernelGGL((k_clf_train<HT, NW, TP, PWL, TRAIN_MAX_N>), dim3(1), dim3(NW * 64), 0, s, a);
 }
 
 hipError_t launch_clf_train(const TrainArgs& a, hipStream_t s) {
   if (a.n < 1 || a.n > TRAIN_MAX_N || a.hidden < 1 || a.hidden > 256 || a.epochs < 0) return hipErrorInvalidValue;
-  if (a.hidden <= 32) launch_clf_train_ht<2, 2>(a, s);
-  else if (a.hidden <= 64) launch_clf_train_ht<4, 4>(a, s);
-  else if (a.hidden <= 128) launch_clf_train_ht<8, 4>(a, s);
-  else launch_clf_train_ht<16, 4>(a, s);
+  if (a.hidden <= 16) launch_clf_train_ht<1>(a, s);
+  else if (a.hidden <= 32) launch_clf_train_ht<2>(a, s);
+  else if (a.hidden <= 64) launch_clf_train_ht<4>(a, s);
+  else if (a.hidden <= 128) launch_clf_train_ht<8>(a, s);
+  else launch_clf_train_ht<16>(a, s);
   return hipGetLastError();
 }
-
 // Scores of given feature vectors and the confusion counts of "accepted iff C >= tau" against the
 // labels: counts[0..3] = true positives, false positives, false negatives, true negatives.
 // The parameters go to LDS once per workgroup and four threads share an example's hidden units (a quarter each, added in

@@ -165,3 +165,10 @@ def test_label_run_training_and_trained_halting():
     static10 = O.spec_decode(ot, od, trained, prompt, n_new, {"mode": "static", "gamma": 10}, force=force)
     assert orc["n_draft_forwards"] < 0.5 * static10["n_draft_forwards"]
     assert orc["n_iterations"] <= 1.15 * static10["n_iterations"]
+
+
+@pytest.mark.parametrize("n,hidden", [(64, 16), (65, 17), (128, 128), (129, 64), (256, 129), (257, 16), (1000, 200), (1280, 128), (2560, 16)])
+def test_train_shape_edges_match_oracle(n, hidden):
+    """One to four tiles of examples per wavefront, operands in registers up to 256 examples and split anew in every step beyond,
+    one reduction pass or several: the edges between those shapes, at the bars of the tests above."""
+    test_train_tile_edges_match_oracle(n, hidden)
