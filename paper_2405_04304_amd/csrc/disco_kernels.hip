@@ -14,6 +14,7 @@
 //   * paged KV: [layer][physical page][K | V][kv head] blocks of page_tokens x d_head bf16; a K block
 //     is [token][d_head], a V block is transposed, [d_head][token] (see the attention kernel).
 #include "disco_internal.h"
+#include <type_traits>
 
 #include <mutex>
 
@@ -1244,20 +1245,23 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
   // the first step's cache loads go out ahead of the q loads; later steps' loads are in flight during
   // the arithmetic of the step before
   constexpr int STEP = NWV * WKEYS;
+  constexpr bool WAITS = !std::is_same<Hook, NoHook>::value;     // there is a wait to fill: two steps' loads go out before it
   int base = s0 + w * WKEYS;
-  const bool early = base + WKEYS <= safe_end;
-  if (base < s1 && early) aw.issue(r0, base);
+  const bool early0 = base + WKEYS <= safe_end, early1 = WAITS && base + STEP + WKEYS <= safe_end;
+  if (base < s1 && early0) aw.issue(r0, base);
+  if (base + STEP < s1 && early1) aw.issue(r1, base + STEP);
   hook();
-  if (base < s1 && !early) aw.issue(r0, base);
+  if (base < s1 && !early0) aw.issue(r0, base);
   aw.load_q(head);
   if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
+  if (base + STEP < s1 && !early1) aw.issue(r1, base + STEP);
   while (base < s1) {
-    if (base + STEP < s1) aw.issue(r1, base + STEP);
     aw.step(r0, base);
+    if (base + 2 * STEP < s1) aw.issue(r0, base + 2 * STEP);
     base += STEP;
     if (base >= s1) break;
-    if (base + STEP < s1) aw.issue(r0, base + STEP);
     aw.step(r1, base);
+    if (base + 2 * STEP < s1) aw.issue(r1, base + 2 * STEP);
     base += STEP;
   }
 
@@ -1348,57 +1352,73 @@ __global__ __launch_bounds__(512) void k_attn_partial(ATTN_EARLY, AttnArgs a) {
   attn_range<DH, 8>(a, blockIdx.x, blockIdx.y, sm, gate_request(a.gate));   // 1.3 % of a 13B verification block against four)
 }
 
-// Short contexts: one workgroup of eight wavefronts takes a whole head (256 positions per step, the
-// loads of step i + 1 in flight during the arithmetic of step i), merges its wavefronts through LDS
-// and writes the O-projection panels itself: no partial records, no hand-off between workgroups.
-template <int DH>
-__device__ __forceinline__ void attn_whole_head(const AttnArgs& a, const int head, const uint32_t halted = 0u) {
-  constexpr int CT = DH / 16, NWV = 8, WKEYS = 32, STEP = NWV * WKEYS;
-  __shared__ f32x4 o_s[NWV][CT][64];
-  __shared__ float m_s[NWV][16], l_s[NWV][16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int j = lane & 15, g = lane >> 4;
-  const int total = a.pos0 + a.M;
-  AttnWave<DH> aw(a, head, total);
-  typename AttnWave<DH>::Raw r0, r1;
-  int base = w * WKEYS;
-  if (base < total) aw.issue(r0, base);
-  aw.load_q(head);
-  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written yet
-  while (base < total) {
-    if (base + STEP < total) aw.issue(r1, base + STEP);
-    aw.step(r0, base);
-    base += STEP;
-    if (base >= total) break;
-    if (base + STEP < total) aw.issue(r0, base + STEP);
-    aw.step(r1, base);
-    base += STEP;
+// Whole head: one workgroup of eight wavefronts takes all positions of a head (256 per step), merges its wavefronts through LDS and
+// writes the O-projection panels itself: no partial records, no hand-off between workgroups.  NR steps' loads are in flight at a
+// time.  request() asks for the first NR steps as far as they lie below safe_end and may run long before run().
+template <int DH, int NR, bool QCOH = false>
+struct AttnWhole {
+  static constexpr int CT = DH / 16, NWV = 8, WKEYS = 32, STEP = NWV * WKEYS;
+  AttnWave<DH, QCOH> aw;
+  typename AttnWave<DH, QCOH>::Raw r[NR];
+  int head, first;
+  __device__ __forceinline__ AttnWhole(const AttnArgs& a, int head_) : aw(a, head_, -1), head(head_), first((int)(threadIdx.x >> 6) * WKEYS) {}
+  __device__ __forceinline__ void request(const int safe_end) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (first + i * STEP + WKEYS <= safe_end) aw.issue(r[i], first + i * STEP);
   }
+  // `requested`: the safe_end that request() was given
+  __device__ __forceinline__ void run(AttnSmem<DH, NWV>& sm, const int requested, const uint32_t halted) {
+    const AttnArgs& a = aw.a;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, j = lane & 15, g = lane >> 4, total = aw.total;
 #pragma unroll
-  for (int c = 0; c < CT; ++c) o_s[w][c][lane] = aw.O[c];
-  if (g == 0) { m_s[w][j] = aw.m_run; l_s[w][j] = aw.l_run; }
-  __syncthreads();
-  if (w >= CT || j >= a.M) return;                               // wavefront w finishes channel tile w
-  float mm = m_s[0][j];
+    for (int i = 0; i < NR; ++i) {
+      const int base = first + i * STEP;
+      if (base + WKEYS > requested && base < total) aw.issue(r[i], base);
+    }
+    aw.load_q(head);
+    if (flag_set(halted)) return;                 // uniform over the launch; nothing has been written yet
+    for (int b0 = first; b0 < total; b0 += NR * STEP) {
 #pragma unroll
-  for (int ww = 1; ww < NWV; ++ww) mm = fmaxf(mm, m_s[ww][j]);
-  float ll = 0.f;
-  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < NR; ++i) {
+        const int base = b0 + i * STEP;
+        if (base < total) {
+          aw.step(r[i], base);
+          if (base + NR * STEP < total) aw.issue(r[i], base + NR * STEP);
+        }
+      }
+    }
+    __syncthreads();                              // the phase before has left the buffers
 #pragma unroll
-  for (int ww = 0; ww < NWV; ++ww) {                             // fixed order: deterministic
-    const float f = expf(m_s[ww][j] - mm);
-    ll += l_s[ww][j] * f;
-    o += o_s[ww][w][lane] * f;
+    for (int c = 0; c < CT; ++c) sm.o_s[w][c][lane] = aw.O[c];
+    if (g == 0) { sm.m_s[w][j] = aw.m_run; sm.l_s[w][j] = aw.l_run; }
+    __syncthreads();
+    if (w >= CT || j >= a.M) return;              // wavefront w finishes channel tile w
+    float mm = sm.m_s[0][j];
+#pragma unroll
+    for (int ww = 1; ww < NWV; ++ww) mm = fmaxf(mm, sm.m_s[ww][j]);
+    float ll = 0.f;
+    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ww = 0; ww < NWV; ++ww) {            // fixed order: deterministic
+      const float f = expf(sm.m_s[ww][j] - mm);
+      ll += sm.l_s[ww][j] * f;
+      o += sm.o_s[ww][w][lane] * f;
+    }
+    const float inv = 1.0f / ll;
+    const float out4[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
+    xpack_store4(a.Xout, (a.nq * DH) >> 5, a.M, j, head * DH + w * 16 + 4 * g, out4);
   }
-  const float inv = 1.0f / ll;
-  const float out4[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-  xpack_store4(a.Xout, (a.nq * DH) >> 5, a.M, j, head * DH + w * 16 + 4 * g, out4);
-}
+};
 
 template <int DH>
 __global__ __launch_bounds__(512) void k_attn_head(ATTN_EARLY, AttnArgs a) {
   ATTN_EARLY_SET(a);
-  attn_whole_head<DH>(a, blockIdx.x, gate_request(a.gate));
+  __shared__ AttnSmem<DH, 8> sm;
+  AttnWhole<DH, 2> at(a, blockIdx.x);
+  const uint32_t halted = gate_request(a.gate);
+  at.request(0x7fffff00);
+  at.run(sm, 0x7fffff00, halted);
 }
 
 // Prompt pass: workgroup = (query head, two consecutive groups of 16 prompt tokens).  Group r sits at positions
@@ -3496,26 +3516,33 @@ hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, flo
 
 
 // ---------------------------------------------------------------------------------------------
-// QKV projection and attention of one layer in ONE launch (models whose heads all have their own K / V)
+// QKV projection and attention of one layer in ONE launch
 // ---------------------------------------------------------------------------------------------
 //
-// The attention of head h needs only the 3 d_head rows of the QKV projection that belong to h, so the dependency
-// between the two phases is per head, not grid-wide.  The launch has the QKV projection's workgroups, dealt so that
-// the G = 3 d_head / (16 RT) workgroups holding the q, K and V rows of one head are neighbours.  Each finishes its
-// rows (rotary, query rows, cache entries: write-through stores), adds 1 to the head's counter, and then acts as
-// range `j` of the head's attention: it waits until the counter shows G (bounded: after `limit` polls it sets the
+// The attention of a head needs only the projection rows of its queries, keys and values, so the dependency
+// between the two phases is per head, not grid-wide.  A projection workgroup finishes its
+// rows (rotary, query rows, cache entries: write-through stores) and adds 1 to the counter of every head that reads them: its own,
+// or all the query heads of a K / V head.  An attention workgroup waits until the counter shows all of its head's
+// (bounded: after `limit` polls it sets the
 // abort word and goes on with unusable data; the LM head then stores NaN logits and the arg-max and loop-finish
 // kernels turn a set abort word into -1 outputs), with its first cache loads already in flight where they cannot touch a 128-byte line that the
-// head's other workgroups are still writing.  The head's ranges are merged by the last one to finish, as in the
-// stand-alone attention kernel; that workgroup also zeroes the head's counter for the next launch.  Nobody waits
-// before it has signalled, so the launch completes whenever all its workgroups are resident at once; the launcher
-// checks that they fit.  The counters are 256 bytes apart.
+// projection is still writing.  The head's ranges are merged by the last one to finish, as in the
+// stand-alone attention kernel; that workgroup also zeroes the head's counter for the next launch.  The counters are 256 bytes apart.
+//
+// OWN: the attention has workgroups of its own, numbered behind the projection's; two steps of their cache entries arrive while the
+// projection runs.  Otherwise (the projection's workgroups fill the chip: one per compute unit) the workgroups of a head are neighbours and become
+// the ranges of its attention when they have counted themselves in.  Either way nobody waits before it has signalled, so the
+// launch completes whenever all its workgroups are resident at once; the launcher checks that they fit.
+// Two layers, 6 tokens, us a pass (OWN / the other form / separate launches): 68M draft at 640 tokens 67.1 / 68.1 / 69.4, at 2475
+// 72.5 / 75.3 / 74; multi-query draft at 1300 75.1 / - / 77.6; 16 heads on 4 K / V heads at 2475 130.2 / - / 134.8; 13B at 640 - / 301.0 /
+// 303.4, at 40 - / 298.2 / 293.0 (so up to 256 positions it takes the separate launches).
 constexpr int QA_READY_SLOT = QKV_ATTN_READY_SLOT;   // ints between two heads' counters
 
 struct HeadWaitHook {
   int* ready; int n; unsigned* abort_word; int limit;   // limit: polls (each a memory round trip, about 1 us) before giving up
+  uint32_t halted;                                // a halted step's projection counts nobody in
   __device__ __forceinline__ void operator()() const {
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && !flag_set(halted)) {
       int spins = 0;
       if (limit < 0) __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       while (limit >= 0 && __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) {
@@ -3531,28 +3558,54 @@ struct HeadWaitHook {
   }
 };
 
-template <int P, int RT, int U, int DH>
+// LN: the model's norms are LayerNorms.  The leading arguments: see k_gemm; heads: query heads + 65536 * K / V heads.
+template <int P, int RT, int U, int DH, bool LN, bool OWN>
 __global__ __launch_bounds__(512) void k_qkv_attn(const bf16_t* W, const bf16_t* X, const uint32_t* gate, const float* ssq, int KT, int grp, int n_ssq,
                                                   int M, int heads, int pos0, GemmArgs g, AttnArgs a, int* ready, unsigned* abort_word, int safe_end, int limit) {
-  g.W = W; g.X = X; g.gate = gate; g.ssq = ssq; g.KT = KT; g.grp = grp; g.n_ssq = n_ssq; g.M = M; a.M = M; g.nq = heads; g.nkv = heads;
-  a.nq = heads; a.nkv = heads; g.pos0 = pos0; a.pos0 = pos0;
-  constexpr int UH = DH / (16 * RT), G = 3 * UH;   // workgroups per q / K / V part of a head, per head
+  g.W = W; g.X = X; g.gate = gate; g.ssq = ssq; g.KT = KT; g.grp = grp; g.n_ssq = n_ssq; g.M = M; a.M = M; g.pos0 = pos0; a.pos0 = pos0;
+  g.nq = heads & 0xffff; g.nkv = heads >> 16; a.nq = g.nq; a.nkv = g.nkv;
+  constexpr int UH = DH / (16 * RT), G = 3 * UH;   // workgroups per q / K / V part of a head; arrivals that a head waits for
   static_assert(UH >= 1 && UH * 16 * RT == DH, "a head part is a whole number of workgroups");
-  union Smem { GemmSmem<RT, 8> gemm; AttnSmem<DH, 8> attn; };
+  union Smem { GemmSmem<RT, 8, LN> gemm; AttnSmem<DH, 8> attn; };
   __shared__ Smem sm;
-  const int head = blockIdx.x / G, j = blockIdx.x % G;
-  const int part = j / UH, sub = j % UH;
-  const int hu = part == 0 ? head : (part == 1 ? g.nq + head : g.nq + g.nkv + head);
+  const int id = blockIdx.x;
   const uint32_t halted = gate_request(g.gate);
-  gemm_unit<P, RT, EPI_QKV, 8, U, true>(g, hu * UH + sub, 0, g.KT, 0, 1, sm.gemm);
-  if (flag_set(halted)) return;                       // uniform over the launch; nothing has been written
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0);                  // this wavefront's write-through stores have completed
-  __syncthreads();                                // ... and those of the whole workgroup
-  int* rdy = ready + head * QA_READY_SLOT;
-  if (threadIdx.x == 0) __hip_atomic_fetch_add(rdy, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (j >= a.n_splits) return;
-  attn_range<DH, 8, false, false, true, HeadWaitHook>(a, head, j, sm.attn, 0u, HeadWaitHook{rdy, G, abort_word, limit}, safe_end, rdy);
+  // projection unit `b`; then, its workgroup's stores having completed, it is counted in for heads first .. first + n - 1
+  auto project = [&](const int b, const int first, const int n) {
+    gemm_unit<P, RT, EPI_QKV, 8, U, true, NoHook, LN>(g, b, 0, g.KT, 0, 1, sm.gemm);
+    if (flag_set(halted)) return false;           // uniform over the launch; nothing has been written
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);                // this wavefront's write-through stores have completed
+    __syncthreads();                              // ... and those of the whole workgroup
+    for (int i = threadIdx.x; i < n; i += 512) __hip_atomic_fetch_add(ready + (first + i) * QA_READY_SLOT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+  };
+  if constexpr (OWN) {
+    const int n_gemm = (g.nq + 2 * g.nkv) * UH;
+    if (id < n_gemm) {
+      const int rep = g.nkv == 1 ? g.nq : (g.nq == g.nkv ? 1 : g.nq / g.nkv), hu = id / UH;
+      project(id, hu < g.nq ? hu : (hu - g.nq) % g.nkv * rep, hu < g.nq ? 1 : rep);
+      return;
+    }
+    const int split = (id - n_gemm) / g.nq, head = id - n_gemm - split * g.nq;
+    int* rdy = ready + head * QA_READY_SLOT;
+    const HeadWaitHook wait{rdy, G, abort_word, limit, halted};
+    if (a.n_splits == 1) {
+      AttnWhole<DH, 2, true> at(a, head);
+      at.request(safe_end);
+      wait();
+      at.run(sm.attn, safe_end, halted);
+      if (threadIdx.x == 0 && !flag_set(halted)) __hip_atomic_store(rdy, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      attn_range<DH, 8, false, false, true, HeadWaitHook>(a, head, split, sm.attn, halted, wait, safe_end, rdy);
+    }
+  } else {                                        // a K / V head per query head
+    const int head = id / G, j = id % G, part = j / UH, sub = j % UH;
+    const int hu = part == 0 ? head : (part == 1 ? g.nq + head : g.nq + g.nkv + head);
+    if (!project(hu * UH + sub, head, 1) || j >= a.n_splits) return;
+    int* rdy = ready + head * QA_READY_SLOT;
+    attn_range<DH, 8, false, false, true, HeadWaitHook>(a, head, j, sm.attn, 0u, HeadWaitHook{rdy, G, abort_word, limit, 0u}, safe_end, rdy);
+  }
 }
 
 // Workgroups of `kernel` (512 threads, static LDS only) that the device holds at once.
@@ -3564,48 +3617,69 @@ static long resident_capacity(const void* kernel) {
   return (long)per_cu * prop.multiProcessorCount;
 }
 
-template <int P, int RT, int DH>
-static hipError_t launch_qkv_attn_cfg(const GemmArgs& g, const AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit,
+template <int P, int RT, int DH, bool LN, bool OWN>
+static hipError_t launch_qkv_attn_cfg(const GemmArgs& g, const AttnArgs& a0, int* ready, unsigned* abort_word, int safe_end, int limit,
                                       bool* launched, hipStream_t s) {
-  constexpr int U = gemm_buffers(RT, P);
-  static const long capacity = resident_capacity(reinterpret_cast<const void*>(k_qkv_attn<P, RT, U, DH>));
-  const int wgs = g.n_rows / (16 * RT);
-  if (wgs > capacity) return hipSuccess;          // not all resident at once: the caller launches the two kernels
-  hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH>), dim3(wgs), dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M, g.nq,
-                     g.pos0, g, a, ready, abort_word, safe_end, limit);
+  constexpr int U = gemm_buffers(RT, P), G = 3 * DH / (16 * RT);
+  static const long capacity = resident_capacity(reinterpret_cast<const void*>(k_qkv_attn<P, RT, U, DH, LN, OWN>));
+  AttnArgs a = a0;
+  const int n_gemm = g.n_rows / (16 * RT), total = a.pos0 + a.M;
+  long wgs = n_gemm;
+  if constexpr (OWN) {
+    // up to 256 positions a workgroup takes a whole head (one step per wavefront, no records: 68M draft at 250 tokens 69.9 us a
+    // token, 71.4 in ranges); beyond that ranges of at least 256 (multi-query draft at 2040 337.8 us a token, 374 in ranges of at least 128)
+    const long room = (capacity - n_gemm) / g.nq;
+    if (room < (total <= ATTN_HEAD_MAX_CTX ? 1 : 2)) return hipSuccess;
+    int len = (int)((total + room - 1) / room + 31) / 32 * 32;
+    if (len < ATTN_HEAD_MAX_CTX) len = ATTN_HEAD_MAX_CTX;
+    a.split_len = len; a.n_splits = (total + len - 1) / len;
+    wgs += (long)g.nq * a.n_splits;
+  } else {
+    if (total <= ATTN_HEAD_MAX_CTX) return hipSuccess;
+    int len = ((total + G - 1) / G + 31) / 32 * 32;
+    if (len < ATTN_SPLIT_LEN) len = ATTN_SPLIT_LEN;                      // (the records are sized for ranges of at least this)
+    a.split_len = len; a.n_splits = (total + len - 1) / len;
+  }
+  if (wgs > capacity) return hipSuccess;          // not all resident at once
+  hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, LN, OWN>), dim3((unsigned)wgs), dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M,
+                     g.nq | (g.nkv << 16), g.pos0, g, a, ready, abort_word, safe_end, limit);
   *launched = true;
   return hipGetLastError();
+}
+template <int RT, int DH>
+static hipError_t launch_qkv_attn_rt(const GemmArgs& g, const AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit,
+                                     bool* launched, hipStream_t s) {
+  const bool p1 = g.M <= 8;
+  if (g.sum != nullptr) return p1 ? launch_qkv_attn_cfg<1, RT, DH, true, true>(g, a, ready, abort_word, safe_end, limit, launched, s)
+                                  : launch_qkv_attn_cfg<2, RT, DH, true, true>(g, a, ready, abort_word, safe_end, limit, launched, s);
+  const hipError_t e = p1 ? launch_qkv_attn_cfg<1, RT, DH, false, true>(g, a, ready, abort_word, safe_end, limit, launched, s)
+                          : launch_qkv_attn_cfg<2, RT, DH, false, true>(g, a, ready, abort_word, safe_end, limit, launched, s);
+  if (e != hipSuccess || *launched || g.nq != g.nkv) return e;
+  return p1 ? launch_qkv_attn_cfg<1, RT, DH, false, false>(g, a, ready, abort_word, safe_end, limit, launched, s)
+            : launch_qkv_attn_cfg<2, RT, DH, false, false>(g, a, ready, abort_word, safe_end, limit, launched, s);
 }
 
 // Sets *launched and enqueues the fused launch when the shape allows it; otherwise leaves *launched false and does
 // nothing (the caller then launches the QKV projection and the attention separately).  a.split_len / a.n_splits are
 // chosen here.
-hipError_t launch_qkv_attn(const GemmArgs& g0, const AttnArgs& a0, int* ready, unsigned* abort_word, int limit, bool* launched, hipStream_t s) {
+hipError_t launch_qkv_attn(const GemmArgs& g0, const AttnArgs& a, int* ready, unsigned* abort_word, int limit, bool* launched, hipStream_t s) {
   *launched = false;
   if (ready == nullptr || abort_word == nullptr) return hipSuccess;
-  if (g0.sum != nullptr || g0.nq != g0.nkv || (g0.dh != 64 && g0.dh != 128)) return hipSuccess;
-  if (g0.M < 1 || g0.M > 16 || g0.KT < 1 || g0.n_rows != 3 * g0.nq * g0.dh || g0.grp != g0.dh / 32) return hipSuccess;
+  if (g0.nkv < 1 || g0.nq % g0.nkv != 0 || (g0.dh != 64 && g0.dh != 128)) return hipSuccess;
+  if (g0.M < 1 || g0.M > 16 || g0.KT < 1 || g0.n_rows != (g0.nq + 2 * g0.nkv) * g0.dh || g0.grp != g0.dh / 32) return hipSuccess;
   if (g0.ssq != nullptr && (g0.n_ssq < 1 || g0.n_ssq > 512)) return hipErrorInvalidValue;
-  if (a0.M != g0.M || a0.nq != g0.nq || a0.nkv != g0.nkv || a0.dh != g0.dh || a0.pos0 != g0.pos0 || a0.counters == nullptr) return hipErrorInvalidValue;
+  if (a.M != g0.M || a.nq != g0.nq || a.nkv != g0.nkv || a.dh != g0.dh || a.pos0 != g0.pos0 || a.counters == nullptr) return hipErrorInvalidValue;
   GemmArgs g = g0;
   g.n_split = 1;
-  AttnArgs a = a0;
-  const int n = g.n_rows, total = a.pos0 + a.M, pt = a.page_tokens;
+  const int n = g.n_rows, pt = a.page_tokens;
   const int rt = (n % 64 == 0 && n / 64 >= 200) ? 4 : 2;                 // the row tiles of the stand-alone QKV launch
-  const int G = 3 * g.dh / (16 * rt);
-  int len = ((total + G - 1) / G + 31) / 32 * 32;
-  if (len < ATTN_SPLIT_LEN) len = ATTN_SPLIT_LEN;                        // (the records are sized for ranges of at least this)
-  a.split_len = len; a.n_splits = (total + len - 1) / len;
   // positions below safe_end share no 128-byte line with the block's own positions: K rows are 128 bytes or more per
   // position; a V^T row holds the positions of one page, 64 to a line
   const int safe_end = (pt % 64 == 0) ? (a.pos0 & ~63) : (a.pos0 / pt) * pt;
-  const bool p1 = g.M <= 8;
-  if (g.dh == 128) {
-    if (rt == 4) return p1 ? launch_qkv_attn_cfg<1, 4, 128>(g, a, ready, abort_word, safe_end, limit, launched, s) : launch_qkv_attn_cfg<2, 4, 128>(g, a, ready, abort_word, safe_end, limit, launched, s);
-    return p1 ? launch_qkv_attn_cfg<1, 2, 128>(g, a, ready, abort_word, safe_end, limit, launched, s) : launch_qkv_attn_cfg<2, 2, 128>(g, a, ready, abort_word, safe_end, limit, launched, s);
-  }
-  if (rt == 4) return p1 ? launch_qkv_attn_cfg<1, 4, 64>(g, a, ready, abort_word, safe_end, limit, launched, s) : launch_qkv_attn_cfg<2, 4, 64>(g, a, ready, abort_word, safe_end, limit, launched, s);
-  return p1 ? launch_qkv_attn_cfg<1, 2, 64>(g, a, ready, abort_word, safe_end, limit, launched, s) : launch_qkv_attn_cfg<2, 2, 64>(g, a, ready, abort_word, safe_end, limit, launched, s);
+  if (g.dh == 128) return rt == 4 ? launch_qkv_attn_rt<4, 128>(g, a, ready, abort_word, safe_end, limit, launched, s)
+                                  : launch_qkv_attn_rt<2, 128>(g, a, ready, abort_word, safe_end, limit, launched, s);
+  return rt == 4 ? launch_qkv_attn_rt<4, 64>(g, a, ready, abort_word, safe_end, limit, launched, s)
+                 : launch_qkv_attn_rt<2, 64>(g, a, ready, abort_word, safe_end, limit, launched, s);
 }
 
 

@@ -250,3 +250,27 @@ def test_fused_launch_over_other_head_layouts():
             (lg0, am0), (lg2, am2) = out
             scale = float(lg2.abs().max())
             assert bool(torch.isfinite(lg0).all()) and float((lg0 - lg2).abs().max()) <= 2e-4 * scale, (si, page_tokens, ctx, M)
+
+
+@pytest.mark.parametrize("si", range(4))
+def test_fused_launch_with_workgroups_of_its_own_for_the_attention(si):
+    """Shared K / V heads and deferred LayerNorms in the shared launch: every K / V workgroup counts itself in for all the query
+    heads that read it.  Contexts around the switch from one workgroup per head to ranges (256 positions) and at several
+    ranges, against the separate launches; two of them against the oracle."""
+    shape = (W.ModelShape("A", 2, 256, 4, 64, 1, 512, 512), W.ModelShape("A", 1, 128, 3, 128, 3, 256, 320),
+             W.ModelShape("B", 2, 256, 6, 64, 2, 512, 512), W.ModelShape("B", 1, 256, 4, 128, 1, 256, 320))[si]
+    for ctx, page_tokens, permute in ((0, 16, False), (17, 8, True), (248, 64, False), (255, 16, True), (700, 128, False), (1500, 16, True)):
+        om, gm, okv, gkv, ws = setup_pair(shape, 70 + si, kv_ctx=ctx, capacity=ctx + 48, page_tokens=page_tokens, permute=permute, sigma=0.05)
+        for M in (1, 8, 9, 16):
+            blk = W.make_tokens(80 + M, M, shape.vocab).tolist()
+            lg0, am0 = _verify(gm, gkv, ws, blk, 0)
+            B.disco_kv_rollback(gkv, ctx)
+            lg2, _ = _verify(gm, gkv, ws, blk, 2)
+            B.disco_kv_rollback(gkv, ctx)
+            tag = f"shape {si}, ctx {ctx}, pages of {page_tokens}, M {M}"
+            assert bool(torch.isfinite(lg0).all()) and float((lg0 - lg2).abs().max()) <= 2e-4 * float(lg2.abs().max()), tag
+            if ctx in (17, 255):
+                ref = om.forward(blk, okv)
+                okv.rollback(ctx)
+                check_logits(lg0, ref, "fused: " + tag)
+                check_argmax(am0, ref, "fused " + tag)
