@@ -423,6 +423,9 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
       a.g.ssq_out = ws.ssq; a.ssq_outs = (size_t)n_tiles * 16;
     }
   };
+  auto rms_input = [&](DenseArgs& a) {              // the launcher decides who adds up the sums of squares
+    if (!fam_a) { a.g.ssq = ws.ssq; a.g.n_ssq = n_tiles; a.g.d_in = d.d_model; a.g.eps = d.norm_eps; a.rstd = ws.rstd; }
+  };
   for (int l = 0; l < d.n_layers; ++l) {
     const disco_layer_weights& L = m->layers[l];
     const bool last = (l + 1 == d.n_layers);
@@ -430,9 +433,8 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
     const float* next_b = last ? m->w.normf_b : m->layers[l + 1].norm1_b;
     bf16_t* kv_layer = kv->pages + (size_t)l * kv->layer_stride;
 
-    if (!fam_a) HIP_TRY(launch_rstd_groups(ws.ssq, n_tiles, d.d_model, d.norm_eps, ws.rstd, G, st), "rstd launch");
     DenseArgs qa = dense(L.wqkv, ws.xn, xs_d, d.d_model, m->d_qkv);
-    qa.rstd = fam_a ? nullptr : ws.rstd; qa.g.grp = d.d_head / 32; qa.g.q = ws.q; qa.qs = (size_t)16 * m->d_q; qa.g.ldq = m->d_q;
+    rms_input(qa); qa.g.grp = d.d_head / 32; qa.g.q = ws.q; qa.qs = (size_t)16 * m->d_q; qa.g.ldq = m->d_q;
     qa.g.nq = d.n_heads; qa.g.nkv = d.n_kv_heads; qa.g.dh = d.d_head; qa.g.pos0 = pos0; qa.g.rope_tab = kv->dev_rope;
     qa.g.kv_layer = kv_layer; qa.g.page_table = kv->dev_page_table; qa.g.page_tokens = kv->page_tokens;
     HIP_TRY(launch_gemm_dense(qa, EPI_QKV, st), "qkv launch");
@@ -451,11 +453,9 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
       NormArgs n2 = na;
       n2.g = L.norm2_g; n2.b = L.norm2_b;
       HIP_TRY(launch_norm(n2, st), "norm launch");
-    } else {
-      HIP_TRY(launch_rstd_groups(ws.ssq, n_tiles, d.d_model, d.norm_eps, ws.rstd, G, st), "rstd launch");
     }
     DenseArgs ua = dense(L.w_in, ws.xn, xs_d, d.d_model, n_in);
-    ua.rstd = fam_a ? nullptr : ws.rstd; ua.g.Xout = ws.xact; ua.xouts = xs_ff; ua.g.KT_out = d.d_ff / 32;
+    rms_input(ua); ua.g.Xout = ws.xact; ua.xouts = xs_ff; ua.g.KT_out = d.d_ff / 32;
     HIP_TRY(probe_record(l, 0, st), "probe event");
     HIP_TRY(launch_gemm_dense(ua, fam_a ? EPI_GELU : EPI_SWIGLU, st), "mlp-in launch");
     HIP_TRY(probe_record(l, 1, st), "probe event");

@@ -60,7 +60,8 @@ struct DenseArgs {
   size_t xs, xouts;     // bf16 elements between the groups' input / output panels
   size_t hs, qs;        // floats between the groups' residual rows / query rows
   size_t ssq_outs;      // floats between the groups' sum-of-squares slots
-  const float* rstd;    // [group][16]: 1 / rms of the input rows (epilogues that read a normalised input)
+  float* rstd;          // [group][16]: 1 / rms of the input rows (epilogues that read a normalised input): formed from g.ssq where
+                        // that is set, in the launch itself or by one before it
   int hi_only;          // bf16 activations: the lo panels are not read
   size_t plane_bytes;   // room for partial sums at g.planes: a matrix is cut along K only as far as they fit
   int k_split;          // set by the launcher: K ranges

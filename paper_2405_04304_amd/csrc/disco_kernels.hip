@@ -1429,7 +1429,10 @@ __global__ __launch_bounds__(512) void k_attn_head(ATTN_EARLY, AttnArgs a) {
 // longest ranges are scheduled first.
 constexpr int ATTN_MG = 2;
 template <int DH, bool LO>
-__global__ __launch_bounds__(512) void k_attn_groups(AttnArgs a, int n_groups, size_t x_stride) {
+__global__ __launch_bounds__(512) void k_attn_groups(const bf16_t* kv_layer, const int32_t* page_table, const float* q, int page_tokens, int heads, int ldq,
+                                                     int pos0, int n_groups, AttnArgs a, size_t x_stride) {    // (leading arguments: see k_gemm)
+  a.kv_layer = kv_layer; a.page_table = page_table; a.q = q; a.page_tokens = page_tokens; a.nq = heads & 0xffff; a.nkv = heads >> 16;
+  a.ldq = ldq; a.pos0 = pos0; a.M = 16;
   constexpr int CT = DH / 16, NWV = 8, WKEYS = 32, STEP = NWV * WKEYS, NG = ATTN_MG;
   __shared__ f32x4 o_s[NWV][CT][64];
   __shared__ float m_s[NWV][16], l_s[NWV][16];
@@ -1748,12 +1751,13 @@ hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, 
     return hipGetLastError();
   }
   const dim3 g1(a.nq, (n_groups + ATTN_MG - 1) / ATTN_MG);
+  const int heads = a.nq | (a.nkv << 16);
   if (a.dh == 128) {
-    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<128, false>), g1, dim3(512), 0, s, a, n_groups, x_stride);
-    else hipLaunchKernelGGL((k_attn_groups<128, true>), g1, dim3(512), 0, s, a, n_groups, x_stride);
+    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<128, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
+    else hipLaunchKernelGGL((k_attn_groups<128, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
   } else if (a.dh == 64) {
-    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<64, false>), g1, dim3(512), 0, s, a, n_groups, x_stride);
-    else hipLaunchKernelGGL((k_attn_groups<64, true>), g1, dim3(512), 0, s, a, n_groups, x_stride);
+    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<64, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
+    else hipLaunchKernelGGL((k_attn_groups<64, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
   } else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -3183,7 +3187,8 @@ hipError_t launch_loop_finish(const int32_t* sl_count, const uint32_t* gate, voi
 // Epilogue of one wavefront: R2 pairs of row tiles (rt[2 q], rt[2 q + 1]; -1 past the matrix) x CA accumulators of 32 rows x
 // 32 tokens.  Lane: token column lane % 32 (two groups of 16), rows 8 i + 4 (lane / 32) .. + 3 of chunk i = 0 .. 3.
 template <int EPI, int R2, int CA, bool HI>
-__device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, const int (&rt)[2 * R2], const f32x16 (&acc)[R2][CA]) {
+__device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, const int (&rt)[2 * R2], const f32x16 (&acc)[R2][CA],
+                                              const float* rstd_s = nullptr /* 1 / rms of the tokens from group g0 on, where the launch forms them */) {
   constexpr bool PAIR = EpiTraits<EPI>::pair;
   const GemmArgs& a = d.g;
   const int lane = threadIdx.x & 63, m = lane & 15, gh = lane >> 5;
@@ -3191,7 +3196,7 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
   for (int c = 0; c < CA; ++c) {
     const int ci = g0 + 2 * c + ((lane >> 4) & 1);
     if (ci >= d.n_groups) continue;               // (half a wavefront at the ragged end)
-    const float rstd = (EPI != EPI_PARTIAL && d.rstd != nullptr) ? d.rstd[ci * 16 + m] : 1.f;
+    const float rstd = EPI == EPI_PARTIAL ? 1.f : (rstd_s != nullptr ? rstd_s[(ci - g0) * 16 + m] : (d.rstd != nullptr ? d.rstd[ci * 16 + m] : 1.f));
     float4 hv[EPI == EPI_PARTIAL ? R2 : 1][4];
     float* hrow = EPI == EPI_PARTIAL ? a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out : nullptr;
     if (EPI == EPI_PARTIAL) {                     // all residual values of the column are requested before the first store
@@ -3264,12 +3269,16 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
 }
 
 template <int EPI, int WR, int WC, int R2, int C2, int NST, int OCC, bool HI>
-__global__ __launch_bounds__(512, OCC) void k_gemm_tile(DenseArgs d) {
+__global__ __launch_bounds__(512, OCC) void k_gemm_tile(const bf16_t* W, const bf16_t* X, size_t xs, int KT_, int n_rows, int n_groups, int grp, int k_split,
+                                                        DenseArgs d) {          // (leading arguments: see k_gemm)
+  d.g.W = W; d.g.X = X; d.xs = xs; d.g.KT = KT_; d.g.n_rows = n_rows; d.n_groups = n_groups; d.g.grp = grp; d.k_split = k_split;
   constexpr int NW = WR * WC, CA = HI ? C2 : C2 / 2;
   constexpr int NA = 2 * R2 * WR, NBT = 2 * C2 * WC, NT = NA + NBT, PER = NT / NW;
   constexpr int WG_G = HI ? NBT : NBT / 2;        // token groups per workgroup
   static_assert(NW == 8 && NT % NW == 0, "eight wavefronts, equal shares of the copies");
+  constexpr bool NORMED = EPI == EPI_QKV || EPI == EPI_SWIGLU;
   __shared__ u32x4 st[NST][NT][64];
+  __shared__ float rstd_s[NORMED ? WG_G * 16 : 1];
   const GemmArgs& a = d.g;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = w / WC, wc = w % WC;
@@ -3320,6 +3329,18 @@ __global__ __launch_bounds__(512, OCC) void k_gemm_tile(DenseArgs d) {
   for (int k = 0; k < NST; ++k)
 #pragma unroll
     for (int i = 0; i < PER; ++i) dma(i, k0 + k, k);
+  const bool own_rstd = NORMED && a.ssq != nullptr;
+  if (own_rstd) {
+    // narrow models (64 sums of squares a row at most): every workgroup adds up its own tokens' while the first copies arrive, in
+    // the order of k_rstd_groups
+    for (int t = threadIdx.x; t < WG_G * 16; t += 512) {
+      const float* sq = a.ssq + (size_t)min(cb * WG_G + (t >> 4), d.n_groups - 1) * a.n_ssq * 16 + (t & 15);
+      float tot = 0.f;
+#pragma unroll 16
+      for (int i = 0; i < a.n_ssq; ++i) tot += sq[i * 16];
+      rstd_s[t] = 1.0f / sqrtf(tot / (float)a.d_in + a.eps);
+    }
+  }
   struct Frag { u32x4 a[R2], b[C2]; };
   Frag f0, f1;
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NST - 1) * PER) : "memory");
@@ -3367,7 +3388,8 @@ __global__ __launch_bounds__(512, OCC) void k_gemm_tile(DenseArgs d) {
     int rt[2 * R2];
 #pragma unroll
     for (int r = 0; r < 2 * R2; ++r) rt[r] = row_tile(wr * 2 * R2 + r);
-    tile_epilogue<EPI, R2, CA, HI>(d, cb * WG_G + wc * 2 * CA, rt, acc);
+    if (own_rstd) __syncthreads();
+    tile_epilogue<EPI, R2, CA, HI>(d, cb * WG_G + wc * 2 * CA, rt, acc, own_rstd ? rstd_s + wc * 2 * CA * 16 : nullptr);
   }
 }
 
@@ -3444,23 +3466,41 @@ DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t
   return DensePlan{tile, split, wgs[tile], split > 1 ? (size_t)wgs[1] * split * split_unit_bytes(hi_only) : 0};
 }
 
+template <int EPI, int WR, int WC, int R2, int C2, int NST, int OCC, bool HI>
+static void launch_tiles(const DenseArgs& d, const dim3 grid, hipStream_t s) {
+  hipLaunchKernelGGL((k_gemm_tile<EPI, WR, WC, R2, C2, NST, OCC, HI>), grid, dim3(512), 0, s, d.g.W, d.g.X, d.xs, d.g.KT, d.g.n_rows, d.n_groups, d.g.grp,
+                     d.k_split, d);
+}
+
+// Ring depths: a grid of at most a workgroup per compute unit takes the whole LDS (c0 six stages instead of three, c3 eight): with two resident
+// workgroups one computes while the other waits for its copies, a lone one has only its own ring to wait with
+// (68M shape at 511 tokens: 2304 and 768 rows, K 768, 12.4 -> 11.0 and 12.7 -> 11.3 us a launch, 6144 rows 15.3 either way).
 template <int EPI, bool HI>
 static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   DenseArgs d = d0;
   const DensePlan p = gemm_dense_plan(d.g.n_rows, d.g.KT, d.n_groups, HI, d.g.planes != nullptr ? d.plane_bytes : 0);
   const dim3 grid(8u * (unsigned)((p.wgs * p.split + 7) / 8));
+  if (d.g.ssq != nullptr && (p.split > 1 || d.g.n_ssq > 64)) {
+    // (a wide row's sums are read by every workgroup of its tokens: one launch for all of them)
+    const hipError_t e = launch_rstd_groups(d.g.ssq, d.g.n_ssq, d.g.d_in, d.g.eps, d.rstd, d.n_groups, s);
+    if (e != hipSuccess) return e;
+    d.g.ssq = nullptr;
+  }
   if (p.split > 1) {
     d.k_split = p.split;
-    hipLaunchKernelGGL((k_gemm_tile<EPI_SPLIT, 2, 4, 4, 2, 4, 2, HI>), grid, dim3(512), 0, s, d);
+    launch_tiles<EPI_SPLIT, 2, 4, 4, 2, 4, 2, HI>(d, grid, s);
     const long waves = (long)(d.g.n_rows / 32) * ((d.n_groups + 1) / 2);
     hipLaunchKernelGGL((k_gemm_sum<EPI, HI>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, d);
     return hipGetLastError();
   }
   switch (p.tile) {
-    case 0: hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 2, 2, 3, 4, HI>), grid, dim3(512), 0, s, d); break;
-    case 1: hipLaunchKernelGGL((k_gemm_tile<EPI, 2, 4, 4, 2, 4, 2, HI>), grid, dim3(512), 0, s, d); break;
-    case 2: if constexpr (!HI) hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 4, 4, 3, 2, HI>), grid, dim3(512), 0, s, d); break;
-    default: hipLaunchKernelGGL((k_gemm_tile<EPI, 4, 2, 1, 2, 3, 4, HI>), grid, dim3(512), 0, s, d); break;
+    case 0:
+      if (p.wgs <= 256) launch_tiles<EPI, 2, 4, 2, 2, 6, 2, HI>(d, grid, s);
+      else launch_tiles<EPI, 2, 4, 2, 2, 3, 4, HI>(d, grid, s);
+      break;
+    case 1: launch_tiles<EPI, 2, 4, 4, 2, 4, 2, HI>(d, grid, s); break;
+    case 2: if constexpr (!HI) launch_tiles<EPI, 4, 2, 4, 4, 3, 2, HI>(d, grid, s); break;
+    default: launch_tiles<EPI, 4, 2, 1, 2, 8, 2, HI>(d, grid, s); break;
   }
   return hipGetLastError();
 }
