@@ -453,9 +453,15 @@ __device__ __forceinline__ void gemm_unit(const GemmArgs& a, const int b, const 
 #pragma unroll
     for (int r = 0; r < RT; ++r) A[r] = __builtin_nontemporal_load(Wp[r] + (size_t)k * 64);
   };
+  // Columns without a token are not fetched by the units that many workgroups of a wide matrix read their panels for: a result column
+  // depends on its own operand column only, and these are never stored (two multi-query layers, 7 tokens: 414.7 -> 408.8 us; the
+  // 16- and 32-row units of the draft models got slower: a 68M draft token 68.4 -> 69.2)
+  const bool live_col = RT < 4 || (lane & (P == 1 ? 7 : 15)) < a.M;
   auto load_x = [&](u32x4 (&B)[P], const int k) {
+    if (live_col) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) B[p] = Xp[((size_t)p * KT + k) * 64];
+      for (int p = 0; p < P; ++p) B[p] = Xp[((size_t)p * KT + k) * 64];
+    }
   };
   u32x4 A[U][RT], B[U][P];
   const int kt0 = kt_begin + w;
