@@ -174,8 +174,8 @@ hipError_t launch_forward(const FwdArgs& f, bool big, bool loop, hipStream_t s);
 constexpr int FWD_BAR_WORDS = (2 * 16 + 2) * 64;   // group counters, top counter, release words, abort word: 256 bytes apart
 constexpr int FWD_BAR_ABORT_WORD = (2 * 16 + 1) * 64;
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s);
-// QKV projection (EPI_QKV arguments) and attention of one layer in one launch, where the shape allows it (every query
-// head with its own K / V head, RMSNorm family): sets *launched; when it stays false nothing was enqueued and the caller
+// QKV projection (EPI_QKV arguments) and attention of one layer in one launch, where the shape allows it (all its workgroups
+// resident at once): sets *launched; when it stays false nothing was enqueued and the caller
 // launches the two kernels.  head_ready: one zeroed counter per query head, QKV_ATTN_READY_SLOT ints apart; abort_word:
 // set when a bounded wait inside the launch ran out (results unusable).
 constexpr int QKV_ATTN_READY_SLOT = 64;
