@@ -109,20 +109,31 @@ template <bool COH> __device__ __forceinline__ void st_h1(bf16_t* p, bf16_t v) {
 
 // Store 4 consecutive-k activations of token m into the packed panels as bf16 hi/lo (LO false: the lo panel has no reader).
 template <bool COH = false, bool LO = true>
-__device__ __forceinline__ void xpack_store4(bf16_t* X, int KT, int M, int m, int k, const float* v) {
+__device__ __forceinline__ void xpack_put4(bf16_t* X, int KT, int M, int m, int k, HiLo x0, HiLo x1) {
   const int kt = k >> 5, grp = (k & 31) >> 3, e = k & 7;
-  uint32_t hi[2], lo[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const HiLo x = split_bf16(v[2 * i], v[2 * i + 1]);
-    hi[i] = x.hi; lo[i] = x.lo;
-  }
   const size_t base = ((size_t)kt * 64 + grp * 16) * 8 + e;
   size_t off_hi, off_lo;
   if (M <= 8) { off_hi = base + (size_t)m * 8; off_lo = base + (size_t)(m + 8) * 8; }
   else { off_hi = base + (size_t)m * 8; off_lo = (size_t)KT * 512 + base + (size_t)m * 8; }
-  st_u2<COH>(X + off_hi, make_uint2(hi[0], hi[1]));
-  if (LO) st_u2<COH>(X + off_lo, make_uint2(lo[0], lo[1]));
+  st_u2<COH>(X + off_hi, make_uint2(x0.hi, x1.hi));
+  if (LO) st_u2<COH>(X + off_lo, make_uint2(x0.lo, x1.lo));
+}
+template <bool COH = false, bool LO = true>
+__device__ __forceinline__ void xpack_store4(bf16_t* X, int KT, int M, int m, int k, const float* v) {
+  xpack_put4<COH, LO>(X, KT, M, m, k, split_bf16(v[0], v[1]), split_bf16(v[2], v[3]));
+}
+
+// The products a * ga and b * gb as bf16 hi + lo.  EXACT: lo is what hi leaves of the exact product, else of the product rounded to
+// fp32.  Written out because a compiler that may contract decides it by what stands around (see norm_row).
+template <bool EXACT>
+__device__ __forceinline__ HiLo split_product(float a, float ga, float b, float gb) {
+#pragma clang fp contract(off)
+  const float x = a * ga, y = b * gb;
+  HiLo r;
+  r.hi = pack_bf16(x, y);
+  const float hx = __uint_as_float(r.hi << 16), hy = __uint_as_float(r.hi & 0xffff0000u);
+  r.lo = EXACT ? pack_bf16(fmaf(a, ga, -hx), fmaf(b, gb, -hy)) : pack_bf16(x - hx, y - hy);
+  return r;
 }
 
 // Wavefront reductions on the DPP cross-lane network (no LDS traffic): xor-1, xor-2 inside quads,
@@ -906,8 +917,11 @@ __device__ __forceinline__ void norm_row(const NormArgs& a, const int row, const
       const int k = (i * NT + t) * 4;
       if (k < d) {
         const float4 g = *reinterpret_cast<const float4*>(a.g + k);
-        const float o[4] = {v[i].x * g.x, v[i].y * g.y, v[i].z * g.z, v[i].w * g.w};
-        xpack_store4<COH>(Xout, KT, a.M, m, k, o);
+        // Which lo the chunks hold is stated: either is as close as the panel's own rounding, but a panel that changes moves cache
+        // entries by a bf16 step and the logits by 1e-4, and the compiler's choice changed with unrelated code
+        const HiLo x0 = i == 0 ? split_product<true>(v[i].x, g.x, v[i].y, g.y) : split_product<false>(v[i].x, g.x, v[i].y, g.y);
+        const HiLo x1 = i == 0 ? split_product<true>(v[i].z, g.z, v[i].w, g.w) : split_product<false>(v[i].z, g.z, v[i].w, g.w);
+        xpack_put4<COH>(Xout, KT, a.M, m, k, x0, x1);
       }
     }
     return;
