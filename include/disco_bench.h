@@ -34,6 +34,14 @@ int disco_set_wait_limit(int polls);
 struct disco_model;
 int disco_prefill_plan(const struct disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[6]);
 
+/* Testing and measurement aid: how launch mode 0 runs the QKV projection and the attention of a layer for a block of
+ * n_tokens behind ctx cached positions, without a launch.  out[0]: 0 two launches, 1 one launch whose projection workgroups
+ * become the attention's, 2 one launch with workgroups of the attention's own; out[1]: 16-row tiles of a projection
+ * workgroup; out[2], out[3]: the deal of the context, positions per range and ranges per head (up to 256 positions one
+ * workgroup takes a head and merges as those ranges would be); out[4]: workgroups of the launch (forms 1 and 2).
+ * capacity: workgroups that the GPU holds at once (0: ask the current device).  0, or DISCO_EINVAL.         */
+int disco_qkv_attn_plan(const struct disco_model* m, int n_tokens, int ctx, int capacity, int out[5]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -137,6 +137,7 @@ _SIGNATURES = {
     "disco_probe_enable": (C.c_int, [C.c_int]),
     "disco_probe_read_ms": (C.c_float, []),
     "disco_set_wait_limit": (C.c_int, [C.c_int]),
+    "disco_qkv_attn_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
     "disco_prefill_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_uint, C.c_int, C.POINTER(C.c_int)]),
 }
 EXPORTS = sorted(_SIGNATURES)
@@ -349,6 +350,13 @@ def disco_prefill_plan(model_handle, n_tokens: int, flags: int = 0, page_tokens:
     out = (C.c_int * 6)()
     _check(lib().disco_prefill_plan(model_handle, n_tokens, flags, page_tokens, out))
     return {"qkv": out[0], "o": out[1], "mlp_in": out[2], "mlp_out": out[3], "attn_tiles": bool(out[4]), "norm_groups": bool(out[5])}
+
+
+def disco_qkv_attn_plan(model_handle, n_tokens: int, ctx: int, capacity: int = 0) -> dict:
+    """How launch mode 0 runs QKV projection and attention (disco_bench.h): form, deal of the context, workgroups."""
+    out = (C.c_int * 5)()
+    _check(lib().disco_qkv_attn_plan(model_handle, n_tokens, ctx, capacity, out))
+    return {"form": ("separate", "shared", "own")[out[0]], "row_tiles": out[1], "range": out[2], "ranges": out[3], "workgroups": out[4]}
 
 
 def disco_probe_enable(layer: int) -> None:

@@ -1075,6 +1075,18 @@ int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int p
   return DISCO_OK;
 }
 
+int disco_qkv_attn_plan(const disco_model* m, int n_tokens, int ctx, int capacity, int out[5]) {
+  if (!m || !out || n_tokens < 1 || n_tokens > DISCO_MAX_BLOCK || ctx < 0 || capacity < 0) return fail(DISCO_EINVAL, "bad argument");
+  const disco_model_desc& d = m->d;
+  const bool ln = d.family == DISCO_FAMILY_A;
+  const int rt = qkv_attn_rt(m->d_qkv);
+  long shared = capacity, own = capacity;
+  if (capacity == 0) qkv_attn_capacities(n_tokens, rt, d.d_head, ln, &shared, &own);
+  const QkvAttnPlan p = qkv_attn_plan(m->d_qkv, d.n_heads, d.n_kv_heads, d.d_head, ln, ctx + n_tokens, rt, shared, own);
+  out[0] = p.form; out[1] = rt; out[2] = p.split_len; out[3] = p.n_splits; out[4] = (int)p.wgs;
+  return DISCO_OK;
+}
+
 int disco_probe_enable(int layer) {
   std::lock_guard<std::mutex> lock(g_probe_mu);
   g_probe_taken = false;

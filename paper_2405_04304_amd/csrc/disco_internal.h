@@ -180,8 +180,15 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s);
 // set when a bounded wait inside the launch ran out (results unusable).
 constexpr int QKV_ATTN_READY_SLOT = 64;
 // wait_limit: polls before a wait gives up (negative: at once).
-hipError_t launch_qkv_attn(const GemmArgs& g, const AttnArgs& a, int* head_ready, unsigned* abort_word, int wait_limit, bool* launched,
+hipError_t launch_qkv_attn(const GemmArgs& g, AttnArgs& a, int* head_ready, unsigned* abort_word, int wait_limit, bool* launched,
                            hipStream_t s);
+// form 0: two launches, 1: the projection's workgroups become the attention's, 2: the attention has workgroups of its own; positions per
+// range, ranges per head (a context of 256 or fewer goes to one workgroup per head, which merges as the ranges would), workgroups.
+// rt: row tiles of a projection workgroup; cap_shared / cap_own: workgroups of forms 1 / 2 that the GPU holds at once.
+struct QkvAttnPlan { int form, split_len, n_splits; long wgs; };
+QkvAttnPlan qkv_attn_plan(int n_rows, int nq, int nkv, int dh, bool layernorm, int total, int rt, long cap_shared, long cap_own);
+int qkv_attn_rt(int n_rows);
+void qkv_attn_capacities(int M, int rt, int dh, bool layernorm, long* shared, long* own);
 // dense prompt pass (groups of 16 tokens; every group holds 16 rows, surplus rows are padding)
 hipError_t launch_gemm_dense(const DenseArgs& a, int epi, hipStream_t s);
 // What the prompt pass launches for a matrix of n_rows x 32 KT and n_groups groups: workgroup tile (0 .. 3, see the function),

@@ -1245,6 +1245,26 @@ struct AttnSmem {
   int s_last;
 };
 
+// Sums of two ranges brought to a common maximum.  The roundings are written out here and in what follows it (the panels of the
+// quotients, see split_product), since ranges are merged by more than one kernel.
+__device__ __forceinline__ float merged(float a, float fa, float b, float fb) { return fmaf(a, fa, b * fb); }
+constexpr bool RANGES_LO_EXACT = true;
+// ... and the sum of the wavefronts' parts of a range: part(i), rescaled by scale(i), i = 0 .. N - 1
+template <int N, typename PartOf, typename ScaleOf>
+__device__ __forceinline__ f32x4 range_sum(PartOf part, ScaleOf scale) {
+  const f32x4 p0 = part(0), p1 = part(1);
+  f32x4 o;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = merged(p0[v], scale(0), p1[v], scale(1));
+#pragma unroll
+  for (int i = 2; i < N; ++i) {
+    const f32x4 p = part(i);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = fmaf(p[v], scale(i), o[v]);
+  }
+  return o;
+}
+
 // Work unit (query head, range `split` of split_len cached positions) run by NWV wavefronts; the last range of
 // a head to finish merges all of the head's records and writes the O-projection panels.
 // `hook` runs once before anything that other workgroups of the launch may still be writing is touched (the queries,
@@ -1304,9 +1324,7 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
     for (int ci = 0; ci < (CT + NWV - 1) / NWV; ++ci) {
       const int c = w + ci * NWV;
       if (c < CT) {
-        f32x4 o = sm.o_s[0][c][lane] * f[0];
-#pragma unroll
-        for (int ww = 1; ww < NWV; ++ww) o += sm.o_s[ww][c][lane] * f[ww];
+        const f32x4 o = range_sum<NWV>([&](int ww) { return sm.o_s[ww][c][lane]; }, [&](int ww) { return f[ww]; });
         st_agent2(rec + c * 16 + 4 * g, o[0], o[1]);
         st_agent2(rec + c * 16 + 4 * g + 2, o[2], o[3]);
       }
@@ -1342,20 +1360,20 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
         if (sp0 + i < a.n_splits) {
           const float m_new = fmaxf(mx, ml[i].x);
           const float f_old = expf(mx - m_new), f_new = expf(ml[i].x - m_new);
-          L = L * f_old + ml[i].y * f_new;
+          L = merged(L, f_old, ml[i].y, f_new);
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            o[2 * c] = o[2 * c] * f_old + v[i][c].x * f_new;
-            o[2 * c + 1] = o[2 * c + 1] * f_old + v[i][c].y * f_new;
+            o[2 * c] = merged(o[2 * c], f_old, v[i][c].x, f_new);
+            o[2 * c + 1] = merged(o[2 * c + 1], f_old, v[i][c].y, f_new);
           }
           mx = m_new;
         }
     }
     const float inv = 1.0f / L;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] *= inv;
-    xpack_store4<COH>(a.Xout, (a.nq * DH) >> 5, a.M, qm, head * DH + 8 * tq, o);
-    xpack_store4<COH>(a.Xout, (a.nq * DH) >> 5, a.M, qm, head * DH + 8 * tq + 4, o + 4);
+    for (int i = 0; i < 8; i += 4)
+      xpack_put4<COH>(a.Xout, (a.nq * DH) >> 5, a.M, qm, head * DH + 8 * tq + i, split_product<RANGES_LO_EXACT>(o[i], inv, o[i + 1], inv),
+                      split_product<RANGES_LO_EXACT>(o[i + 2], inv, o[i + 3], inv));
   }
 }
 
@@ -1372,62 +1390,69 @@ __global__ __launch_bounds__(512) void k_attn_partial(ATTN_EARLY, AttnArgs a) {
   attn_range<DH, 8>(a, blockIdx.x, blockIdx.y, sm, gate_request(a.gate));   // 1.3 % of a 13B verification block against four)
 }
 
-// Whole head: one workgroup of eight wavefronts takes all positions of a head (256 per step), merges its wavefronts through LDS and
-// writes the O-projection panels itself: no partial records, no hand-off between workgroups.  NR steps' loads are in flight at a
-// time.  request() asks for the first NR steps as far as they lie below safe_end and may run long before run().
-template <int DH, int NR, bool QCOH = false>
+// Whole head: one workgroup of eight wavefronts takes all positions of a head (256 at most, one step of a wavefront), merges its
+// wavefronts through LDS and writes the O-projection panels itself: no partial records, no hand-off between workgroups.  request() asks
+// for the cache entries as far as they lie below safe_end and may run long before run().  split_len 128: the wavefronts
+// are merged as two ranges would be, rounding for rounding, so that it does not show which kernel took a context of that deal.
+template <int DH, bool QCOH = false>
 struct AttnWhole {
-  static constexpr int CT = DH / 16, NWV = 8, WKEYS = 32, STEP = NWV * WKEYS;
+  static constexpr int CT = DH / 16, NWV = 8, WKEYS = 32;
   AttnWave<DH, QCOH> aw;
-  typename AttnWave<DH, QCOH>::Raw r[NR];
+  typename AttnWave<DH, QCOH>::Raw r;
   int head, first;
   __device__ __forceinline__ AttnWhole(const AttnArgs& a, int head_) : aw(a, head_, -1), head(head_), first((int)(threadIdx.x >> 6) * WKEYS) {}
   __device__ __forceinline__ void request(const int safe_end) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-      if (first + i * STEP + WKEYS <= safe_end) aw.issue(r[i], first + i * STEP);
+    if (first + WKEYS <= safe_end) aw.issue(r, first);
   }
   // `requested`: the safe_end that request() was given
   __device__ __forceinline__ void run(AttnSmem<DH, NWV>& sm, const int requested, const uint32_t halted) {
     const AttnArgs& a = aw.a;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, j = lane & 15, g = lane >> 4, total = aw.total;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int base = first + i * STEP;
-      if (base + WKEYS > requested && base < total) aw.issue(r[i], base);
-    }
+    if (first + WKEYS > requested && first < total) aw.issue(r, first);
     aw.load_q(head);
     if (flag_set(halted)) return;                 // uniform over the launch; nothing has been written yet
-    for (int b0 = first; b0 < total; b0 += NR * STEP) {
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const int base = b0 + i * STEP;
-        if (base < total) {
-          aw.step(r[i], base);
-          if (base + NR * STEP < total) aw.issue(r[i], base + NR * STEP);
-        }
-      }
-    }
+    if (first < total) aw.step(r, first);
     __syncthreads();                              // the phase before has left the buffers
 #pragma unroll
     for (int c = 0; c < CT; ++c) sm.o_s[w][c][lane] = aw.O[c];
     if (g == 0) { sm.m_s[w][j] = aw.m_run; sm.l_s[w][j] = aw.l_run; }
     __syncthreads();
     if (w >= CT || j >= a.M) return;              // wavefront w finishes channel tile w
-    float mm = sm.m_s[0][j];
+    struct Part { float m, l; };
+    // maximum and sum of wavefronts w0 .. w0 + N - 1, and what brings each to that maximum
+    auto part = [&](const int w0, auto& f) {
+      constexpr int N = sizeof(f) / sizeof(f[0]);
+      Part p{sm.m_s[w0][j], 0.f};
 #pragma unroll
-    for (int ww = 1; ww < NWV; ++ww) mm = fmaxf(mm, sm.m_s[ww][j]);
-    float ll = 0.f;
-    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 1; i < N; ++i) p.m = fmaxf(p.m, sm.m_s[w0 + i][j]);
 #pragma unroll
-    for (int ww = 0; ww < NWV; ++ww) {            // fixed order: deterministic
-      const float f = expf(sm.m_s[ww][j] - mm);
-      ll += sm.l_s[ww][j] * f;
-      o += sm.o_s[ww][w][lane] * f;
+      for (int i = 0; i < N; ++i) { f[i] = expf(sm.m_s[w0 + i][j] - p.m); p.l = fmaf(sm.l_s[w0 + i][j], f[i], p.l); }
+      return p;
+    };
+    bf16_t* const X = a.Xout;
+    const int KT = (a.nq * DH) >> 5, k = head * DH + w * 16 + 4 * g;
+    if (a.split_len >= NWV * WKEYS) {             // uniform
+      float f[NWV];
+      const Part p = part(0, f);
+      const float inv = 1.0f / p.l;
+      f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NWV; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = fmaf(sm.o_s[i][w][lane][v], f[i], o[v]);
+      xpack_put4(X, KT, a.M, j, k, split_product<true>(o[0], inv, o[1], inv), split_product<true>(o[2], inv, o[3], inv));
+    } else {
+      constexpr int N = NWV / 2;
+      float f0[N], f1[N];
+      const Part p0 = part(0, f0), p1 = part(N, f1);
+      const float m = fmaxf(p0.m, p1.m), e0 = expf(p0.m - m), e1 = expf(p1.m - m), inv = 1.0f / merged(p0.l, e0, p1.l, e1);
+      const f32x4 o0 = range_sum<N>([&](int i) { return sm.o_s[i][w][lane]; }, [&](int i) { return f0[i]; });
+      const f32x4 o1 = range_sum<N>([&](int i) { return sm.o_s[N + i][w][lane]; }, [&](int i) { return f1[i]; });
+      f32x4 o;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v] = merged(o0[v], e0, o1[v], e1);
+      xpack_put4(X, KT, a.M, j, k, split_product<RANGES_LO_EXACT>(o[0], inv, o[1], inv), split_product<RANGES_LO_EXACT>(o[2], inv, o[3], inv));
     }
-    const float inv = 1.0f / ll;
-    const float out4[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-    xpack_store4(a.Xout, (a.nq * DH) >> 5, a.M, j, head * DH + w * 16 + 4 * g, out4);
   }
 };
 
@@ -1435,7 +1460,7 @@ template <int DH>
 __global__ __launch_bounds__(512) void k_attn_head(ATTN_EARLY, AttnArgs a) {
   ATTN_EARLY_SET(a);
   __shared__ AttnSmem<DH, 8> sm;
-  AttnWhole<DH, 2> at(a, blockIdx.x);
+  AttnWhole<DH> at(a, blockIdx.x);
   const uint32_t halted = gate_request(a.gate);
   at.request(0x7fffff00);
   at.run(sm, 0x7fffff00, halted);
@@ -1721,6 +1746,7 @@ constexpr int ATTN_HEAD_MAX_CTX = 256;    // positions up to which the whole-hea
 // range and query; measured best on MI355X at the 13B-class shape: 128 up to ~768 positions, then
 // about total / 4 .. total / 8.
 int attn_split_len(int total) {
+  if (total <= ATTN_HEAD_MAX_CTX) return ATTN_HEAD_MAX_CTX;       // (one workgroup per head)
   if (total <= 768) return ATTN_SPLIT_LEN;
   if (total <= 1536) return 2 * ATTN_SPLIT_LEN;
   if (total <= 3072) return 4 * ATTN_SPLIT_LEN;
@@ -3593,9 +3619,10 @@ hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, flo
 // projection runs.  Otherwise (the projection's workgroups fill the chip: one per compute unit) the workgroups of a head are neighbours and become
 // the ranges of its attention when they have counted themselves in.  Either way nobody waits before it has signalled, so the
 // launch completes whenever all its workgroups are resident at once; the launcher checks that they fit.
-// Two layers, 6 tokens, us a pass (OWN / the other form / separate launches): 68M draft at 640 tokens 67.1 / 68.1 / 69.4, at 2475
-// 72.5 / 75.3 / 74; multi-query draft at 1300 75.1 / - / 77.6; 16 heads on 4 K / V heads at 2475 130.2 / - / 134.8; 13B at 640 - / 301.0 /
-// 303.4, at 40 - / 298.2 / 293.0 (so up to 256 positions it takes the separate launches).
+// us a pass, one launch / two: a 68M draft token 66.8 / 67.8 at 250 positions, 68.1 / 69.3 at 523, 72.3 / 76.6 at 2475; a multi-query draft token
+// (12 layers) 300.3 / 309.3 at 250, 314.3 / 324.6 at 640, 329.6 / 366.3 at 2475; two layers of 16 heads on 4 K / V heads, 6 tokens, 122.4 / 125.1
+// at 640, 127.3 / 135.8 at 2475; two 13B layers (not OWN: 240 projection workgroups) 298.4 / 301.0 for 6 tokens at 640, 321.6 / 321.9 for 12 at
+// 2475, and at 40 the two launches: 291.5 (301 when the projection's workgroups took the attention there too).
 constexpr int QA_READY_SLOT = QKV_ATTN_READY_SLOT;   // ints between two heads' counters
 
 struct HeadWaitHook {
@@ -3650,8 +3677,8 @@ __global__ __launch_bounds__(512) void k_qkv_attn(const bf16_t* W, const bf16_t*
     const int split = (id - n_gemm) / g.nq, head = id - n_gemm - split * g.nq;
     int* rdy = ready + head * QA_READY_SLOT;
     const HeadWaitHook wait{rdy, G, abort_word, limit, halted};
-    if (a.n_splits == 1) {
-      AttnWhole<DH, 2, true> at(a, head);
+    if (pos0 + M <= ATTN_HEAD_MAX_CTX) {
+      AttnWhole<DH, true> at(a, head);
       at.request(safe_end);
       wait();
       at.run(sm.attn, safe_end, halted);
@@ -3678,51 +3705,70 @@ static long resident_capacity(const void* kernel) {
 }
 
 template <int P, int RT, int DH, bool LN, bool OWN>
-static hipError_t launch_qkv_attn_cfg(const GemmArgs& g, const AttnArgs& a0, int* ready, unsigned* abort_word, int safe_end, int limit,
-                                      bool* launched, hipStream_t s) {
-  constexpr int U = gemm_buffers(RT, P), G = 3 * DH / (16 * RT);
-  static const long capacity = resident_capacity(reinterpret_cast<const void*>(k_qkv_attn<P, RT, U, DH, LN, OWN>));
-  AttnArgs a = a0;
-  const int n_gemm = g.n_rows / (16 * RT), total = a.pos0 + a.M;
-  long wgs = n_gemm;
-  if constexpr (OWN) {
-    // up to 256 positions a workgroup takes a whole head (one step per wavefront, no records: 68M draft at 250 tokens 69.9 us a
-    // token, 71.4 in ranges); beyond that ranges of at least 256 (multi-query draft at 2040 337.8 us a token, 374 in ranges of at least 128)
-    const long room = (capacity - n_gemm) / g.nq;
-    if (room < (total <= ATTN_HEAD_MAX_CTX ? 1 : 2)) return hipSuccess;
-    int len = (int)((total + room - 1) / room + 31) / 32 * 32;
-    if (len < ATTN_HEAD_MAX_CTX) len = ATTN_HEAD_MAX_CTX;
-    a.split_len = len; a.n_splits = (total + len - 1) / len;
-    wgs += (long)g.nq * a.n_splits;
+static long qkv_attn_capacity() {
+  static const long c = resident_capacity(reinterpret_cast<const void*>(k_qkv_attn<P, RT, gemm_buffers(RT, P), DH, LN, OWN>));
+  return c;
+}
+
+// How the context is dealt, and which form the launch takes.  The deal is the one of the workgroups that shared the projection's
+// before there were others: a workgroup per G-th of the context, 128 positions at least, where heads have their own K / V; the ranges of
+// the stand-alone attention elsewhere.  It decides the order of the sums, so a form is chosen by what fits and the deal is left alone.
+QkvAttnPlan qkv_attn_plan(int n_rows, int nq, int nkv, int dh, bool layernorm, int total, int rt, long cap_shared, long cap_own) {
+  QkvAttnPlan p{0, 0, 0, 0};
+  const long n_gemm = n_rows / (16 * rt);
+  const bool whole = total <= ATTN_HEAD_MAX_CTX, sharing = !layernorm && nq == nkv && n_gemm <= cap_shared;
+  if (sharing) {
+    const int G = 3 * dh / (16 * rt);
+    p.split_len = ((total + G - 1) / G + 31) / 32 * 32;
+    if (p.split_len < ATTN_SPLIT_LEN) p.split_len = ATTN_SPLIT_LEN;
   } else {
-    if (total <= ATTN_HEAD_MAX_CTX) return hipSuccess;
-    int len = ((total + G - 1) / G + 31) / 32 * 32;
-    if (len < ATTN_SPLIT_LEN) len = ATTN_SPLIT_LEN;                      // (the records are sized for ranges of at least this)
-    a.split_len = len; a.n_splits = (total + len - 1) / len;
+    p.split_len = attn_split_len(total);
   }
-  if (wgs > capacity) return hipSuccess;          // not all resident at once
-  hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, LN, OWN>), dim3((unsigned)wgs), dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M,
-                     g.nq | (g.nkv << 16), g.pos0, g, a, ready, abort_word, safe_end, limit);
+  p.n_splits = (total + p.split_len - 1) / p.split_len;
+  const long own = n_gemm + (long)nq * (whole ? 1 : p.n_splits);
+  if (own <= cap_own) { p.form = 2; p.wgs = own; }                // all resident at once
+  else if (sharing && !whole) { p.form = 1; p.wgs = n_gemm; }
+  return p;
+}
+int qkv_attn_rt(int n_rows) { return (n_rows % 64 == 0 && n_rows / 64 >= 200) ? 4 : 2; }      // the row tiles of the stand-alone QKV launch
+
+// Workgroups of the two forms that the GPU holds at once.
+template <int P, int RT, int DH>
+static void qkv_attn_capacities_rt(bool ln, long* shared, long* own) {
+  *shared = qkv_attn_capacity<P, RT, DH, false, false>();
+  *own = ln ? qkv_attn_capacity<P, RT, DH, true, true>() : qkv_attn_capacity<P, RT, DH, false, true>();
+}
+#define QKV_ATTN_BY_SHAPE(f, p1, rt, dh, ...) \
+  ((dh) == 128 ? ((rt) == 4 ? ((p1) ? f<1, 4, 128>(__VA_ARGS__) : f<2, 4, 128>(__VA_ARGS__)) : ((p1) ? f<1, 2, 128>(__VA_ARGS__) : f<2, 2, 128>(__VA_ARGS__))) \
+               : ((rt) == 4 ? ((p1) ? f<1, 4, 64>(__VA_ARGS__) : f<2, 4, 64>(__VA_ARGS__)) : ((p1) ? f<1, 2, 64>(__VA_ARGS__) : f<2, 2, 64>(__VA_ARGS__))))
+void qkv_attn_capacities(int M, int rt, int dh, bool layernorm, long* shared, long* own) {
+  QKV_ATTN_BY_SHAPE(qkv_attn_capacities_rt, M <= 8, rt, dh, layernorm, shared, own);
+}
+
+template <int P, int RT, int DH>
+static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit,
+                                     bool* launched, hipStream_t s) {
+  constexpr int U = gemm_buffers(RT, P);
+  const bool ln = g.sum != nullptr;
+  long cap_shared, cap_own;
+  qkv_attn_capacities_rt<P, RT, DH>(ln, &cap_shared, &cap_own);
+  const QkvAttnPlan p = qkv_attn_plan(g.n_rows, g.nq, g.nkv, DH, ln, a.pos0 + a.M, RT, cap_shared, cap_own);
+  a.split_len = p.split_len; a.n_splits = p.n_splits;
+  if (p.form == 0) return hipSuccess;
+  const dim3 grid((unsigned)p.wgs);
+#define QKV_ATTN_ARGS grid, dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M, g.nq | (g.nkv << 16), g.pos0, g, a, ready, abort_word, safe_end, limit
+  if (p.form == 1) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, false>), QKV_ATTN_ARGS);
+  else if (ln) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, true, true>), QKV_ATTN_ARGS);
+  else hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, true>), QKV_ATTN_ARGS);
+#undef QKV_ATTN_ARGS
   *launched = true;
   return hipGetLastError();
 }
-template <int RT, int DH>
-static hipError_t launch_qkv_attn_rt(const GemmArgs& g, const AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit,
-                                     bool* launched, hipStream_t s) {
-  const bool p1 = g.M <= 8;
-  if (g.sum != nullptr) return p1 ? launch_qkv_attn_cfg<1, RT, DH, true, true>(g, a, ready, abort_word, safe_end, limit, launched, s)
-                                  : launch_qkv_attn_cfg<2, RT, DH, true, true>(g, a, ready, abort_word, safe_end, limit, launched, s);
-  const hipError_t e = p1 ? launch_qkv_attn_cfg<1, RT, DH, false, true>(g, a, ready, abort_word, safe_end, limit, launched, s)
-                          : launch_qkv_attn_cfg<2, RT, DH, false, true>(g, a, ready, abort_word, safe_end, limit, launched, s);
-  if (e != hipSuccess || *launched || g.nq != g.nkv) return e;
-  return p1 ? launch_qkv_attn_cfg<1, RT, DH, false, false>(g, a, ready, abort_word, safe_end, limit, launched, s)
-            : launch_qkv_attn_cfg<2, RT, DH, false, false>(g, a, ready, abort_word, safe_end, limit, launched, s);
-}
 
-// Sets *launched and enqueues the fused launch when the shape allows it; otherwise leaves *launched false and does
-// nothing (the caller then launches the QKV projection and the attention separately).  a.split_len / a.n_splits are
-// chosen here.
-hipError_t launch_qkv_attn(const GemmArgs& g0, const AttnArgs& a, int* ready, unsigned* abort_word, int limit, bool* launched, hipStream_t s) {
+// Sets *launched and enqueues the fused launch when the shape allows it; otherwise leaves *launched false and enqueues
+// nothing (the caller then launches the QKV projection and the attention separately, the latter over a.split_len / a.n_splits,
+// which are chosen here either way).
+hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned* abort_word, int limit, bool* launched, hipStream_t s) {
   *launched = false;
   if (ready == nullptr || abort_word == nullptr) return hipSuccess;
   if (g0.nkv < 1 || g0.nq % g0.nkv != 0 || (g0.dh != 64 && g0.dh != 128)) return hipSuccess;
@@ -3731,15 +3777,11 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, const AttnArgs& a, int* ready, un
   if (a.M != g0.M || a.nq != g0.nq || a.nkv != g0.nkv || a.dh != g0.dh || a.pos0 != g0.pos0 || a.counters == nullptr) return hipErrorInvalidValue;
   GemmArgs g = g0;
   g.n_split = 1;
-  const int n = g.n_rows, pt = a.page_tokens;
-  const int rt = (n % 64 == 0 && n / 64 >= 200) ? 4 : 2;                 // the row tiles of the stand-alone QKV launch
+  const int pt = a.page_tokens;
   // positions below safe_end share no 128-byte line with the block's own positions: K rows are 128 bytes or more per
   // position; a V^T row holds the positions of one page, 64 to a line
   const int safe_end = (pt % 64 == 0) ? (a.pos0 & ~63) : (a.pos0 / pt) * pt;
-  if (g.dh == 128) return rt == 4 ? launch_qkv_attn_rt<4, 128>(g, a, ready, abort_word, safe_end, limit, launched, s)
-                                  : launch_qkv_attn_rt<2, 128>(g, a, ready, abort_word, safe_end, limit, launched, s);
-  return rt == 4 ? launch_qkv_attn_rt<4, 64>(g, a, ready, abort_word, safe_end, limit, launched, s)
-                 : launch_qkv_attn_rt<2, 64>(g, a, ready, abort_word, safe_end, limit, launched, s);
+  return QKV_ATTN_BY_SHAPE(launch_qkv_attn_rt, g.M <= 8, qkv_attn_rt(g.n_rows), g.dh, g, a, ready, abort_word, safe_end, limit, launched, s);
 }
 
 

@@ -340,6 +340,33 @@ def test_tiled_prompt_attention_only_where_a_page_offset_fits_32_bits(nh, nkv, d
     B.lib().disco_model_destroy(m)
 
 
+@pytest.mark.parametrize("family, nh, nkv, dh, per_head", [
+    (1, 12, 12, 64, 6), (1, 4, 4, 64, 6), (1, 40, 40, 128, 6), (1, 20, 20, 128, 12), (1, 80, 80, 64, 3), (1, 48, 48, 128, 0),
+    (1, 16, 4, 128, 0), (1, 6, 2, 64, 0), (0, 12, 1, 64, 0), (0, 48, 1, 128, 0), (0, 12, 12, 64, 0)])
+def test_the_deal_of_the_context_does_not_depend_on_the_launch(family, nh, nkv, dh, per_head):
+    """The deal decides the order in which the attention adds up, so it is a function of the model and the length alone: a
+    `per_head`-th of the context, 128 positions at least and in steps of 32, in models with K / V heads of their own whose
+    projection has at most 256 workgroups (per_head of them for each head); one, 128, 256, 512 or 1024 positions a range elsewhere."""
+    rc, m = _model(family=family, n_heads=nh, n_kv_heads=nkv, d_head=dh)
+    assert rc == 0
+    gemm = (nh + 2 * nkv) * dh
+    rows = 64 if gemm % 64 == 0 and gemm // 64 >= 200 else 32
+    for ctx in list(range(0, 1700, 7)) + [255, 256, 2475, 4000, 6000]:
+        for n in (1, 6, 16):
+            total = ctx + n
+            if per_head:
+                want = max(128, -(-(-(-total // per_head)) // 32) * 32)
+            else:
+                want = next(l for most, l in ((256, 256), (768, 128), (1536, 256), (3072, 512), (1 << 30, 1024)) if total <= most)
+            ranges = -(-total // want)
+            plan = B.disco_qkv_attn_plan(m, n, ctx, 256)
+            assert (plan["range"], plan["ranges"], plan["row_tiles"]) == (want, ranges, rows // 16), (total, plan)
+            own = gemm // rows + nh * (1 if total <= 256 else ranges)
+            form = "own" if own <= 256 else ("shared" if per_head and total > 256 else "separate")
+            assert plan["form"] == form and plan["workgroups"] == {"own": own, "shared": gemm // rows, "separate": 0}[form], (total, plan)
+    B.lib().disco_model_destroy(m)
+
+
 def test_heuristic_lookahead_rule_by_hand():
     """The acceptance-following lookahead rule (the reading of the paper's unnamed heuristic: +up after a fully
     accepted block, -down otherwise, inside [1, cap]; nothing drafted: unchanged), on hand cases and on the

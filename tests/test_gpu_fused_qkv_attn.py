@@ -274,3 +274,62 @@ def test_fused_launch_with_workgroups_of_its_own_for_the_attention(si):
                 okv.rollback(ctx)
                 check_logits(lg0, ref, "fused: " + tag)
                 check_argmax(am0, ref, "fused " + tag)
+
+
+@pytest.mark.parametrize("family, nh, nkv, dh", [("A", 4, 1, 64), ("A", 3, 3, 128), ("B", 6, 2, 64), ("B", 4, 1, 128)])
+@pytest.mark.parametrize("ctx", [120, 250, 700, 1500, 2400])
+def test_launch_structure_does_not_show_in_models_without_a_kv_head_per_head(family, nh, nkv, dh, ctx):
+    """Shared K / V heads and LayerNorm models: one launch or two, the context is dealt the same way: logits and cache bit by bit."""
+    shape = W.ModelShape(family, 2, 256, nh, dh, nkv, 512, 512)
+    gm = B.DiscoModel(shape, W.make_weights(shape, 90, "bf16", sigma=0.05), dev())
+    fill = W.make_kv_fill(shape, ctx, 3).to(dev())
+    for M in (1, 8, 9, 16):
+        assert B.disco_qkv_attn_plan(gm.handle, M, ctx)["form"] == "own"
+        blk, out = W.make_tokens(80 + M, M, shape.vocab).tolist(), []
+        for mode in (0, 2):
+            gkv, ws = B.DiscoKV(gm, ctx + 32, 16), gm.workspace(16, ctx + 32)
+            gkv.buf.zero_()
+            gkv.fill(fill)
+            out.append((_verify(gm, gkv, ws, blk, mode)[0], gkv.buf.clone()))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), M
+
+
+def _attention_panels(shape, weights, fill, ctx, mode):
+    """Attention output of a one-layer model for 16 tokens as bytes of its two panels, and the workspace it lies in."""
+    gm = B.DiscoModel(shape, weights, dev())
+    gkv, ws = B.DiscoKV(gm, ctx + 32, 16), gm.workspace(16, ctx + 32)
+    gkv.fill(fill)
+    _verify(gm, gkv, ws, W.make_tokens(3, 16, shape.vocab).tolist(), mode)
+    r = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    d, dq = shape.d_model, shape.n_heads * shape.d_head
+    first = 2 * r(64 * d) + r(64 * dq)                # behind the residual rows, the query rows and the input panels
+    return ws.buf[first:first + 64 * dq].cpu().numpy().tobytes(), ws.buf.cpu().numpy().tobytes(), B.disco_qkv_attn_plan(gm.handle, 16, ctx)["form"]
+
+
+@pytest.mark.parametrize("ctx", [20, 112, 113, 150, 240])
+def test_a_whole_head_is_merged_as_its_ranges_are(ctx):
+    """K / V heads of their own, up to 256 positions: one workgroup per head merges as two ranges of 128 do.  The persistent launch (mode
+    1) has those ranges; its panels are looked for in its workspace."""
+    shape = W.ModelShape("B", 1, 768, 12, 64, 12, 3072, 512)
+    w, fill = W.make_weights(shape, 5, "bf16", sigma=0.05), W.make_kv_fill(shape, ctx, 3).to(dev())
+    panels, _, form = _attention_panels(shape, w, fill, ctx, 0)
+    assert form == "own" and panels in _attention_panels(shape, w, fill, ctx, 1)[1]
+
+
+@pytest.mark.parametrize("many, dh", [(20, 128), (40, 64)])
+@pytest.mark.parametrize("ctx", [100, 230, 300, 1500])
+def test_the_form_of_the_shared_launch_does_not_show(many, dh, ctx):
+    """Four heads take workgroups of their own; many fill the chip, so their projection workgroups become the attention's (two
+    launches up to 256 positions).  The first four heads' panels are the same bytes."""
+    got = []
+    for nh in (4, many):
+        shape = W.ModelShape("B", 1, 256, nh, dh, nh, 256, 512)
+        w, fill, dq = W.make_weights(shape, 6, "bf16", sigma=0.05), W.make_kv_fill(shape, ctx, 3).to(dev()), nh * dh
+        if got:                                       # the first heads' rows of the projection and of the cache are the small model's
+            w["l0.wqkv"].view(3, dq, 256)[:, :4 * dh] = got[0][1]["l0.wqkv"].view(3, 4 * dh, 256)
+            w["tok_emb"], w["l0.norm1_g"] = got[0][1]["tok_emb"], got[0][1]["l0.norm1_g"]
+            fill[:, :, :, :4] = got[0][2]
+        panels, _, form = _attention_panels(shape, w, fill.contiguous(), ctx, 0)
+        got.append((torch.frombuffer(bytearray(panels), dtype=torch.int16).view(2, dq // 32, 512)[:, :4 * dh // 32], w, fill, form))
+    assert got[0][3] == "own" and got[1][3] == ("shared" if ctx + 16 > 256 else "separate")
+    assert torch.equal(got[0][0], got[1][0]) and got[0][0].any()
