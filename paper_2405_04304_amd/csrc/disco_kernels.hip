@@ -2045,7 +2045,7 @@ struct SoftStat { float m; int i; float S, T; };
 __device__ __forceinline__ SoftStat stat_rescaled(SoftStat a, const float m) {      // relative to another maximum, m >= a.m
   const float d = a.m - m, f = expf(d);
   a.T = f > 0.f ? f * (a.T + d * a.S) : 0.f;                                        // (nothing was there: 0, not 0 * -inf)
-  a.S = f > 0.f ? f * a.S : 0.f;
+  a.S = a.S == 0.f ? 0.f : f * a.S;                                                 // (a logit that is not a number stays one however small its neighbours)
   return a;
 }
 

@@ -45,3 +45,25 @@ def test_embedding_norm_panels_bit_by_bit(d, chunk):
     want = (hi + lo) * rstd
     bad = np.nonzero(got != want)[0]
     assert bad.size == 0, (bad.size, bad[:8], got[bad[:4]], want[bad[:4]])
+
+
+@pytest.mark.parametrize("vocab", [4096, 32000])
+@pytest.mark.parametrize("force", [None, 7])
+def test_features_of_logits_that_are_not_numbers(vocab, force):
+    """A NaN logit shows in every feature, also where its 256 neighbours (a wavefront's share) weigh nothing beside the largest logit or
+    are NaN themselves; a wavefront's share of -inf weighs nothing.  One workgroup and many agree."""
+    from test_gpu_parity import _run_classify
+    clf = W.make_classifier(100)
+    base = torch.randn(vocab, generator=torch.Generator().manual_seed(1))
+    for first, width, value, around in ((1100, 1, float("nan"), -300.0), (1024, 256, float("nan"), None),
+                                        (1024, 256, -float("inf"), None), (2048, 1024, -float("inf"), None)):
+        x = base.clone()
+        if around is not None:
+            x[1024:1280] = around
+        x[first:first + width] = value
+        one, many = (_run_classify(x, clf, 3, 0.5, force, multi=m)[0] for m in (False, True))
+        if value != value:
+            assert all(f != f for f in list(one.feats)[:11]) and all(f != f for f in list(many.feats)[:11]), (first, list(many.feats))
+        else:
+            assert torch.allclose(torch.tensor(list(many.feats)), torch.tensor(list(one.feats)), rtol=1e-5, atol=1e-7)
+        assert one.token == many.token
