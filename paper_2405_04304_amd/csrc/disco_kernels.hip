@@ -1377,12 +1377,12 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const int head, co
   }
 }
 
-// Leading arguments of the attention kernels (see k_gemm); heads: query heads + 65536 * K / V heads.
-#define ATTN_EARLY const bf16_t* kv_layer, const int32_t* page_table, const float* q, const uint32_t* gate, int page_tokens, int heads, int ldq, \
+// Leading arguments of the attention kernels (see k_gemm).  A query row is as wide as its heads (the launcher checks it).
+#define ATTN_EARLY const bf16_t* kv_layer, const int32_t* page_table, const float* q, const uint32_t* gate, int page_tokens, int nq, int nkv, \
                    int pos0, int M, int split_len
 #define ATTN_EARLY_SET(a) do { a.kv_layer = kv_layer; a.page_table = page_table; a.q = q; a.gate = gate; a.page_tokens = page_tokens; \
-  a.nq = heads & 0xffff; a.nkv = heads >> 16; a.ldq = ldq; a.pos0 = pos0; a.M = M; a.split_len = split_len; } while (0)
-#define ATTN_EARLY_ARGS(a) a.kv_layer, a.page_table, a.q, a.gate, a.page_tokens, a.nq | (a.nkv << 16), a.ldq, a.pos0, a.M, a.split_len
+  a.nq = nq; a.nkv = nkv; a.ldq = nq * DH; a.pos0 = pos0; a.M = M; a.split_len = split_len; } while (0)
+#define ATTN_EARLY_ARGS(a) a.kv_layer, a.page_table, a.q, a.gate, a.page_tokens, a.nq, a.nkv, a.pos0, a.M, a.split_len
 template <int DH>
 __global__ __launch_bounds__(512) void k_attn_partial(ATTN_EARLY, AttnArgs a) {
   ATTN_EARLY_SET(a);
@@ -1474,9 +1474,9 @@ __global__ __launch_bounds__(512) void k_attn_head(ATTN_EARLY, AttnArgs a) {
 // longest ranges are scheduled first.
 constexpr int ATTN_MG = 2;
 template <int DH, bool LO>
-__global__ __launch_bounds__(512) void k_attn_groups(const bf16_t* kv_layer, const int32_t* page_table, const float* q, int page_tokens, int heads, int ldq,
+__global__ __launch_bounds__(512) void k_attn_groups(const bf16_t* kv_layer, const int32_t* page_table, const float* q, int page_tokens, int nq, int nkv, int ldq,
                                                      int pos0, int n_groups, AttnArgs a, size_t x_stride) {    // (leading arguments: see k_gemm)
-  a.kv_layer = kv_layer; a.page_table = page_table; a.q = q; a.page_tokens = page_tokens; a.nq = heads & 0xffff; a.nkv = heads >> 16;
+  a.kv_layer = kv_layer; a.page_table = page_table; a.q = q; a.page_tokens = page_tokens; a.nq = nq; a.nkv = nkv;
   a.ldq = ldq; a.pos0 = pos0; a.M = 16;
   constexpr int CT = DH / 16, NWV = 8, WKEYS = 32, STEP = NWV * WKEYS, NG = ATTN_MG;
   __shared__ f32x4 o_s[NWV][CT][64];
@@ -1754,7 +1754,7 @@ int attn_split_len(int total) {
 }
 
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s) {
-  if (a.M < 1 || a.M > 16 || a.n_splits < 1 || a.counters == nullptr) return hipErrorInvalidValue;
+  if (a.M < 1 || a.M > 16 || a.n_splits < 1 || a.counters == nullptr || a.ldq != a.nq * a.dh) return hipErrorInvalidValue;
   if (a.pos0 + a.M <= ATTN_HEAD_MAX_CTX) {
     if (a.dh == 128) hipLaunchKernelGGL(k_attn_head<128>, dim3(a.nq), dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
     else if (a.dh == 64) hipLaunchKernelGGL(k_attn_head<64>, dim3(a.nq), dim3(512), 0, s, ATTN_EARLY_ARGS(a), a);
@@ -1797,13 +1797,12 @@ hipError_t launch_attn_groups(const AttnArgs& a, int n_groups, size_t x_stride, 
     return hipGetLastError();
   }
   const dim3 g1(a.nq, (n_groups + ATTN_MG - 1) / ATTN_MG);
-  const int heads = a.nq | (a.nkv << 16);
   if (a.dh == 128) {
-    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<128, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
-    else hipLaunchKernelGGL((k_attn_groups<128, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
+    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<128, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, a.nq, a.nkv, a.ldq, a.pos0, n_groups, a, x_stride);
+    else hipLaunchKernelGGL((k_attn_groups<128, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, a.nq, a.nkv, a.ldq, a.pos0, n_groups, a, x_stride);
   } else if (a.dh == 64) {
-    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<64, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
-    else hipLaunchKernelGGL((k_attn_groups<64, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, heads, a.ldq, a.pos0, n_groups, a, x_stride);
+    if (bf16_operands) hipLaunchKernelGGL((k_attn_groups<64, false>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, a.nq, a.nkv, a.ldq, a.pos0, n_groups, a, x_stride);
+    else hipLaunchKernelGGL((k_attn_groups<64, true>), g1, dim3(512), 0, s, a.kv_layer, a.page_table, a.q, a.page_tokens, a.nq, a.nkv, a.ldq, a.pos0, n_groups, a, x_stride);
   } else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -3645,12 +3644,12 @@ struct HeadWaitHook {
   }
 };
 
-// LN: the model's norms are LayerNorms.  The leading arguments: see k_gemm; heads: query heads + 65536 * K / V heads.
+// LN: the model's norms are LayerNorms.  The leading arguments: see k_gemm.
 template <int P, int RT, int U, int DH, bool LN, bool OWN>
-__global__ __launch_bounds__(512) void k_qkv_attn(const bf16_t* W, const bf16_t* X, const uint32_t* gate, const float* ssq, int KT, int grp, int n_ssq,
-                                                  int M, int heads, int pos0, GemmArgs g, AttnArgs a, int* ready, unsigned* abort_word, int safe_end, int limit) {
-  g.W = W; g.X = X; g.gate = gate; g.ssq = ssq; g.KT = KT; g.grp = grp; g.n_ssq = n_ssq; g.M = M; a.M = M; g.pos0 = pos0; a.pos0 = pos0;
-  g.nq = heads & 0xffff; g.nkv = heads >> 16; a.nq = g.nq; a.nkv = g.nkv;
+__global__ __launch_bounds__(512) void k_qkv_attn(const bf16_t* W, const bf16_t* X, const uint32_t* gate, const float* ssq, int KT, int n_ssq,
+                                                  int M, int nq, int nkv, int pos0, GemmArgs g, AttnArgs a, int* ready, unsigned* abort_word, int safe_end, int limit) {
+  g.W = W; g.X = X; g.gate = gate; g.ssq = ssq; g.KT = KT; g.grp = DH / 32; g.n_ssq = n_ssq; g.M = M; a.M = M; g.pos0 = pos0; a.pos0 = pos0;
+  g.nq = nq; g.nkv = nkv; a.nq = nq; a.nkv = nkv;
   constexpr int UH = DH / (16 * RT), G = 3 * UH;   // workgroups per q / K / V part of a head; arrivals that a head waits for
   static_assert(UH >= 1 && UH * 16 * RT == DH, "a head part is a whole number of workgroups");
   union Smem { GemmSmem<RT, 8, LN> gemm; AttnSmem<DH, 8> attn; };
@@ -3756,7 +3755,7 @@ static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready,
   a.split_len = p.split_len; a.n_splits = p.n_splits;
   if (p.form == 0) return hipSuccess;
   const dim3 grid((unsigned)p.wgs);
-#define QKV_ATTN_ARGS grid, dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.grp, g.n_ssq, g.M, g.nq | (g.nkv << 16), g.pos0, g, a, ready, abort_word, safe_end, limit
+#define QKV_ATTN_ARGS grid, dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.n_ssq, g.M, g.nq, g.nkv, g.pos0, g, a, ready, abort_word, safe_end, limit
   if (p.form == 1) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, false>), QKV_ATTN_ARGS);
   else if (ln) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, true, true>), QKV_ATTN_ARGS);
   else hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, true>), QKV_ATTN_ARGS);
