@@ -30,9 +30,11 @@ int disco_set_wait_limit(int polls);
  * page_tokens tokens per page, without a launch.  out[0 .. 3]: QKV projection, O-projection, MLP input, MLP output:
  * the workgroup tile (0: 128 rows x 256 panel columns, 1: 256 x 256, 2: 512 x 256, 3: 128 x 128), or 100 + S where
  * the matrix is cut along K into S ranges; out[4]: 1 if the attention runs in LDS tiles; out[5]: 1 if the LayerNorm
- * launches take whole groups of 16 tokens.  0, or DISCO_EINVAL.                                            */
+ * launches take whole groups of 16 tokens; out[6 .. 9]: stages of the copy ring of the four matrices; out[10], out[11]: 1
+ * if the QKV projection / the MLP input forms 1 / rms of its rows itself, 0 if a launch in front does (or the norms are
+ * LayerNorms).  0, or DISCO_EINVAL.                                                                         */
 struct disco_model;
-int disco_prefill_plan(const struct disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[6]);
+int disco_prefill_plan(const struct disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[12]);
 
 /* Testing and measurement aid: how launch mode 0 runs the QKV projection and the attention of a layer for a block of
  * n_tokens behind ctx cached positions, without a launch.  out[0]: 0 two launches, 1 one launch whose projection workgroups

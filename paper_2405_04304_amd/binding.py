@@ -346,10 +346,11 @@ def disco_set_wait_limit(polls: int) -> int:
 
 
 def disco_prefill_plan(model_handle, n_tokens: int, flags: int = 0, page_tokens: int = 16) -> dict:
-    """The kernels a prompt pass would launch (disco_bench.h): tile codes of its four matrices, attention, LayerNorm."""
-    out = (C.c_int * 6)()
+    """The kernels a prompt pass would launch (disco_bench.h): tile codes of its four matrices, attention, LayerNorm, copy rings, 1 / rms."""
+    out = (C.c_int * 12)()
     _check(lib().disco_prefill_plan(model_handle, n_tokens, flags, page_tokens, out))
-    return {"qkv": out[0], "o": out[1], "mlp_in": out[2], "mlp_out": out[3], "attn_tiles": bool(out[4]), "norm_groups": bool(out[5])}
+    return {"qkv": out[0], "o": out[1], "mlp_in": out[2], "mlp_out": out[3], "attn_tiles": bool(out[4]), "norm_groups": bool(out[5]),
+            "stages": dict(zip(("qkv", "o", "mlp_in", "mlp_out"), out[6:10])), "rms_in_launch": {"qkv": bool(out[10]), "mlp_in": bool(out[11])}}
 
 
 def disco_qkv_attn_plan(model_handle, n_tokens: int, ctx: int, capacity: int = 0) -> dict:

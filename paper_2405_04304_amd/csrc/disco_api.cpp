@@ -1059,7 +1059,7 @@ int disco_set_wait_limit(int polls) {
   return prev;
 }
 
-int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[6]) {
+int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int page_tokens, int out[12]) {
   if (!m || !out || n_tokens < 1 || n_tokens > DISCO_PREFILL_MAX || page_tokens < 4 || page_tokens % 4) return fail(DISCO_EINVAL, "bad argument");
   const disco_model_desc& d = m->d;
   const bool fam_a = d.family == DISCO_FAMILY_A, hi = (flags & DISCO_PREFILL_BF16_ACTIVATIONS) != 0;
@@ -1069,6 +1069,8 @@ int disco_prefill_plan(const disco_model* m, int n_tokens, unsigned flags, int p
   for (int i = 0; i < 4; ++i) {
     const DensePlan p = gemm_dense_plan(s[i].rows, s[i].k / 32, G, hi, SIZE_MAX);
     out[i] = p.split > 1 ? 100 + p.split : p.tile;
+    out[6 + i] = p.stages;
+    if (i % 2 == 0) out[10 + i / 2] = !fam_a && dense_rms_in_launch(p, d.d_model / 16) ? 1 : 0;
   }
   out[4] = attn_tiles_fit(d.n_heads, d.n_kv_heads, d.d_head, page_tokens, G) ? 1 : 0;
   out[5] = fam_a && norm_groups_fit(d.d_model, G) ? 1 : 0;

@@ -194,7 +194,8 @@ hipError_t launch_gemm_dense(const DenseArgs& a, int epi, hipStream_t s);
 // What the prompt pass launches for a matrix of n_rows x 32 KT and n_groups groups: workgroup tile (0 .. 3, see the function),
 // K ranges (1: not cut), workgroups per range and bytes of partial sums (at most plane_bytes); whether its attention and its
 // LayerNorms take the tiled kernels.
-struct DensePlan { int tile, split; long wgs; size_t plane_bytes; };
+struct DensePlan { int tile, split; long wgs; size_t plane_bytes; int stages /* of the copy ring */; };
+bool dense_rms_in_launch(const DensePlan& p, int n_ssq);         // (for matrices that read a normalised row)
 DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t plane_bytes);
 bool attn_tiles_fit(int nq, int nkv, int dh, int page_tokens, int n_groups);
 bool norm_groups_fit(int d, int n_groups);

@@ -3508,8 +3508,12 @@ DensePlan gemm_dense_plan(int n_rows, int KT, int n_groups, bool hi_only, size_t
     if (us < best) { best = us; split = S; }
   }
   const int tile = split > 1 ? 1 : (c3 < c0 ? 3 : (c2 < c0 && c2 < c1 ? 2 : (c1 < c0 ? 1 : 0)));
-  return DensePlan{tile, split, wgs[tile], split > 1 ? (size_t)wgs[1] * split * split_unit_bytes(hi_only) : 0};
+  const int stages = tile == 0 ? (wgs[0] <= 256 && KT >= 64 ? 6 : 3) : (tile == 1 ? 4 : (tile == 2 ? 3 : 8));
+  return DensePlan{tile, split, wgs[tile], split > 1 ? (size_t)wgs[1] * split * split_unit_bytes(hi_only) : 0, stages};
 }
+// A matrix that reads a normalised row forms 1 / rms itself (narrow models: 64 sums of squares a row at most); a wide row's sums are read by
+// every workgroup of its tokens, so one launch in front adds them up for all, and so it is where the matrix is cut along K.
+bool dense_rms_in_launch(const DensePlan& p, int n_ssq) { return p.split == 1 && n_ssq <= 64; }
 
 template <int EPI, int WR, int WC, int R2, int C2, int NST, int OCC, bool HI>
 static void launch_tiles(const DenseArgs& d, const dim3 grid, hipStream_t s) {
@@ -3517,16 +3521,18 @@ static void launch_tiles(const DenseArgs& d, const dim3 grid, hipStream_t s) {
                      d.k_split, d);
 }
 
-// Ring depths: a grid of at most a workgroup per compute unit takes the whole LDS (c0 six stages instead of three, c3 eight): with two resident
-// workgroups one computes while the other waits for its copies, a lone one has only its own ring to wait with
-// (68M shape at 511 tokens: 2304 and 768 rows, K 768, 12.4 -> 11.0 and 12.7 -> 11.3 us a launch, 6144 rows 15.3 either way).
+// Ring depths: a grid of at most a workgroup per compute unit takes the whole LDS: with two resident workgroups one computes while the
+// other waits for its copies, a lone one has only its own ring to wait with.  c3 eight stages instead of three (68M shape at 511
+// tokens: 2304 and 768 rows, K 768, 12.4 -> 11.0 and 12.7 -> 11.3 us a launch).  c0 six instead of three from K 2048 on, a whole pass: 13B layer
+// at 130 tokens 358 -> 350 us, at 300 in bf16 391 -> 386, multi-query target layer at 1000 in bf16 939 -> 928, four layers of 2048 at 511 in bf16
+// 545.6 -> 540; with K 768 filling the ring costs more than it hides (68M shape at 511 tokens 142.3 with three, 143.2 with six, at 1000
+// 194.0 and 195.3).
 template <int EPI, bool HI>
 static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   DenseArgs d = d0;
   const DensePlan p = gemm_dense_plan(d.g.n_rows, d.g.KT, d.n_groups, HI, d.g.planes != nullptr ? d.plane_bytes : 0);
   const dim3 grid(8u * (unsigned)((p.wgs * p.split + 7) / 8));
-  if (d.g.ssq != nullptr && (p.split > 1 || d.g.n_ssq > 64)) {
-    // (a wide row's sums are read by every workgroup of its tokens: one launch for all of them)
+  if (d.g.ssq != nullptr && !dense_rms_in_launch(p, d.g.n_ssq)) {
     const hipError_t e = launch_rstd_groups(d.g.ssq, d.g.n_ssq, d.g.d_in, d.g.eps, d.rstd, d.n_groups, s);
     if (e != hipSuccess) return e;
     d.g.ssq = nullptr;
@@ -3540,7 +3546,7 @@ static hipError_t launch_gemm_tile(const DenseArgs& d0, hipStream_t s) {
   }
   switch (p.tile) {
     case 0:
-      if (p.wgs <= 256) launch_tiles<EPI, 2, 4, 2, 2, 6, 2, HI>(d, grid, s);
+      if (p.stages == 6) launch_tiles<EPI, 2, 4, 2, 2, 6, 2, HI>(d, grid, s);
       else launch_tiles<EPI, 2, 4, 2, 2, 3, 4, HI>(d, grid, s);
       break;
     case 1: launch_tiles<EPI, 2, 4, 4, 2, 4, 2, HI>(d, grid, s); break;

@@ -323,6 +323,30 @@ def test_tile_cases_cover_the_launch_rule_of_the_prompt_pass():
     assert len(chosen) >= 30 and not chosen - covered, chosen - covered
 
 
+def test_tile_cases_cover_copy_rings_and_the_source_of_the_norm():
+    """The finer key of the same rule: (epilogue, tile or K ranges, precision, stages of the copy ring, who forms 1 / rms, in the launch or
+    one before it; none in models of LayerNorms and for matrices that read no normalised row)."""
+    from test_gpu_prefill import MORE_TILE_CASES, TILE_CASES
+
+    def keys(shape, lengths):
+        rc, h = _model(family=0 if shape.family == "A" else 1, n_layers=1, d_model=shape.d_model, n_heads=shape.n_heads, d_head=shape.d_head,
+                       n_kv_heads=shape.n_kv_heads, d_ff=shape.d_ff, vocab=512, max_pos=8192)
+        assert rc == 0
+        out, fam_b = set(), shape.family == "B"
+        epi = {"qkv": "qkv", "o": "residual", "mlp_in": "swiglu" if fam_b else "gelu", "mlp_out": "residual"}
+        for n in lengths:
+            for flags in (0, B.PREFILL_BF16_ACTIVATIONS):
+                p = B.disco_prefill_plan(h, n, flags)
+                out |= {(e, "s" if p[k] > 100 else p[k], bool(flags), p["stages"][k], p["rms_in_launch"].get(k) if fam_b else None) for k, e in epi.items()}
+        B.lib().disco_model_destroy(h)
+        return out
+
+    gqa = W.ModelShape("B", 4, 2048, 16, 128, 4, 5632, 32000)
+    chosen = set().union(*(keys(s, range(1, 3002, 16)) for s in (W.CFG0_TARGET, W.CFG1_DRAFT, W.CFG2_TARGET, W.CFG3_TARGET, W.CFG3_DRAFT, gqa)))
+    covered = set().union(*(keys(shape, [n]) for shape, pre, n, *_ in TILE_CASES + MORE_TILE_CASES))
+    assert len(chosen) >= 55 and not chosen - covered, chosen - covered
+
+
 @pytest.mark.parametrize("nh, nkv, dh", [(40, 40, 128), (48, 1, 128), (32, 8, 64), (32, 1, 64)])
 def test_tiled_prompt_attention_only_where_a_page_offset_fits_32_bits(nh, nkv, dh):
     """The tiled kernel's offsets inside a page are 32-bit numbers of elements: a page of 2^32 elements or more (a cache kept as

@@ -397,3 +397,35 @@ def test_engine_uses_the_dense_pass_and_matches_the_oracle_loop():
                 break
         else:
             assert gpu["tokens"] == orc["tokens"] == ref
+
+
+# What the list above leaves out of the rule's finer choices (depth of the copy ring, who forms 1 / rms, the family where it has its own
+# instances): rows of more than 64 sums of squares over every tile, and the six-stage ring (K of 2048 and more) over every epilogue.
+MORE_TILE_CASES = [
+    (_one("B", 1088, 43, 128, 43, 8256), 3, 37, {"qkv": 3, "mlp_in": 3}, {"qkv": 3, "mlp_in": 3}),
+    (_one("B", 1088, 43, 128, 43, 8256), 0, 299, {"qkv": 1, "mlp_in": 1}, {"qkv": 1, "mlp_in": 1}),
+    (_one("B", 1088, 43, 128, 43, 8256), 0, 395, {"qkv": 0, "mlp_in": 0}, {"qkv": 1, "mlp_in": 1}),
+    (_one("B", 1088, 43, 128, 43, 8256), 5, 795, {"qkv": 2, "mlp_in": 2}, {"qkv": 0, "mlp_in": 0}),
+    (_one("A", 64, 43, 128, 43, 64), 0, 299, {"qkv": 1}, {"qkv": 1}),
+    (_one("A", 64, 43, 128, 43, 64), 2, 395, {"qkv": 0}, {"qkv": 1}),
+    (_one("A", 64, 43, 128, 43, 64), 0, 795, {"qkv": 2}, {"qkv": 0}),
+    (_one("B", 2048, 29, 128, 29, 5568), 0, 139, {"qkv": 0, "mlp_in": 0}, {"qkv": 3, "mlp_in": 3}),
+    (_one("B", 2048, 29, 128, 29, 5568), 4, 299, {}, {"qkv": 0, "mlp_in": 0}),
+    (_one("A", 2048, 29, 128, 29, 11136), 0, 139, {"qkv": 0, "mlp_in": 0}, {"qkv": 3, "mlp_in": 3}),
+    (_one("A", 2048, 29, 128, 29, 11136), 1, 299, {}, {"qkv": 0, "mlp_in": 0}),
+    (_one("B", 8000, 1, 64, 1, 2048), 0, 325, {"mlp_out": 0}, {}),
+    (_one("A", 8000, 1, 64, 1, 2048), 0, 785, {}, {"mlp_out": 0}),
+]
+
+
+@pytest.mark.parametrize("flags", [0, BF16_ACT])
+@pytest.mark.parametrize("case", range(len(MORE_TILE_CASES)))
+def test_prefill_every_copy_ring_and_source_of_the_norm(case, flags):
+    """As test_prefill_every_tile_and_epilogue, over the second list."""
+    shape, pre, n, *want = MORE_TILE_CASES[case]
+    gm = _smooth_model(shape, 71)
+    plan = B.disco_prefill_plan(gm.handle, n, flags)
+    for what, code in want[1 if flags else 0].items():
+        assert plan[what] == code, (what, plan)
+    print(f"[prefill] rings: {shape.family} d {shape.d_model} ff {shape.d_ff} n {n} pre {pre} flags {flags}: {plan}", flush=True)
+    _against_blocks(gm, pre, n, flags)
