@@ -2749,6 +2749,9 @@ hipError_t launch_accept_sample(const AcceptSampleArgs& a, hipStream_t s) {
 // units take 2.0 us a step (5000 cycles: products and masks 1800 for the two wavefronts of a SIMD, sums and sigmoid 800, backward 900,
 // update 1100), 4.4 on the fp32 matrix instruction; 1000 examples 7.6 (14.7), 200 examples with 128 units 3.5 (10.3).  More workgroups
 // would put a hand-off between workgroups (about 2.5 us) into every step.  Features that are not numbers make all parameters and the loss NaN.
+// Error against 64 bits, twelve shapes of 60 .. 2000 examples and 16 .. 128 units, ten seeds each (relative 2-norms; in brackets the fp32
+// matrix instruction): loss 6.7e-8 (8.5e-8) in the geometric mean, scores 1.04e-7 (1.07e-7), parameters 4.8e-7 (4.9e-7).  Where an
+// activation crosses the kink in one run and not in the other, either form is off by up to 2.7e-6, 2.3e-5 and 1.3e-4.
 
 constexpr int TRAIN_MAX_N = 2560;               // examples that fit in LDS (12 floats each)
 
@@ -2961,8 +2964,9 @@ __global__ __launch_bounds__(NW * 64) void k_clf_train(TrainArgs a) {
         const Bf16x3 s0 = split3(e4[q][0] * bt.x[0], e4[q][1] * bt.x[1]), s1 = split3(e4[q][2] * bt.x[2], e4[q][3] * bt.x[3]);
         const u32x4 x01 = {s0.p[0], s1.p[0], s0.p[1], s1.p[1]};
         const u32x4 x2 = {s0.p[2], s1.p[2], 0u, 0u};
-        // one opcode for all of them: the accumulator is passed on only between like instructions (16x16x16 products among them
-        // gave wrong sums where two on one accumulator stood close together)
+        // the third part takes the instruction of the other two, half of it empty.  (That is a choice, not a rule of the chip: 16x16x16 and
+        // 16x16x32 products back to back on one accumulator, either first, are exact in 51200 elements checked.  A variant that mixed them here
+        // gave wrong sums; it also read matrix results in inline assembly, which gets no wait states, see relu.)
 #pragma unroll
         for (int r = 0; r < HT; ++r) {
           const u32x4 mk = {m01[r][q], m23[r][q], m01[r][q], m23[r][q]};
@@ -3032,14 +3036,18 @@ __global__ __launch_bounds__(NW * 64) void k_clf_train(TrainArgs a) {
   if (t == NW * 64 - 1) a.params[H * 14] = b2;
 }
 
-// Shapes by the number of examples.  Up to 64: four wavefronts, a tile each; 128: eight; 256: eight with two tiles each (of 16 wavefronts with one
-// tile the update waits longer than the shared sigmoids save: 2.07 us a step against 2.32 at 200 examples and 64 units; four
+// Shapes by the number of examples, ms for 400 steps.  Up to 64, up to 32 units or above 128: four wavefronts, a tile each (64 examples: 16 units 0.302,
+// 0.322 in the next shape; 32 0.362 / 0.366; 200 1.44 / 1.97; but 64 units 0.534 / 0.480 and 128 0.816 / 0.778).  Up to 128: eight wavefronts, a tile each
+// (100 examples: 16 units 0.397, 0.497 in the next shape; 64 0.594 / 0.811; 128 0.938 / 1.374).  Up to 256: eight with two tiles each (of 16
+// wavefronts with one tile the update waits longer than the shared sigmoids save: 2.07 us a step against 2.32 at 200 examples and 64 units; four
 // wavefronts with four tiles 2.33).  Beyond that rounds of 32 tiles (16 with more than 64 units, whose masks take the registers), over
 // examples that are split anew in every step.  More than 128 units: four wavefronts, 512 registers each.
 template <int HT>
 static void launch_clf_train_ht(const TrainArgs& a, hipStream_t s) {
-  constexpr int NW = HT > 8 ? 4 : 8, TP = HT > 4 ? 2 : 4, PW = HT > NW ? NW : HT, P4 = HT > 4 ? 4 : HT, PWL = HT > 8 ? 1 : (HT > 2 ? 2 : HT);
-  if (a.n <= 64) { hipLaunchKernelGGL((k_clf_train<HT, 4, 1, P4, 64>), dim3(1), dim3(256), 0, s, a); return; }
+  constexpr int NW = HT > 8 ? 4 : 8, TP = HT > 4 ? 2 : 4, PW = HT > NW ? NW : HT, PWL = HT > 8 ? 1 : (HT > 2 ? 2 : HT), P4 = HT > 4 ? 4 : HT;
+  if constexpr (HT <= 2 || HT > 8) {
+    if (a.n <= 64) { hipLaunchKernelGGL((k_clf_train<HT, 4, 1, P4, 64>), dim3(1), dim3(256), 0, s, a); return; }
+  }
   if constexpr (HT <= 8) {
     if (a.n <= 128) { hipLaunchKernelGGL((k_clf_train<HT, 8, 1, HT, 128>), dim3(1), dim3(512), 0, s, a); return; }
     if (a.n <= 256) { hipLaunchKernelGGL((k_clf_train<HT, 8, 2, HT, 256>), dim3(1), dim3(512), 0, s, a); return; }

@@ -172,3 +172,9 @@ def test_train_shape_edges_match_oracle(n, hidden):
     """One to four tiles of examples per wavefront, operands in registers up to 256 examples and split anew in every step beyond,
     one reduction pass or several: the edges between those shapes, at the bars of the tests above."""
     test_train_tile_edges_match_oracle(n, hidden)
+
+
+@pytest.mark.parametrize("n,hidden", [(33, 32), (33, 64), (64, 65), (64, 128), (64, 129), (7, 256)])
+def test_train_up_to_64_examples_match_oracle(n, hidden):
+    """Up to 64 examples: four wavefronts up to 32 units and above 128, eight between, at the bars of the tests above."""
+    test_train_tile_edges_match_oracle(n, hidden)
