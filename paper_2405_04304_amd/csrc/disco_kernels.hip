@@ -3739,7 +3739,8 @@ QkvAttnPlan qkv_attn_plan(int n_rows, int nq, int nkv, int dh, bool layernorm, i
   }
   p.n_splits = (total + p.split_len - 1) / p.split_len;
   const long own = n_gemm + (long)nq * (whole ? 1 : p.n_splits);
-  if (own <= cap_own) { p.form = 2; p.wgs = own; }                // all resident at once
+  // (form 2 for 32-row units only: 64-row units are 200 workgroups or more, which leave room for a few head counts up to 256 positions)
+  if (rt == 2 && own <= cap_own) { p.form = 2; p.wgs = own; }     // all resident at once
   else if (sharing && !whole) { p.form = 1; p.wgs = n_gemm; }
   return p;
 }
@@ -3749,7 +3750,8 @@ int qkv_attn_rt(int n_rows) { return (n_rows % 64 == 0 && n_rows / 64 >= 200) ? 
 template <int P, int RT, int DH>
 static void qkv_attn_capacities_rt(bool ln, long* shared, long* own) {
   *shared = qkv_attn_capacity<P, RT, DH, false, false>();
-  *own = ln ? qkv_attn_capacity<P, RT, DH, true, true>() : qkv_attn_capacity<P, RT, DH, false, true>();
+  *own = 0;
+  if constexpr (RT == 2) *own = ln ? qkv_attn_capacity<P, RT, DH, true, true>() : qkv_attn_capacity<P, RT, DH, false, true>();
 }
 #define QKV_ATTN_BY_SHAPE(f, p1, rt, dh, ...) \
   ((dh) == 128 ? ((rt) == 4 ? ((p1) ? f<1, 4, 128>(__VA_ARGS__) : f<2, 4, 128>(__VA_ARGS__)) : ((p1) ? f<1, 2, 128>(__VA_ARGS__) : f<2, 2, 128>(__VA_ARGS__))) \
@@ -3771,8 +3773,10 @@ static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready,
   const dim3 grid((unsigned)p.wgs);
 #define QKV_ATTN_ARGS grid, dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.n_ssq, g.M, g.nq, g.nkv, g.pos0, g, a, ready, abort_word, safe_end, limit
   if (p.form == 1) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, false>), QKV_ATTN_ARGS);
-  else if (ln) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, true, true>), QKV_ATTN_ARGS);
-  else hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, true>), QKV_ATTN_ARGS);
+  if constexpr (RT == 2) {
+    if (p.form == 2 && ln) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, true, true>), QKV_ATTN_ARGS);
+    if (p.form == 2 && !ln) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, true>), QKV_ATTN_ARGS);
+  }
 #undef QKV_ATTN_ARGS
   *launched = true;
   return hipGetLastError();
