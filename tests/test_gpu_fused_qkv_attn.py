@@ -1,8 +1,10 @@
-"""QKV projection and attention of a layer in ONE launch (the default for models whose heads all have their own K / V
-head, RMSNorm family) against the two separate launches (launch mode 2) and against the oracle.  The fused launch deals
-the context to 3, 6 or 12 workgroups per head where the separate attention kernel uses ranges of 128 .. 1024 positions,
-so the two agree to fp32 summation order (the projection's arithmetic is the same: the cache entries of a one-layer
-model must be bitwise equal); both are held to the parity tests' bars against the oracle."""
+"""QKV projection and attention of a layer in ONE launch (where all its workgroups fit the GPU at once) against the two separate
+launches (launch mode 2) and against the oracle.  The context is dealt by a rule on the model and the length that does not depend on
+the launch: models with a K / V head per query head give it to 3, 6 or 12 ranges of 128 positions or more, where mode 2 has
+ranges of 128 .. 1024, so the two modes agree to fp32 summation order there (the projection's arithmetic is the same: the cache
+entries of a one-layer model must be bitwise equal) and bit by bit in all other models.  Both are held to the parity tests' bars against
+the oracle.  The attention has workgroups of its own, or (one projection workgroup per compute unit) shares the projection's:
+disco_qkv_attn_plan says which, and the tests that are about one form assert it."""
 import pytest
 import torch
 
@@ -333,3 +335,41 @@ def test_the_form_of_the_shared_launch_does_not_show(many, dh, ctx):
         got.append((torch.frombuffer(bytearray(panels), dtype=torch.int16).view(2, dq // 32, 512)[:, :4 * dh // 32], w, fill, form))
     assert got[0][3] == "own" and got[1][3] == ("shared" if ctx + 16 > 256 else "separate")
     assert torch.equal(got[0][0], got[1][0]) and got[0][0].any()
+
+
+# (shape, context, form): each branch that waits.  20 heads of 128 and 40 of 64 give 240 projection workgroups of 32 rows, 13B 240 of 64.
+FORMS = ((W.scaled_shape(W.CFG1_DRAFT, vocab=4096), 150, "own", 2), (W.scaled_shape(W.CFG1_DRAFT, vocab=4096), 900, "own", 2),
+         (W.ModelShape("A", 2, 256, 12, 64, 1, 512, 512), 900, "own", 2), (W.ModelShape("B", 2, 256, 20, 128, 20, 256, 512), 400, "shared", 2),
+         (W.ModelShape("B", 2, 256, 40, 64, 40, 256, 512), 900, "shared", 2), (W.ModelShape("B", 1, 256, 40, 128, 40, 256, 512), 900, "shared", 4))
+
+
+@pytest.mark.parametrize("si", range(len(FORMS)))
+def test_every_form_matches_oracle_and_reports_a_wait_that_gives_up(si):
+    """Each form at a context that reaches it, block lengths of one and two panels: against the oracle, and with the waits forced to give up at
+    once (see above: every kernel still runs to its end) NaN logits and -1, until the workspace is initialised again."""
+    shape, ctx, form, row_tiles = FORMS[si]
+    om, gm, okv, gkv, ws = setup_pair(shape, 60 + si, kv_ctx=ctx, capacity=ctx + 32, page_tokens=16, permute=True, sigma=0.05)
+    for M in (5, 13):
+        plan = B.disco_qkv_attn_plan(gm.handle, M, ctx)
+        assert plan["form"] == form and plan["row_tiles"] == row_tiles and plan["workgroups"] <= 256, plan
+        blk = W.make_tokens(50 + M, M, shape.vocab).tolist()
+        ref = om.forward(blk, okv)
+        okv.rollback(ctx)
+        want, am = _verify(gm, gkv, ws, blk, 0)
+        B.disco_kv_rollback(gkv, ctx)
+        check_logits(want, ref, f"{form}, {shape.n_heads} x {shape.d_head}, ctx {ctx}, M {M}")
+        check_argmax(am, ref, form)
+        prev = B.disco_set_wait_limit(-1)
+        try:
+            lg, gave_up = _verify(gm, gkv, ws, blk, 0)
+            B.disco_kv_rollback(gkv, ctx)
+        finally:
+            B.disco_set_wait_limit(prev)
+        assert gave_up == [-1] * M and bool(torch.isnan(lg).all())
+        lg, gave_up = _verify(gm, gkv, ws, blk, 2)       # sticky
+        B.disco_kv_rollback(gkv, ctx)
+        assert gave_up == [-1] * M and bool(torch.isnan(lg).all())
+        B.lib().disco_workspace_init(gm.handle, ws.buf.data_ptr(), ws.nbytes, 16, ctx + 32, B._stream())
+        lg, again = _verify(gm, gkv, ws, blk, 0)
+        B.disco_kv_rollback(gkv, ctx)
+        assert again == am and torch.equal(lg, want)
