@@ -464,10 +464,12 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   with a grid barrier between the phases (in a draft loop also the features / classifier and the next token's
  *   embedding, the kernel leaving at the first halting step), where the model's shapes allow it (else mode 0 is
  *   used silently); results agree with mode 0 to fp32 summation order.
- * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order (the context
- *   is dealt to the attention's workgroups differently).
- * On MI355X mode 0 is the fastest (a 13B-class verification block: 4.97 ms, against 5.03 ms in mode 2 and
- * 5.8 ms in mode 1; a 68M-class draft step: 68 us against 71 us and 139 us): a phase boundary inside a
+ * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order where every query
+ *   head has its own K / V head in the RMSNorm family (the context is dealt differently), bit for bit in other models.
+ *   No launch of it waits for another workgroup: the mode for programs that decode on many streams at once, where
+ *   mode 0's launches hold compute units for each other's waiting workgroups.
+ * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
+ * 5.69 ms in mode 1; a 68M-class draft step: 68 us against 69 us and 128 us): a phase boundary inside a
  * launch costs more than a kernel boundary there, a per-head hand-off a little less.                     */
 int disco_set_launch_mode(int mode);
 
