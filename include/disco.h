@@ -456,7 +456,8 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   layer; LM head), except that the QKV projection and the attention of a layer share ONE launch where all its
  *   workgroups fit the GPU at once: the attention of a head
  *   needs only that head's rows of the projection, so its workgroups wait for those alone (a counter per head)
- *   instead of for the whole grid.  Every such wait is bounded; if one ever runs out (about a second; it needs the
+ *   instead of for the whole grid.  A narrow model (up to 1024 columns, heads of 64 channels) runs ALL its layers in one launch for one or
+ *   two tokens, whose workgroups wait for each other's results.  Every such wait is bounded; if one ever runs out (about a second; it needs the
  *   launch's workgroups not to be resident together for that long) the launch still ends, the workspace is
  *   marked, and every later result of that workspace says so -- NaN logits, -1 in disco_verify's arg-max and in
  *   disco_loop_out.sl, DISCO_EHIP from disco_iterate -- until disco_workspace_init is called again.
@@ -469,8 +470,8 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   No launch of it waits for another workgroup: the mode for programs that decode on many streams at once, where
  *   mode 0's launches hold compute units for each other's waiting workgroups.
  * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
- * 5.69 ms in mode 1; a 68M-class draft step: 68 us against 69 us and 128 us): a phase boundary inside a
- * launch costs more than a kernel boundary there, a per-head hand-off a little less.                     */
+ * 5.69 ms in mode 1; a 68M-class draft step: 54 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a
+ * launch costs more than a kernel boundary there, a hand-off whose data is its own flag half of one.     */
 int disco_set_launch_mode(int mode);
 
 #ifdef __cplusplus

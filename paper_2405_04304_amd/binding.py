@@ -138,6 +138,7 @@ _SIGNATURES = {
     "disco_probe_read_ms": (C.c_float, []),
     "disco_set_wait_limit": (C.c_int, [C.c_int]),
     "disco_qkv_attn_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
+    "disco_layers_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
     "disco_prefill_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_uint, C.c_int, C.POINTER(C.c_int)]),
 }
 EXPORTS = sorted(_SIGNATURES)
@@ -358,6 +359,13 @@ def disco_qkv_attn_plan(model_handle, n_tokens: int, ctx: int, capacity: int = 0
     out = (C.c_int * 5)()
     _check(lib().disco_qkv_attn_plan(model_handle, n_tokens, ctx, capacity, out))
     return {"form": ("separate", "shared", "own")[out[0]], "row_tiles": out[1], "range": out[2], "ranges": out[3], "workgroups": out[4]}
+
+
+def disco_layers_plan(model_handle, n_tokens: int, ctx: int, page_tokens: int, capacity: int = 0) -> dict:
+    """Whether launch mode 0 runs all layers of a forward in one launch (disco_bench.h), and its workgroups."""
+    out = (C.c_int * 4)()
+    _check(lib().disco_layers_plan(model_handle, n_tokens, ctx, page_tokens, capacity, out))
+    return {"one_launch": bool(out[0]), "workgroups": out[1], "groups": out[2], "parts": out[3]}
 
 
 def disco_probe_enable(layer: int) -> None:

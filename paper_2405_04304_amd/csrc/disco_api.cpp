@@ -34,6 +34,12 @@ hipError_t probe_record(int layer, int which, hipStream_t s) {
   return e;
 }
 
+// Whether the probe brackets a layer of a model of n_layers layers (such a forward runs a launch per phase).
+bool probe_on(int n_layers) {
+  std::lock_guard<std::mutex> lock(g_probe_mu);
+  return g_probe_layer >= 0 && g_probe_layer < n_layers && g_probe_ev[0] != nullptr;
+}
+
 int fail(int code, const char* fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
@@ -75,7 +81,7 @@ struct disco_kv {
 namespace {
 
 struct Ws {
-  float* h; float* q; bf16_t* xn; bf16_t* xattn; bf16_t* xact; float* part; float* gpart; float* logits;
+  float* h; float* q; bf16_t* xn; bf16_t* xattn; bf16_t* xact; float* part; float* gpart; size_t gpart_bytes; float* logits;
   float* ssq; int* gemm_counters; int* attn_counters; int n_counters; float* clf_scratch;
   uint32_t* gate; int32_t* sl_count; int32_t* tok_next;
   int* head_ready; unsigned* abort_word;     // fused QKV + attention launch: per-head counters, sticky failure flag
@@ -115,7 +121,8 @@ Ws carve(const disco_model* m, int max_block, int max_ctx, void* base) {
   if (2 * d.d_ff > max_rows) max_rows = 2 * d.d_ff;
   if (d.d_model > max_rows) max_rows = d.d_model;
   const int max_tiles = max_rows / 16;
-  w.gpart = static_cast<float*>(take(sizeof(float) * GEMM_MAX_SPLIT * 256 * (size_t)max_tiles));
+  w.gpart_bytes = sizeof(float) * GEMM_MAX_SPLIT * 256 * (size_t)max_tiles;
+  w.gpart = static_cast<float*>(take(w.gpart_bytes));
   w.logits = static_cast<float*>(take(sizeof(float) * 16 * (size_t)d.vocab));
   w.ssq = static_cast<float*>(take(sizeof(float) * 16 * (size_t)(d.d_model / 16)));
   w.sum = nullptr; w.ln_vec = nullptr; w.ln_layer_stride = 2 * ((size_t)m->d_qkv + d.d_ff);
@@ -185,6 +192,15 @@ FwdArgs forward_args(const disco_model* m, const disco_kv* kv, const Ws& ws) {
   return f;
 }
 
+// Plan of the launch that holds all layers (k_chain), for n tokens behind pos0 positions; false: the model or the block does not take it.
+bool chain_args(const disco_model* m, int n, int pos0, int page_tokens, size_t kv_layer_stride, size_t room, long capacity, ChainArgs& ch) {
+  const disco_model_desc& d = m->d;
+  ch = ChainArgs{};
+  ch.n_layers = d.n_layers; ch.M = n; ch.pos0 = pos0; ch.d = d.d_model; ch.d_ff = d.d_ff; ch.nq = d.n_heads; ch.nkv = d.n_kv_heads;
+  ch.eps = d.norm_eps; ch.scale = 1.0f / sqrtf((float)d.d_head); ch.kv_layer_stride = kv_layer_stride; ch.page_tokens = page_tokens;
+  return chain_plan(ch, m->d_qkv, d.d_head, d.family == DISCO_FAMILY_A, room, capacity);
+}
+
 // One forward of n tokens at positions kv->len ..: the shared body of draft step and verification.
 // logits_out: [vocab] of the last token (only_last) or [n x vocab].
 int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n, float* logits_out,
@@ -213,6 +229,8 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
     kv->len = pos0 + n;
     return DISCO_OK;
   }
+  ChainArgs ch;                                  // a narrow model's one or two tokens: all layers in one launch
+  const bool chained = g_launch_mode == 0 && !probe_on(d.n_layers) && chain_args(m, n, pos0, kv->page_tokens, kv->layer_stride, ws.gpart_bytes, 0, ch);
   const int split_o = gemm_split_for(d.d_model, m->d_q / 32, n), split_dn = gemm_split_for(d.d_model, d.d_ff / 32, n);
 
   NormArgs na{};
@@ -242,9 +260,22 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
     n0.g = m->layers[0].norm1_g; n0.b = m->layers[0].norm1_b;
     n0.tokens = dev_tokens; n0.tok_emb = static_cast<const bf16_t*>(m->w.tok_emb);
     n0.tok_stride = m->w.tok_emb_stride; n0.pos_emb = static_cast<const bf16_t*>(m->w.pos_emb);
-    HIP_TRY(launch_norm(n0, s), "embedding launch");
+    if (chained) {
+      ch.h = ws.h; ch.x_out = ws.xn; ch.ssq_out = ws.ssq; ch.sum_out = ws.sum; ch.q_last = ws.q; ch.hand = reinterpret_cast<char*>(ws.gpart);
+      ch.kv_pages = kv->pages; ch.page_table = kv->dev_page_table;
+      ch.rope = kv->dev_rope; ch.gate = gate; ch.abort_word = ws.abort_word; ch.limit = g_wait_limit;
+      for (int l = 0; l < d.n_layers; ++l) {
+        const disco_layer_weights& L = m->layers[l];
+        ch.layers[l] = ChainLayer{static_cast<const bf16_t*>(L.wqkv), static_cast<const bf16_t*>(L.wo), static_cast<const bf16_t*>(L.w_in),
+                                  static_cast<const bf16_t*>(L.w_out), L.norm2_g, l + 1 == d.n_layers ? m->w.normf_g : m->layers[l + 1].norm1_g,
+                                  fam_a ? ws.ln_vec + ws.ln_layer_stride * l : nullptr};
+      }
+      HIP_TRY(launch_chain(n0, ch, fam_a, s), "layers launch");
+    } else {
+      HIP_TRY(launch_norm(n0, s), "embedding launch");
+    }
   }
-  for (int l = 0; l < d.n_layers; ++l) {
+  for (int l = 0; l < (chained ? 0 : d.n_layers); ++l) {
     const disco_layer_weights& L = m->layers[l];
     const bool last = (l + 1 == d.n_layers);
     const float* next_g = last ? m->w.normf_g : m->layers[l + 1].norm1_g;
@@ -1086,6 +1117,15 @@ int disco_qkv_attn_plan(const disco_model* m, int n_tokens, int ctx, int capacit
   if (capacity == 0) qkv_attn_capacities(n_tokens, rt, d.d_head, ln, &shared, &own);
   const QkvAttnPlan p = qkv_attn_plan(m->d_qkv, d.n_heads, d.n_kv_heads, d.d_head, ln, ctx + n_tokens, rt, shared, own);
   out[0] = p.form; out[1] = rt; out[2] = p.split_len; out[3] = p.n_splits; out[4] = (int)p.wgs;
+  return DISCO_OK;
+}
+
+int disco_layers_plan(const disco_model* m, int n_tokens, int ctx, int page_tokens, int capacity, int out[4]) {
+  if (!m || !out || n_tokens < 1 || n_tokens > DISCO_MAX_BLOCK || ctx < 0 || page_tokens < 4 || page_tokens % 4 || capacity < 0) return fail(DISCO_EINVAL, "bad argument");
+  ChainArgs ch;
+  const size_t stride = (size_t)2 * m->d.n_kv_heads * m->d.d_head * round_up((size_t)ctx + n_tokens, (size_t)page_tokens);
+  const bool one = chain_args(m, n_tokens, ctx, page_tokens, stride, carve(m, n_tokens, ctx + n_tokens, nullptr).gpart_bytes, capacity, ch);
+  out[0] = one ? 1 : 0; out[1] = one ? ch.wgs : 0; out[2] = one ? ch.n_groups : 0; out[3] = one ? ch.parts : 0;
   return DISCO_OK;
 }
 

@@ -160,6 +160,30 @@ struct FwdArgs {
   ClassifyArgs clf;
 };
 
+// All layers of a narrow model's forward over one or two tokens in one launch: see k_chain.
+constexpr int CHAIN_MAX_WGS = 192 /* of the 512 that fit: two such launches on streams of their own always do */;
+constexpr int CHAIN_MAX_LAYERS = 24, CHAIN_MAX_TOKENS = 2, CHAIN_MAX_RANGES = 8, CHAIN_REC = 80 /* floats between two ranges' records */;
+struct ChainLayer {
+  const bf16_t* wqkv; const bf16_t* wo; const bf16_t* w_in; const bf16_t* w_out; const float* norm2_g;
+  const float* next_g;               // gain of the norm behind the layer
+  const float* ln;                   // LayerNorm family: W . g and W . b of the QKV matrix, then of the MLP input matrix
+};
+struct ChainArgs {
+  int n_layers, M, pos0, d, d_ff, nq, nkv; float eps, scale;
+  const float* h;                    // residual rows (the embedding)
+  bf16_t* x_out; float* ssq_out; float* sum_out;             // input of the LM head: panels, sums of squares, sums
+  float* q_last;                     // queries of the last layer
+  bf16_t* kv_pages; size_t kv_layer_stride; const int32_t* page_table; int page_tokens; const float* rope;
+  const uint32_t* gate; unsigned* abort_word; int limit;
+  char* hand;                        // hand-off buffers, layer_bytes apart
+  // set by chain_plan: workgroups of the two projections and of the launch; groups of heads that share products, heads of a group, workgroups
+  // of a group; K ranges of the MLP output; k-tiles of a wavefront; the deal of the context; the buffers' places in a layer's
+  int n_pu, wgs, n_groups, heads, parts, n_seg, kpw, split_len, n_splits;
+  unsigned o_xn, o_q, o_kv, o_xattn, o_xn2, o_act, o_rec;
+  size_t layer_bytes;
+  ChainLayer layers[CHAIN_MAX_LAYERS];
+};
+
 constexpr size_t CLASSIFY_SCRATCH_BYTES = 256 + 64 * 16 * sizeof(float);
 
 hipError_t launch_pack(const bf16_t* src, int64_t n, int64_t k, bf16_t* dst, int64_t tile_mul,
@@ -189,6 +213,10 @@ struct QkvAttnPlan { int form, split_len, n_splits; long wgs; };
 QkvAttnPlan qkv_attn_plan(int n_rows, int nq, int nkv, int dh, bool layernorm, int total, int rt, long cap_shared, long cap_own);
 int qkv_attn_rt(int n_rows);
 void qkv_attn_capacities(int M, int rt, int dh, bool layernorm, long* shared, long* own);
+// Whether a forward takes k_chain (room: bytes at a.hand; the fields in front of n_pu but layers are set by the caller), and its launches:
+// embedding + empty hand-off buffers, then all layers.
+bool chain_plan(ChainArgs& a, int d_qkv, int dh, bool layernorm, size_t room, long capacity = 0 /* workgroups that the GPU holds at once; 0: ask it */);
+hipError_t launch_chain(const NormArgs& n, const ChainArgs& a, bool layernorm, hipStream_t s);
 // dense prompt pass (groups of 16 tokens; every group holds 16 rows, surplus rows are padding)
 hipError_t launch_gemm_dense(const DenseArgs& a, int epi, hipStream_t s);
 // What the prompt pass launches for a matrix of n_rows x 32 KT and n_groups groups: workgroup tile (0 .. 3, see the function),

@@ -3804,6 +3804,872 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
 
 
 // ---------------------------------------------------------------------------------------------
+// all layers of a narrow model's forward over one or two tokens in ONE launch
+// ---------------------------------------------------------------------------------------------
+//
+// A forward of a draft model is a chain of small dependent phases.  A launch per phase costs 2.4 us before it does anything and its
+// weights arrive a round trip later: 26 us a layer for 9 MB (68M-class draft).  Here the phases of all layers run in workgroups that
+// stay, each with a role: QKV projection + MLP input (n_pu of them), attention (n_groups x parts), O-projection + MLP output (16 columns of
+// the residual stream each, whose rows live in registers from the first layer to the last).  A workgroup requests the weights of its next
+// phase and the cache entries of its next layer while it waits.  14.6 us a layer; a 68M-class draft token with its features at 523
+// positions 68.9 -> 54.3 us, four tokens of the 12-layer multi-query draft at 1490 1311 -> 870 us.  What bounds it: five hand-offs of about
+// 1.2 us a layer and, between them, the instructions of the one wavefront that finishes a tile.
+//
+// Hand-off: the data is its own flag.  Every buffer that one workgroup writes and others read inside the launch has an address of its
+// own per layer and is filled with CHAIN_EMPTY words by the launch in front (k_chain_begin); a reader polls the words it needs until
+// none is empty, so a hand-off is one write-through store and one L2-bypassing load (1.3 us over chains of 200, with 48 to 168 workgroups
+// polling; store, drain, counter, poll and load 2.6).  A value that happens to be the empty word (a NaN
+// with every bit set) is stored as another NaN.
+// The sums are formed in the order of the launches per phase (the wavefronts' k-tiles, the K ranges of the MLP output, the deal of the
+// context over ranges and wavefronts), so results do not depend on which of the two runs.
+//
+// All workgroups are resident at once (chain_plan checks it), and nobody waits without a bound (`limit` polls, then the abort word is set
+// and the launch ends with unusable data, as in k_qkv_attn).  At most CHAIN_MAX_WGS of the 512 workgroups that fit are one launch's.
+constexpr uint32_t CHAIN_EMPTY = 0xFFFFFFFFu;
+
+__device__ __forceinline__ uint32_t chain_word(uint32_t x) { return x == CHAIN_EMPTY ? 0x7FC07FC0u : x; }
+__device__ __forceinline__ void chain_put2(void* p, uint32_t a, uint32_t b) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)chain_word(a) | ((unsigned long long)chain_word(b) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void chain_put16(void* base /* uniform */, uint32_t at, u32x4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = chain_word(v[i]);
+  __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000), (int)at, 0, 16 /* sc1: write-through, as the atomics */);
+}
+// Compact panels: a block per 16 columns and token, [hi 16 | lo 16], and S (the panel of a normalised input) the columns' sum of squares and sum
+// behind them.  A block leaves its workgroup with one store instruction: a second write-through store of a wavefront becomes
+// visible 0.6 us after the first (chains of 200 hand-offs: 1.3 us with one store, 1.6 with hi and lo apart, 2.4 with the statistics in two more).
+template <bool S> constexpr int chain_block_bytes() { return S ? 128 : 64; }
+// Lane's share of a block, 8 bytes: lanes m + 2 g (+ 8: lo; + 16, S: statistics) of a wavefront hold columns 4 g .. 4 g + 3 of token m.
+template <int M, bool S>
+__device__ __forceinline__ void chain_put_block(char* panel, const int slot, const int lane, HiLo x0, HiLo x1, float sq, float sx) {
+  const int m = lane & 1, g = (lane >> 1) & 3, kind = lane >> 3;
+  const uint32_t a = kind == 0 ? x0.hi : (kind == 1 ? x0.lo : (g == 0 ? __float_as_uint(sq) : 0u));
+  const uint32_t b = kind == 0 ? x1.hi : (kind == 1 ? x1.lo : (g == 0 ? __float_as_uint(sx) : 0u));
+  if (m < M && (kind < 2 || (S && kind == 2 && g < 2))) chain_put2(panel + (slot * M + m) * chain_block_bytes<S>() + kind * 32 + g * 8, a, b);
+}
+
+// What the addresses of a phase are formed from, hidden from the compiler: it would form those of every phase in front of the loop over the
+// layers and keep them in registers that the weights in flight need.
+__device__ __forceinline__ void chain_opaque(int& lane, int& w) { asm volatile("" : "+v"(lane), "+s"(w)); }
+
+// Polls N 16-byte pieces per lane, at `base` (uniform) + p, until none has an empty word.  A lane without a piece of its own polls one of its
+// wavefront's (`on` false): no branches around the loads.
+template <int N>
+struct ChainWait {
+  const char* base; uint32_t p[N]; bool on[N]; u32x4 v[N];
+  __device__ __forceinline__ bool attempt() {
+    unsigned long long lo[N], hi[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      lo[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(base + p[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      hi[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(base + p[i] + 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      v[i] = u32x4{(uint32_t)lo[i], (uint32_t)(lo[i] >> 32), (uint32_t)hi[i], (uint32_t)(hi[i] >> 32)};
+      ok = ok && v[i][0] != CHAIN_EMPTY && v[i][1] != CHAIN_EMPTY && v[i][2] != CHAIN_EMPTY && v[i][3] != CHAIN_EMPTY;
+    }
+    return ok;
+  }
+  __device__ __forceinline__ void run(unsigned* abort_word, const int limit) {
+    for (int spins = 0;; ++spins) {
+      const bool ok = attempt();
+      if (limit >= 0 && __ballot(!ok) == 0ull) return;
+      // (once another wavefront has given up, what this one waits for may never come)
+      if (spins >= limit || ((spins & 1023) == 1023 && __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
+        __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+      }
+    }
+  }
+};
+
+constexpr int CHAIN_PARTS = 128;       // (range, wavefront, column) sums of a workgroup's share of the attention
+struct ChainGemmSmem {
+  u32x4 stage[8][64 * 3], stage2[8][64];       // a wavefront's panel pieces on their way to the operand order; zeros where a tile has none
+  f32x4 red[2][8][4][8];               // [phase parity][wavefront][tile or K range][4-row group, token]
+  alignas(16) float ssq[2][CHAIN_MAX_TOKENS][64], sum[2][CHAIN_MAX_TOKENS][64];      // a row's slots in the order they are added up
+};
+struct ChainAttnSmem {
+  alignas(16) float o[CHAIN_PARTS][64]; float m[CHAIN_PARTS], l[CHAIN_PARTS];
+  alignas(16) float ro[32][64]; float rm[32], rl[32];                   // ranges' records, where one workgroup has them all
+  u32x4 q[2][2][64];                   // the queries as operands: [hi | lo][32 channels][lane]
+  alignas(16) bf16_t kv[CHAIN_MAX_TOKENS][2][64];                       // the block's own keys and values
+};
+
+// One matrix phase of a workgroup: RT row tiles (or K ranges: NS of them) x the wavefront's KPW k-tiles per range.
+// k-tile i of a range: kb + w + 8 i.
+template <int M, int RT, int NS, int KPW>
+struct ChainTiles {
+  u32x4 A[NS * KPW][RT];
+  static __device__ __forceinline__ int seg_begin(const int KT, const int s, const int n_seg) {
+    return NS == 1 ? (s == 0 ? 0 : KT) : (int)((unsigned)(KT * s) / (unsigned)n_seg);
+  }
+  __device__ __forceinline__ void request(const bf16_t* W, const int (&rt)[RT], const int KT, const int n_seg, const int w, const int lane) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int i = 0; i < KPW; ++i) {
+        // (past the range: a tile that is multiplied by zeros, without a branch around registers that are in flight)
+        const int kt = min(seg_begin(KT, s, n_seg) + w + 8 * i, (s < n_seg ? seg_begin(KT, s + 1, n_seg) : KT) - 1);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          A[s * KPW + i][r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(W) + (size_t)((uint32_t)(rt[r] * KT + kt) * 1024u)) + lane);
+      }
+  }
+  // sets up the wait for this wavefront's pieces of `panel`: piece lane + 64 r of the list [tile][token][two blocks of hi 2 | lo 2 (| statistics)]
+  template <bool S, int N>
+  __device__ __forceinline__ void pieces(ChainWait<N>& wt, const char* panel, const int KT, const int n_seg, const int w, const int lane) const {
+    constexpr int PB = S ? 5 : 4, PT = 2 * PB;
+    static_assert(N * 64 >= NS * KPW * PT * M, "a lane per piece");
+    wt.base = panel;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const unsigned c = lane + 64 * r, q = c / (PT * M), of = c - q * (PT * M), sg = q / KPW, i = q - sg * KPW;
+      const int kt = seg_begin(KT, sg, n_seg) + w + 8 * (int)i;
+      wt.on[r] = q < NS * KPW && (int)sg < n_seg && kt < seg_begin(KT, sg + 1, n_seg);
+      const unsigned token = of / PT, pc = of - token * PT, blk = pc / PB;
+      wt.p[r] = ((wt.on[r] ? 2u * kt + blk : 2u * min(w, KT - 1)) * M + (wt.on[r] ? token : 0u)) * chain_block_bytes<S>() + (pc - blk * PB) * 16u;
+    }
+  }
+  template <bool S, int N, int NST>
+  __device__ __forceinline__ void products(const ChainWait<N>& wt, u32x4 (&stage)[NST], f32x4 (*red)[8] /* [tile or range][8] */, const int lane) const {
+    constexpr int PB = S ? 5 : 4, PT = 2 * PB;
+    static_assert(NST >= N * 64, "a place per piece");
+#pragma unroll
+    for (int r = 0; r < N; ++r) if (wt.on[r]) stage[lane + 64 * r] = wt.v[r];
+    __builtin_amdgcn_wave_barrier();
+    const int n = lane & 15, g = lane >> 4, m = M == 1 ? 0 : n & 1;          // columns without a token repeat one that has
+    const u32x4* at = stage + m * PT + (g >> 1) * PB + (n >> 3) * 2 + (g & 1);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      f32x4 acc[RT];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < KPW; ++i) {
+        const bf16x8 b = as_bf16x8(at[(s * KPW + i) * (PT * M)]);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(A[s * KPW + i][r]), b, acc[r], 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        f32x4 y;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[v] = acc[r][v] + dpp_f<DPP_ROW_ROR8, 0xF>(0.f, acc[r][v]);     // hi + lo
+        if (n < M) red[s * RT + r][g * 2 + n] = y;
+      }
+    }
+  }
+};
+
+template <bool LN>
+struct ChainNorm {
+  // the statistics among this lane's pieces, to where the sum finds them: slots in the order of gemm_unit (wavefront, then row of the
+  // wavefront; a second slot 32 further on is added to the first)
+  template <int M, int N>
+  static __device__ __forceinline__ void share(const ChainWait<N>& wt, float (&ssq)[CHAIN_MAX_TOKENS][64], float (&sum)[CHAIN_MAX_TOKENS][64], const int w, const int lane) {
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const unsigned c = lane + 64 * r, q = c / (10 * M), of = c - q * (10 * M), token = of / 10, pc = of - token * 10;
+      if (wt.on[r] && (pc == 4 || pc == 9)) {
+        const int s = 2 * (w + 8 * (int)q) + (pc == 9 ? 1 : 0), at = (s & 7) * 4 + ((s & 31) >> 3) + (s & 32);
+        ssq[token][at] = __uint_as_float(wt.v[r][0]);
+        if (LN) sum[token][at] = __uint_as_float(wt.v[r][1]);
+      }
+    }
+  }
+  static __device__ __forceinline__ float total(const float (&x)[64]) {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 32; i += 4) {
+      const f32x4 u = *reinterpret_cast<const f32x4*>(&x[i]) + *reinterpret_cast<const f32x4*>(&x[32 + i]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t += u[v];
+    }
+    return t;
+  }
+  // y of one or two tiles, normalised; vg, vb: the LayerNorm's vectors for this lane's four rows
+  template <int T>
+  static __device__ __forceinline__ void apply(f32x4 (&y)[T], const float (&ssq)[64], const float (&sum)[64], const int d, const float eps,
+                                               const float4 (&vg)[T], const float4 (&vb)[T]) {
+    const float ss = total(ssq);
+    if (LN) {
+      const float mean = total(sum) / (float)d;
+      const float var = fmaxf(ss / (float)d - mean * mean, 0.f);
+      const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        y[i][0] = rstd * (y[i][0] - mean * vg[i].x) + vb[i].x; y[i][1] = rstd * (y[i][1] - mean * vg[i].y) + vb[i].y;
+        y[i][2] = rstd * (y[i][2] - mean * vg[i].z) + vb[i].z; y[i][3] = rstd * (y[i][3] - mean * vg[i].w) + vb[i].w;
+      }
+    } else {
+      const float rstd = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+      for (int i = 0; i < T; ++i) y[i] *= rstd;
+    }
+  }
+};
+
+// Sums of the wavefronts' partial tiles in wavefront order.  A tile's 16 rows x 2 tokens are eight lanes, 2 (4-row group) + token, and every eight
+// lanes of a finishing wavefront have a copy (each stores something else of it).
+__device__ __forceinline__ f32x4 chain_sum(const f32x4 (&red)[8][4][8], const int tile, const int lane) {
+  f32x4 y = red[0][tile][lane & 7];
+#pragma unroll
+  for (int ww = 1; ww < 8; ++ww) y += red[ww][tile][lane & 7];
+  return y;
+}
+__device__ __forceinline__ f32x4 chain_from(const f32x4 y, const int lane) {            // another lane's
+  f32x4 o;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = __shfl(y[v], lane);
+  return o;
+}
+
+// QKV projection and MLP input of every layer.
+template <int M, bool LN, int KPW>
+__device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmSmem& sm, const int b, const uint32_t halted) {
+  constexpr int RU = LN ? 2 : 4, TU = LN ? 1 : 2;         // MLP input: tiles per workgroup, per output unit (32 outputs either way)
+  constexpr int N = (KPW * 10 * M + 63) / 64;     // pieces per lane
+  int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = M == 1 ? 0 : lane & 1, g = (lane >> 1) & 3, half = (lane >> 3) & 1;          // of a finishing wavefront: see chain_sum
+  const int KT = a.d >> 5, n_p = (a.nq + 2 * a.nkv) * 2, n_u = a.d_ff >> 5;
+  const int rp[2] = {((b >> 1) << 2) + (b & 1), ((b >> 1) << 2) + (b & 1) + 2};      // tiles 32 rows apart: rotary partners
+  const int head = rp[0] >> 2, c = (rp[0] & 3) * 16 + 4 * g;          // this workgroup's head part and the lane's channels c .. c + 3, c + 32 ..
+  const bool is_q = head < a.nq, is_v = head >= a.nq + a.nkv;
+  const int kvh = is_q ? 0 : (is_v ? head - a.nq - a.nkv : head - a.nq);
+  int ru[RU];
+#pragma unroll
+  for (int i = 0; i < RU; ++i) ru[i] = b * RU + i;
+  const int pos = a.pos0 + m;
+  const int pt = a.page_tokens, lp = pos >> __builtin_ctz(pt), off = pos & (pt - 1);
+  const bool p_ep = b < n_p && w == 0, puts = lane < 16 && (lane & 1) < M;             // lanes 8 ..: the upper half of the head's channels
+  for (int i = threadIdx.x; i < 2 * CHAIN_MAX_TOKENS * 64; i += 512) { (&sm.ssq[0][0][0])[i] = 0.f; (&sm.sum[0][0][0])[i] = 0.f; }   // slots past the row
+  for (int i = threadIdx.x; i < 8 * 64 * 3; i += 512) (&sm.stage[0][0])[i] = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  int page = lp;
+  float4 t0 = make_float4(1.f, 0.f, 1.f, 0.f), t1 = t0;
+  if (p_ep) {
+    if (!is_q && a.page_table != nullptr) page = a.page_table[lp];
+    if (!LN && a.rope != nullptr && !is_v) {
+      const float4* tab = reinterpret_cast<const float4*>(a.rope + ((size_t)pos * 32 + c) * 2);
+      t0 = tab[0]; t1 = tab[1];
+    }
+  }
+  bool first = true;
+  for (int l = 0; l < a.n_layers; ++l) {
+    chain_opaque(lane, w);
+    const ChainLayer& L = a.layers[l];
+    char* hand = a.hand + (size_t)l * a.layer_bytes;
+    if (b < n_p) {
+      ChainTiles<M, 2, 1, KPW> wq;
+      wq.request(L.wqkv, rp, KT, 1, w, lane);
+      float4 vg[2], vb[2];
+      if (LN && p_ep) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          vg[i] = *reinterpret_cast<const float4*>(L.ln + rp[i] * 16 + 4 * g);
+          vb[i] = *reinterpret_cast<const float4*>(L.ln + n_p * 32 + rp[i] * 16 + 4 * g);
+        }
+      }
+      if (first && flag_set(halted)) return;
+      first = false;
+      ChainWait<N> wt;
+      wq.template pieces<true>(wt, hand + a.o_xn, KT, 1, w, lane);
+      wt.run(a.abort_word, a.limit);
+      wq.template products<true>(wt, sm.stage[w], sm.red[0][w], lane);
+      ChainNorm<LN>::template share<M, N>(wt, sm.ssq[0], sm.sum[0], w, lane);
+      __syncthreads();
+      if (p_ep) {
+        int c_l = c + 32 * half, off_l = off;
+        asm volatile("" : "+v"(c_l), "+v"(off_l));
+        const f32x4 part = chain_sum(sm.red[0], half, lane);
+        f32x4 y[2] = {chain_from(part, lane & 7), chain_from(part, (lane & 7) + 8)};
+        ChainNorm<LN>::template apply<2>(y, sm.ssq[0][m], sm.sum[0][m], a.d, a.eps, vg, vb);
+        float lo4[4], hi4[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { lo4[v] = y[0][v]; hi4[v] = y[1][v]; }
+        if (!LN && a.rope != nullptr && !is_v) {
+          const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {           // (the rounding of qkv_store)
+            const float x0 = lo4[v], x1 = hi4[v];
+            lo4[v] = fmaf(x0, cs[v], -(x1 * sn[v]));
+            hi4[v] = fmaf(x1, cs[v], x0 * sn[v]);
+          }
+        }
+        float x[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = half ? hi4[v] : lo4[v];
+        if (is_q) {
+          if (puts) chain_put16(l + 1 == a.n_layers ? a.q_last : reinterpret_cast<float*>(hand + a.o_q), (uint32_t)((m * a.nq + head) * 64 + c_l) * 4u,
+                                u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])});
+        } else if (puts) {
+          const uint32_t x0 = pack_bf16(x[0], x[1]), x1 = pack_bf16(x[2], x[3]);
+          chain_put2(hand + a.o_kv + (uint32_t)((((kvh * M + m) * 2 + (is_v ? 1 : 0)) * 64 + c_l) * 2), x0, x1);
+          // the cache entry, for later launches
+          bf16_t* blk = a.kv_pages + (size_t)l * a.kv_layer_stride + (((size_t)page * 2 + (is_v ? 1 : 0)) * a.nkv + kvh) * pt * 64;
+          if (!is_v) {
+            st_u2<false>(blk + (size_t)off_l * 64 + c_l, make_uint2(x0, x1));
+          } else {
+            blk[(size_t)c_l * pt + off_l] = (bf16_t)x0; blk[(size_t)(c_l + 1) * pt + off_l] = (bf16_t)(x0 >> 16);
+            blk[(size_t)(c_l + 2) * pt + off_l] = (bf16_t)x1; blk[(size_t)(c_l + 3) * pt + off_l] = (bf16_t)(x1 >> 16);
+          }
+        }
+      }
+    }
+    if (b < n_u) {
+      chain_opaque(lane, w);
+      ChainTiles<M, RU, 1, KPW> wu;
+      wu.request(L.w_in, ru, KT, 1, w, lane);
+      const bool ep = w < 2;
+      float4 vg[TU], vb[TU];
+      if (LN && ep) {
+        vg[0] = *reinterpret_cast<const float4*>(L.ln + 2 * n_p * 32 + (b * 2 + w) * 16 + 4 * g);
+        vb[0] = *reinterpret_cast<const float4*>(L.ln + 2 * n_p * 32 + a.d_ff + (b * 2 + w) * 16 + 4 * g);
+      }
+      if (first && flag_set(halted)) return;
+      first = false;
+      ChainWait<N> wt;
+      wu.template pieces<true>(wt, hand + a.o_xn2, KT, 1, w, lane);
+      wt.run(a.abort_word, a.limit);
+      wu.template products<true>(wt, sm.stage[w], sm.red[1][w], lane);
+      ChainNorm<LN>::template share<M, N>(wt, sm.ssq[1], sm.sum[1], w, lane);
+      __syncthreads();
+      if (ep) {
+        const f32x4 part = chain_sum(sm.red[1], w * TU + (TU == 2 ? half : 0), lane);
+        f32x4 y[TU];
+        y[0] = TU == 2 ? chain_from(part, lane & 7) : part;
+        if (TU == 2) y[TU - 1] = chain_from(part, (lane & 7) + 8);
+        ChainNorm<LN>::template apply<TU>(y, sm.ssq[1][m], sm.sum[1][m], a.d, a.eps, vg, vb);
+        float u[4], z[4];                         // the activation is u z
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          u[v] = LN ? 0.5f * y[0][v] : y[0][v] / (1.0f + expf(-y[0][v]));
+          z[v] = LN ? 1.0f + erff(y[0][v] * 0.70710678118654752f) : y[TU - 1][v];
+        }
+        chain_put_block<M, false>(hand + a.o_act, b * 2 + w, lane, split_product<true>(u[0], z[0], u[1], z[1]), split_product<true>(u[2], z[2], u[3], z[3]), 0.f, 0.f);
+      }
+    }
+  }
+}
+
+// O-projection and MLP output of every layer for 16 columns of the residual stream.
+template <int M, bool LN, int KPW, int NSEG>
+__device__ __forceinline__ void chain_residual(const ChainArgs& a, ChainGemmSmem& sm, const int b, const uint32_t halted) {
+  int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = M == 1 ? 0 : lane & 1, g = (lane >> 1) & 3;          // of the finishing wavefront: see chain_sum
+  const int KTQ = a.nq * 2, KTF = a.d_ff >> 5, col = b * 16 + 4 * g;
+  const bool ep = w == 0;
+  float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (ep) h = *reinterpret_cast<const float4*>(a.h + (size_t)m * a.d + col);
+  const int rt[1] = {b};
+  for (int i = threadIdx.x; i < 8 * 64 * 4; i += 512) (i < 8 * 64 * 3 ? (&sm.stage[0][0])[i] : (&sm.stage2[0][0])[i - 8 * 64 * 3]) = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  // over the four 4-row groups of a token, in the order of row4_sum
+  auto rows_sum = [&](float v) { v += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, v); return v + __shfl_xor(v, 4); };
+  auto next_input = [&](const f32x4 y, const float4 gn, char* panel) {
+    h.x += y[0]; h.y += y[1]; h.z += y[2]; h.w += y[3];
+    const float sq = rows_sum((h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w)), sx = LN ? rows_sum((h.x + h.y) + (h.z + h.w)) : 0.f;
+    chain_put_block<M, true>(panel, b, lane, split_product<true>(h.x, gn.x, h.y, gn.y), split_product<true>(h.z, gn.z, h.w, gn.w), sq, sx);
+  };
+  for (int l = 0; l < a.n_layers; ++l) {
+    chain_opaque(lane, w);
+    const ChainLayer& L = a.layers[l];
+    char* hand = a.hand + (size_t)l * a.layer_bytes;
+    const bool last = l + 1 == a.n_layers;
+    ChainTiles<M, 1, 1, KPW> wo;
+    wo.request(L.wo, rt, KTQ, 1, w, lane);
+    ChainTiles<M, 1, NSEG, KPW> wd;
+    wd.request(L.w_out, rt, KTF, a.n_seg, w, lane);
+    float4 g2 = make_float4(0.f, 0.f, 0.f, 0.f), g1 = g2;
+    if (ep) {
+      g2 = *reinterpret_cast<const float4*>(L.norm2_g + col);
+      g1 = *reinterpret_cast<const float4*>(L.next_g + col);
+    }
+    if (l == 0 && flag_set(halted)) return;
+    {
+      ChainWait<1> wt;
+      wo.template pieces<false>(wt, hand + a.o_xattn, KTQ, 1, w, lane);
+      wt.run(a.abort_word, a.limit);
+      wo.template products<false>(wt, sm.stage2[w], sm.red[0][w], lane);
+      __syncthreads();
+      if (w == 0) next_input(chain_sum(sm.red[0], 0, lane), g2, hand + a.o_xn2);
+    }
+    {
+      ChainWait<(NSEG * KPW * 8 * M + 63) / 64> wt;
+      wd.template pieces<false>(wt, hand + a.o_act, KTF, a.n_seg, w, lane);
+      wt.run(a.abort_word, a.limit);
+      wd.template products<false>(wt, sm.stage[w], sm.red[1][w], lane);
+      __syncthreads();
+      if (w == 0) {
+        const f32x4 part = chain_sum(sm.red[1], min((lane >> 3) & 3, NSEG - 1), lane);     // lanes 8 s ..: K range s
+        f32x4 y = chain_from(part, lane & 7);
+#pragma unroll
+        for (int s = 1; s < NSEG; ++s) {
+          const f32x4 z = chain_from(part, (lane & 7) + 8 * s);
+          if (s < a.n_seg) y += z;
+        }
+        if (!last) {
+          next_input(y, g1, hand + a.layer_bytes + a.o_xn);
+        } else {                                  // the LM head's launch reads the ordinary panels
+          h.x += y[0]; h.y += y[1]; h.z += y[2]; h.w += y[3];
+          const float sq = rows_sum((h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w)), sx = LN ? rows_sum((h.x + h.y) + (h.z + h.w)) : 0.f;
+          if (lane < 8 && (lane & 1) < M) {
+            xpack_put4(a.x_out, a.d >> 5, M, m, col, split_product<true>(h.x, g1.x, h.y, g1.y), split_product<true>(h.z, g1.z, h.w, g1.w));
+            if (g == 0) a.ssq_out[b * 16 + m] = sq;
+            if (LN && g == 0) a.sum_out[b * 16 + m] = sx;
+          }
+        }
+      }
+    }
+  }
+}
+
+// Lane i of a 16-lane row's v to all of the row, i = 0 .. 7.
+__device__ __forceinline__ void row_bcast8(const float v, float (&o)[8]) {
+  o[0] = dpp_f<0x150, 0xF>(0.f, v); o[1] = dpp_f<0x151, 0xF>(0.f, v); o[2] = dpp_f<0x152, 0xF>(0.f, v); o[3] = dpp_f<0x153, 0xF>(0.f, v);
+  o[4] = dpp_f<0x154, 0xF>(0.f, v); o[5] = dpp_f<0x155, 0xF>(0.f, v); o[6] = dpp_f<0x156, 0xF>(0.f, v); o[7] = dpp_f<0x157, 0xF>(0.f, v);
+}
+
+// Attention of a group of query heads that read one K / V head, in every layer: part `part` of the ranges of their deal.  A column of
+// the products is a (head, token).  What one of the eight wavefronts of the launch per phase takes of a range (32 positions, and every
+// 256th after) is a sum of its own here too; those sums are dealt to the wavefronts and merged as there.  Where a group's ranges
+// are spread over workgroups, each hands its ranges' records round, and a column is merged by one of them.
+template <int M>
+__device__ __forceinline__ void chain_attention(const ChainArgs& a, ChainAttnSmem& sm, const int group, const int part, const uint32_t halted) {
+  const int total = a.pos0 + M, SL = a.split_len, n_r = a.n_splits;
+  int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = n_r * part / a.parts, r1 = n_r * (part + 1) / a.parts;
+  const int rep = a.nq / a.nkv, per_kv = a.n_groups / a.nkv, kvh = group / per_kv, h_in = (group - kvh * per_kv) * a.heads;
+  const int head0 = kvh * rep + h_in, n_col = min(a.heads, rep - h_in) * M;
+  const int per = min(8, SL >> 5);                // sums of a whole range
+  const int tail = min(per, (min(r1 * SL, total) - (r1 - 1) * SL + 31) >> 5), n_items = (r1 - 1 - r0) * per + tail;
+  const int pt = a.page_tokens, pshift = __builtin_ctz(pt);             // pages of a power of two
+  const uint32_t page_bytes = 256u * (uint32_t)(a.nkv * pt), k_off = 128u * (uint32_t)(kvh * pt), v_off = 128u * (uint32_t)((a.nkv + kvh) * pt);
+  const int per_inv = (65536 + per - 1) / per;    // item / per = item per_inv >> 16 for the few items there are
+  struct Cur { int item, base, s1, more; };       // a step of 32 positions, of a sum that has had steps (more) or not; s1 0: none
+  auto open = [&](const int item) {
+    Cur c{item, 0, 0, 0};
+    if (item < n_items) {
+      const int q = item * per_inv >> 16, r = r0 + q;
+      c.base = r * SL + (item - q * per) * 32; c.s1 = min((r + 1) * SL, total);
+    }
+    return c;
+  };
+  auto next = [&](const Cur& c) { return c.item < n_items && c.base + 256 < c.s1 ? Cur{c.item, c.base + 256, c.s1, 1} : open(c.item + 8); };
+  struct Raw { u32x4 k[2][2]; uint2 v[2][4]; } x0, x1;       // K rows of two 16-position tiles, V^T tiles of the same positions
+  // Entries in front of the block (a position at or behind it reads the last one's, whatever the step: no branch around registers in flight).
+  auto request = [&](Raw& x, const Cur& c, const int l) {
+    const char* kv = reinterpret_cast<const char*>(a.kv_pages + (size_t)l * a.kv_layer_stride);
+    const int j = lane & 15, g = lane >> 4, last = max(a.pos0 - 1, 0);
+    int p[2], q[2];                               // a K row's position; the first of the four positions of a V^T piece
+    uint32_t pp[2], qp[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      p[t] = min(c.base + 16 * t + j, last); q[t] = min(c.base + 16 * t + 4 * g, last & ~3);
+      pp[t] = (uint32_t)p[t] >> pshift; qp[t] = (uint32_t)q[t] >> pshift;
+    }
+    if (a.page_table != nullptr) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) { pp[t] = (uint32_t)a.page_table[pp[t]]; qp[t] = (uint32_t)a.page_table[qp[t]]; }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const uint32_t at = pp[t] * page_bytes + k_off + (uint32_t)(p[t] & (pt - 1)) * 128u + 16u * g;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) x.k[t][ks] = *reinterpret_cast<const u32x4*>(kv + at + ks * 64);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {                 // channel row = lane % 16 of each 16-channel tile, 4 consecutive positions
+      const uint32_t at = qp[t] * page_bytes + v_off + 2u * (uint32_t)(j * pt + (q[t] & (pt - 1)));
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) x.v[t][ch] = *reinterpret_cast<const uint2*>(kv + at + (uint32_t)(ch * pt) * 32u);
+    }
+  };
+  const Cur c0 = open(w), c1 = next(c0);
+  request(x0, c0, 0);
+  request(x1, c1, 0);
+  if (flag_set(halted)) return;
+  for (int l = 0; l < a.n_layers; ++l) {
+    chain_opaque(lane, w);
+    const int j = lane & 15, g = lane >> 4;
+    char* hand = a.hand + (size_t)l * a.layer_bytes;
+    {
+      // the group's queries (16 pieces a column, two columns a wavefront), and the block's own keys and values (16 pieces a token, the first wavefront's)
+      ChainWait<1> wt;
+      const int pc = lane & 15, col = 2 * w + (lane >> 4), kvm = (lane >> 4) - 2;
+      const bool is_q = lane < 32 && col < n_col, is_kv = w == 0 && lane >= 32 && kvm < M;
+      const uint32_t h_at = (uint32_t)(hand - reinterpret_cast<const char*>(a.q_last)), q_at = l + 1 == a.n_layers ? 0u : h_at + a.o_q;      // (see chain_plan)
+      wt.on[0] = is_q || is_kv;
+      wt.base = reinterpret_cast<const char*>(a.q_last);
+      wt.p[0] = (is_kv ? h_at + a.o_kv + (kvh * M + kvm) * 256u : q_at + ((min(col, n_col - 1) % M) * a.nq + head0 + min(col, n_col - 1) / M) * 256u) + pc * 16u;
+      wt.run(a.abort_word, a.limit);
+      if (is_q) {
+        const HiLo s0 = split_bf16(__uint_as_float(wt.v[0][0]), __uint_as_float(wt.v[0][1])), s1 = split_bf16(__uint_as_float(wt.v[0][2]), __uint_as_float(wt.v[0][3]));
+        reinterpret_cast<uint2*>(&sm.q[0][pc >> 3][((pc & 7) >> 1) * 16 + col])[pc & 1] = make_uint2(s0.hi, s1.hi);
+        reinterpret_cast<uint2*>(&sm.q[1][pc >> 3][((pc & 7) >> 1) * 16 + col])[pc & 1] = make_uint2(s0.lo, s1.lo);
+      }
+      if (is_kv) reinterpret_cast<u32x4*>(&sm.kv[kvm][0][0])[pc] = wt.v[0];
+      __syncthreads();
+    }
+    // AttnWave::step, in its order; what a sum has so far waits for its next step in LDS, not in registers that loads in flight need
+    auto take = [&](Raw& x, const Cur& c) {
+      if (c.base + 32 > a.pos0) {                 // the block's own entries come from the hand-off, not from the cache
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int mk = c.base + 16 * t + j - a.pos0;
+          if (mk >= 0 && mk < M) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) x.k[t][ks] = *reinterpret_cast<const u32x4*>(&sm.kv[mk][0][ks * 32 + 8 * g]);
+          }
+#pragma unroll
+          for (int m = 0; m < M; ++m) {
+            const int e = a.pos0 + m - (c.base + 16 * t + 4 * g);
+            if (e >= 0 && e < 4) {
+              const uint32_t keep = (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+#pragma unroll
+              for (int ch = 0; ch < 4; ++ch) {
+                const uint32_t nv = (uint32_t)sm.kv[m][1][ch * 16 + j] << (16 * (e & 1));
+                if (e < 2) x.v[t][ch].x = (x.v[t][ch].x & keep) | nv;
+                else x.v[t][ch].y = (x.v[t][ch].y & keep) | nv;
+              }
+            }
+          }
+        }
+      }
+      if (c.base + 32 > c.s1) {                   // beyond the range: zeros (0 * NaN would poison the sum)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int p0 = c.base + 16 * t + 4 * g;
+          const uint2 keep = make_uint2((p0 < c.s1 ? 0x0000FFFFu : 0u) | (p0 + 1 < c.s1 ? 0xFFFF0000u : 0u),
+                                        (p0 + 2 < c.s1 ? 0x0000FFFFu : 0u) | (p0 + 3 < c.s1 ? 0xFFFF0000u : 0u));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { x.v[t][i].x &= keep.x; x.v[t][i].y &= keep.y; }
+        }
+      }
+      f32x4 S[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x.k[t][ks]), as_bf16x8(sm.q[0][ks][lane]), S[t], 0, 0, 0);
+          S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x.k[t][ks]), as_bf16x8(sm.q[1][ks][lane]), S[t], 0, 0, 0);
+        }
+        S[t] *= a.scale;
+      }
+      if (c.base + 32 > min(c.s1, a.pos0 + 1)) {  // some column does not see all of it
+        const int lim = min(c.s1 - 1, a.pos0 + (M == 1 ? 0 : j & 1));           // last position of the range that column j sees
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) S[t][v] = c.base + 16 * t + 4 * g + v <= lim ? S[t][v] : NEG_BIG;
+      }
+      float mx = fmaxf(fmaxf(fmaxf(S[0][0], S[0][1]), fmaxf(S[0][2], S[0][3])), fmaxf(fmaxf(S[1][0], S[1][1]), fmaxf(S[1][2], S[1][3])));
+      mx = row4_max(mx);
+      const int at = c.item * n_col + j;
+      float m_run = NEG_BIG, l_run = 0.f;
+      if (c.more && j < n_col) { m_run = sm.m[at]; l_run = sm.l[at]; }
+      const float m_new = fmaxf(m_run, mx), alpha = __expf(m_run - m_new);
+      float sum = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float e = (S[t][v] > 0.5f * NEG_BIG) ? __expf(S[t][v] - m_new) : 0.f;
+          S[t][v] = e;
+          sum += e;
+        }
+      sum = row4_sum(sum);
+      l_run = l_run * alpha + sum;
+      f32x4 O[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (c.more && j < n_col) O[i] = *reinterpret_cast<const f32x4*>(&sm.o[at][i * 16 + 4 * g]) * alpha;
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        union { uint32_t u[2]; s16x4 v; } ph, pl;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) { const HiLo y = split_bf16(S[t][2 * v], S[t][2 * v + 1]); ph.u[v] = y.hi; pl.u[v] = y.lo; }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          union { uint2 u; s16x4 v; } vv;
+          vv.u = x.v[t][i];
+          O[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vv.v, ph.v, O[i], 0, 0, 0);
+          O[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vv.v, pl.v, O[i], 0, 0, 0);
+        }
+      }
+      if (j < n_col) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(&sm.o[at][i * 16 + 4 * g]) = O[i];
+        if (g == 0) { sm.m[at] = m_new; sm.l[at] = l_run; }
+      }
+    };
+    Cur ca = c0, cb = c1;
+    while (ca.item < n_items) {
+      take(x0, ca);
+      ca = next(cb);
+      if (ca.item < n_items) request(x0, ca, l);
+      if (cb.item >= n_items) break;
+      take(x1, cb);
+      cb = next(ca);
+      if (cb.item < n_items) request(x1, cb, l);
+    }
+    __syncthreads();
+    // ranges: a row of 16 lanes (four channels each) per range and column; lane i of a row knows sum i, and hands it round
+    chain_opaque(lane, w);
+    const int c4 = (lane & 15) * 4, own = lane & 7;
+    const bool plain = SL >= 256 && total <= ATTN_HEAD_MAX_CTX;      // (the order of a head in one workgroup)
+    float* recs = reinterpret_cast<float*>(hand + a.o_rec) + (size_t)group * n_r * a.heads * M * CHAIN_REC;
+    // (32 lanes where the record goes to another workgroup: the second row of lanes stores its maximum and sum with the same instruction)
+    const int rows = a.parts == 1 ? 4 : 2;
+    for (int rc = w * rows + (lane >> (a.parts == 1 ? 4 : 5)); rc < (r1 - r0) * n_col; rc += 8 * rows) {
+      const int r = rc / n_col, col = rc - r * n_col, n = r0 + r == r1 - 1 ? tail : per;
+      const float* o_r = &sm.o[r * per * n_col + col][c4];
+      f32x4 piece[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        piece[i] = *reinterpret_cast<const f32x4*>(o_r + min(i, n - 1) * n_col * 64);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) piece[i][v] = i < n ? piece[i][v] : 0.f;
+      }
+      const int at = (r * per + min(own, n - 1)) * n_col + col;
+      const float mi = own < n ? sm.m[at] : NEG_BIG, li = own < n ? sm.l[at] : 0.f;
+      float mm = fmaxf(mi, dpp_f<DPP_QUAD_XOR1, 0xF>(mi, mi));
+      mm = fmaxf(mm, dpp_f<DPP_QUAD_XOR2, 0xF>(mm, mm));
+      mm = fmaxf(mm, dpp_f<DPP_ROW_HALF_MIRROR, 0xF>(mm, mm));
+      float f[8], ls[8], ll = 0.f;
+      row_bcast8(expf(mi - mm), f);               // 0 past the range's sums
+      row_bcast8(li, ls);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ll = fmaf(ls[i], f[i], ll);
+      f32x4 o;
+      if (plain) {
+        o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) o[v] = fmaf(piece[i][v], f[i], o[v]);
+      } else {
+        o = range_sum<8>([&](int i) { return piece[i]; }, [&](int i) { return f[i]; });
+      }
+      if (a.parts == 1) {
+        *reinterpret_cast<f32x4*>(&sm.ro[rc][c4]) = o;
+        if (c4 == 0) { sm.rm[rc] = mm; sm.rl[rc] = ll; }
+      } else {
+        const bool second = (lane & 16) != 0;
+        if (!second || c4 == 0)
+          chain_put16(recs, (uint32_t)(((r0 + r) * n_col + col) * CHAIN_REC + (second ? 64 : c4)) * 4u,
+                      second ? u32x4{__float_as_uint(mm), __float_as_uint(ll), 0u, 0u}
+                             : u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])});
+      }
+    }
+    if (a.parts == 1) __syncthreads();
+    // columns: a row of lanes each; column t is merged by the workgroup of part parts - 1 - t % parts
+    const int col = a.parts - 1 - part + (w * 4 + (lane >> 4)) * a.parts;
+    if (__ballot(col < n_col) != 0ull) {
+      const bool on = col < n_col;
+      const int cc = on ? col : 0;
+      f32x4 ro[CHAIN_MAX_RANGES];
+      float mi = NEG_BIG, li = 0.f;
+      if (a.parts == 1) {
+#pragma unroll
+        for (int r = 0; r < CHAIN_MAX_RANGES; ++r) ro[r] = *reinterpret_cast<const f32x4*>(&sm.ro[min(r, n_r - 1) * n_col + cc][c4]);
+        if (own < n_r) { mi = sm.rm[own * n_col + cc]; li = sm.rl[own * n_col + cc]; }
+      } else {
+        ChainWait<CHAIN_MAX_RANGES + 1> wt;
+        wt.base = reinterpret_cast<const char*>(recs);
+        const uint32_t rec = (uint32_t)(cc * CHAIN_REC * 4), next_range = (uint32_t)(n_col * CHAIN_REC * 4);
+#pragma unroll
+        for (int r = 0; r < CHAIN_MAX_RANGES; ++r) wt.p[r] = rec + (uint32_t)min(r, n_r - 1) * next_range + c4 * 4;
+        wt.p[CHAIN_MAX_RANGES] = rec + (uint32_t)min(own, n_r - 1) * next_range + 256;
+        wt.run(a.abort_word, a.limit);
+#pragma unroll
+        for (int r = 0; r < CHAIN_MAX_RANGES; ++r)
+          ro[r] = f32x4{__uint_as_float(wt.v[r][0]), __uint_as_float(wt.v[r][1]), __uint_as_float(wt.v[r][2]), __uint_as_float(wt.v[r][3])};
+        if (own < n_r) { mi = __uint_as_float(wt.v[CHAIN_MAX_RANGES][0]); li = __uint_as_float(wt.v[CHAIN_MAX_RANGES][1]); }
+      }
+      // lane i of a row: the running maximum in front of range i and with it
+      float ms[8], ls[8], fo[8], fn[8], mx = NEG_BIG, before = NEG_BIG, with = NEG_BIG;
+      row_bcast8(mi, ms);
+      row_bcast8(li, ls);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (own == r) before = mx;
+        mx = fmaxf(mx, ms[r]);
+        if (own == r) with = mx;
+      }
+      row_bcast8(expf(before - with), fo);
+      row_bcast8(expf(mi - with), fn);
+      float Ls = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < CHAIN_MAX_RANGES; ++r)
+        if (r < n_r) {
+          Ls = merged(Ls, fo[r], ls[r], fn[r]);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) o[v] = merged(o[v], fo[r], ro[r][v], fn[r]);
+        }
+      const float inv = 1.0f / Ls;
+      const HiLo s0 = split_product<RANGES_LO_EXACT>(o[0], inv, o[1], inv), s1 = split_product<RANGES_LO_EXACT>(o[2], inv, o[3], inv);
+      // four lanes hold a block of 16 channels: lanes 0, 1 store its hi, lanes 2, 3 its lo, 16 bytes each, gathered from two lanes
+      auto quad = [&](const uint32_t h, const uint32_t l) {
+        const uint32_t h0 = (uint32_t)dpp_i<0x88, 0xF>(0, (int)h), l0 = (uint32_t)dpp_i<0x88, 0xF>(0, (int)l);       // lanes 0, 2, 0, 2 of the four
+        return (lane & 2) ? l0 : h0;
+      };
+      auto quad1 = [&](const uint32_t h, const uint32_t l) {
+        const uint32_t h1 = (uint32_t)dpp_i<0xDD, 0xF>(0, (int)h), l1 = (uint32_t)dpp_i<0xDD, 0xF>(0, (int)l);       // lanes 1, 3, 1, 3
+        return (lane & 2) ? l1 : h1;
+      };
+      const u32x4 out = {quad(s0.hi, s0.lo), quad(s1.hi, s1.lo), quad1(s0.hi, s0.lo), quad1(s1.hi, s1.lo)};
+      if (on) chain_put16(hand + a.o_xattn, (uint32_t)((((head0 + col / M) * 4 + ((lane & 15) >> 2)) * M + col % M) * 64 + (lane & 3) * 16), out);
+    }
+    if (l + 1 < a.n_layers) {                     // the next layer's entries arrive while its queries are being formed
+      request(x0, c0, l + 1);
+      request(x1, c1, l + 1);
+    }
+  }
+}
+
+template <int M, bool LN, int KPW, int NSEG>
+__global__ __launch_bounds__(512, 4) void k_chain(ChainArgs a) {
+  union Smem { ChainGemmSmem gemm; ChainAttnSmem attn; };
+  __shared__ Smem sm;
+  const uint32_t halted = gate_request(a.gate);
+  const int id = blockIdx.x, n_attn = a.n_groups * a.parts;
+  if (id < a.n_pu) chain_projections<M, LN, KPW>(a, sm.gemm, id, halted);
+  else if (id < a.n_pu + n_attn) chain_attention<M>(a, sm.attn, (id - a.n_pu) % a.n_groups, (id - a.n_pu) / a.n_groups, halted);
+  else chain_residual<M, LN, KPW, NSEG>(a, sm.gemm, id - a.n_pu - n_attn, halted);
+}
+
+// In front of k_chain: the embedding rows with the first layer's input (one workgroup per token, the arithmetic of norm_row), and empty
+// words into everything that k_chain hands over.
+__global__ __launch_bounds__(256) void k_chain_begin(NormArgs n, ChainArgs a) {
+  __shared__ float red[5];
+  const uint32_t halted = gate_request(n.gate);
+  const int t = threadIdx.x, M = a.M;
+  if ((int)blockIdx.x >= M) {
+    if (flag_set(halted)) return;
+    const size_t words = (a.layer_bytes * a.n_layers - a.o_q) / 8, q_words = (size_t)M * a.nq * 32;
+    const size_t stride = (size_t)(gridDim.x - M) * 256;
+    unsigned long long* p = reinterpret_cast<unsigned long long*>(a.hand + a.o_q);
+    for (size_t i = (size_t)(blockIdx.x - M) * 256 + t; i < words + q_words; i += stride)
+      __hip_atomic_store(i < words ? p + i : reinterpret_cast<unsigned long long*>(a.q_last) + (i - words), ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  const int m = blockIdx.x, d = n.d, k = t * 4;
+  int tok = n.tokens[m];
+  tok = tok < 0 ? 0 : (tok >= n.vocab ? n.vocab - 1 : tok);
+  int pos = n.pos0 + m;
+  if (pos >= n.max_pos) pos = n.max_pos - 1;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f), gn = v;
+  if (k < d) {
+    const uint2 u = *reinterpret_cast<const uint2*>(n.tok_emb + (size_t)tok * n.tok_stride + k);
+    gn = *reinterpret_cast<const float4*>(n.g + k);
+    v = make_float4(bf16_to_f32(u.x & 0xFFFF), bf16_to_f32(u.x >> 16), bf16_to_f32(u.y & 0xFFFF), bf16_to_f32(u.y >> 16));
+    if (n.pos_emb) {
+      const uint2 p = *reinterpret_cast<const uint2*>(n.pos_emb + (size_t)pos * d + k);
+      v.x += bf16_to_f32(p.x & 0xFFFF); v.y += bf16_to_f32(p.x >> 16);
+      v.z += bf16_to_f32(p.y & 0xFFFF); v.w += bf16_to_f32(p.y >> 16);
+    }
+  }
+  if (flag_set(halted)) return;
+  if (k < d) {
+    *reinterpret_cast<float4*>(n.h + (size_t)m * d + k) = v;
+    const HiLo x0 = split_product<true>(v.x, gn.x, v.y, gn.y), x1 = split_product<true>(v.z, gn.z, v.w, gn.w);
+    char* blk = a.hand + a.o_xn + ((k >> 4) * M + m) * chain_block_bytes<true>() + (k & 12) * 2;
+    chain_put2(blk, x0.hi, x1.hi);
+    chain_put2(blk + 32, x0.lo, x1.lo);
+  }
+  const float ss = block_sum<256>((v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w), red);
+  const float sx = block_sum<256>((v.x + v.y) + (v.z + v.w), red);
+  if (t < d / 16) {
+    char* stats = a.hand + a.o_xn + (t * M + m) * chain_block_bytes<true>() + 64;
+    chain_put2(stats, t == 0 ? __float_as_uint(ss) : 0u, t == 0 ? __float_as_uint(sx) : 0u);
+    chain_put2(stats + 8, 0u, 0u);
+  }
+}
+
+// The instance for a model and a block: f<M, LN, KPW, NSEG>.
+#define CHAIN_BY_SHAPE(f, M, ln, kpw, ...) \
+  ((M) == 1 ? ((ln) ? ((kpw) == 3 ? f<1, true, 3, 4>(__VA_ARGS__) : f<1, true, 4, 3>(__VA_ARGS__)) \
+                    : ((kpw) == 3 ? f<1, false, 3, 4>(__VA_ARGS__) : f<1, false, 4, 3>(__VA_ARGS__))) \
+            : ((ln) ? ((kpw) == 3 ? f<2, true, 3, 4>(__VA_ARGS__) : f<2, true, 4, 3>(__VA_ARGS__)) \
+                    : ((kpw) == 3 ? f<2, false, 3, 4>(__VA_ARGS__) : f<2, false, 4, 3>(__VA_ARGS__))))
+template <int M, bool LN, int KPW, int NSEG>
+static long chain_capacity() {
+  static const long c = resident_capacity(reinterpret_cast<const void*>(k_chain<M, LN, KPW, NSEG>));
+  return c;
+}
+template <int M, bool LN, int KPW, int NSEG>
+static hipError_t chain_start(const ChainArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_chain<M, LN, KPW, NSEG>), dim3((unsigned)a.wgs), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+
+// Whether a forward of M tokens behind pos0 positions takes k_chain, and how.  Heads of 64 channels in a model of at most 1024 columns whose layers fit the
+// kernel's registers: k-tiles of a wavefront per matrix (three, or four with fewer K ranges of the MLP output).  `room`: bytes at a.hand.
+bool chain_plan(ChainArgs& a, int d_qkv, int dh, bool layernorm, size_t room, long capacity) {
+  const int d = a.d, d_q = a.nq * 64, KTF = a.d_ff >> 5, total = a.pos0 + a.M;
+  if (a.kv_layer_stride >= (size_t)1 << 30 || (a.page_tokens & (a.page_tokens - 1)) != 0) return false;      // 32-bit offsets into a layer's cache, shifts
+  if (dh != 64 || a.M > CHAIN_MAX_TOKENS || a.n_layers > CHAIN_MAX_LAYERS || d > 1024 || d_q > 1024 || d_qkv != (a.nq + 2 * a.nkv) * 64) return false;
+  a.n_seg = gemm_split_for(d, KTF, a.M);
+  const int wide = d > d_q ? d : d_q, per_seg = (KTF + a.n_seg - 1) / a.n_seg;
+  const int kpw = (wide > 768 || per_seg > 24) ? 4 : 3;
+  if (per_seg > 8 * kpw || a.n_seg > (kpw == 3 ? 4 : 3)) return false;
+  if (gemm_split_for(d, d_q >> 5, a.M) != 1) return false;
+  long cap_shared = capacity, cap_own = capacity;
+  const int rt = qkv_attn_rt(d_qkv);
+  if (rt != 2) return false;
+  if (capacity == 0) qkv_attn_capacities(a.M, rt, dh, layernorm, &cap_shared, &cap_own);
+  const QkvAttnPlan p = qkv_attn_plan(d_qkv, a.nq, a.nkv, dh, layernorm, total, rt, cap_shared, cap_own);
+  if (p.form != 2 || p.n_splits > CHAIN_MAX_RANGES) return false;
+  a.split_len = p.split_len; a.n_splits = p.n_splits;
+  // The heads of a K / V head share its keys and values as columns of the same products, as far as sixteen columns go; a group's ranges go to
+  // as many workgroups as leave the attention 24: a step of 32 positions costs a wavefront about half a microsecond.
+  const int rep = a.nq / a.nkv, per_kv = (rep * a.M + 15) / 16;
+  a.heads = (rep + per_kv - 1) / per_kv;
+  a.n_groups = a.nkv * per_kv;
+  a.parts = 24 / a.n_groups < 1 ? 1 : 24 / a.n_groups;
+  if (a.parts > a.n_splits) a.parts = a.n_splits;
+  const int most = (a.n_splits + a.parts - 1) / a.parts;          // ranges of a workgroup
+  const int part_len = a.split_len / 32 < 8 ? a.split_len / 32 : 8;
+  if (most * part_len * a.heads * a.M > CHAIN_PARTS || most * a.heads * a.M > 32) return false;
+  const int n_p = d_qkv / 32, n_u = a.d_ff / 32;
+  a.n_pu = n_p > n_u ? n_p : n_u;
+  a.kpw = kpw;
+  a.wgs = a.n_pu + a.n_groups * a.parts + d / 16;
+  if (a.wgs > CHAIN_MAX_WGS || a.wgs > (capacity != 0 ? capacity : CHAIN_BY_SHAPE(chain_capacity, a.M, layernorm, kpw))) return false;
+  // the hand-off buffers of a layer, each on a line of its own
+  size_t off = 0;
+  auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 127) / 128 * 128; return (unsigned)o; };
+  const size_t M = (size_t)a.M;
+  a.o_xn = take(M * 8 * d);
+  a.o_q = take(M * 4 * d_q); a.o_kv = take(M * 256 * a.nkv); a.o_xattn = take(M * 4 * d_q); a.o_xn2 = take(M * 8 * d);
+  a.o_act = take(M * 4 * a.d_ff);
+  a.o_rec = take(a.parts > 1 ? M * 4 * CHAIN_REC * a.n_splits * a.heads * a.n_groups : 0);
+  a.layer_bytes = off;
+  return off * (size_t)a.n_layers <= room;
+}
+
+hipError_t launch_chain(const NormArgs& n, const ChainArgs& a, bool layernorm, hipStream_t s) {
+  if (n.tokens == nullptr || n.M != a.M || n.d != a.d || a.hand == nullptr || a.q_last == nullptr) return hipErrorInvalidValue;
+  if (a.hand < reinterpret_cast<const char*>(a.q_last) || (size_t)(a.hand - reinterpret_cast<const char*>(a.q_last)) + a.layer_bytes * a.n_layers >= (size_t)1 << 32)
+    return hipErrorInvalidValue;                  // 32-bit offsets
+  const size_t words = (a.layer_bytes * a.n_layers - a.o_q) / 8 + (size_t)a.M * a.nq * 32;
+  const size_t fill = (words + 1023) / 1024;      // four words a thread
+  hipLaunchKernelGGL(k_chain_begin, dim3((unsigned)(a.M + (fill < 128 ? fill : 128))), dim3(256), 0, s, n, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return CHAIN_BY_SHAPE(chain_start, a.M, layernorm, a.kpw, a, s);
+}
+
+// ---------------------------------------------------------------------------------------------
 // one launch per forward or per draft loop: persistent workgroups, phases separated by a grid barrier
 // ---------------------------------------------------------------------------------------------
 //
