@@ -3811,8 +3811,8 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
 // weights arrive a round trip later: 26 us a layer for 9 MB (68M-class draft).  Here the phases of all layers run in workgroups that
 // stay, each with a role: QKV projection + MLP input (n_pu of them), attention (n_groups x parts), O-projection + MLP output (16 columns of
 // the residual stream each, whose rows live in registers from the first layer to the last).  A workgroup requests the weights of its next
-// phase and the cache entries of its next layer while it waits.  14.6 us a layer; a 68M-class draft token with its features at 523
-// positions 68.9 -> 54.3 us, four tokens of the 12-layer multi-query draft at 1490 1311 -> 870 us.  What bounds it: five hand-offs of about
+// phase and the cache entries of its next layer while it waits.  13.8 us a layer; a 68M-class draft token with its features at 523
+// positions 68.8 -> 52.5 us, four tokens of the 12-layer multi-query draft at 1490 1310 -> 836 us.  What bounds it: five hand-offs of about
 // 1.2 us a layer and, between them, the instructions of the one wavefront that finishes a tile.
 //
 // Hand-off: the data is its own flag.  Every buffer that one workgroup writes and others read inside the launch has an address of its
@@ -3841,13 +3841,25 @@ __device__ __forceinline__ void chain_put16(void* base /* uniform */, uint32_t a
 // behind them.  A block leaves its workgroup with one store instruction: a second write-through store of a wavefront becomes
 // visible 0.6 us after the first (chains of 200 hand-offs: 1.3 us with one store, 1.6 with hi and lo apart, 2.4 with the statistics in two more).
 template <bool S> constexpr int chain_block_bytes() { return S ? 128 : 64; }
-// Lane's share of a block, 8 bytes: lanes m + 2 g (+ 8: lo; + 16, S: statistics) of a wavefront hold columns 4 g .. 4 g + 3 of token m.
+// A finishing wavefront has one value a lane: row r = lane % 16 of a tile, token m = lane / 32; lanes 16 .. 31 of a token are its second tile's rows, or
+// copies of the first's.  The instructions of that one wavefront are what a phase waits for: with four rows a lane, as the matrix unit
+// leaves them, a phase took 0.3 us longer.
+__device__ __forceinline__ float chain_neighbour(float v) { return dpp_f<DPP_QUAD_XOR1, 0xF>(0.f, v); }          // lane ^ 1's
+// x z of this lane and its neighbour as bf16 hi (lanes 0 .. 15 of a token) or lo (16 .. 31), in the even lanes
+__device__ __forceinline__ uint32_t chain_halves(const float x, const float z, const int lane) {
+  const HiLo s = split_product<true>(x, z, chain_neighbour(x), chain_neighbour(z));
+  return (lane & 16) ? s.lo : s.hi;
+}
+__device__ __forceinline__ void chain_put4b(char* p, uint32_t v) {
+  __hip_atomic_store(reinterpret_cast<uint32_t*>(p), chain_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Stores a block: even lanes the words of chain_halves, odd ones (S) the statistics.
 template <int M, bool S>
-__device__ __forceinline__ void chain_put_block(char* panel, const int slot, const int lane, HiLo x0, HiLo x1, float sq, float sx) {
-  const int m = lane & 1, g = (lane >> 1) & 3, kind = lane >> 3;
-  const uint32_t a = kind == 0 ? x0.hi : (kind == 1 ? x0.lo : (g == 0 ? __float_as_uint(sq) : 0u));
-  const uint32_t b = kind == 0 ? x1.hi : (kind == 1 ? x1.lo : (g == 0 ? __float_as_uint(sx) : 0u));
-  if (m < M && (kind < 2 || (S && kind == 2 && g < 2))) chain_put2(panel + (slot * M + m) * chain_block_bytes<S>() + kind * 32 + g * 8, a, b);
+__device__ __forceinline__ void chain_put_block(char* panel, const int slot, const int lane, const uint32_t word, const float sq, const float sx) {
+  const int r = lane & 15, hi = (lane & 16) == 0, m = lane >> 5;
+  const bool even = (r & 1) == 0;
+  const uint32_t v = even ? word : (r == 1 ? __float_as_uint(sq) : (r == 3 ? __float_as_uint(sx) : 0u));
+  if (m < M && (even || (S && hi && r < 8))) chain_put4b(panel + (slot * M + m) * chain_block_bytes<S>() + (even ? (hi ? 0 : 32) + r * 2 : 64 + (r >> 1) * 4), v);
 }
 
 // What the addresses of a phase are formed from, hidden from the compiler: it would form those of every phase in front of the loop over the
@@ -3982,51 +3994,46 @@ struct ChainNorm {
       }
     }
   }
-  static __device__ __forceinline__ float total(const float (&x)[64]) {
+  // Sum of 32 pairs (slot, slot 32 further on) in order: a lane of a 16-lane row reads two pairs, and the additions take them from lane to lane
+  // (a lane that reads them all adds twice as often, behind sixteen reads: 0.2 us a phase).
+  static __device__ __forceinline__ float total(const float (&x)[64], const int lane) {
+    const int i = lane & 15;
+    const float u0 = x[i] + x[32 + i], u1 = x[16 + i] + x[48 + i];
     float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < 32; i += 4) {
-      const f32x4 u = *reinterpret_cast<const f32x4*>(&x[i]) + *reinterpret_cast<const f32x4*>(&x[32 + i]);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) t += u[v];
-    }
+#define CHAIN_ADD(u, k) t += dpp_f<0x150 + k, 0xF>(0.f, u);
+#define CHAIN_ADD8(u, k) CHAIN_ADD(u, k) CHAIN_ADD(u, k + 1) CHAIN_ADD(u, k + 2) CHAIN_ADD(u, k + 3) CHAIN_ADD(u, k + 4) CHAIN_ADD(u, k + 5) CHAIN_ADD(u, k + 6) CHAIN_ADD(u, k + 7)
+    CHAIN_ADD8(u0, 0) CHAIN_ADD8(u0, 8) CHAIN_ADD8(u1, 0) CHAIN_ADD8(u1, 8)
+#undef CHAIN_ADD8
+#undef CHAIN_ADD
     return t;
   }
-  // y of one or two tiles, normalised; vg, vb: the LayerNorm's vectors for this lane's four rows
-  template <int T>
-  static __device__ __forceinline__ void apply(f32x4 (&y)[T], const float (&ssq)[64], const float (&sum)[64], const int d, const float eps,
-                                               const float4 (&vg)[T], const float4 (&vb)[T]) {
-    const float ss = total(ssq);
+  // y normalised; vg, vb: the LayerNorm's two vectors at this lane's row
+  template <int M>
+  static __device__ __forceinline__ float apply(const float y, const float (&ssq)[CHAIN_MAX_TOKENS][64], const float (&sum)[CHAIN_MAX_TOKENS][64], const int d, const float eps,
+                                                const float vg, const float vb, const int lane) {
+    float ss = total(ssq[0], lane);
+    if (M == 2) { const float s1 = total(ssq[1], lane); ss = (lane & 32) ? s1 : ss; }
     if (LN) {
-      const float mean = total(sum) / (float)d;
+      float sx = total(sum[0], lane);
+      if (M == 2) { const float s1 = total(sum[1], lane); sx = (lane & 32) ? s1 : sx; }
+      const float mean = sx / (float)d;
       const float var = fmaxf(ss / (float)d - mean * mean, 0.f);
       const float rstd = 1.0f / sqrtf(var + eps);
-#pragma unroll
-      for (int i = 0; i < T; ++i) {
-        y[i][0] = rstd * (y[i][0] - mean * vg[i].x) + vb[i].x; y[i][1] = rstd * (y[i][1] - mean * vg[i].y) + vb[i].y;
-        y[i][2] = rstd * (y[i][2] - mean * vg[i].z) + vb[i].z; y[i][3] = rstd * (y[i][3] - mean * vg[i].w) + vb[i].w;
-      }
-    } else {
-      const float rstd = 1.0f / sqrtf(ss / (float)d + eps);
-#pragma unroll
-      for (int i = 0; i < T; ++i) y[i] *= rstd;
+      return rstd * (y - mean * vg) + vb;
     }
+    const float rstd = 1.0f / sqrtf(ss / (float)d + eps);
+    return y * rstd;
   }
 };
 
-// Sums of the wavefronts' partial tiles in wavefront order.  A tile's 16 rows x 2 tokens are eight lanes, 2 (4-row group) + token, and every eight
-// lanes of a finishing wavefront have a copy (each stores something else of it).
-__device__ __forceinline__ f32x4 chain_sum(const f32x4 (&red)[8][4][8], const int tile, const int lane) {
-  f32x4 y = red[0][tile][lane & 7];
+// Sum of the wavefronts' partial tiles in wavefront order, this lane's row and token.
+template <int M>
+__device__ __forceinline__ float chain_sum(const f32x4 (&red)[8][4][8], const int tile, const int lane) {
+  const float* p = reinterpret_cast<const float*>(&red[0][tile][((lane & 15) >> 2) * 2 + (M == 1 ? 0 : lane >> 5)]) + (lane & 3);
+  float y = p[0];
 #pragma unroll
-  for (int ww = 1; ww < 8; ++ww) y += red[ww][tile][lane & 7];
+  for (int ww = 1; ww < 8; ++ww) y += p[ww * 4 * 8 * 4];
   return y;
-}
-__device__ __forceinline__ f32x4 chain_from(const f32x4 y, const int lane) {            // another lane's
-  f32x4 o;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) o[v] = __shfl(y[v], lane);
-  return o;
 }
 
 // QKV projection and MLP input of every layer.
@@ -4035,10 +4042,10 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
   constexpr int RU = LN ? 2 : 4, TU = LN ? 1 : 2;         // MLP input: tiles per workgroup, per output unit (32 outputs either way)
   constexpr int N = (KPW * 10 * M + 63) / 64;     // pieces per lane
   int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = M == 1 ? 0 : lane & 1, g = (lane >> 1) & 3, half = (lane >> 3) & 1;          // of a finishing wavefront: see chain_sum
+  const int m = M == 1 ? 0 : lane >> 5, r = lane & 15, half = (lane >> 4) & 1;          // of a finishing wavefront: see chain_put_block
   const int KT = a.d >> 5, n_p = (a.nq + 2 * a.nkv) * 2, n_u = a.d_ff >> 5;
   const int rp[2] = {((b >> 1) << 2) + (b & 1), ((b >> 1) << 2) + (b & 1) + 2};      // tiles 32 rows apart: rotary partners
-  const int head = rp[0] >> 2, c = (rp[0] & 3) * 16 + 4 * g;          // this workgroup's head part and the lane's channels c .. c + 3, c + 32 ..
+  const int head = rp[0] >> 2, ch = (rp[0] & 3) * 16 + r + 32 * half;          // this workgroup's head part and the lane's channel: tiles 32 apart
   const bool is_q = head < a.nq, is_v = head >= a.nq + a.nkv;
   const int kvh = is_q ? 0 : (is_v ? head - a.nq - a.nkv : head - a.nq);
   int ru[RU];
@@ -4046,17 +4053,16 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
   for (int i = 0; i < RU; ++i) ru[i] = b * RU + i;
   const int pos = a.pos0 + m;
   const int pt = a.page_tokens, lp = pos >> __builtin_ctz(pt), off = pos & (pt - 1);
-  const bool p_ep = b < n_p && w == 0, puts = lane < 16 && (lane & 1) < M;             // lanes 8 ..: the upper half of the head's channels
+  const bool p_ep = b < n_p && w == 0, puts = (lane >> 5) < M;
   for (int i = threadIdx.x; i < 2 * CHAIN_MAX_TOKENS * 64; i += 512) { (&sm.ssq[0][0][0])[i] = 0.f; (&sm.sum[0][0][0])[i] = 0.f; }   // slots past the row
   for (int i = threadIdx.x; i < 8 * 64 * 3; i += 512) (&sm.stage[0][0])[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   int page = lp;
-  float4 t0 = make_float4(1.f, 0.f, 1.f, 0.f), t1 = t0;
+  float2 cs = make_float2(1.f, 0.f);              // cos, sin of the channel pair
   if (p_ep) {
     if (!is_q && a.page_table != nullptr) page = a.page_table[lp];
     if (!LN && a.rope != nullptr && !is_v) {
-      const float4* tab = reinterpret_cast<const float4*>(a.rope + ((size_t)pos * 32 + c) * 2);
-      t0 = tab[0]; t1 = tab[1];
+      cs = *reinterpret_cast<const float2*>(a.rope + ((size_t)pos * 32 + (ch & 31)) * 2);
     }
   }
   bool first = true;
@@ -4067,14 +4073,8 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
     if (b < n_p) {
       ChainTiles<M, 2, 1, KPW> wq;
       wq.request(L.wqkv, rp, KT, 1, w, lane);
-      float4 vg[2], vb[2];
-      if (LN && p_ep) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          vg[i] = *reinterpret_cast<const float4*>(L.ln + rp[i] * 16 + 4 * g);
-          vb[i] = *reinterpret_cast<const float4*>(L.ln + n_p * 32 + rp[i] * 16 + 4 * g);
-        }
-      }
+      float vg = 0.f, vb = 0.f;
+      if (LN && p_ep) { vg = L.ln[rp[half] * 16 + r]; vb = L.ln[n_p * 32 + rp[half] * 16 + r]; }
       if (first && flag_set(halted)) return;
       first = false;
       ChainWait<N> wt;
@@ -4084,40 +4084,22 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
       ChainNorm<LN>::template share<M, N>(wt, sm.ssq[0], sm.sum[0], w, lane);
       __syncthreads();
       if (p_ep) {
-        int c_l = c + 32 * half, off_l = off;
-        asm volatile("" : "+v"(c_l), "+v"(off_l));
-        const f32x4 part = chain_sum(sm.red[0], half, lane);
-        f32x4 y[2] = {chain_from(part, lane & 7), chain_from(part, (lane & 7) + 8)};
-        ChainNorm<LN>::template apply<2>(y, sm.ssq[0][m], sm.sum[0][m], a.d, a.eps, vg, vb);
-        float lo4[4], hi4[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) { lo4[v] = y[0][v]; hi4[v] = y[1][v]; }
-        if (!LN && a.rope != nullptr && !is_v) {
-          const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {           // (the rounding of qkv_store)
-            const float x0 = lo4[v], x1 = hi4[v];
-            lo4[v] = fmaf(x0, cs[v], -(x1 * sn[v]));
-            hi4[v] = fmaf(x1, cs[v], x0 * sn[v]);
-          }
+        int ch_l = ch, off_l = off;
+        asm volatile("" : "+v"(ch_l), "+v"(off_l));
+        float x = ChainNorm<LN>::template apply<M>(chain_sum<M>(sm.red[0], half, lane), sm.ssq[0], sm.sum[0], a.d, a.eps, vg, vb, lane);
+        if (!LN && a.rope != nullptr && !is_v) {  // (the rounding of qkv_store)
+          const Pair32 p = swap16(x);             // the channel of the lower half and its partner
+          x = half ? fmaf(p.b, cs.x, p.a * cs.y) : fmaf(p.a, cs.x, -(p.b * cs.y));
         }
-        float x[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = half ? hi4[v] : lo4[v];
         if (is_q) {
-          if (puts) chain_put16(l + 1 == a.n_layers ? a.q_last : reinterpret_cast<float*>(hand + a.o_q), (uint32_t)((m * a.nq + head) * 64 + c_l) * 4u,
-                                u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])});
-        } else if (puts) {
-          const uint32_t x0 = pack_bf16(x[0], x[1]), x1 = pack_bf16(x[2], x[3]);
-          chain_put2(hand + a.o_kv + (uint32_t)((((kvh * M + m) * 2 + (is_v ? 1 : 0)) * 64 + c_l) * 2), x0, x1);
+          if (puts) chain_put4b(reinterpret_cast<char*>(l + 1 == a.n_layers ? a.q_last : reinterpret_cast<float*>(hand + a.o_q)) + (uint32_t)((m * a.nq + head) * 64 + ch_l) * 4u,
+                                __float_as_uint(x));
+        } else {
+          const uint32_t xx = pack_bf16(x, chain_neighbour(x));
+          if (puts && (lane & 1) == 0) chain_put4b(hand + a.o_kv + (uint32_t)((((kvh * M + m) * 2 + (is_v ? 1 : 0)) * 64 + ch_l) * 2), xx);
           // the cache entry, for later launches
           bf16_t* blk = a.kv_pages + (size_t)l * a.kv_layer_stride + (((size_t)page * 2 + (is_v ? 1 : 0)) * a.nkv + kvh) * pt * 64;
-          if (!is_v) {
-            st_u2<false>(blk + (size_t)off_l * 64 + c_l, make_uint2(x0, x1));
-          } else {
-            blk[(size_t)c_l * pt + off_l] = (bf16_t)x0; blk[(size_t)(c_l + 1) * pt + off_l] = (bf16_t)(x0 >> 16);
-            blk[(size_t)(c_l + 2) * pt + off_l] = (bf16_t)x1; blk[(size_t)(c_l + 3) * pt + off_l] = (bf16_t)(x1 >> 16);
-          }
+          if (puts) blk[is_v ? (size_t)ch_l * pt + off_l : (size_t)off_l * 64 + ch_l] = (bf16_t)xx;
         }
       }
     }
@@ -4126,11 +4108,8 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
       ChainTiles<M, RU, 1, KPW> wu;
       wu.request(L.w_in, ru, KT, 1, w, lane);
       const bool ep = w < 2;
-      float4 vg[TU], vb[TU];
-      if (LN && ep) {
-        vg[0] = *reinterpret_cast<const float4*>(L.ln + 2 * n_p * 32 + (b * 2 + w) * 16 + 4 * g);
-        vb[0] = *reinterpret_cast<const float4*>(L.ln + 2 * n_p * 32 + a.d_ff + (b * 2 + w) * 16 + 4 * g);
-      }
+      float vg = 0.f, vb = 0.f;
+      if (LN && ep) { vg = L.ln[2 * n_p * 32 + (b * 2 + w) * 16 + r]; vb = L.ln[2 * n_p * 32 + a.d_ff + (b * 2 + w) * 16 + r]; }
       if (first && flag_set(halted)) return;
       first = false;
       ChainWait<N> wt;
@@ -4140,18 +4119,10 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
       ChainNorm<LN>::template share<M, N>(wt, sm.ssq[1], sm.sum[1], w, lane);
       __syncthreads();
       if (ep) {
-        const f32x4 part = chain_sum(sm.red[1], w * TU + (TU == 2 ? half : 0), lane);
-        f32x4 y[TU];
-        y[0] = TU == 2 ? chain_from(part, lane & 7) : part;
-        if (TU == 2) y[TU - 1] = chain_from(part, (lane & 7) + 8);
-        ChainNorm<LN>::template apply<TU>(y, sm.ssq[1][m], sm.sum[1][m], a.d, a.eps, vg, vb);
-        float u[4], z[4];                         // the activation is u z
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          u[v] = LN ? 0.5f * y[0][v] : y[0][v] / (1.0f + expf(-y[0][v]));
-          z[v] = LN ? 1.0f + erff(y[0][v] * 0.70710678118654752f) : y[TU - 1][v];
-        }
-        chain_put_block<M, false>(hand + a.o_act, b * 2 + w, lane, split_product<true>(u[0], z[0], u[1], z[1]), split_product<true>(u[2], z[2], u[3], z[3]), 0.f, 0.f);
+        const float y = ChainNorm<LN>::template apply<M>(chain_sum<M>(sm.red[1], w * TU + (TU == 2 ? half : 0), lane), sm.ssq[1], sm.sum[1], a.d, a.eps, vg, vb, lane);
+        const Pair32 p = swap16(y);               // TU 2: the row's gate and up
+        const float u = LN ? 0.5f * y : p.a / (1.0f + expf(-p.a)), z = LN ? 1.0f + erff(y * 0.70710678118654752f) : p.b;       // the activation is u z
+        chain_put_block<M, false>(hand + a.o_act, b * 2 + w, lane, chain_halves(u, z, lane), 0.f, 0.f);
       }
     }
   }
@@ -4161,20 +4132,28 @@ __device__ __forceinline__ void chain_projections(const ChainArgs& a, ChainGemmS
 template <int M, bool LN, int KPW, int NSEG>
 __device__ __forceinline__ void chain_residual(const ChainArgs& a, ChainGemmSmem& sm, const int b, const uint32_t halted) {
   int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = M == 1 ? 0 : lane & 1, g = (lane >> 1) & 3;          // of the finishing wavefront: see chain_sum
-  const int KTQ = a.nq * 2, KTF = a.d_ff >> 5, col = b * 16 + 4 * g;
+  const int m = M == 1 ? 0 : lane >> 5, r = lane & 15;          // of the finishing wavefront: see chain_put_block
+  const int KTQ = a.nq * 2, KTF = a.d_ff >> 5, col = b * 16 + r;
   const bool ep = w == 0;
-  float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (ep) h = *reinterpret_cast<const float4*>(a.h + (size_t)m * a.d + col);
+  float h = ep ? a.h[(size_t)m * a.d + col] : 0.f;
   const int rt[1] = {b};
   for (int i = threadIdx.x; i < 8 * 64 * 4; i += 512) (i < 8 * 64 * 3 ? (&sm.stage[0][0])[i] : (&sm.stage2[0][0])[i - 8 * 64 * 3]) = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
-  // over the four 4-row groups of a token, in the order of row4_sum
-  auto rows_sum = [&](float v) { v += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, v); return v + __shfl_xor(v, 4); };
-  auto next_input = [&](const f32x4 y, const float4 gn, char* panel) {
-    h.x += y[0]; h.y += y[1]; h.z += y[2]; h.w += y[3];
-    const float sq = rows_sum((h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w)), sx = LN ? rows_sum((h.x + h.y) + (h.z + h.w)) : 0.f;
-    chain_put_block<M, true>(panel, b, lane, split_product<true>(h.x, gn.x, h.y, gn.y), split_product<true>(h.z, gn.z, h.w, gn.w), sq, sx);
+  // sums over a token's 16 columns, in the order of gemm_unit: four at a time, then the four in pairs
+  auto columns_sum = [](float v) { v += dpp_f<DPP_ROW_HALF_MIRROR, 0xF>(0.f, v); return v + dpp_f<DPP_ROW_MIRROR, 0xF>(0.f, v); };
+  auto squares = [&] {
+    const float e = fmaf(h, h, chain_neighbour(h * h));            // (even lanes)
+    const float q = e + dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, e);
+    return columns_sum(dpp_f<0x00, 0xF>(0.f, q));                  // (lane 0 of four to all of them)
+  };
+  auto values = [&] {
+    float q = h + chain_neighbour(h);
+    q += dpp_f<DPP_QUAD_XOR2, 0xF>(0.f, q);
+    return columns_sum(q);
+  };
+  auto next_input = [&](const float y, const float gn, char* panel) {
+    h += y;
+    chain_put_block<M, true>(panel, b, lane, chain_halves(h, gn, lane), squares(), LN ? values() : 0.f);
   };
   for (int l = 0; l < a.n_layers; ++l) {
     chain_opaque(lane, w);
@@ -4185,11 +4164,8 @@ __device__ __forceinline__ void chain_residual(const ChainArgs& a, ChainGemmSmem
     wo.request(L.wo, rt, KTQ, 1, w, lane);
     ChainTiles<M, 1, NSEG, KPW> wd;
     wd.request(L.w_out, rt, KTF, a.n_seg, w, lane);
-    float4 g2 = make_float4(0.f, 0.f, 0.f, 0.f), g1 = g2;
-    if (ep) {
-      g2 = *reinterpret_cast<const float4*>(L.norm2_g + col);
-      g1 = *reinterpret_cast<const float4*>(L.next_g + col);
-    }
+    float g2 = 0.f, g1 = 0.f;
+    if (ep) { g2 = L.norm2_g[col]; g1 = L.next_g[col]; }
     if (l == 0 && flag_set(halted)) return;
     {
       ChainWait<1> wt;
@@ -4197,7 +4173,7 @@ __device__ __forceinline__ void chain_residual(const ChainArgs& a, ChainGemmSmem
       wt.run(a.abort_word, a.limit);
       wo.template products<false>(wt, sm.stage2[w], sm.red[0][w], lane);
       __syncthreads();
-      if (w == 0) next_input(chain_sum(sm.red[0], 0, lane), g2, hand + a.o_xn2);
+      if (w == 0) next_input(chain_sum<M>(sm.red[0], 0, lane), g2, hand + a.o_xn2);
     }
     {
       ChainWait<(NSEG * KPW * 8 * M + 63) / 64> wt;
@@ -4206,22 +4182,23 @@ __device__ __forceinline__ void chain_residual(const ChainArgs& a, ChainGemmSmem
       wd.template products<false>(wt, sm.stage[w], sm.red[1][w], lane);
       __syncthreads();
       if (w == 0) {
-        const f32x4 part = chain_sum(sm.red[1], min((lane >> 3) & 3, NSEG - 1), lane);     // lanes 8 s ..: K range s
-        f32x4 y = chain_from(part, lane & 7);
+        float y = chain_sum<M>(sm.red[1], 0, lane);
 #pragma unroll
         for (int s = 1; s < NSEG; ++s) {
-          const f32x4 z = chain_from(part, (lane & 7) + 8 * s);
+          const float z = chain_sum<M>(sm.red[1], s, lane);
           if (s < a.n_seg) y += z;
         }
         if (!last) {
           next_input(y, g1, hand + a.layer_bytes + a.o_xn);
         } else {                                  // the LM head's launch reads the ordinary panels
-          h.x += y[0]; h.y += y[1]; h.z += y[2]; h.w += y[3];
-          const float sq = rows_sum((h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w)), sx = LN ? rows_sum((h.x + h.y) + (h.z + h.w)) : 0.f;
-          if (lane < 8 && (lane & 1) < M) {
-            xpack_put4(a.x_out, a.d >> 5, M, m, col, split_product<true>(h.x, g1.x, h.y, g1.y), split_product<true>(h.z, g1.z, h.w, g1.w));
-            if (g == 0) a.ssq_out[b * 16 + m] = sq;
-            if (LN && g == 0) a.sum_out[b * 16 + m] = sx;
+          h += y;
+          const uint32_t word = chain_halves(h, g1, lane);
+          const float sq = squares(), sx = LN ? values() : 0.f;
+          if ((lane >> 5) < M) {
+            if ((lane & 1) == 0)
+              *reinterpret_cast<uint32_t*>(a.x_out + ((size_t)(col >> 5) * 64 + ((col & 31) >> 3) * 16 + m + ((lane & 16) ? 8 : 0)) * 8 + (col & 7)) = word;
+            if ((lane & 31) == 0) a.ssq_out[b * 16 + m] = sq;
+            if (LN && (lane & 31) == 0) a.sum_out[b * 16 + m] = sx;
           }
         }
       }
@@ -4547,33 +4524,38 @@ __global__ __launch_bounds__(512, 4) void k_chain(ChainArgs a) {
   else chain_residual<M, LN, KPW, NSEG>(a, sm.gemm, id - a.n_pu - n_attn, halted);
 }
 
+// (plain 16-byte stores: the launch's end makes them visible)
+__device__ __forceinline__ void chain_empty16(char* p, uint32_t at) { *reinterpret_cast<u32x4*>(p + at) = u32x4{CHAIN_EMPTY, CHAIN_EMPTY, CHAIN_EMPTY, CHAIN_EMPTY}; }
+struct ChainBegin {
+  const float* g; float* h; int64_t tok_stride; int pos0, vocab, max_pos;
+  uint32_t fill_from, fill, fill_q;    // empty words: from byte fill_from behind the first input panel, 16-byte pieces there and in the last layer's queries
+};
 // In front of k_chain: the embedding rows with the first layer's input (one workgroup per token, the arithmetic of norm_row), and empty
 // words into everything that k_chain hands over.
-__global__ __launch_bounds__(256) void k_chain_begin(NormArgs n, ChainArgs a) {
+__global__ __launch_bounds__(256) void k_chain_begin(const int32_t* tokens, const bf16_t* tok_emb, const bf16_t* pos_emb, const uint32_t* gate, char* xn, float* q_last,
+                                                     int d, int M, ChainBegin n) {
   __shared__ float red[5];
-  const uint32_t halted = gate_request(n.gate);
-  const int t = threadIdx.x, M = a.M;
+  const uint32_t halted = gate_request(gate);
+  const int t = threadIdx.x;
   if ((int)blockIdx.x >= M) {
     if (flag_set(halted)) return;
-    const size_t words = (a.layer_bytes * a.n_layers - a.o_q) / 8, q_words = (size_t)M * a.nq * 32;
-    const size_t stride = (size_t)(gridDim.x - M) * 256;
-    unsigned long long* p = reinterpret_cast<unsigned long long*>(a.hand + a.o_q);
-    for (size_t i = (size_t)(blockIdx.x - M) * 256 + t; i < words + q_words; i += stride)
-      __hip_atomic_store(i < words ? p + i : reinterpret_cast<unsigned long long*>(a.q_last) + (i - words), ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t i = (blockIdx.x - M) * 256u + t;              // 16 bytes a thread
+    if (i < n.fill + n.fill_q)
+      chain_empty16(i < n.fill ? xn + n.fill_from : reinterpret_cast<char*>(q_last), (i < n.fill ? i : i - n.fill) * 16u);
     return;
   }
-  const int m = blockIdx.x, d = n.d, k = t * 4;
-  int tok = n.tokens[m];
+  const int m = blockIdx.x, k = t * 4;
+  int tok = tokens[m];
   tok = tok < 0 ? 0 : (tok >= n.vocab ? n.vocab - 1 : tok);
   int pos = n.pos0 + m;
   if (pos >= n.max_pos) pos = n.max_pos - 1;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f), gn = v;
   if (k < d) {
-    const uint2 u = *reinterpret_cast<const uint2*>(n.tok_emb + (size_t)tok * n.tok_stride + k);
+    const uint2 u = *reinterpret_cast<const uint2*>(tok_emb + (size_t)tok * n.tok_stride + k);
     gn = *reinterpret_cast<const float4*>(n.g + k);
     v = make_float4(bf16_to_f32(u.x & 0xFFFF), bf16_to_f32(u.x >> 16), bf16_to_f32(u.y & 0xFFFF), bf16_to_f32(u.y >> 16));
-    if (n.pos_emb) {
-      const uint2 p = *reinterpret_cast<const uint2*>(n.pos_emb + (size_t)pos * d + k);
+    if (pos_emb) {
+      const uint2 p = *reinterpret_cast<const uint2*>(pos_emb + (size_t)pos * d + k);
       v.x += bf16_to_f32(p.x & 0xFFFF); v.y += bf16_to_f32(p.x >> 16);
       v.z += bf16_to_f32(p.y & 0xFFFF); v.w += bf16_to_f32(p.y >> 16);
     }
@@ -4582,14 +4564,14 @@ __global__ __launch_bounds__(256) void k_chain_begin(NormArgs n, ChainArgs a) {
   if (k < d) {
     *reinterpret_cast<float4*>(n.h + (size_t)m * d + k) = v;
     const HiLo x0 = split_product<true>(v.x, gn.x, v.y, gn.y), x1 = split_product<true>(v.z, gn.z, v.w, gn.w);
-    char* blk = a.hand + a.o_xn + ((k >> 4) * M + m) * chain_block_bytes<true>() + (k & 12) * 2;
+    char* blk = xn + ((k >> 4) * M + m) * chain_block_bytes<true>() + (k & 12) * 2;
     chain_put2(blk, x0.hi, x1.hi);
     chain_put2(blk + 32, x0.lo, x1.lo);
   }
   const float ss = block_sum<256>((v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w), red);
   const float sx = block_sum<256>((v.x + v.y) + (v.z + v.w), red);
   if (t < d / 16) {
-    char* stats = a.hand + a.o_xn + (t * M + m) * chain_block_bytes<true>() + 64;
+    char* stats = xn + (t * M + m) * chain_block_bytes<true>() + 64;
     chain_put2(stats, t == 0 ? __float_as_uint(ss) : 0u, t == 0 ? __float_as_uint(sx) : 0u);
     chain_put2(stats + 8, 0u, 0u);
   }
@@ -4661,9 +4643,9 @@ hipError_t launch_chain(const NormArgs& n, const ChainArgs& a, bool layernorm, h
   if (n.tokens == nullptr || n.M != a.M || n.d != a.d || a.hand == nullptr || a.q_last == nullptr) return hipErrorInvalidValue;
   if (a.hand < reinterpret_cast<const char*>(a.q_last) || (size_t)(a.hand - reinterpret_cast<const char*>(a.q_last)) + a.layer_bytes * a.n_layers >= (size_t)1 << 32)
     return hipErrorInvalidValue;                  // 32-bit offsets
-  const size_t words = (a.layer_bytes * a.n_layers - a.o_q) / 8 + (size_t)a.M * a.nq * 32;
-  const size_t fill = (words + 1023) / 1024;      // four words a thread
-  hipLaunchKernelGGL(k_chain_begin, dim3((unsigned)(a.M + (fill < 128 ? fill : 128))), dim3(256), 0, s, n, a);
+  const ChainBegin b{n.g, n.h, n.tok_stride, n.pos0, n.vocab, n.max_pos, a.o_q - a.o_xn, (uint32_t)((a.layer_bytes * a.n_layers - a.o_q) / 16), (uint32_t)(a.M * a.nq * 16)};
+  hipLaunchKernelGGL(k_chain_begin, dim3((unsigned)a.M + (b.fill + b.fill_q + 255) / 256), dim3(256), 0, s, n.tokens, n.tok_emb, n.pos_emb, n.gate, a.hand + a.o_xn, a.q_last,
+                     n.d, a.M, b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return CHAIN_BY_SHAPE(chain_start, a.M, layernorm, a.kpw, a, s);
