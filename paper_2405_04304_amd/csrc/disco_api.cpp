@@ -663,7 +663,7 @@ int disco_workspace_init(const disco_model* m, void* dev_ws, size_t ws_bytes, in
   const Ws ws = carve(m, max_block, max_ctx, dev_ws);
   const disco_model_desc& d0 = m->d;
   HIP_TRY(launch_zero(ws.gemm_counters, ws.n_counters, static_cast<hipStream_t>(s)), "workspace init launch");
-  HIP_TRY(launch_zero(reinterpret_cast<int*>(ws.clf_scratch), 64, static_cast<hipStream_t>(s)), "workspace init launch");
+  HIP_TRY(launch_zero(reinterpret_cast<int*>(ws.clf_scratch), CLASSIFY_SCRATCH_BYTES / 4, static_cast<hipStream_t>(s)), "workspace init launch");
   HIP_TRY(launch_zero(ws.head_ready, QKV_ATTN_READY_SLOT * d0.n_heads, static_cast<hipStream_t>(s)), "workspace init launch");
   HIP_TRY(launch_zero(reinterpret_cast<int*>(ws.gate), 64, static_cast<hipStream_t>(s)), "workspace init launch");
   if (ws.ln_vec != nullptr) {
@@ -702,7 +702,7 @@ int disco_workspace_init(const disco_model* m, void* dev_ws, size_t ws_bytes, in
 
 int disco_classify_scratch_init(void* dev_scratch, disco_stream s) {
   if (!dev_scratch || !aligned(dev_scratch, 256)) return fail(DISCO_EINVAL, "scratch pointer null or not 256-byte aligned");
-  HIP_TRY(launch_zero(static_cast<int*>(dev_scratch), 64, static_cast<hipStream_t>(s)), "scratch init launch");
+  HIP_TRY(launch_zero(static_cast<int*>(dev_scratch), CLASSIFY_SCRATCH_BYTES / 4, static_cast<hipStream_t>(s)), "scratch init launch");
   return DISCO_OK;
 }
 
@@ -732,7 +732,7 @@ static int classify_impl(const disco_clf* clf, float* dev_logits, int vocab, flo
   a.logits = dev_logits; a.vocab = vocab; a.clf_params = clf ? clf->dev_params : nullptr; a.hidden = clf ? clf->hidden : 0;
   a.pos_feature = pos_feature; a.tau = tau; a.force_halt = force_halt; a.out = dev_out; a.token_next = dev_token_next;
   a.block_slot = dev_block_slot; a.gate = dev_gate; a.sl_count = dev_sl_count; a.force_token = dev_force_token;
-  a.scratch = scratch;
+  a.scratch = scratch; a.limit = g_wait_limit;
   HIP_TRY(launch_classify(a, st), "classify launch");
   return DISCO_OK;
 }
@@ -753,9 +753,8 @@ int disco_classify_static(const disco_clf* clf, float* dev_logits, int vocab, fl
   float* scratch = nullptr;
   HIP_TRY(classify_static_scratch(&scratch), "address of the scratch array");
   hipStream_t st = static_cast<hipStream_t>(s);
-  // the array keeps the last call's contents: the ticket word must start at zero (a fill kernel, which
-  // a captured graph replays correctly)
-  HIP_TRY(launch_zero(reinterpret_cast<int*>(scratch), 64, st), "scratch clear launch");
+  // the array must start at zero whatever a call before left (a fill kernel, which a captured graph replays correctly)
+  HIP_TRY(launch_zero(reinterpret_cast<int*>(scratch), CLASSIFY_SCRATCH_BYTES / 4, st), "scratch clear launch");
   return classify_impl(clf, dev_logits, vocab, pos_feature, tau, force_halt, dev_out, dev_token_next, dev_block_slot, dev_gate,
                        dev_sl_count, dev_force_token, scratch, st);
 }
@@ -883,7 +882,7 @@ static int draft_loop_impl(const disco_model* draft, disco_kv* kv, const disco_c
     a.sl_count = ws.sl_count; a.force_token = dev_force_tokens ? dev_force_tokens + (j - 1) : nullptr;
     a.ref_token = dev_ref_tokens ? dev_ref_tokens + (j - 1) : nullptr;
     a.ppl_threshold = ppl_threshold;
-    a.scratch = ws.clf_scratch;
+    a.scratch = ws.clf_scratch; a.limit = g_wait_limit;
     { const hipError_t e = launch_classify(a, st); if (e != hipSuccess) { kv->len = len_entry; return hip_fail(e, "classify launch"); } }
   }
   HIP_TRY(launch_loop_finish(ws.sl_count, ws.gate, dev_out, host_out, ws.abort_word, st), "loop finish launch");

@@ -99,7 +99,8 @@ struct ClassifyArgs {
   const int32_t* force_token;
   const int32_t* ref_token;          // optional: known continuation; a different arg-max ends the block and stays out of it
   float ppl_threshold;               // > 0: perplexity rule (needs sl_count; the float after it holds -sum ln p of the block)
-  float* scratch;                    // optional: >= CLASSIFY_SCRATCH_BYTES, first word zero (ticket counter)
+  float* scratch;                    // optional: >= CLASSIFY_SCRATCH_BYTES, zeros (a ticket counter, then records, which every launch leaves at zero)
+  int limit;                         // polls before the wait for the other workgroups' records gives up (negative: at once)
 };
 struct SampleArgs {
   const float* logits; int64_t ld; int vocab; float inv_t;

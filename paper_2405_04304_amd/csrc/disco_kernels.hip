@@ -1822,8 +1822,8 @@ constexpr int FEAT_NT = 1024;
 // wavefronts in a fixed order.  Top-10: every wavefront finds the ten largest of the values its
 // lanes hold by ten cross-lane arg-max rounds, and one wavefront picks the ten largest of those 160.
 constexpr int CM_NT = 512;     // threads per slice inside the persistent draft loop (its workgroups have 512 threads): 2048 logits
-constexpr int CM_MULTI_NT = 256;   // threads per slice of the many-workgroup launch: 1024 logits (32 workgroups at vocab 32000, 64
-                                   // records at most: measured 2 us per draft step better than slices of 2048)
+constexpr int CM_SLICE = 1024;     // logits of a workgroup of the many-workgroup launch (32 of them at vocab 32000, 64 at most)
+constexpr int CM_MULTI_NT = 256;   // its threads
 constexpr int CM_REC = 16;     // floats per record
 
 // Order-preserving map float -> uint32 (larger float <=> larger key; -inf maps above key 0, which marks
@@ -2058,6 +2058,44 @@ struct ClassifySmem {
   int last;
 };
 
+// Score, halting decision and the loop's words, from the features and the classifier's sum z: by one thread.
+__device__ __forceinline__ void classify_decide(const ClassifyArgs& a, const float* feat_s, const float z, const float b2, const int best_i) {
+  ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
+  float score = __builtin_nanf("");
+  uint32_t halt = a.force_halt ? 1u : 0u;
+  if (a.clf_params) {
+    score = 1.0f / (1.0f + expf(-(z + b2)));
+    if (score < a.tau) halt = 1u;
+  }
+  // reference lookahead: a token that differs from the known continuation ends the block and is
+  // not part of it (bit 1 of halt)
+  bool mismatch = false;
+  if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && best_i != ref; }
+  if (mismatch) halt = 3u;
+  // perplexity rule (App. F's rule-based baseline): the block's draft tokens so far have perplexity
+  // exp(-(1/j) sum ln p_i), p_i the draft's probability of its own token (the largest one); above the
+  // threshold this token is the block's last.  The running sum sits in the word after sl_count.
+  // (the loop's words may have been written by another workgroup of the same launch: hand-off accesses)
+  const int sl_before = a.sl_count ? __hip_atomic_load(a.sl_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  if (a.ppl_threshold > 0.f && a.sl_count) {
+    float* nll = reinterpret_cast<float*>(a.sl_count + 1);
+    const float sum = ld_f1<true>(nll) - logf(feat_s[0]);
+    st_f1<true>(nll, sum);
+    score = expf(sum / (float)(sl_before + 1));
+    if (score > a.ppl_threshold) halt |= 1u;
+  }
+  out->token = best_i;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) out->feats[i] = feat_s[i];
+  out->score = score; out->halt = halt; out->executed = 1u;
+  if (!mismatch) {
+    if (a.token_next) *a.token_next = best_i;
+    if (a.block_slot) *a.block_slot = best_i;
+    if (a.sl_count) __hip_atomic_store(a.sl_count, sl_before + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (a.gate && halt) __hip_atomic_store(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Position of candidate `me` in descending order among NC candidates: how many beat it (larger, or equal with a lower slot): a
 // permutation of 0 .. NC - 1 without a dependent cross-lane chain.
 template <int NC>
@@ -2151,54 +2189,21 @@ __device__ __forceinline__ int classify_merge_finish(const ClassifyArgs& a, cons
   }
   float z = wave_sum(contrib);
   if (a.hidden > 64) z = block_sum<NT>(contrib, sm.sum);     // (up to 64 units: all in the first wavefront, which finishes)
-  if (t == 0) {
-    float score = __builtin_nanf("");
-    uint32_t halt = a.force_halt ? 1u : 0u;
-    if (a.clf_params) {
-      score = 1.0f / (1.0f + expf(-(z + k.b2)));
-      if (score < a.tau) halt = 1u;
-    }
-    // reference lookahead: a token that differs from the known continuation ends the block and is
-    // not part of it (bit 1 of halt)
-    bool mismatch = false;
-    if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && best_i != ref; }
-    if (mismatch) halt = 3u;
-    // perplexity rule (App. F's rule-based baseline): the block's draft tokens so far have perplexity
-    // exp(-(1/j) sum ln p_i), p_i the draft's probability of its own token (the largest one); above the
-    // threshold this token is the block's last.  The running sum sits in the word after sl_count.
-    // (the loop's words may have been written by another workgroup of the same launch: hand-off accesses)
-    const int sl_before = a.sl_count ? __hip_atomic_load(a.sl_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-    if (a.ppl_threshold > 0.f && a.sl_count) {
-      float* nll = reinterpret_cast<float*>(a.sl_count + 1);
-      const float sum = ld_f1<true>(nll) - logf(feat_s[0]);
-      st_f1<true>(nll, sum);
-      score = expf(sum / (float)(sl_before + 1));
-      if (score > a.ppl_threshold) halt |= 1u;
-    }
-    out->token = best_i;
-#pragma unroll
-    for (int i = 0; i < 12; ++i) out->feats[i] = feat_s[i];
-    out->score = score; out->halt = halt; out->executed = 1u;
-    if (!mismatch) {
-      if (a.token_next) *a.token_next = best_i;
-      if (a.block_slot) *a.block_slot = best_i;
-      if (a.sl_count) __hip_atomic_store(a.sl_count, sl_before + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (a.gate && halt) __hip_atomic_store(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (t == 0) classify_decide(a, feat_s, z, k.b2, best_i);
+  // (the launch of many workgroups polls these records: they are left empty)
+  for (int i = t; i < nb * CM_REC; i += NT) __hip_atomic_store(reinterpret_cast<uint32_t*>(const_cast<float*>(recs)) + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return best_i;
 }
 
-// The same computation spread over ceil(V / (4 NT)) workgroups (used when the caller gives scratch
-// memory).  Each workgroup reduces its slice of the logits (4 per thread) to a record {max, arg-max, S, T relative to its own
+// The same computation spread over ceil(V / (4 NT)) workgroups of a persistent launch.  Each workgroup reduces its slice of the logits (4 per thread) to a record {max, arg-max, S, T relative to its own
 // max, its ten largest values}; the last workgroup to finish (ticket, no waiting) merges the
 // records in index order: S = sum S_b e^(m_b - M), T = sum e^(m_b - M) (T_b + (m_b - M) S_b), the ten
 // largest of the records' candidates (ten per record), then features, classifier and halt decision.  Forcing a token
 // to max + 4 is applied to the merged sums in closed form.
 // b = index of this workgroup's slice of NT * 4 logits, nb = number of slices.  Returns the arg-max token in
 // every thread of the workgroup that finished the computation (the last to arrive), -1 in all others.
-// COH: the logits were written by other workgroups of the same launch.
-template <int NT, bool COH = false>
+// The logits were written by other workgroups of the same launch.
+template <int NT>
 __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b, const int nb, const uint32_t halted) {
   constexpr int NW = NT / 64;
   ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
@@ -2209,18 +2214,18 @@ __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b,
   const int idx = (b * NT + t) * 4;
   float r4[4];
   if (idx + 3 < V) {
-    const float4 v = ld_f4<COH>(x + idx);
+    const float4 v = ld_f4<true>(x + idx);
     r4[0] = v.x; r4[1] = v.y; r4[2] = v.z; r4[3] = v.w;
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r4[e] = idx + e < V ? ld_f1<COH>(x + idx + e) : -INFINITY;
+    for (int e = 0; e < 4; ++e) r4[e] = idx + e < V ? ld_f1<true>(x + idx + e) : -INFINITY;
   }
   // operands of the final stage that depend on no reduction are fetched now, so that the merging
   // workgroup does not pay their round trips one after another at the end
   int force = -1;
   float xf = 0.f;
   if (a.force_token) { force = *a.force_token; if (force >= V) force = -1; }
-  if (force >= 0) xf = ld_f1<COH>(x + force);
+  if (force >= 0) xf = ld_f1<true>(x + force);
   float w1[12], cb1 = 0.f, cw2 = 0.f, cb2 = 0.f;
 #pragma unroll
   for (int i = 0; i < 12; ++i) w1[i] = 0.f;
@@ -2276,16 +2281,276 @@ __device__ __forceinline__ int classify_unit(const ClassifyArgs& a, const int b,
   return classify_merge_finish<NT>(a, a.scratch + 64, nb, force, xf, k, sm);
 }
 
+// The ten largest of a wavefront's keys (N a lane; 0: none), as a list of candidates: a lower bound of the tenth largest, and every key that reaches it.
+// The lanes' maxima are taken over four lanes (16 groups); ten of those reach the tenth largest of them, which is the bound (about 15 of 1024
+// keys pass it).  Ten rounds of a wavefront-wide maximum, one key out per round, are a chain of 1 us; they remain for lists that do not fit
+// (many equal keys).
+__device__ __forceinline__ uint32_t row4_max_u32(uint32_t v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  const uint32_t m = max(r[0], r[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  return max(q[0], q[1]);
+}
+template <int D> __device__ __forceinline__ int reaches(const uint32_t g) {           // whether the lane D further on in the row has a key >= g
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)g, 0x120 + D, 0xF, 0xF, false) >= g ? 1 : 0;
+}
+__device__ __forceinline__ uint32_t tenth_bound(uint32_t g /* the lane's maximum */) {
+  g = row4_max_u32(g);
+  const int c = 1 + ((((reaches<1>(g) + reaches<2>(g)) + (reaches<3>(g) + reaches<4>(g))) + ((reaches<5>(g) + reaches<6>(g)) + (reaches<7>(g) + reaches<8>(g)))) +
+                     (((reaches<9>(g) + reaches<10>(g)) + (reaches<11>(g) + reaches<12>(g))) + ((reaches<13>(g) + reaches<14>(g)) + reaches<15>(g))));
+  uint32_t t = c >= 10 ? g : 0u;                  // the largest of those that ten reach: the same in every row of 16 lanes
+  t = dpp_max_u32<DPP_QUAD_XOR1, 0xF>(t);
+  t = dpp_max_u32<DPP_QUAD_XOR2, 0xF>(t);
+  t = dpp_max_u32<DPP_ROW_HALF_MIRROR, 0xF>(t);
+  return dpp_max_u32<DPP_ROW_MIRROR, 0xF>(t);
+}
+// As wave_top10, over keys.
+template <int N>
+__device__ __forceinline__ void rounds_of_ten(uint32_t (&k)[N], uint32_t* out10) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll 1
+  for (int rnd = 0; rnd < 10; ++rnd) {
+    uint32_t cur = k[0];
+#pragma unroll
+    for (int e = 1; e < N; ++e) cur = max(cur, k[e]);
+    const uint32_t w = wave_max_u32(cur);
+    if (w == 0u) break;                           // none left
+    if (lane == 0) out10[rnd] = w;
+    const unsigned long long owners = __ballot(cur == w);
+    bool drop = lane == __builtin_ctzll(owners);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const bool hit = drop && k[e] == w;
+      k[e] = hit ? 0u : k[e];
+      drop = drop && !hit;
+    }
+  }
+}
+// Appends the keys >= bound to list (64 places); returns how many there are (more than 64: the list is not complete).  SORTED: a lane's keys descend.
+template <int N, bool SORTED>
+__device__ __forceinline__ int append_keys(const uint32_t (&k)[N], const uint32_t bound, uint32_t* list) {
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const bool in = k[e] >= bound;
+    const unsigned long long b = __ballot(in);
+    if (SORTED && b == 0ull) break;
+    const int at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    if (in && at < 64) list[at] = k[e];
+    n += __builtin_popcountll(b);
+  }
+  __builtin_amdgcn_wave_barrier();
+  return n;
+}
+// The ten largest keys (of them those that reach the bound) in descending order to out10 (LDS; places without a key: minus infinity's).  list: 64 words of LDS.
+constexpr uint32_t KEY_NEG_INF = 0x007FFFFFu;
+template <int N, bool SORTED>
+__device__ __forceinline__ void select_ten(uint32_t (&k)[N], const uint32_t bound, uint32_t* list, uint32_t* out10) {
+  const int lane = threadIdx.x & 63;
+  if (lane < 10) out10[lane] = KEY_NEG_INF;
+  const int n = append_keys<N, SORTED>(k, bound, list);
+  if (n > 64) { rounds_of_ten(k, out10); return; }
+  // position of a candidate: how many beat it (larger, or equal and in front of it); lanes without one hold 0, which beats none
+  const uint32_t v = lane < n ? list[lane] : 0u;
+  int rank = 0;
+#pragma unroll 1
+  for (int j0 = 0; j0 < n; j0 += 8) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, j0 + q);
+      rank += o > (lane > j0 + q ? v - 1u : v) ? 1 : 0;
+    }
+  }
+  if (lane < n && rank < 10) out10[rank] = v;
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The many-workgroup form.  A workgroup reduces 1024 logits to a record of 16 words: {max, arg-max + 1, S, T, its ten largest}, floats as their
+// order-preserving keys, so that no word is 0.  The LAST workgroup of the grid polls the records until no word is 0 (the data is its own flag, see
+// k_chain; a record's statistics and its largest leave from two wavefronts, a store instruction each), merges them and leaves them at 0 for the next
+// launch.  It waits for workgroups that were started before it, and not without a bound: after `limit` polls it reports token -1, a score that is not
+// a number, and a halt.  What bounds it: a chain of dependent instructions, of about ten cycles each: load 0.7 us, a wavefront's 256 logits 1.1, the
+// workgroup's 1.4, hand-off 1, final selection 1, features and classifier 1.  32000 logits 8.5 -> 7.65 us a call (a ticket and a load in place of the
+// polls, ten rounds of maxima in place of the candidate lists; one wavefront for all 1024 logits of a workgroup 8.5: 3.4 us for the first two).
+struct MultiSmem {
+  alignas(16) uint32_t list[4][64], all[64], top[12];
+  uint32_t n[4], bound[4];
+  SoftStat st[4], best;
+  alignas(16) float feat[12];
+  float sum[CM_MULTI_NT / 64 + 1];
+  int lost;
+};
 __global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, const float* clf_params, const int32_t* force_token, uint32_t* gate, float* scratch,
                                                                 int vocab, int hidden, ClassifyArgs a) {
   a.logits = logits; a.clf_params = clf_params; a.force_token = force_token; a.gate = gate; a.scratch = scratch; a.vocab = vocab; a.hidden = hidden;
-  classify_unit<CM_MULTI_NT>(a, blockIdx.x, gridDim.x, gate_request(const_cast<const uint32_t*>(a.gate)));
+  __shared__ MultiSmem sm;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), V = vocab, b = blockIdx.x, nb = gridDim.x - 1;
+  const uint32_t halted = gate_request(gate);
+  uint32_t* recs = reinterpret_cast<uint32_t*>(scratch + 64);
+  if (b < nb) {
+    const int idx = (b * CM_MULTI_NT + t) * 4;
+    float r[4];
+    uint32_t key[4];
+    if (idx + 3 < V) {
+      const float4 v = *reinterpret_cast<const float4*>(logits + idx);
+      r[0] = v.x; r[1] = v.y; r[2] = v.z; r[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = idx + e < V ? logits[idx + e] : -INFINITY;
+    }
+    if (flag_set(halted)) {                       // uniform over the launch; the loads above are dropped
+      if (t == 0 && b == 0) reinterpret_cast<ClfOut*>(a.out)->executed = 0u;
+      return;
+    }
+    // every wavefront reduces its own 256 logits
+    {
+      VI mine{-INFINITY, 0x7fffffff};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        mine = vi_best(mine, VI{r[e], idx + e});
+        key[e] = idx + e < V ? f32_key(r[e]) : 0u;
+      }
+      const uint32_t bound = max(tenth_bound(max(max(key[0], key[1]), max(key[2], key[3]))), 1u);
+      int n = append_keys<4, false>(key, bound, sm.list[wv]);
+      const VI wb = wave_argmax(mine);
+      float S = 0.f, T = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float d = r[e] - wb.v, ex = r[e] == -INFINITY ? 0.f : expf(d);
+        S += ex; T += ex > 0.f ? ex * d : 0.f;
+      }
+      S = wave_sum(S); T = wave_sum(T);
+      if (n > 64) {
+        if (lane < 10) sm.list[wv][lane] = 0u;
+        rounds_of_ten(key, sm.list[wv]);
+        n = 10;
+      }
+      if (lane == 0) { sm.st[wv] = SoftStat{wb.v, wb.i, S, T}; sm.bound[wv] = bound; sm.n[wv] = (uint32_t)n; }
+    }
+    __syncthreads();
+    if (wv == 0) {                                // the workgroup's ten largest, from the wavefronts' candidates
+      const uint32_t bound = max(max(sm.bound[0], sm.bound[1]), max(sm.bound[2], sm.bound[3]));
+#pragma unroll
+      for (int w = 0; w < 4; ++w) { const uint32_t c = sm.list[w][lane]; key[w] = (uint32_t)lane < sm.n[w] ? c : 0u; }
+      select_ten<4, false>(key, bound, sm.all, sm.top);
+      if (lane < 12)
+        __hip_atomic_store(recs + b * CM_REC + 4 + lane, max(sm.top[min(lane, 9)], 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (a key is 0 for one bit pattern of a NaN)
+    } else if (wv == 1) {                         // its statistics, a wavefront's in each of four lanes
+      SoftStat q = sm.st[lane & 3];
+      VI best = vi_step<DPP_QUAD_XOR1, 0xF>(VI{q.m, q.i});
+      best = vi_step<DPP_QUAD_XOR2, 0xF>(best);
+      q = stat_rescaled(q, best.v);
+      float Sg = 0.f, Tg = 0.f;
+      Sg += dpp_f<0x00, 0xF>(0.f, q.S); Sg += dpp_f<0x55, 0xF>(0.f, q.S); Sg += dpp_f<0xAA, 0xF>(0.f, q.S); Sg += dpp_f<0xFF, 0xF>(0.f, q.S);
+      Tg += dpp_f<0x00, 0xF>(0.f, q.T); Tg += dpp_f<0x55, 0xF>(0.f, q.T); Tg += dpp_f<0xAA, 0xF>(0.f, q.T); Tg += dpp_f<0xFF, 0xF>(0.f, q.T);
+      const uint32_t w = lane == 0 ? f32_key(best.v) : (lane == 1 ? (uint32_t)best.i + 1u : f32_key(lane == 2 ? Sg : Tg));
+      if (lane < 4) __hip_atomic_store(recs + b * CM_REC + lane, max(w, 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return;
+  }
+  // the last workgroup; operands of the final stage that depend on no record first
+  int force = -1;
+  float xf = 0.f;
+  ClfCoef k;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) k.w1[i] = 0.f;
+  k.b1 = 0.f; k.w2 = 0.f; k.b2 = 0.f;
+  if (force_token) { force = *force_token; if (force >= V) force = -1; }
+  if (force >= 0) xf = logits[force];
+  if (clf_params) {
+    k.b2 = clf_params[hidden * 14];
+    if (t < hidden) {
+#pragma unroll
+      for (int i = 0; i < 12; ++i) k.w1[i] = clf_params[t * 12 + i];
+      k.b1 = clf_params[hidden * 12 + t];
+      k.w2 = clf_params[hidden * 13 + t];
+    }
+  }
+  if (flag_set(halted)) return;
+  if (wv == 1 || wv == 2) {
+    // a record per lane: the first wavefront of the two selects, the other merges the statistics
+    constexpr int Q = 3;
+    const uint32_t* rec = recs + min(lane, nb - 1) * CM_REC;
+    const int q0 = wv == 1 ? 1 : 0, nq = wv == 1 ? Q : 1;
+    u32x4 v[Q];
+    bool lost = a.limit < 0;
+    for (int spins = 0;; ++spins) {
+      bool ok = true;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const unsigned long long* p = reinterpret_cast<const unsigned long long*>(rec + (q0 + (q < nq ? q : 0)) * 4);
+        const unsigned long long x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[q] = u32x4{(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
+        ok = ok && v[q][0] != 0u && v[q][1] != 0u && v[q][2] != 0u && v[q][3] != 0u;
+      }
+      if (lost || __ballot(!ok) == 0ull) break;
+      if (spins >= a.limit) { lost = true; break; }
+    }
+    if (lane < nb) {                              // empty for the next launch
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (q < nq) *reinterpret_cast<u32x4*>(recs + lane * CM_REC + (q0 + q) * 4) = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (wv == 1) {
+      uint32_t key[10];
+#pragma unroll
+      for (int e = 0; e < 10; ++e) key[e] = lane < nb ? v[e >> 2][e & 3] : 0u;
+      select_ten<10, true>(key, max(tenth_bound(key[0]), 1u), sm.all, sm.top);
+      if (lane == 0) sm.lost = lost ? 1 : 0;
+    } else {
+      SoftStat r{-INFINITY, 0x7fffffff, 0.f, 0.f};
+      if (lane < nb) r = SoftStat{key_f32(v[0][0]), (int)(v[0][1] - 1u), key_f32(v[0][2]), key_f32(v[0][3])};
+      const VI best = wave_argmax(VI{r.m, r.i});
+      r = stat_rescaled(r, best.v);
+      const float S = wave_sum(r.S), T = wave_sum(r.T);
+      if (lane == 0) sm.best = SoftStat{best.v, best.i, S, T};
+    }
+  }
+  __syncthreads();
+  float mx = sm.best.m, Sg = sm.best.S, Tg = sm.best.T;
+  int best_i = sm.best.i;
+  if (wv == 0) {
+    float top = lane < 10 ? key_f32(sm.top[lane]) : -INFINITY;
+    if (force >= 0) {
+      // raise logit[force] from x_f to M + 4: shift every term to the new maximum, take the old
+      // contribution of x_f out and put the new one (e^0 = 1, with (x - max) = 0) in
+      const float mnew = mx + 4.0f;
+      const float sh = expf(-4.0f), ef = expf(xf - mnew);
+      Tg = sh * (Tg - 4.0f * Sg) - (ef > 0.f ? ef * (xf - mnew) : 0.f);
+      Sg = sh * Sg - ef + 1.0f;
+      // new top ten: M + 4 first, then the old ones without one instance of x_f (or without the last)
+      const unsigned long long same = __ballot(lane < 10 && top == xf);
+      const int drop = same != 0ull ? __builtin_ctzll(same) : 9;
+      const float before = __shfl(top, max(lane - 1, 0));
+      top = lane == 0 ? mnew : (lane <= drop ? before : top);
+      if (lane == 0) a.logits[force] = mnew;
+      mx = mnew; best_i = force;
+    }
+    if (lane < 10) sm.feat[lane] = (top == -INFINITY) ? 0.f : expf(top - mx) / Sg;
+    if (lane == 10) sm.feat[10] = logf(Sg) - Tg / Sg;
+    if (lane == 11) sm.feat[11] = a.pos_feature;
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (hidden > 64) __syncthreads();
+  else if (wv != 0) return;                       // (up to 64 units: all in the first wavefront, which finishes)
+  float contrib = 0.f;
+  if (clf_params && t < hidden) {
+    float acc = k.b1;
+#pragma unroll
+    for (int i = 0; i < 12; ++i) acc += k.w1[i] * sm.feat[i];
+    contrib = fmaxf(acc, 0.f) * k.w2;
+  }
+  const float z = hidden > 64 ? block_sum<CM_MULTI_NT>(contrib, sm.sum) : wave_sum(contrib);
+  if (t == 0) {
+    if (sm.lost != 0) { a.tau = INFINITY; a.force_halt = 1; }
+    classify_decide(a, sm.feat, sm.lost != 0 ? __builtin_nanf("") : z, k.b2, sm.lost != 0 ? -1 : best_i);
+  }
 }
 
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s) {
   if (a.vocab < 1 || a.vocab > 65536) return hipErrorInvalidValue;
   if (a.scratch != nullptr && a.vocab >= 4096) {
-    hipLaunchKernelGGL(k_classify_multi, dim3((a.vocab + 4 * CM_MULTI_NT - 1) / (4 * CM_MULTI_NT)), dim3(CM_MULTI_NT), 0, s, a.logits, a.clf_params,
+    hipLaunchKernelGGL(k_classify_multi, dim3((a.vocab + CM_SLICE - 1) / CM_SLICE + 1), dim3(CM_MULTI_NT), 0, s, a.logits, a.clf_params,
                        a.force_token, a.gate, a.scratch, a.vocab, a.hidden, a);
     return hipGetLastError();
   }
@@ -4894,7 +5159,7 @@ __device__ FWD_PHASE_FN void fwd_classify(const FwdCtx c) {
   ca.ref_token = f->clf.ref_token ? f->clf.ref_token + c.step : nullptr;
   const int nb = (f->vocab + 4 * CM_NT - 1) / (4 * CM_NT);
   if ((int)blockIdx.x < nb) {
-    const int tok = classify_unit<CM_NT, true>(ca, blockIdx.x, nb, 0u);
+    const int tok = classify_unit<CM_NT>(ca, blockIdx.x, nb, 0u);
     if (tok >= 0 && c.step + 1 < f->n_steps) {
       NormArgs na{};
       na.h = f->h; na.d = f->d; na.M = 1; na.layernorm = 0; na.eps = f->eps; na.g = f->layers[0].norm1_g;

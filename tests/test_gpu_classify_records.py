@@ -1,0 +1,71 @@
+"""The many-workgroup classify (records handed over by polling) against the one-workgroup form, which sorts by rounds: edges of the slices of 1024
+logits and of the wavefronts' 256, rows with fewer than ten numbers, rows whose candidates do not fit a list (many equal logits), and a wait that gives up."""
+import pytest
+import torch
+
+from paper_2405_04304_amd import binding as B
+from workloads import synth as W
+
+from test_gpu_parity import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _row(kind, vocab, g):
+    x = torch.randn(vocab, generator=g)
+    if kind == "equal":
+        x = torch.full((vocab,), 0.25)
+    elif kind == "few values":
+        x = torch.randint(0, 3, (vocab,), generator=g).float()
+    elif kind == "seven numbers":
+        y = torch.full((vocab,), float("-inf"))
+        at = torch.randperm(vocab, generator=g)[:7]
+        y[at] = x[at]
+        x = y
+    elif kind == "one slice":                            # all of the ten largest, and equal ones, in the last slice
+        x[-200:-150] = 9.0
+    elif kind == "zeros and signs":
+        x = torch.where(x > 0, 0.0, -0.0)
+    return x
+
+
+def _classify(clf, x, force, scratch):
+    d = dev()
+    rec = B.struct_tensor(B.ClfOut, 1, d)
+    lg = x.to(d).contiguous()
+    f = torch.tensor([force], dtype=torch.int32, device=d) if force is not None else None
+    B.disco_classify(clf, lg, x.numel(), 3.0, 0.5, False, rec, force_token=f, scratch=scratch)
+    torch.cuda.synchronize()
+    return B.read_struct(B.ClfOut, rec, 0), lg.cpu()
+
+
+@pytest.mark.parametrize("kind", ["normal", "equal", "few values", "seven numbers", "one slice", "zeros and signs"])
+def test_records_against_one_workgroup(kind):
+    g = torch.Generator().manual_seed(5)
+    scratch = B.classify_scratch(dev())
+    clf = B.DiscoClf(W.make_classifier(100), dev())
+    for vocab in (4096, 4097, 5119, 5120, 5376, 32000, 49152, 65535, 65536):
+        x = _row(kind, vocab, g)
+        for force in (None, int(torch.argmax(x)), vocab - 1):
+            (a, la), (b, lb) = _classify(clf, x, force, scratch), _classify(clf, x, force, None)
+            assert a.token == b.token and a.halt == b.halt and a.executed == b.executed == 1, (vocab, force)
+            # the same logits are selected; sums in another order: a few units in the last place of the probabilities, of the entropy's terms (< 12) absolutely
+            assert torch.allclose(torch.tensor(list(a.feats)), torch.tensor(list(b.feats)), rtol=2e-6, atol=5e-6), (vocab, force)
+            assert abs(a.score - b.score) < 1e-5 and torch.equal(la, lb)
+    assert int(scratch.view(torch.int32).abs().sum()) == 0           # every launch leaves its scratch empty
+
+
+def test_a_wait_that_gives_up_is_reported():
+    scratch = B.classify_scratch(dev())
+    clf = B.DiscoClf(W.make_classifier(100), dev())
+    x = _row("normal", 32000, torch.Generator().manual_seed(6))
+    want = _classify(clf, x, None, scratch)[0]
+    prev = B.disco_set_wait_limit(-1)
+    try:
+        got = _classify(clf, x, None, scratch)[0]
+    finally:
+        B.disco_set_wait_limit(prev)
+    assert got.token == -1 and got.halt == 1 and got.score != got.score
+    B._check(B.lib().disco_classify_scratch_init(scratch.data_ptr(), B._stream()))
+    again = _classify(clf, x, None, scratch)[0]
+    assert list(again.feats) == list(want.feats) and again.token == want.token and again.score == want.score
