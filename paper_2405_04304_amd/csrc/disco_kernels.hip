@@ -343,15 +343,16 @@ __device__ __forceinline__ KvSlot kv_slot(const GemmArgs& a, const int pos) {
 // QKV epilogue of one lane: output features n0 .. n0+3 (lo4) and their rotary partners n0 + d_head/2 ..
 // (hi4) of token row m at position pos: rotation, then the query row or the paged K / V entry.
 // ROPE false: the model has no rotation (the LayerNorm family has learned positions).  SLOT: the caller has looked up kv_slot.
+// factors: the two table entries, where the caller has loaded them.
 template <bool COH = false, bool ROPE = true, bool SLOT = false>
 __device__ __forceinline__ void qkv_store(const GemmArgs& a, float* q, const int n0, const int m, const int pos, KvSlot slot,
-                                          float (&lo4)[4], float (&hi4)[4]) {
+                                          float (&lo4)[4], float (&hi4)[4], const float4* factors = nullptr) {
   const int dsh = a.dh == 128 ? 7 : 6;            // d_head is 64 or 128
   const int head = n0 >> dsh, c = n0 & (a.dh - 1), half = a.dh >> 1;
   const bool is_v = head >= a.nq + a.nkv;
   if (ROPE && a.rope_tab != nullptr && !is_v) {
     // (cos, sin) of pos * base^(-2 (c + v) / d_head), tabulated per cached position
-    const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
+    const float4* tab = factors != nullptr ? factors : reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * half + c) * 2);
     const float4 t0 = tab[0], t1 = tab[1];
     const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
 #pragma unroll
@@ -3503,11 +3504,63 @@ hipError_t launch_loop_finish(const int32_t* sl_count, const uint32_t* gate, voi
 // stores a range's sums, k_gemm_sum adds the ranges in order and runs the epilogue.  (Partial sums through write-through
 // stores and a ticket in one launch measured slower than no split at all: 110 us against 50 + 16 for 5120 x 5120 at 511 tokens.)
 
+// Sum of four squares.  The roundings are those that the compiler chooses for (x x + y y) + (z z + w w) in an epilogue of one pair of row
+// tiles: in its first chunk the first square of a pair is rounded, in the others the second (written out: see split_product).
+__device__ __forceinline__ float squares_of_chunk(const bool first, const float4 h) {
+#pragma clang fp contract(off)
+  const float xx = h.x * h.x, yy = h.y * h.y, zz = h.z * h.z, ww = h.w * h.w;
+  return first ? fmaf(h.y, h.y, xx) + fmaf(h.w, h.w, zz) : fmaf(h.x, h.x, yy) + fmaf(h.z, h.z, ww);
+}
+
+// What the epilogue of a wavefront with one pair of row tiles reads: requested in front of the products, whose end it would
+// otherwise wait behind; k_gemm_sum requests it with the partial sums.  A pass of the 68M shape at 60 tokens 113.9 -> 112.1 us, at 511 142.2 -> 139.0,
+// at 600 in bf16 151.3 -> 146.8, of the mid-size grouped-query shape at 100 tokens 401 -> 397.  (The tokens' sums of squares requested there too and
+// added up behind the products gained nothing: the first copies take as long.)
+template <int EPI, int CA>
+struct TileAhead {
+  float4 h[EPI == EPI_PARTIAL ? CA : 1][4], gain[4];       // residual values and gains of the four chunks
+  float4 rope[EPI == EPI_QKV ? CA : 1][2][2];              // rotary factors of the two 4-row groups
+  KvSlot slot[EPI == EPI_QKV ? CA : 1];
+  __device__ __forceinline__ void request(const DenseArgs& d, const int g0, const int (&rt)[2]) {
+    const GemmArgs& a = d.g;
+    const int lane = threadIdx.x & 63, m = lane & 15, gh = lane >> 5;
+    if constexpr (EPI == EPI_PARTIAL) {
+      if (a.Xout != nullptr)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gain[i] = *reinterpret_cast<const float4*>(a.gain + max(rt[i >> 1], 0) * 16 + 8 * (i & 1) + 4 * gh);
+    }
+    if constexpr (EPI == EPI_PARTIAL || EPI == EPI_QKV) {
+#pragma unroll
+      for (int c = 0; c < CA; ++c) {
+        const int ci = min(g0 + 2 * c + ((lane >> 4) & 1), d.n_groups - 1);
+        if constexpr (EPI == EPI_PARTIAL) {
+          const float* hrow = a.h + (size_t)ci * d.hs + (size_t)m * a.ld_out;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) h[c][i] = *reinterpret_cast<const float4*>(hrow + max(rt[i >> 1], 0) * 16 + 8 * (i & 1) + 4 * gh);
+        } else {
+          const int pos = a.pos0 + 16 * ci + m;
+          slot[c] = kv_slot(a, pos);
+          if (a.rope_tab != nullptr)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const int ch = (max(rt[0], 0) * 16 + 4 * (2 * i + gh)) & (a.dh - 1);
+              const float4* tab = reinterpret_cast<const float4*>(a.rope_tab + ((size_t)pos * (a.dh >> 1) + ch) * 2);
+              rope[c][i][0] = tab[0]; rope[c][i][1] = tab[1];
+            }
+        }
+      }
+    }
+  }
+};
+
 // Epilogue of one wavefront: R2 pairs of row tiles (rt[2 q], rt[2 q + 1]; -1 past the matrix) x CA accumulators of 32 rows x
 // 32 tokens.  Lane: token column lane % 32 (two groups of 16), rows 8 i + 4 (lane / 32) .. + 3 of chunk i = 0 .. 3.
-template <int EPI, int R2, int CA, bool HI>
+// AHEAD: one pair of row tiles, whose inputs `ahead` holds.
+template <int EPI, int R2, int CA, bool HI, bool AHEAD = false>
 __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, const int (&rt)[2 * R2], const f32x16 (&acc)[R2][CA],
-                                              const float* rstd_s = nullptr /* 1 / rms of the tokens from group g0 on, where the launch forms them */) {
+                                              const float* rstd_s /* 1 / rms of the tokens from group g0 on, where the launch forms them */,
+                                              const TileAhead<EPI, CA>& ahead) {
+  static_assert(!AHEAD || R2 == 1, "one pair");
   constexpr bool PAIR = EpiTraits<EPI>::pair;
   const GemmArgs& a = d.g;
   const int lane = threadIdx.x & 63, m = lane & 15, gh = lane >> 5;
@@ -3522,8 +3575,10 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
 #pragma unroll
       for (int q = 0; q < R2; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          hv[q][i] = *reinterpret_cast<const float4*>(hrow + max(rt[2 * q + (i >> 1)], 0) * 16 + 8 * (i & 1) + 4 * gh);
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (AHEAD) hv[q][i] = ahead.h[c][i];
+          else hv[q][i] = *reinterpret_cast<const float4*>(hrow + max(rt[2 * q + (i >> 1)], 0) * 16 + 8 * (i & 1) + 4 * gh);
+        }
     }
 #pragma unroll
     for (int q = 0; q < R2; ++q) {
@@ -3540,7 +3595,8 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
             const int g = 2 * i + gh;             // 4-row group of the 16-row tile
             if constexpr (EPI == EPI_QKV) {
               const int n0 = t0 * 16 + 4 * g, pos = a.pos0 + 16 * ci + m;
-              qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, KvSlot{}, y[i], y[i + 2]);
+              if constexpr (AHEAD) qkv_store<false, true, true>(a, a.q + (size_t)ci * d.qs, n0, m, pos, ahead.slot[c], y[i], y[i + 2], ahead.rope[c][i]);
+              else qkv_store(a, a.q + (size_t)ci * d.qs, n0, m, pos, KvSlot{}, y[i], y[i + 2]);
             } else {
               float act[4];
 #pragma unroll
@@ -3563,10 +3619,15 @@ __device__ __forceinline__ void tile_epilogue(const DenseArgs& d, const int g0, 
               h.x += y[i][0]; h.y += y[i][1]; h.z += y[i][2]; h.w += y[i][3];
               *reinterpret_cast<float4*>(hrow + col) = h;
               if (a.Xout != nullptr) {            // deferred RMSNorm of the next GEMM
-                const float4 gn = *reinterpret_cast<const float4*>(a.gain + col);
+                const float4 gn = AHEAD ? ahead.gain[i] : *reinterpret_cast<const float4*>(a.gain + col);
+                if constexpr (AHEAD) {
+                  xpack_put4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, col, split_product<true>(h.x, gn.x, h.y, gn.y), split_product<true>(h.z, gn.z, h.w, gn.w));
+                  sq += squares_of_chunk(i == 0, h);
+                } else {
                 const float o[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
                 xpack_store4(a.Xout + (size_t)ci * d.xouts, a.KT_out, 16, m, col, o);
                 sq += (h.x * h.x + h.y * h.y) + (h.z * h.z + h.w * h.w);
+                }
               }
             } else {
               float act[4];
@@ -3644,8 +3705,21 @@ __global__ __launch_bounds__(512, OCC) void k_gemm_tile(const bf16_t* W, const b
     for (int c = 0; c < CA; ++c)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+  // (the first stages' copies need only leading arguments and go out while the others arrive.  What is requested between the copies only
+  // makes the waits below longer, which count the copies: everything is counted in order)
+  constexpr int FIRST = 3;
 #pragma unroll
-  for (int k = 0; k < NST; ++k)
+  for (int k = 0; k < FIRST; ++k)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) dma(i, k0 + k, k);
+  constexpr bool AHEAD = EPI != EPI_SPLIT && R2 == 1;
+  int rt[2 * R2];
+#pragma unroll
+  for (int r = 0; r < 2 * R2; ++r) rt[r] = row_tile(wr * 2 * R2 + r);
+  TileAhead<EPI, CA> ahead;
+  if constexpr (AHEAD) ahead.request(d, cb * WG_G + wc * 2 * CA, rt);
+#pragma unroll
+  for (int k = FIRST; k < NST; ++k)
 #pragma unroll
     for (int i = 0; i < PER; ++i) dma(i, k0 + k, k);
   const bool own_rstd = NORMED && a.ssq != nullptr;
@@ -3704,11 +3778,8 @@ __global__ __launch_bounds__(512, OCC) void k_gemm_tile(const bf16_t* W, const b
           *reinterpret_cast<float4*>(plane + (size_t)((q * CA + c) * 4 + i) * (NW * 256)) =
               make_float4(acc[q][c][4 * i], acc[q][c][4 * i + 1], acc[q][c][4 * i + 2], acc[q][c][4 * i + 3]);
   } else {
-    int rt[2 * R2];
-#pragma unroll
-    for (int r = 0; r < 2 * R2; ++r) rt[r] = row_tile(wr * 2 * R2 + r);
     if (own_rstd) __syncthreads();
-    tile_epilogue<EPI, R2, CA, HI>(d, cb * WG_G + wc * 2 * CA, rt, acc, own_rstd ? rstd_s + wc * 2 * CA * 16 : nullptr);
+    tile_epilogue<EPI, R2, CA, HI, AHEAD>(d, cb * WG_G + wc * 2 * CA, rt, acc, own_rstd ? rstd_s + wc * 2 * CA * 16 : nullptr, ahead);
   }
 }
 
@@ -3728,6 +3799,10 @@ __global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
   const int per_pg = nrb * 8, pg = cb / 8, width = min(8, ncb - pg * 8), ti = pg * per_pg + rb * width + (cb - pg * 8);
   const size_t PLANE = (size_t)R2 * CA * 16 * NW * 64;
   const float* plane = a.planes + (size_t)ti * d.k_split * PLANE + (size_t)(q * CA + c) * 4 * (NW * 256) + ((size_t)(wr * 4 + wc) * 64 + lane) * 4;
+  const int gs = __builtin_ctz(a.grp), t0 = ((pr >> gs) << (gs + 1)) + (pr & (a.grp - 1));
+  const int rt[2] = {t0, t0 + a.grp};
+  TileAhead<EPI, 1> ahead;
+  ahead.request(d, 2 * gp, rt);
   f32x16 acc[1][1];
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
@@ -3746,9 +3821,7 @@ __global__ __launch_bounds__(256) void k_gemm_sum(DenseArgs d) {
           acc[0][0][4 * i] += t[s][i].x; acc[0][0][4 * i + 1] += t[s][i].y; acc[0][0][4 * i + 2] += t[s][i].z; acc[0][0][4 * i + 3] += t[s][i].w;
         }
   }
-  const int gs = __builtin_ctz(a.grp), t0 = ((pr >> gs) << (gs + 1)) + (pr & (a.grp - 1));
-  const int rt[2] = {t0, t0 + a.grp};
-  tile_epilogue<EPI, 1, 1, HI>(d, 2 * gp, rt, acc);
+  tile_epilogue<EPI, 1, 1, HI, true>(d, 2 * gp, rt, acc, nullptr, ahead);
 }
 
 // Bytes of one workgroup's partial sums of a K range.
