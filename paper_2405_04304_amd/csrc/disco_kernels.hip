@@ -965,7 +965,16 @@ __global__ __launch_bounds__(NT) void k_norm(const int32_t* tokens, const bf16_t
                                              int n_tok, int vocab, NormArgs a) {
   a.tokens = tokens; a.tok_emb = tok_emb; a.pos_emb = pos_emb; a.h = h; a.gate = gate; a.d = d; a.pos0 = pos0; a.n_tok = n_tok; a.vocab = vocab;
   __shared__ float red[NT / 64 + 1];
-  norm_row<NT>(a, blockIdx.x, -1, red, gate_request(a.gate));
+  // The sixteen rows of a group go to one XCD (ids go round-robin to the eight), whose L2 then puts their panel's lines together, which four
+  // rows share; the last groups of a number that is not a multiple of eight go round-robin.
+  // (Rows round-robin: embedding of 511 rows of 5120 17 us, 2048 rows 53, 3008 of 6144 98; now 11.6, 41 and 79.)
+  const int id = blockIdx.x, groups = gridDim.x >> 4, whole = groups & ~7, rest = groups & 7;
+  int row = id;
+  if (groups > 1) {
+    if (id < whole * 16) row = ((id >> 7) * 8 + (id & 7)) * 16 + ((id >> 3) & 15);
+    else row = (whole + (id - whole * 16) % rest) * 16 + (id - whole * 16) / rest;
+  }
+  norm_row<NT>(a, row, -1, red, gate_request(a.gate));
 }
 
 // One-token activation panel of an fp32 vector (the operand of the GEMVs that give the correction vectors of a
@@ -1052,7 +1061,7 @@ __global__ __launch_bounds__(1024) void k_norm_groups(NormArgs a) {
 }
 
 // a workgroup per group needs groups for half the compute units: the embedding of 511 rows of 5120 (32 groups) took 39 us that
-// way against 17, so fewer groups, and the embedding, which gathers, keep a workgroup per row
+// way against 17 (11.6 since the rows of a group share an XCD), so fewer groups, and the embedding, which gathers, keep a workgroup per row
 bool norm_groups_fit(int d, int n_groups) { return n_groups >= 128 && d <= NORM_GROUPS_MAX_D; }
 
 hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
