@@ -3980,7 +3980,7 @@ hipError_t launch_rstd_groups(const float* ssq, int n_ssq, int d, float eps, flo
 // projection runs.  Otherwise (the projection's workgroups fill the chip: one per compute unit) the workgroups of a head are neighbours and become
 // the ranges of its attention when they have counted themselves in.  Either way nobody waits before it has signalled, so the
 // launch completes whenever all its workgroups are resident at once; the launcher checks that they fit.
-// us a pass, one launch / two: a 68M draft token 66.8 / 67.8 at 250 positions, 68.1 / 69.3 at 523, 72.3 / 76.6 at 2475; a multi-query draft token
+// us a pass, one launch / two (the draft models' one or two tokens take k_chain since): a 68M draft token 66.8 / 67.8 at 250 positions, 68.1 / 69.3 at 523, 72.3 / 76.6 at 2475; a multi-query draft token
 // (12 layers) 300.3 / 309.3 at 250, 314.3 / 324.6 at 640, 329.6 / 366.3 at 2475; two layers of 16 heads on 4 K / V heads, 6 tokens, 122.4 / 125.1
 // at 640, 127.3 / 135.8 at 2475; two 13B layers (not OWN: 240 projection workgroups) 298.4 / 301.0 for 6 tokens at 640, 321.6 / 321.9 for 12 at
 // 2475, and at 40 the two launches: 291.5 (301 when the projection's workgroups took the attention there too).
@@ -4159,8 +4159,9 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
 // stay, each with a role: QKV projection + MLP input (n_pu of them), attention (n_groups x parts), O-projection + MLP output (16 columns of
 // the residual stream each, whose rows live in registers from the first layer to the last).  A workgroup requests the weights of its next
 // phase and the cache entries of its next layer while it waits.  13.8 us a layer; a 68M-class draft token with its features at 523
-// positions 68.8 -> 52.5 us, four tokens of the 12-layer multi-query draft at 1490 1310 -> 836 us.  What bounds it: five hand-offs of about
-// 1.2 us a layer and, between them, the instructions of the one wavefront that finishes a tile.
+// positions 68.8 -> 50.8 us, four tokens of the 12-layer multi-query draft at 1490 1309 -> 828 us (feature kernel included).  What bounds it: five
+// hand-offs of about 1.3 us a layer (six where a head's ranges are spread over workgroups) and, between them, the instructions of the one wavefront
+// that finishes a tile.
 //
 // Hand-off: the data is its own flag.  Every buffer that one workgroup writes and others read inside the launch has an address of its
 // own per layer and is filled with CHAIN_EMPTY words by the launch in front (k_chain_begin); a reader polls the words it needs until
