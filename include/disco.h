@@ -470,7 +470,7 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   No launch of it waits for another workgroup: the mode for programs that decode on many streams at once, where
  *   mode 0's launches hold compute units for each other's waiting workgroups.
  * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
- * 5.69 ms in mode 1; a 68M-class draft step: 51 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a
+ * 5.69 ms in mode 1; a 68M-class draft step: 50 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a
  * launch costs more than a kernel boundary there, a hand-off whose data is its own flag half of one.     */
 int disco_set_launch_mode(int mode);
 

@@ -4159,7 +4159,7 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
 // stay, each with a role: QKV projection + MLP input (n_pu of them), attention (n_groups x parts), O-projection + MLP output (16 columns of
 // the residual stream each, whose rows live in registers from the first layer to the last).  A workgroup requests the weights of its next
 // phase and the cache entries of its next layer while it waits.  13.8 us a layer; a 68M-class draft token with its features at 523
-// positions 68.8 -> 50.8 us, four tokens of the 12-layer multi-query draft at 1490 1309 -> 828 us (feature kernel included).  What bounds it: five
+// positions 68.8 -> 49.6 us, four tokens of the 12-layer multi-query draft at 1490 1309 -> 828 us (feature kernel included).  What bounds it: five
 // hand-offs of about 1.3 us a layer (six where a head's ranges are spread over workgroups) and, between them, the instructions of the one wavefront
 // that finishes a tile.
 //
@@ -4961,17 +4961,20 @@ bool chain_plan(ChainArgs& a, int d_qkv, int dh, bool layernorm, size_t room, lo
   if (p.form != 2 || p.n_splits > CHAIN_MAX_RANGES) return false;
   a.split_len = p.split_len; a.n_splits = p.n_splits;
   // The heads of a K / V head share its keys and values as columns of the same products, as far as sixteen columns go; a group's ranges go to
-  // as many workgroups as leave the attention 24: a step of 32 positions costs a wavefront about half a microsecond.
+  // as many workgroups as make up 24, or 36 where the launch keeps within CHAIN_MAX_WGS: a step of 32 positions costs a wavefront about half a
+  // microsecond.  68M-class token, 24 / 36 / 48: at 523 positions 49.8 / 48.5 / 48.7 us, at 1024 50.5 / 49.5 / 49.4, at 2048 58.4 / 54.1 / 54.0.
   const int rep = a.nq / a.nkv, per_kv = (rep * a.M + 15) / 16;
   a.heads = (rep + per_kv - 1) / per_kv;
   a.n_groups = a.nkv * per_kv;
-  a.parts = 24 / a.n_groups < 1 ? 1 : 24 / a.n_groups;
+  const int n_p = d_qkv / 32, n_u = a.d_ff / 32;
+  a.n_pu = n_p > n_u ? n_p : n_u;
+  const int room_for = (CHAIN_MAX_WGS - a.n_pu - d / 16) / a.n_groups, few = 24 / a.n_groups < 1 ? 1 : 24 / a.n_groups;
+  a.parts = 36 / a.n_groups < room_for ? 36 / a.n_groups : room_for;
+  if (a.parts < few) a.parts = few;
   if (a.parts > a.n_splits) a.parts = a.n_splits;
   const int most = (a.n_splits + a.parts - 1) / a.parts;          // ranges of a workgroup
   const int part_len = a.split_len / 32 < 8 ? a.split_len / 32 : 8;
   if (most * part_len * a.heads * a.M > CHAIN_PARTS || most * a.heads * a.M > 32) return false;
-  const int n_p = d_qkv / 32, n_u = a.d_ff / 32;
-  a.n_pu = n_p > n_u ? n_p : n_u;
   a.kpw = kpw;
   a.wgs = a.n_pu + a.n_groups * a.parts + d / 16;
   if (a.wgs > CHAIN_MAX_WGS || a.wgs > (capacity != 0 ? capacity : CHAIN_BY_SHAPE(chain_capacity, a.M, layernorm, kpw))) return false;
