@@ -960,7 +960,8 @@ __device__ __forceinline__ void norm_row(const NormArgs& a, const int row, const
   }
 }
 
-template <int NT>
+// GROUPS: the rows of a prompt pass, groups of sixteen.
+template <int NT, bool GROUPS>
 __global__ __launch_bounds__(NT) void k_norm(const int32_t* tokens, const bf16_t* tok_emb, const bf16_t* pos_emb, float* h, const uint32_t* gate, int d, int pos0,
                                              int n_tok, int vocab, NormArgs a) {
   a.tokens = tokens; a.tok_emb = tok_emb; a.pos_emb = pos_emb; a.h = h; a.gate = gate; a.d = d; a.pos0 = pos0; a.n_tok = n_tok; a.vocab = vocab;
@@ -968,9 +969,10 @@ __global__ __launch_bounds__(NT) void k_norm(const int32_t* tokens, const bf16_t
   // The sixteen rows of a group go to one XCD (ids go round-robin to the eight), whose L2 then puts their panel's lines together, which four
   // rows share; the last groups of a number that is not a multiple of eight go round-robin.
   // (Rows round-robin: embedding of 511 rows of 5120 17 us, 2048 rows 53, 3008 of 6144 98; now 11.6, 41 and 79.)
-  const int id = blockIdx.x, groups = gridDim.x >> 4, whole = groups & ~7, rest = groups & 7;
+  const int id = blockIdx.x;
   int row = id;
-  if (groups > 1) {
+  if (GROUPS) {
+    const int groups = gridDim.x >> 4, whole = groups & ~7, rest = groups & 7;
     if (id < whole * 16) row = ((id >> 7) * 8 + (id & 7)) * 16 + ((id >> 3) & 15);
     else row = (whole + (id - whole * 16) % rest) * 16 + (id - whole * 16) / rest;
   }
@@ -1074,7 +1076,8 @@ hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
   }
   const unsigned rows = a.n_groups > 0 ? 16u * (unsigned)a.n_groups : (unsigned)a.M;
   const int nt = a.d <= 2048 ? 256 : 1024;
-  hipLaunchKernelGGL(nt == 256 ? k_norm<256> : k_norm<1024>, dim3(rows), dim3(nt), 0, s, a.tokens, a.tok_emb, a.pos_emb, a.h, a.gate, a.d, a.pos0,
+  const bool groups = a.n_groups > 1;             // (one group's rows do without the read of the grid's size)
+  hipLaunchKernelGGL(nt == 256 ? (groups ? k_norm<256, true> : k_norm<256, false>) : (groups ? k_norm<1024, true> : k_norm<1024, false>), dim3(rows), dim3(nt), 0, s, a.tokens, a.tok_emb, a.pos_emb, a.h, a.gate, a.d, a.pos0,
                      a.n_tok, a.vocab, a);
   return hipGetLastError();
 }
