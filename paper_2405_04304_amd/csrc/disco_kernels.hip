@@ -1076,8 +1076,10 @@ hipError_t launch_norm(const NormArgs& a, hipStream_t s) {
   }
   const unsigned rows = a.n_groups > 0 ? 16u * (unsigned)a.n_groups : (unsigned)a.M;
   const int nt = a.d <= 2048 ? 256 : 1024;
-  const bool groups = a.n_groups > 1;             // (one group's rows do without the read of the grid's size)
-  hipLaunchKernelGGL(nt == 256 ? (groups ? k_norm<256, true> : k_norm<256, false>) : (groups ? k_norm<1024, true> : k_norm<1024, false>), dim3(rows), dim3(nt), 0, s, a.tokens, a.tok_emb, a.pos_emb, a.h, a.gate, a.d, a.pos0,
+  // reading the grid's size costs a launch about 0.2 us, more than narrow rows gain (twelve layers of 768 columns at 39 tokens 633 -> 638 us a
+  // pass), and fewer than eight groups have no XCD of their own
+  const bool groups = nt == 1024 && a.n_groups >= 8;
+  hipLaunchKernelGGL((nt == 256 ? k_norm<256, false> : (groups ? k_norm<1024, true> : k_norm<1024, false>)), dim3(rows), dim3(nt), 0, s, a.tokens, a.tok_emb, a.pos_emb, a.h, a.gate, a.d, a.pos0,
                      a.n_tok, a.vocab, a);
   return hipGetLastError();
 }
