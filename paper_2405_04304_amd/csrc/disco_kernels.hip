@@ -960,13 +960,13 @@ __device__ __forceinline__ void norm_row(const NormArgs& a, const int row, const
   }
 }
 
-// GROUPS: the rows of a prompt pass, groups of sixteen.
+// GROUPS: wide rows of a prompt pass, in groups of sixteen.
 template <int NT, bool GROUPS>
 __global__ __launch_bounds__(NT) void k_norm(const int32_t* tokens, const bf16_t* tok_emb, const bf16_t* pos_emb, float* h, const uint32_t* gate, int d, int pos0,
                                              int n_tok, int vocab, NormArgs a) {
   a.tokens = tokens; a.tok_emb = tok_emb; a.pos_emb = pos_emb; a.h = h; a.gate = gate; a.d = d; a.pos0 = pos0; a.n_tok = n_tok; a.vocab = vocab;
   __shared__ float red[NT / 64 + 1];
-  // The sixteen rows of a group go to one XCD (ids go round-robin to the eight), whose L2 then puts their panel's lines together, which four
+  // GROUPS: the sixteen rows of a group go to one XCD (ids go round-robin to the eight), whose L2 then puts their panel's lines together, which four
   // rows share; the last groups of a number that is not a multiple of eight go round-robin.
   // (Rows round-robin: embedding of 511 rows of 5120 17 us, 2048 rows 53, 3008 of 6144 98; now 11.6, 41 and 79.)
   const int id = blockIdx.x;
@@ -3528,7 +3528,7 @@ __device__ __forceinline__ float squares_of_chunk(const bool first, const float4
 
 // What the epilogue of a wavefront with one pair of row tiles reads: requested in front of the products, whose end it would
 // otherwise wait behind; k_gemm_sum requests it with the partial sums.  A pass of the 68M shape at 60 tokens 113.9 -> 112.1 us, at 511 142.2 -> 139.0,
-// at 600 in bf16 151.3 -> 146.8, of the mid-size grouped-query shape at 100 tokens 401 -> 397.  (The tokens' sums of squares requested there too and
+// at 600 in bf16 151.5 -> 148.9, of the mid-size grouped-query shape at 100 tokens 401 -> 397.  (The tokens' sums of squares requested there too and
 // added up behind the products gained nothing: the first copies take as long.)
 template <int EPI, int CA>
 struct TileAhead {
