@@ -69,3 +69,20 @@ def test_a_wait_that_gives_up_is_reported():
     B._check(B.lib().disco_classify_scratch_init(scratch.data_ptr(), B._stream()))
     again = _classify(clf, x, None, scratch)[0]
     assert list(again.feats) == list(want.feats) and again.token == want.token and again.score == want.score
+
+
+@pytest.mark.parametrize("arrived", ["ten largest", "statistics"])
+def test_either_polling_wavefront_may_give_up_alone(arrived):
+    """Two wavefronts poll different words of the records.  With one part in place beforehand and a limit of one poll, one of them succeeds and the other
+    runs out: the call reports the failure."""
+    scratch = B.classify_scratch(dev())
+    clf = B.DiscoClf(W.make_classifier(100), dev())
+    x = _row("normal", 32000, torch.Generator().manual_seed(6))
+    recs = scratch.view(torch.int32)[64:].view(64, 16)
+    (recs[:, 4:] if arrived == "ten largest" else recs[:, :4]).fill_(0x7F000000)
+    prev = B.disco_set_wait_limit(0)
+    try:
+        got = _classify(clf, x, None, scratch)[0]
+    finally:
+        B.disco_set_wait_limit(prev)
+    assert got.token == -1 and got.halt == 1 and got.score != got.score and got.executed == 1
