@@ -183,12 +183,14 @@ int disco_draft_step(const disco_model* draft, disco_kv* kv, const int32_t* dev_
  * dev_scratch (may be NULL): DISCO_CLASSIFY_SCRATCH_BYTES of device memory, 256-byte aligned,
  * prepared once by disco_classify_scratch_init and used by one stream at a time; with it the
  * reduction over the vocabulary is spread over many workgroups, without it one workgroup does it
- * all (same results up to fp32 summation order).  vocab <= 65536; dev_logits 16-byte aligned.       */
+ * all (same results up to fp32 summation order).  One of the many workgroups waits for the others' results; should that wait
+ * run out (about a second), the call reports token -1, score NaN and halt 1, and so does every later call with this
+ * scratch until disco_classify_scratch_init prepares it again.  vocab <= 65536; dev_logits 16-byte aligned.  */
 int disco_classify(const disco_clf* clf, float* dev_logits, int vocab, float pos_feature, float tau,
                    int force_halt, disco_clf_out* dev_out, int32_t* dev_token_next,
                    int32_t* dev_block_slot, uint32_t* dev_gate, int32_t* dev_sl_count,
                    const int32_t* dev_force_token, void* dev_scratch, disco_stream s);
-/* Zeroes a classify scratch buffer (kernels leave it at zero afterwards).                           */
+/* Zeroes a classify scratch buffer (kernels leave it at zero afterwards, but for the mark of a wait that ran out). */
 int disco_classify_scratch_init(void* dev_scratch, disco_stream s);
 
 /* disco_classify for callers that cannot allocate device memory or pass a scratch buffer of their own
@@ -196,7 +198,7 @@ int disco_classify_scratch_init(void* dev_scratch, disco_stream s);
  * workgroup reduction uses an array inside the library's code object instead of dev_scratch
  * (DISCO_CLASSIFY_SCRATCH_BYTES per GPU, held until the process ends).  Same arguments, same results
  * and the same kernels as disco_classify with a scratch buffer; the call allocates nothing, enqueues a
- * small fill kernel that zeroes the array and then the classify kernel.  vocab above
+ * small fill kernel that zeroes the array (a wait that ran out marks its own call only) and then the classify kernel.  vocab above
  * DISCO_CLASSIFY_STATIC_MAX_VOCAB is refused with DISCO_ECAP.  Every call on one GPU shares that GPU's
  * array: calls that overlap on one GPU (different streams, or replays of graphs that hold it) race;
  * serialise them.  The first call on a device looks the array's address up (make it before a capture). */

@@ -99,7 +99,8 @@ struct ClassifyArgs {
   const int32_t* force_token;
   const int32_t* ref_token;          // optional: known continuation; a different arg-max ends the block and stays out of it
   float ppl_threshold;               // > 0: perplexity rule (needs sl_count; the float after it holds -sum ln p of the block)
-  float* scratch;                    // optional: >= CLASSIFY_SCRATCH_BYTES, zeros (a ticket counter, then records, which every launch leaves at zero)
+  float* scratch;                    // optional: >= CLASSIFY_SCRATCH_BYTES, zeros (a ticket counter, the word below, then records, which every launch leaves at zero)
+  unsigned* abort_word;              // with scratch: set for good by a wait that gives up, and then every result says so
   int limit;                         // polls before the wait for the other workgroups' records gives up (negative: at once)
 };
 struct SampleArgs {

@@ -2073,8 +2073,10 @@ struct ClassifySmem {
   int last;
 };
 
-// Score, halting decision and the loop's words, from the features and the classifier's sum z: by one thread.
-__device__ __forceinline__ void classify_decide(const ClassifyArgs& a, const float* feat_s, const float z, const float b2, const int best_i) {
+// Score, halting decision and the loop's words, from the features and the classifier's sum z: by one thread.  lost: the features are
+// not this row's (a wait has given up): token -1, a score that is not a number, and a halt.
+__device__ __forceinline__ void classify_decide(const ClassifyArgs& a, const float* feat_s, const float z, const float b2, const int arg_max, const bool lost = false) {
+  const int best_i = lost ? -1 : arg_max;
   ClfOut* out = reinterpret_cast<ClfOut*>(a.out);
   float score = __builtin_nanf("");
   uint32_t halt = a.force_halt ? 1u : 0u;
@@ -2085,7 +2087,7 @@ __device__ __forceinline__ void classify_decide(const ClassifyArgs& a, const flo
   // reference lookahead: a token that differs from the known continuation ends the block and is
   // not part of it (bit 1 of halt)
   bool mismatch = false;
-  if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && best_i != ref; }
+  if (a.ref_token) { const int ref = *a.ref_token; mismatch = ref >= 0 && best_i != ref && !lost; }
   if (mismatch) halt = 3u;
   // perplexity rule (App. F's rule-based baseline): the block's draft tokens so far have perplexity
   // exp(-(1/j) sum ln p_i), p_i the draft's probability of its own token (the largest one); above the
@@ -2099,6 +2101,7 @@ __device__ __forceinline__ void classify_decide(const ClassifyArgs& a, const flo
     score = expf(sum / (float)(sl_before + 1));
     if (score > a.ppl_threshold) halt |= 1u;
   }
+  if (lost) { score = __builtin_nanf(""); halt = 1u; }
   out->token = best_i;
 #pragma unroll
   for (int i = 0; i < 12; ++i) out->feats[i] = feat_s[i];
@@ -2384,7 +2387,8 @@ __device__ __forceinline__ void select_ten(uint32_t (&k)[N], const uint32_t boun
 // order-preserving keys, so that no word is 0.  The LAST workgroup of the grid polls the records until no word is 0 (the data is its own flag, see
 // k_chain; a record's statistics and its largest leave from two wavefronts, a store instruction each), merges them and leaves them at 0 for the next
 // launch.  It waits for workgroups that were started before it, and not without a bound: after `limit` polls it reports token -1, a score that is not
-// a number, and a halt.  What bounds it: a chain of dependent instructions, of about ten cycles each: load 0.7 us, a wavefront's 256 logits 1.1, the
+// a number, and a halt, and marks the scratch (abort_word).  A workgroup that was late then leaves a record that nothing clears, so every later launch on a marked
+// scratch reports the same, until it is initialised.  What bounds it: a chain of dependent instructions, of about ten cycles each: load 0.7 us, a wavefront's 256 logits 1.1, the
 // workgroup's 1.4, hand-off 1, final selection 1, features and classifier 1.  32000 logits 8.5 -> 7.65 us a call (a ticket and a load in place of the
 // polls, ten rounds of maxima in place of the candidate lists; one wavefront for all 1024 logits of a workgroup 8.5: 3.4 us for the first two).
 struct MultiSmem {
@@ -2472,6 +2476,7 @@ __global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, c
   k.b1 = 0.f; k.w2 = 0.f; k.b2 = 0.f;
   if (force_token) { force = *force_token; if (force >= V) force = -1; }
   if (force >= 0) xf = logits[force];
+  const uint32_t lost_before = __hip_atomic_load(a.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (clf_params) {
     k.b2 = clf_params[hidden * 14];
     if (t < hidden) {
@@ -2501,7 +2506,10 @@ __global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, c
       if (lost || __ballot(!ok) == 0ull) break;
       if (spins >= a.limit) { lost = true; break; }
     }
-    if (lane == 0) sm.lost[wv - 1] = lost ? 1 : 0;
+    if (lane == 0) {
+      sm.lost[wv - 1] = lost ? 1 : 0;
+      if (lost) __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (lane < nb) {                              // empty for the next launch
 #pragma unroll
       for (int q = 0; q < Q; ++q)
@@ -2558,15 +2566,14 @@ __global__ __launch_bounds__(CM_MULTI_NT) void k_classify_multi(float* logits, c
   const float z = hidden > 64 ? block_sum<CM_MULTI_NT>(contrib, sm.sum) : wave_sum(contrib);
   if (t == 0) {
     // (the two poll different words at different rates, so one of them can give up alone)
-    const bool lost = (sm.lost[0] | sm.lost[1]) != 0;
-    if (lost) { a.tau = INFINITY; a.force_halt = 1; }
-    classify_decide(a, sm.feat, lost ? __builtin_nanf("") : z, k.b2, lost ? -1 : best_i);
+    classify_decide(a, sm.feat, z, k.b2, best_i, (sm.lost[0] | sm.lost[1]) != 0 || flag_set(lost_before));
   }
 }
 
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s) {
   if (a.vocab < 1 || a.vocab > 65536) return hipErrorInvalidValue;
   if (a.scratch != nullptr && a.vocab >= 4096) {
+    if (a.abort_word == nullptr) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_classify_multi, dim3((a.vocab + CM_SLICE - 1) / CM_SLICE + 1), dim3(CM_MULTI_NT), 0, s, a.logits, a.clf_params,
                        a.force_token, a.gate, a.scratch, a.vocab, a.hidden, a);
     return hipGetLastError();

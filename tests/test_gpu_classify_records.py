@@ -86,3 +86,45 @@ def test_either_polling_wavefront_may_give_up_alone(arrived):
     finally:
         B.disco_set_wait_limit(prev)
     assert got.token == -1 and got.halt == 1 and got.score != got.score and got.executed == 1
+
+
+def test_a_give_up_stays_on_its_scratch_until_that_is_initialised():
+    """A workgroup that is late stores its record behind the give-up: no later call may take that for a record of its own row."""
+    scratch = B.classify_scratch(dev())
+    clf = B.DiscoClf(W.make_classifier(100), dev())
+    g = torch.Generator().manual_seed(7)
+    x, y = _row("normal", 32000, g), _row("normal", 32000, g)
+    want = _classify(clf, y, None, scratch)[0]
+    prev = B.disco_set_wait_limit(-1)
+    try:
+        assert _classify(clf, x, None, scratch)[0].token == -1
+    finally:
+        B.disco_set_wait_limit(prev)
+    for _ in range(3):
+        got = _classify(clf, y, None, scratch)[0]
+        assert got.token == -1 and got.halt == 1 and got.score != got.score and got.executed == 1
+    B._check(B.lib().disco_classify_scratch_init(scratch.data_ptr(), B._stream()))
+    for _ in range(2):
+        got = _classify(clf, y, None, scratch)[0]
+        assert got.token == want.token and list(got.feats) == list(want.feats) and got.score == want.score
+
+
+def test_a_give_up_on_the_array_of_the_library_ends_with_its_call():
+    d, clf = dev(), B.DiscoClf(W.make_classifier(100), dev())
+    g = torch.Generator().manual_seed(8)
+    x, y = _row("normal", 32000, g).to(d), _row("normal", 32000, g).to(d)
+    rec = B.struct_tensor(B.ClfOut, 1, d)
+
+    def call(t):
+        B.disco_classify_static(clf, t, 32000, 3.0, 0.5, 0, rec)
+        torch.cuda.synchronize()
+        return B.read_struct(B.ClfOut, rec, 0)
+
+    want = call(y)
+    prev = B.disco_set_wait_limit(-1)
+    try:
+        assert call(x).token == -1
+    finally:
+        B.disco_set_wait_limit(prev)
+    got = call(y)
+    assert got.token == want.token and list(got.feats) == list(want.feats) and got.score == want.score
