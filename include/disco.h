@@ -459,7 +459,8 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   workgroups fit the GPU at once: the attention of a head
  *   needs only that head's rows of the projection, so its workgroups wait for those alone (a counter per head)
  *   instead of for the whole grid.  A narrow model (up to 1024 columns, heads of 64 channels) runs ALL its layers in one launch for one or
- *   two tokens, whose workgroups wait for each other's results.  Every such wait is bounded; if one ever runs out (about a second; it needs the
+ *   two tokens, whose workgroups wait for each other's results.  The features of a draft
+ *   loop (many workgroups) have a wait as well, see disco_classify.  Every such wait is bounded; if one ever runs out (about a second; it needs the
  *   launch's workgroups not to be resident together for that long) the launch still ends, the workspace is
  *   marked, and every later result of that workspace says so -- NaN logits, -1 in disco_verify's arg-max and in
  *   disco_loop_out.sl, DISCO_EHIP from disco_iterate -- until disco_workspace_init is called again.

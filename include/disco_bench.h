@@ -24,7 +24,7 @@ float disco_probe_read_ms(void);
  * unusable data (default 2^20, about a second).  A negative value makes every such wait give up at once, so the
  * failure path (NaN logits, -1 from the arg-max and loop-finish kernels, DISCO_EHIP from disco_iterate) can be
  * exercised with kernels that still run to their end.  After a failure the workspace has to be initialised again
- * (disco_workspace_init), and so has a scratch buffer given to disco_classify (disco_classify_scratch_init), whose mark is its own.  Returns the previous value.  Process-wide.                                     */
+ * (disco_workspace_init); a scratch buffer given to disco_classify is marked instead and needs disco_classify_scratch_init.  Returns the previous value.  Process-wide.                                     */
 int disco_set_wait_limit(int polls);
 
 /* Testing and measurement aid: the kernels that disco_prefill_ex chooses for a prompt of n_tokens in a cache of

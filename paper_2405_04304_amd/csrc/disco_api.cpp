@@ -882,7 +882,7 @@ static int draft_loop_impl(const disco_model* draft, disco_kv* kv, const disco_c
     a.sl_count = ws.sl_count; a.force_token = dev_force_tokens ? dev_force_tokens + (j - 1) : nullptr;
     a.ref_token = dev_ref_tokens ? dev_ref_tokens + (j - 1) : nullptr;
     a.ppl_threshold = ppl_threshold;
-    a.scratch = ws.clf_scratch; a.abort_word = reinterpret_cast<unsigned*>(ws.clf_scratch) + 1; a.limit = g_wait_limit;
+    a.scratch = ws.clf_scratch; a.abort_word = ws.abort_word; a.limit = g_wait_limit;      // (the loop's end reports -1)
     { const hipError_t e = launch_classify(a, st); if (e != hipSuccess) { kv->len = len_entry; return hip_fail(e, "classify launch"); } }
   }
   HIP_TRY(launch_loop_finish(ws.sl_count, ws.gate, dev_out, host_out, ws.abort_word, st), "loop finish launch");

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2405_04304_amd import binding as B
+from paper_2405_04304_amd.engine import SpecEngine
 from workloads import synth as W
 
 from test_gpu_parity import dev
@@ -128,3 +129,53 @@ def test_a_give_up_on_the_array_of_the_library_ends_with_its_call():
         B.disco_set_wait_limit(prev)
     got = call(y)
     assert got.token == want.token and list(got.feats) == list(want.feats) and got.score == want.score
+
+
+def _draft_loop(gm, clf, ws, ctx, tau=0.0, ppl=0.0):
+    d = dev()
+    kv = B.DiscoKV(gm, ctx + 32, 16)
+    B.disco_kv_rollback(kv, 0)
+    steps, lo_d, lo_h = B.struct_tensor(B.ClfOut, 16, d), B.struct_tensor(B.LoopOut, 1, d), B.struct_tensor(B.LoopOut, 1, pinned=True)
+    tok, lg = torch.tensor([5], dtype=torch.int32, device=d), torch.empty(gm.shape.vocab, dtype=torch.float32, device=d)
+    B.disco_draft_loop_ex(gm, kv, clf, tok, 1, 3, 0, 1.0, tau, lg, steps, lo_d, lo_h, ws, ppl_threshold=ppl)
+    torch.cuda.synchronize()
+    lo = B.LoopOut.from_buffer_copy(lo_h.numpy().tobytes())
+    return lo.sl, list(lo.block[:4]), bool(torch.isfinite(lg).all())
+
+
+def test_a_give_up_inside_a_draft_loop_is_reported():
+    """A model whose forward waits nowhere (68 heads of their own, at most 256 positions: a launch per phase), so the features' launch is the only wait
+    of its draft loop: the loop reports -1 and an iteration DISCO_EHIP until the workspace is initialised, as for every other wait."""
+    d = dev()
+    shape = W.ModelShape("B", 1, 64, 68, 64, 68, 64, 4096)
+    gm, clf = B.DiscoModel(shape, W.make_weights(shape, 9, "bf16", sigma=0.05), d), B.DiscoClf(W.make_classifier(100), d)
+    assert B.disco_qkv_attn_plan(gm.handle, 1, 40)["form"] == "separate" and not B.disco_layers_plan(gm.handle, 1, 40, 16)["one_launch"]
+    ws = gm.workspace(16, 96)
+    for kind in ("classifier", "perplexity"):
+        args = {"tau": 0.0} if kind == "classifier" else {"ppl": 1e30}
+        c = clf if kind == "classifier" else None
+        want = _draft_loop(gm, c, ws, 40, **args)
+        assert want[0] == 3 and want[2]
+        prev = B.disco_set_wait_limit(-1)
+        try:
+            assert _draft_loop(gm, c, ws, 40, **args)[0] == -1
+        finally:
+            B.disco_set_wait_limit(prev)
+        assert _draft_loop(gm, c, ws, 40, **args)[0] == -1                    # the workspace stays marked
+        B._check(B.lib().disco_workspace_init(gm.handle, ws.buf.data_ptr(), ws.nbytes, 16, 96, B._stream()))
+        assert _draft_loop(gm, c, ws, 40, **args) == want
+    eng = SpecEngine(gm, gm, clf, max_ctx=96)
+    prompt, pol = list(range(5, 25)), {"mode": "disco", "tau": 0.0, "sl_max": 3, "pos_mode": "block"}
+    text = eng.generate(prompt, 8, pol)["tokens"]
+    for extra in ({}, {"mode": "oracle", "reference": text}):
+        eng.reset()
+        eng.prefill(prompt[:-1])
+        prev = B.disco_set_wait_limit(-1)
+        try:
+            with pytest.raises(B.DiscoError) as e:
+                eng.generate(prompt, 8, dict(pol, **extra), do_prefill=False)
+            assert e.value.code == B.EHIP
+        finally:
+            B.disco_set_wait_limit(prev)
+        B._check(B.lib().disco_workspace_init(gm.handle, eng.ws_d.buf.data_ptr(), eng.ws_d.nbytes, 16, 96, B._stream()))
+        assert eng.generate(prompt, 8, dict(pol, **extra))["tokens"] == text
