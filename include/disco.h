@@ -183,7 +183,7 @@ int disco_draft_step(const disco_model* draft, disco_kv* kv, const int32_t* dev_
  * dev_scratch (may be NULL): DISCO_CLASSIFY_SCRATCH_BYTES of device memory, 256-byte aligned,
  * prepared once by disco_classify_scratch_init and used by one stream at a time; with it the
  * reduction over the vocabulary is spread over many workgroups, without it one workgroup does it
- * all (same results up to fp32 summation order).  One of the many workgroups waits for the others' results; should that wait
+ * all (same results up to fp32 summation order).  In launch modes 0 and 1 one of the many workgroups waits for the others' results; should that wait
  * run out (about a second), the call reports token -1, score NaN and halt 1, and so does every later call with this
  * scratch until disco_classify_scratch_init prepares it again.  vocab <= 65536; dev_logits 16-byte aligned.  */
 int disco_classify(const disco_clf* clf, float* dev_logits, int vocab, float pos_feature, float tau,
@@ -470,7 +470,7 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   used silently); results agree with mode 0 to fp32 summation order.
  * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order where every query
  *   head has its own K / V head in the RMSNorm family (the context is dealt differently), bit for bit in other models.
- *   No launch of it waits for another workgroup: the mode for programs that decode on many streams at once, where
+ *   No launch of it waits for another workgroup (disco_classify included): the mode for programs that decode on many streams at once, where
  *   mode 0's launches hold compute units for each other's waiting workgroups.
  * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
  * 5.69 ms in mode 1; a 68M-class draft step: 50 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a

@@ -732,7 +732,8 @@ static int classify_impl(const disco_clf* clf, float* dev_logits, int vocab, flo
   a.logits = dev_logits; a.vocab = vocab; a.clf_params = clf ? clf->dev_params : nullptr; a.hidden = clf ? clf->hidden : 0;
   a.pos_feature = pos_feature; a.tau = tau; a.force_halt = force_halt; a.out = dev_out; a.token_next = dev_token_next;
   a.block_slot = dev_block_slot; a.gate = dev_gate; a.sl_count = dev_sl_count; a.force_token = dev_force_token;
-  a.scratch = scratch; a.abort_word = scratch ? reinterpret_cast<unsigned*>(scratch) + 1 : nullptr; a.limit = g_wait_limit;
+  a.scratch = scratch; a.abort_word = scratch ? reinterpret_cast<unsigned*>(scratch) + 1 : nullptr;
+  a.limit = g_wait_limit; a.ticket = g_launch_mode == 2;
   HIP_TRY(launch_classify(a, st), "classify launch");
   return DISCO_OK;
 }
@@ -882,7 +883,7 @@ static int draft_loop_impl(const disco_model* draft, disco_kv* kv, const disco_c
     a.sl_count = ws.sl_count; a.force_token = dev_force_tokens ? dev_force_tokens + (j - 1) : nullptr;
     a.ref_token = dev_ref_tokens ? dev_ref_tokens + (j - 1) : nullptr;
     a.ppl_threshold = ppl_threshold;
-    a.scratch = ws.clf_scratch; a.abort_word = ws.abort_word; a.limit = g_wait_limit;      // (the loop's end reports -1)
+    a.scratch = ws.clf_scratch; a.abort_word = ws.abort_word; a.limit = g_wait_limit; a.ticket = g_launch_mode == 2;      // (the loop's end reports -1)
     { const hipError_t e = launch_classify(a, st); if (e != hipSuccess) { kv->len = len_entry; return hip_fail(e, "classify launch"); } }
   }
   HIP_TRY(launch_loop_finish(ws.sl_count, ws.gate, dev_out, host_out, ws.abort_word, st), "loop finish launch");

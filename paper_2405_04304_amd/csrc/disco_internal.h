@@ -102,6 +102,7 @@ struct ClassifyArgs {
   float* scratch;                    // optional: >= CLASSIFY_SCRATCH_BYTES, zeros (a ticket counter, the word below, then records, which every launch leaves at zero)
   unsigned* abort_word;              // with scratch: set for good by a wait that gives up, and then every result says so
   int limit;                         // polls before the wait for the other workgroups' records gives up (negative: at once)
+  int ticket;                        // 1: no workgroup waits, the last to arrive merges
 };
 struct SampleArgs {
   const float* logits; int64_t ld; int vocab; float inv_t;

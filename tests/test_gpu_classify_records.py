@@ -179,3 +179,36 @@ def test_a_give_up_inside_a_draft_loop_is_reported():
             B.disco_set_wait_limit(prev)
         B._check(B.lib().disco_workspace_init(gm.handle, eng.ws_d.buf.data_ptr(), eng.ws_d.nbytes, 16, 96, B._stream()))
         assert eng.generate(prompt, 8, dict(pol, **extra))["tokens"] == text
+
+
+@pytest.mark.parametrize("vocab", [4096, 5119, 32000, 65536])
+def test_launch_mode_2_waits_nowhere(vocab):
+    """In launch mode 2 the last workgroup to arrive merges: the same bits, with every bounded wait forced to give up at once."""
+    scratch, clf = B.classify_scratch(dev()), B.DiscoClf(W.make_classifier(100), dev())
+    x = _row("normal", vocab, torch.Generator().manual_seed(9))
+    for force in (None, 17):
+        want, wl = _classify(clf, x, force, scratch)
+        prev_mode, prev = B.disco_set_launch_mode(2), B.disco_set_wait_limit(-1)
+        try:
+            got = [_classify(clf, x, force, scratch) for _ in range(2)]
+        finally:
+            B.disco_set_wait_limit(prev)
+            B.disco_set_launch_mode(prev_mode)
+        for r, l in got:
+            assert r.token == want.token and list(r.feats) == list(want.feats) and r.score == want.score and r.halt == want.halt and torch.equal(l, wl)
+        again = _classify(clf, x, force, scratch)[0]
+        assert again.token == want.token and list(again.feats) == list(want.feats)
+    assert int(scratch.view(torch.int32).abs().sum()) == 0
+    shape = W.ModelShape("A", 2, 256, 4, 64, 4, 512, 4096)
+    gm = B.DiscoModel(shape, W.make_weights(shape, 9, "bf16", sigma=0.05), dev())
+    ws = gm.workspace(16, 96)
+    prev_mode = B.disco_set_launch_mode(2)
+    try:
+        want = _draft_loop(gm, clf, ws, 40)
+        prev = B.disco_set_wait_limit(-1)
+        try:
+            assert _draft_loop(gm, clf, ws, 40) == want and want[0] == 3
+        finally:
+            B.disco_set_wait_limit(prev)
+    finally:
+        B.disco_set_launch_mode(prev_mode)
