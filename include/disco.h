@@ -459,7 +459,11 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   workgroups fit the GPU at once: the attention of a head
  *   needs only that head's rows of the projection, so its workgroups wait for those alone (a counter per head)
  *   instead of for the whole grid.  A narrow model (up to 1024 columns, heads of 64 channels) runs ALL its layers in one launch for one or
- *   two tokens, whose workgroups wait for each other's results.  The features of a draft
+ *   two tokens, whose workgroups wait for each other's results.  Forwards with such launches run one at a time on a GPU: one that is sent
+ *   while another workspace's is in flight on another stream takes a launch per phase that waits nowhere, with the same results, so any number
+ *   of streams may decode at once.  (Not seen by this: other processes on the GPU, and replays of captured graphs, which hold no launch of
+ *   all layers but the shared ones: programs that replay on several streams at once capture in mode 2.  The library keeps a page of pinned host memory
+ *   for it from the first disco_workspace_init on, until the process ends.)  The features of a draft
  *   loop (many workgroups) have a wait as well, see disco_classify.  Every such wait is bounded; if one ever runs out (about a second; it needs the
  *   launch's workgroups not to be resident together for that long) the launch still ends, the workspace is
  *   marked, and every later result of that workspace says so -- NaN logits, -1 in disco_verify's arg-max and in
@@ -471,7 +475,7 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order where every query
  *   head has its own K / V head in the RMSNorm family (the context is dealt differently), bit for bit in other models.
  *   No launch of it waits for another workgroup (disco_classify included): the mode for programs that decode on many streams at once, where
- *   mode 0's launches hold compute units for each other's waiting workgroups.
+ *   mode 0's waiting workgroups hold compute units.
  * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
  * 5.69 ms in mode 1; a 68M-class draft step: 50 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a
  * launch costs more than a kernel boundary there, a hand-off whose data is its own flag half of one.     */

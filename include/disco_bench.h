@@ -51,6 +51,10 @@ int disco_qkv_attn_plan(const struct disco_model* m, int n_tokens, int ctx, int 
  * groups of query heads that share the attention's products, workgroups of a group.  capacity: as above.   0, or DISCO_EINVAL.  */
 int disco_layers_plan(const struct disco_model* m, int n_tokens, int ctx, int page_tokens, int capacity, int out[4]);
 
+/* Testing and measurement aid: how the last forward that this thread sent was launched: 0 a launch per phase, 1 the QKV projection
+ * and the attention of a layer in one launch, 2 all layers in one launch, 3 one cooperative launch.                               */
+int disco_forward_route(void);
+
 #ifdef __cplusplus
 }
 #endif

@@ -139,6 +139,7 @@ _SIGNATURES = {
     "disco_set_wait_limit": (C.c_int, [C.c_int]),
     "disco_qkv_attn_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
     "disco_layers_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
+    "disco_forward_route": (C.c_int, []),
     "disco_prefill_plan": (C.c_int, [C.c_void_p, C.c_int, C.c_uint, C.c_int, C.POINTER(C.c_int)]),
 }
 EXPORTS = sorted(_SIGNATURES)
@@ -366,6 +367,11 @@ def disco_layers_plan(model_handle, n_tokens: int, ctx: int, page_tokens: int, c
     out = (C.c_int * 4)()
     _check(lib().disco_layers_plan(model_handle, n_tokens, ctx, page_tokens, capacity, out))
     return {"one_launch": bool(out[0]), "workgroups": out[1], "groups": out[2], "parts": out[3]}
+
+
+def disco_forward_route() -> str:
+    """How the last forward that this thread sent was launched (disco_bench.h)."""
+    return ("phases", "shared", "layers", "cooperative")[lib().disco_forward_route()]
 
 
 def disco_probe_enable(layer: int) -> None:

@@ -201,6 +201,81 @@ bool chain_args(const disco_model* m, int n, int pos0, int page_tokens, size_t k
   return chain_plan(ch, m->d_qkv, d.d_head, d.family == DISCO_FAMILY_A, room, capacity);
 }
 
+// How the QKV projection and the attention of a layer run for n tokens behind pos0 positions (qkv_attn_plan): 0 two launches.
+int qkv_attn_form(const disco_model* m, int n, int pos0) {
+  const disco_model_desc& d = m->d;
+  const int rt = qkv_attn_rt(m->d_qkv);
+  long shared = 0, own = 0;
+  qkv_attn_capacities(n, rt, d.d_head, d.family == DISCO_FAMILY_A, &shared, &own);
+  return qkv_attn_plan(m->d_qkv, d.n_heads, d.n_kv_heads, d.d_head, d.family == DISCO_FAMILY_A, pos0 + n, rt, shared, own).form;
+}
+
+// Forwards in flight that hold launches whose workgroups wait for each other (k_chain, k_qkv_attn).  Such a launch ends because its workgroups fit the
+// GPU together.  Several at once on streams of their own need not: 180 workgroups for a 68M-class draft and two to a compute unit, so of three launches that
+// start together none might become whole.  So at most one such forward is in flight on a GPU: a forward takes the place when no other
+// workspace's holds it, its LM head gives it back by a store to host memory, and a forward that finds it taken launches per phase (which waits nowhere, and
+// forms the same sums).  Forwards on one stream run one after another and share the place.  A captured forward runs whenever its graph is
+// replayed, unseen from here: it does not take k_chain.
+struct PlaceEntry { const void* ws; hipStream_t stream; int device; uint32_t sent; };
+constexpr int PLACE_ENTRIES = 64;
+std::mutex g_place_mu;
+PlaceEntry g_place[PLACE_ENTRIES];           // a workspace each: the forwards it has sent
+uint32_t* g_place_done = nullptr;            // in host memory that the GPU writes: the last of them that is done (kept until the process ends)
+
+// (the capture mode of this thread is set aside for the allocation, which a capture on another thread would otherwise refuse)
+void place_init() {
+  std::lock_guard<std::mutex> lock(g_place_mu);
+  if (g_place_done != nullptr) return;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  void* p = nullptr;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return; }
+  if (hipHostMalloc(&p, sizeof(uint32_t) * PLACE_ENTRIES, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+    memset(p, 0, sizeof(uint32_t) * PLACE_ENTRIES);
+    g_place_done = static_cast<uint32_t*>(p);
+  } else {
+    (void)hipGetLastError();
+  }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
+// The place for a forward of workspace `ws` on stream s: its entry, or -1.  g.done and g.done_value give it back.
+int place_take(const void* ws, hipStream_t s, GemmArgs& g) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return -1;
+  std::lock_guard<std::mutex> lock(g_place_mu);
+  if (g_place_done == nullptr) return -1;
+  int own = -1, unused = -1;
+  for (int i = 0; i < PLACE_ENTRIES; ++i) {
+    const PlaceEntry& e = g_place[i];
+    if (e.ws == ws) { own = i; continue; }   // (one stream at a time, in order)
+    if (__atomic_load_n(g_place_done + i, __ATOMIC_RELAXED) == e.sent) { if (unused < 0) unused = i; continue; }
+    if (e.device == device && (e.stream != s || s == hipStreamPerThread)) return -1;
+  }
+  const int i = own >= 0 ? own : unused;
+  if (i < 0) return -1;
+  g_place[i] = PlaceEntry{ws, s, device, g_place[i].sent + 1};
+  g.done = g_place_done + i; g.done_value = g_place[i].sent;
+  return i;
+}
+
+// The forward that took entry i was not sent to its end.
+void place_untake(int i) {
+  std::lock_guard<std::mutex> lock(g_place_mu);
+  --g_place[i].sent;
+}
+
+bool stream_captures(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+thread_local int t_forward_route = 0;        // disco_forward_route
+
+int forward_launches(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n, float* logits_out, bool only_last, const Ws& ws,
+                     const uint32_t* gate, bool chained, ChainArgs& ch, bool may_wait, GemmArgs& lm, hipStream_t s);
+
 // One forward of n tokens at positions kv->len ..: the shared body of draft step and verification.
 // logits_out: [vocab] of the last token (only_last) or [n x vocab].
 int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n, float* logits_out,
@@ -227,10 +302,37 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
     f.M = n; f.pos0 = pos0; f.logits = logits_out; f.only_last = only_last ? 1 : 0;
     HIP_TRY(launch_forward(f, m->persist_big, false, s), "forward launch");
     kv->len = pos0 + n;
+    t_forward_route = 3;
     return DISCO_OK;
   }
   ChainArgs ch;                                  // a narrow model's one or two tokens: all layers in one launch
-  const bool chained = g_launch_mode == 0 && !probe_on(d.n_layers) && chain_args(m, n, pos0, kv->page_tokens, kv->layer_stride, ws.gpart_bytes, 0, ch);
+  GemmArgs lm{};
+  int place = -1;
+  bool chained = false, may_wait = false;
+  if (g_launch_mode != 2) {
+    const bool one = g_launch_mode == 0 && !probe_on(d.n_layers) && chain_args(m, n, pos0, kv->page_tokens, kv->layer_stride, ws.gpart_bytes, 0, ch);
+    if (one || qkv_attn_form(m, n, pos0) != 0) {
+      if (stream_captures(s)) {
+        may_wait = true;
+      } else {
+        place = place_take(ws.h, s, lm);
+        may_wait = place >= 0; chained = may_wait && one;
+      }
+    }
+  }
+  t_forward_route = chained ? 2 : (may_wait ? 1 : 0);
+  const int rc = forward_launches(m, kv, dev_tokens, n, logits_out, only_last, ws, gate, chained, ch, may_wait, lm, s);
+  if (rc != DISCO_OK && place >= 0) place_untake(place);
+  return rc;
+}
+
+// The launches of forward_block: all layers in one (chained, by ch's plan), or per phase, the QKV projection and the attention of a layer in one where
+// that fits and launches may wait.  lm: what forward_block has to say to the LM head's launch.
+int forward_launches(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens, int n, float* logits_out, bool only_last, const Ws& ws,
+                     const uint32_t* gate, bool chained, ChainArgs& ch, bool may_wait, GemmArgs& lm, hipStream_t s) {
+  const disco_model_desc& d = m->d;
+  const int pos0 = kv->len, n_tiles = d.d_model / 16;
+  const bool fam_a = d.family == DISCO_FAMILY_A;
   const int split_o = gemm_split_for(d.d_model, m->d_q / 32, n), split_dn = gemm_split_for(d.d_model, d.d_ff / 32, n);
 
   NormArgs na{};
@@ -299,7 +401,7 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
     // (a bounded wait inside the fused launch that runs out sets the workspace's abort word: the LM head then stores
     // NaN logits, the arg-max and loop-finish kernels report -1)
     if (g_launch_mode != 2)
-      HIP_TRY(launch_qkv_attn(g, at, ws.head_ready, ws.abort_word, g_wait_limit, &fused, s), "qkv + attention launch");
+      HIP_TRY(launch_qkv_attn(g, at, ws.head_ready, ws.abort_word, g_wait_limit, may_wait, &fused, s), "qkv + attention launch");
     if (!fused) {
       HIP_TRY(launch_gemm(g, EPI_QKV, s), "qkv launch");
       HIP_TRY(launch_attn(at, s), "attention launch");
@@ -322,7 +424,6 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
     HIP_TRY(launch_gemm(dn, EPI_PARTIAL, s), "mlp-out launch");
 
   }
-  GemmArgs lm{};
   lm.M = n; lm.gate = gate; lm.planes = ws.gpart; lm.counters = ws.gemm_counters;
   lm.W = static_cast<const bf16_t*>(m->w.wlm); normed_input(lm, fam_a ? ws.ln_vec + ws.ln_layer_stride * d.n_layers : nullptr, d.vocab);
   lm.n_rows = d.vocab; lm.out = logits_out; lm.ld_out = d.vocab; lm.only_row = only_last ? n - 1 : -1;
@@ -662,6 +763,7 @@ int disco_workspace_init(const disco_model* m, void* dev_ws, size_t ws_bytes, in
   if (need == 0 || ws_bytes < need) return fail(DISCO_EINVAL, "workspace of %zu bytes, %zu needed", ws_bytes, need);
   const Ws ws = carve(m, max_block, max_ctx, dev_ws);
   const disco_model_desc& d0 = m->d;
+  place_init();
   HIP_TRY(launch_zero(ws.gemm_counters, ws.n_counters, static_cast<hipStream_t>(s)), "workspace init launch");
   HIP_TRY(launch_zero(reinterpret_cast<int*>(ws.clf_scratch), CLASSIFY_SCRATCH_BYTES / 4, static_cast<hipStream_t>(s)), "workspace init launch");
   HIP_TRY(launch_zero(ws.head_ready, QKV_ATTN_READY_SLOT * d0.n_heads, static_cast<hipStream_t>(s)), "workspace init launch");
@@ -857,6 +959,7 @@ static int draft_loop_impl(const disco_model* draft, disco_kv* kv, const disco_c
     a.block_slot = block_base + 1; a.gate = ws.gate; a.sl_count = ws.sl_count; a.force_token = dev_force_tokens;
     a.ref_token = dev_ref_tokens; a.ppl_threshold = ppl_threshold; a.scratch = ws.clf_scratch;
     HIP_TRY(launch_forward(f, draft->persist_big, true, st), "draft loop launch");
+    t_forward_route = 3;
     kv->len = pos0 + n_in + steps - 1;
     HIP_TRY(launch_loop_finish(ws.sl_count, ws.gate, dev_out, host_out, ws.bar + FWD_BAR_ABORT_WORD, st), "loop finish launch");
     return DISCO_OK;
@@ -1128,6 +1231,8 @@ int disco_layers_plan(const disco_model* m, int n_tokens, int ctx, int page_toke
   out[0] = one ? 1 : 0; out[1] = one ? ch.wgs : 0; out[2] = one ? ch.n_groups : 0; out[3] = one ? ch.parts : 0;
   return DISCO_OK;
 }
+
+int disco_forward_route(void) { return t_forward_route; }
 
 int disco_probe_enable(int layer) {
   std::lock_guard<std::mutex> lock(g_probe_mu);

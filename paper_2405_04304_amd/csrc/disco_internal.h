@@ -44,6 +44,7 @@ struct GemmArgs {
   int64_t ld_out;
   int only_row;         // STORE: write only this token's row to out[0..N) (-1: all rows)
   const unsigned* abort_word;   // STORE, optional: when the word is set (a bounded wait of an earlier launch ran out) NaN is stored
+  uint32_t* done; uint32_t done_value;   // STORE, optional: a word of host memory that the launch sets to done_value
   // QKV epilogue
   float* q; int ldq; int nq, nkv, dh; int pos0;
   const float* rope_tab;  // rotary table [position][d_head / 2][cos, sin], or nullptr for no rotation
@@ -164,7 +165,7 @@ struct FwdArgs {
 };
 
 // All layers of a narrow model's forward over one or two tokens in one launch: see k_chain.
-constexpr int CHAIN_MAX_WGS = 192 /* of the 512 that fit: two such launches on streams of their own always do */;
+constexpr int CHAIN_MAX_WGS = 192 /* of the 512 that fit */;
 constexpr int CHAIN_MAX_LAYERS = 24, CHAIN_MAX_TOKENS = 2, CHAIN_MAX_RANGES = 8, CHAIN_REC = 80 /* floats between two ranges' records */;
 struct ChainLayer {
   const bf16_t* wqkv; const bf16_t* wo; const bf16_t* w_in; const bf16_t* w_out; const float* norm2_g;
@@ -207,7 +208,7 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s);
 // set when a bounded wait inside the launch ran out (results unusable).
 constexpr int QKV_ATTN_READY_SLOT = 64;
 // wait_limit: polls before a wait gives up (negative: at once).
-hipError_t launch_qkv_attn(const GemmArgs& g, AttnArgs& a, int* head_ready, unsigned* abort_word, int wait_limit, bool* launched,
+hipError_t launch_qkv_attn(const GemmArgs& g, AttnArgs& a, int* head_ready, unsigned* abort_word, int wait_limit, bool may_wait, bool* launched,
                            hipStream_t s);
 // form 0: two launches, 1: the projection's workgroups become the attention's, 2: the attention has workgroups of its own; positions per
 // range, ranges per head (a context of 256 or fewer goes to one workgroup per head, which merges as the ranges would), workgroups.

@@ -744,6 +744,10 @@ __global__ __launch_bounds__(NW * 64) void k_gemm(const bf16_t* W, const bf16_t*
   const int kt_begin = n_split == 1 ? 0 : (int)((unsigned)(KT * split) / (unsigned)n_split);
   const int kt_end = n_split == 1 ? KT : (int)((unsigned)(KT * (split + 1)) / (unsigned)n_split);
   gemm_unit<P, RT, EPI, NW, U, false, NoHook, LN>(a, blockIdx.x, kt_begin, kt_end, split, a.n_split, sm);
+  // (behind the unit: a store in front of it would be waited for with its loads)
+  if constexpr (EPI == EPI_STORE) {
+    if (a.done != nullptr && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(a.done, a.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 template <int P, int RT, int EPI, int NW, int U>
@@ -4139,7 +4143,7 @@ void qkv_attn_capacities(int M, int rt, int dh, bool layernorm, long* shared, lo
 }
 
 template <int P, int RT, int DH>
-static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit,
+static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready, unsigned* abort_word, int safe_end, int limit, bool may_wait,
                                      bool* launched, hipStream_t s) {
   constexpr int U = gemm_buffers(RT, P);
   const bool ln = g.sum != nullptr;
@@ -4147,7 +4151,7 @@ static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready,
   qkv_attn_capacities_rt<P, RT, DH>(ln, &cap_shared, &cap_own);
   const QkvAttnPlan p = qkv_attn_plan(g.n_rows, g.nq, g.nkv, DH, ln, a.pos0 + a.M, RT, cap_shared, cap_own);
   a.split_len = p.split_len; a.n_splits = p.n_splits;
-  if (p.form == 0) return hipSuccess;
+  if (p.form == 0 || !may_wait) return hipSuccess;
   const dim3 grid((unsigned)p.wgs);
 #define QKV_ATTN_ARGS grid, dim3(512), 0, s, g.W, g.X, g.gate, g.ssq, g.KT, g.n_ssq, g.M, g.nq, g.nkv, g.pos0, g, a, ready, abort_word, safe_end, limit
   if (p.form == 1) hipLaunchKernelGGL((k_qkv_attn<P, RT, U, DH, false, false>), QKV_ATTN_ARGS);
@@ -4160,10 +4164,10 @@ static hipError_t launch_qkv_attn_rt(const GemmArgs& g, AttnArgs& a, int* ready,
   return hipGetLastError();
 }
 
-// Sets *launched and enqueues the fused launch when the shape allows it; otherwise leaves *launched false and enqueues
+// Sets *launched and enqueues the fused launch when the shape allows it and the forward may hold launches that wait; otherwise leaves *launched false and enqueues
 // nothing (the caller then launches the QKV projection and the attention separately, the latter over a.split_len / a.n_splits,
 // which are chosen here either way).
-hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned* abort_word, int limit, bool* launched, hipStream_t s) {
+hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned* abort_word, int limit, bool may_wait, bool* launched, hipStream_t s) {
   *launched = false;
   if (ready == nullptr || abort_word == nullptr) return hipSuccess;
   if (g0.nkv < 1 || g0.nq % g0.nkv != 0 || (g0.dh != 64 && g0.dh != 128)) return hipSuccess;
@@ -4176,7 +4180,7 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
   // positions below safe_end share no 128-byte line with the block's own positions: K rows are 128 bytes or more per
   // position; a V^T row holds the positions of one page, 64 to a line
   const int safe_end = (pt % 64 == 0) ? (a.pos0 & ~63) : (a.pos0 / pt) * pt;
-  return QKV_ATTN_BY_SHAPE(launch_qkv_attn_rt, g.M <= 8, qkv_attn_rt(g.n_rows), g.dh, g, a, ready, abort_word, safe_end, limit, launched, s);
+  return QKV_ATTN_BY_SHAPE(launch_qkv_attn_rt, g.M <= 8, qkv_attn_rt(g.n_rows), g.dh, g, a, ready, abort_word, safe_end, limit, may_wait, launched, s);
 }
 
 
