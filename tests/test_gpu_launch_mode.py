@@ -157,3 +157,21 @@ def test_mode1_iteration_driver_with_chunks_equals_mode0():
             else:
                 assert abs(rec.score - TAU) < 1e-3, (chunk, diff)
             break
+
+
+def test_what_mode_1_does_not_take_runs_as_in_mode_0(mode1):
+    """A LayerNorm model, and a gated step: the launches of mode 0, the launch of all layers among them, and its bits."""
+    d = dev()
+    for shape, gated in ((W.ModelShape("A", 2, 768, 12, 64, 1, 3072, 512), False), (W.ModelShape("B", 2, 768, 12, 64, 12, 3072, 4096), True)):
+        gm = B.DiscoModel(shape, W.make_weights(shape, 3, "bf16", sigma=0.05), d)
+        kv, ws = B.DiscoKV(gm, 332, 16), gm.workspace(16, 332)
+        kv.fill(W.make_kv_fill(shape, 300, 2).to(d))
+        tok, gate, out = torch.tensor([11], dtype=torch.int32, device=d), torch.zeros(1, dtype=torch.int32, device=d) if gated else None, []
+        for mode in (0, 1):
+            B.disco_set_launch_mode(mode)
+            lg = torch.empty(shape.vocab, device=d)
+            B.disco_draft_step(gm, kv, tok, 1, lg, ws, gate=gate)
+            out.append((B.disco_forward_route(), lg))
+            B.disco_kv_rollback(kv, 300)
+            torch.cuda.synchronize()
+        assert out[0][0] == out[1][0] == "layers" and torch.equal(out[0][1], out[1][1])
