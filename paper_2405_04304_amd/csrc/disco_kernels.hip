@@ -4997,13 +4997,19 @@ bool chain_plan(ChainArgs& a, int d_qkv, int dh, bool layernorm, size_t room, lo
   // The heads of a K / V head share its keys and values as columns of the same products, as far as sixteen columns go; a group's ranges go to
   // as many workgroups as make up 24, or 36 where the launch keeps within CHAIN_MAX_WGS: a step of 32 positions costs a wavefront about half a
   // microsecond.  68M-class token, 24 / 36 / 48: at 523 positions 49.8 / 48.5 / 48.7 us, at 1024 50.5 / 49.5 / 49.4, at 2048 58.4 / 54.1 / 54.0.
+  // Thirteen groups and more have two of the 36: there, and where ranges are long, a workgroup gets two ranges at most (from 512 positions on
+  // one) as far as there is room.  One layer of 16 heads of their own, 128 columns, 3071 positions, two tokens: a launch per phase 26.6 us, two workgroups a
+  // group 29.1, now 24.9; six LayerNorm layers at 2400, one token: 136.6, 124.9, 93.5.  Over 1224 models and blocks that take it (64 to 1024 columns,
+  // 1 to 16 heads, 1 to 6 layers, 20 to 3071 positions) this launch is 1.03 (one layer of 16 heads at 3071) to 1.7 times as fast as a launch per phase,
+  // 1.34 at the median.
   const int rep = a.nq / a.nkv, per_kv = (rep * a.M + 15) / 16;
   a.heads = (rep + per_kv - 1) / per_kv;
   a.n_groups = a.nkv * per_kv;
   const int n_p = d_qkv / 32, n_u = a.d_ff / 32;
   a.n_pu = n_p > n_u ? n_p : n_u;
   const int room_for = (CHAIN_MAX_WGS - a.n_pu - d / 16) / a.n_groups, few = 24 / a.n_groups < 1 ? 1 : 24 / a.n_groups;
-  a.parts = 36 / a.n_groups < room_for ? 36 / a.n_groups : room_for;
+  const int two = a.split_len < 512 ? 2 : 1, want = 36 / a.n_groups > (a.n_splits + two - 1) / two ? 36 / a.n_groups : (a.n_splits + two - 1) / two;
+  a.parts = want < room_for ? want : room_for;
   if (a.parts < few) a.parts = few;
   if (a.parts > a.n_splits) a.parts = a.n_splits;
   const int most = (a.n_splits + a.parts - 1) / a.parts;          // ranges of a workgroup

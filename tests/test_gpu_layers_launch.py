@@ -71,6 +71,23 @@ def test_heads_with_keys_of_their_own_against_the_oracle(ctx, page_tokens):
         assert float((lg - lg2).abs().max()) <= 2e-4 * float(lg2.abs().max())
 
 
+@pytest.mark.parametrize("ctx, parts", [(1300, (3, 3)), (1700, (4, 4)), (2400, (5, 5)), (3071, (5, 4))])
+def test_the_context_of_many_heads_over_more_workgroups(ctx, parts):
+    """Sixteen heads of their own: as many workgroups a head as ranges of 512 positions, or pairs of shorter ranges; the same bits."""
+    shape = W.ModelShape("A", 2, 128, 16, 64, 16, 512, 512)
+    gm = B.DiscoModel(shape, W.make_weights(shape, 90, "bf16", sigma=0.05), dev())
+    fill = W.make_kv_fill(shape, ctx, 3).to(dev())
+    for M in (1, 2):
+        plan = B.disco_layers_plan(gm.handle, M, ctx, 16)
+        assert plan["one_launch"] and plan["groups"] == 16 and plan["parts"] == parts[M - 1]
+        blk, out = W.make_tokens(80 + M, M, shape.vocab).tolist(), []
+        for mode in (0, 2):
+            gkv, ws = B.DiscoKV(gm, ctx + 32, 16), gm.workspace(16, ctx + 32)
+            gkv.fill(fill)
+            out.append(_verify(gm, gkv, ws, blk, mode)[0])
+        assert bool(torch.isfinite(out[0]).all()) and torch.equal(out[0], out[1]), M
+
+
 def test_captured_forward_replays():
     """The hand-off buffers are emptied by a launch of the forward itself, so a captured graph replays it."""
     d = dev()
