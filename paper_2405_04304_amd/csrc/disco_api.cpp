@@ -220,6 +220,7 @@ struct PlaceEntry { const void* ws; hipStream_t stream; int device; uint32_t sen
 constexpr int PLACE_ENTRIES = 64;
 std::mutex g_place_mu;
 PlaceEntry g_place[PLACE_ENTRIES];           // a workspace each: the forwards it has sent
+int g_place_used = 0;                        // entries that have had one
 uint32_t* g_place_done = nullptr;            // in host memory that the GPU writes: the last of them that is done (kept until the process ends)
 
 // (the capture mode of this thread is set aside for the allocation, which a capture on another thread would otherwise refuse)
@@ -245,14 +246,17 @@ int place_take(const void* ws, hipStream_t s, GemmArgs& g) {
   std::lock_guard<std::mutex> lock(g_place_mu);
   if (g_place_done == nullptr) return -1;
   int own = -1, unused = -1;
-  for (int i = 0; i < PLACE_ENTRIES; ++i) {
+  for (int i = 0; i < g_place_used; ++i) {
     const PlaceEntry& e = g_place[i];
     if (e.ws == ws) { own = i; continue; }   // (one stream at a time, in order)
     if (__atomic_load_n(g_place_done + i, __ATOMIC_RELAXED) == e.sent) { if (unused < 0) unused = i; continue; }
     if (e.device == device && (e.stream != s || s == hipStreamPerThread)) return -1;
   }
-  const int i = own >= 0 ? own : unused;
-  if (i < 0) return -1;
+  int i = own >= 0 ? own : unused;
+  if (i < 0) {
+    if (g_place_used == PLACE_ENTRIES) return -1;
+    i = g_place_used++;
+  }
   g_place[i] = PlaceEntry{ws, s, device, g_place[i].sent + 1};
   g.done = g_place_done + i; g.done_value = g_place[i].sent;
   return i;
