@@ -212,3 +212,34 @@ def test_launch_mode_2_waits_nowhere(vocab):
             B.disco_set_wait_limit(prev)
     finally:
         B.disco_set_launch_mode(prev_mode)
+
+
+def test_rows_with_logits_that_are_not_numbers():
+    """A NaN among the logits, or infinities of one sign: token, halt and which features are numbers as the one-workgroup form has them."""
+    scratch, clf = B.classify_scratch(dev()), B.DiscoClf(W.make_classifier(100), dev())
+    g = torch.Generator().manual_seed(10)
+
+    def num(r):
+        return [f == f for f in list(r.feats) + [r.score]]
+
+    for vocab in (4096, 32000, 65535):
+        for kind in ("one", "last", "many", "all", "sign", "+inf", "-inf"):
+            x = _row("normal", vocab, g)
+            if kind in ("one", "last", "sign"):
+                x[vocab - 1 if kind == "last" else 700] = float("nan")
+                if kind == "sign":
+                    x.view(torch.int32)[700] = -1                 # every bit set
+            elif kind == "many":
+                x[::7] = float("nan")
+            elif kind == "all":
+                x[:] = float("nan")
+            elif kind == "+inf":
+                x[123] = float("inf")
+            else:
+                x[:] = float("-inf")
+            (a, _), (b, _) = _classify(clf, x, None, scratch), _classify(clf, x, None, None)
+            if kind == "all":                                     # no arg-max: no token of the vocabulary, and an entropy that is no number
+                assert min(a.token, b.token) >= vocab and a.feats[10] != a.feats[10] and b.feats[10] != b.feats[10] and a.halt == b.halt, vocab
+            else:
+                assert a.token == b.token and a.halt == b.halt and num(a) == num(b), (vocab, kind)
+    assert int(scratch.view(torch.int32).abs().sum()) == 0
