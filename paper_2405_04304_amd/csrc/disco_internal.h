@@ -176,7 +176,7 @@ struct ChainArgs {
   int n_layers, M, pos0, d, d_ff, nq, nkv; float eps, scale;
   const float* h;                    // residual rows (the embedding)
   bf16_t* x_out; float* ssq_out; float* sum_out;             // input of the LM head: panels, sums of squares, sums
-  float* q_last;                     // queries of the last layer
+  float* q_last;                     // queries of the last layer: in the workspace's query rows, where the launches per phase leave them and a reader of the workspace finds them
   bf16_t* kv_pages; size_t kv_layer_stride; const int32_t* page_table; int page_tokens; const float* rope;
   const uint32_t* gate; unsigned* abort_word; int limit;
   char* hand;                        // hand-off buffers, layer_bytes apart

@@ -4205,8 +4205,8 @@ hipError_t launch_qkv_attn(const GemmArgs& g0, AttnArgs& a, int* ready, unsigned
 // The sums are formed in the order of the launches per phase (the wavefronts' k-tiles, the K ranges of the MLP output, the deal of the
 // context over ranges and wavefronts), so results do not depend on which of the two runs.
 //
-// All workgroups are resident at once (chain_plan checks it), and nobody waits without a bound (`limit` polls, then the abort word is set
-// and the launch ends with unusable data, as in k_qkv_attn).  At most CHAIN_MAX_WGS of the 512 workgroups that fit are one launch's.
+// All workgroups are resident at once: they fit the GPU (chain_plan), and no other launch that waits inside is in flight with it (forward_block).  Nobody
+// waits without a bound (`limit` polls, then the abort word is set and the launch ends with unusable data, as in k_qkv_attn).
 constexpr uint32_t CHAIN_EMPTY = 0xFFFFFFFFu;
 
 __device__ __forceinline__ uint32_t chain_word(uint32_t x) { return x == CHAIN_EMPTY ? 0x7FC07FC0u : x; }
@@ -4662,7 +4662,7 @@ __device__ __forceinline__ void chain_attention(const ChainArgs& a, ChainAttnSme
       ChainWait<1> wt;
       const int pc = lane & 15, col = 2 * w + (lane >> 4), kvm = (lane >> 4) - 2;
       const bool is_q = lane < 32 && col < n_col, is_kv = w == 0 && lane >= 32 && kvm < M;
-      const uint32_t h_at = (uint32_t)(hand - reinterpret_cast<const char*>(a.q_last)), q_at = l + 1 == a.n_layers ? 0u : h_at + a.o_q;      // (see chain_plan)
+      const uint32_t h_at = (uint32_t)(hand - reinterpret_cast<const char*>(a.q_last)), q_at = l + 1 == a.n_layers ? 0u : h_at + a.o_q;      // (the distance fits: launch_chain)
       wt.on[0] = is_q || is_kv;
       wt.base = reinterpret_cast<const char*>(a.q_last);
       wt.p[0] = (is_kv ? h_at + a.o_kv + (kvh * M + kvm) * 256u : q_at + ((min(col, n_col - 1) % M) * a.nq + head0 + min(col, n_col - 1) / M) * 256u) + pc * 16u;

@@ -89,7 +89,7 @@ def test_the_context_of_many_heads_over_more_workgroups(ctx, parts):
 
 
 def test_captured_forward_replays():
-    """The hand-off buffers are emptied by a launch of the forward itself, so a captured graph replays it."""
+    """Replays of a captured forward, which holds a launch per phase, between eager ones with all layers in one launch, on one workspace: the same bits."""
     d = dev()
     shape = SHAPES["one K / V head, 12 query heads"]
     gm = B.DiscoModel(shape, W.make_weights(shape, 90, "bf16", sigma=0.05), d)
