@@ -474,8 +474,8 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   used silently); results agree with mode 0 to fp32 summation order.
  * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order where every query
  *   head has its own K / V head in the RMSNorm family (the context is dealt differently), bit for bit in other models.
- *   No launch of it waits for another workgroup (disco_classify included): the mode for programs that decode on many streams at once, where
- *   mode 0's waiting workgroups hold compute units.
+ *   No launch of it waits for another workgroup (disco_classify included): the mode for programs that replay captured forwards on several
+ *   streams at once or share the GPU with another process.
  * On MI355X mode 0 is the fastest (a 13B-class verification block of 6 tokens: 4.85 ms, against 4.87 ms in mode 2 and
  * 5.69 ms in mode 1; a 68M-class draft step: 50 us against 69 us and 128 us): a phase boundary of a whole grid of 256 inside a
  * launch costs more than a kernel boundary there, a hand-off whose data is its own flag half of one.     */
