@@ -470,8 +470,9 @@ int disco_prefill_ex(const disco_model* m, disco_kv* kv, const int32_t* dev_toke
  *   disco_loop_out.sl, DISCO_EHIP from disco_iterate -- until disco_workspace_init is called again.
  * mode 1: a forward (and a whole draft loop) of the RMSNorm / rotary / SwiGLU family as ONE cooperative launch of persistent workgroups
  *   with a grid barrier between the phases (in a draft loop also the features / classifier and the next token's
- *   embedding, the kernel leaving at the first halting step), where the model's shapes allow it (else mode 0 is
- *   used silently); results agree with mode 0 to fp32 summation order.
+ *   embedding, the kernel leaving at the first halting step), where the model's shapes allow it (else the launches of
+ *   mode 0 are used silently, but for the one of all layers, which would wait for compute units that a cooperative launch on another stream
+ *   holds); results agree with mode 0 to fp32 summation order.
  * mode 2: one launch per phase, nothing shared; results agree with mode 0 to fp32 summation order where every query
  *   head has its own K / V head in the RMSNorm family (the context is dealt differently), bit for bit in other models.
  *   No launch of it waits for another workgroup (disco_classify included): the mode for programs that replay captured forwards on several

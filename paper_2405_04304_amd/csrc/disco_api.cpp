@@ -314,7 +314,8 @@ int forward_block(const disco_model* m, disco_kv* kv, const int32_t* dev_tokens,
   int place = -1;
   bool chained = false, may_wait = false;
   if (g_launch_mode != 2) {
-    const bool one = !probe_on(d.n_layers) && chain_args(m, n, pos0, kv->page_tokens, kv->layer_stride, ws.gpart_bytes, 0, ch);
+    // (not in mode 1: a cooperative launch on another stream needs its workgroups resident together as well)
+    const bool one = g_launch_mode == 0 && !probe_on(d.n_layers) && chain_args(m, n, pos0, kv->page_tokens, kv->layer_stride, ws.gpart_bytes, 0, ch);
     if (one || qkv_attn_form(m, n, pos0) != 0) {
       if (stream_captures(s)) {
         may_wait = true;
