@@ -1068,7 +1068,7 @@ int disco_iterate(const disco_model* target, disco_kv* kv_t, void* dev_ws_t, siz
       enq += todo;
       HIP_TRY(hipStreamSynchronize(st), "stream synchronisation");
       sl = buf->host_loop_out->sl;
-      if (sl < 0) return fail(DISCO_EHIP, "the draft loop's grid barrier timed out");
+      if (sl < 0) return fail(DISCO_EHIP, "a wait inside the draft loop's launches ran out");
       halted = buf->host_loop_out->halted != 0;
     }
     if (sl > DISCO_MAX_BLOCK - 1) return fail(DISCO_ESTATE, "draft loop reported %d tokens", sl);
@@ -1088,7 +1088,7 @@ int disco_iterate(const disco_model* target, disco_kv* kv_t, void* dev_ws_t, siz
   HIP_TRY(hipStreamSynchronize(st), "stream synchronisation");
   const disco_accept_out& acc = *buf->host_accept_out;
   if (acc.n < 0 || acc.n > sl) return fail(DISCO_ESTATE, "acceptance reported %d of %d tokens", acc.n, sl);
-  if (acc.emit[acc.n] < 0) return fail(DISCO_EHIP, "the verification forward's grid barrier timed out");
+  if (acc.emit[acc.n] < 0) return fail(DISCO_EHIP, "a wait inside the verification forward's launches ran out");
   rc = disco_kv_rollback(kv_t, len_t0 + acc.n + 1);
   if (rc) return rc;
   if (kv_d && kv_d->len > len_t0 + acc.n + 1) { rc = disco_kv_rollback(kv_d, len_t0 + acc.n + 1); if (rc) return rc; }

@@ -2393,7 +2393,7 @@ __device__ __forceinline__ void select_ten(uint32_t (&k)[N], const uint32_t boun
 // launch.  It waits for workgroups that were started before it, and not without a bound: after `limit` polls it reports token -1, a score that is not
 // a number, and a halt, and marks the scratch (abort_word).  A workgroup that was late then leaves a record that nothing clears, so every later launch on a marked
 // scratch reports the same, until it is initialised.  What bounds it: a chain of dependent instructions, of about ten cycles each: load 0.7 us, a wavefront's 256 logits 1.1, the
-// workgroup's 1.4, hand-off 1, final selection 1, features and classifier 1.  32000 logits 8.5 -> 7.65 us a call (a ticket and a load in place of the
+// workgroup's 1.4, hand-off 1, final selection 1, features and classifier 1.  32000 logits 8.5 -> 7.65 us a call (a ticket, 0.3 us, and a load in place of the
 // polls, ten rounds of maxima in place of the candidate lists; one wavefront for all 1024 logits of a workgroup 8.5: 3.4 us for the first two).
 struct MultiSmem {
   alignas(16) uint32_t list[4][64], all[64], top[12];
